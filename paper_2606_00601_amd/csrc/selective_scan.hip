@@ -642,6 +642,8 @@ template <typename IN>
 int launch_row16_states(const SelArgs& a, hipStream_t s);
 template <typename IN>
 SelPlan plan_row16(const SelArgs& a, int cus);
+template <typename IN>
+int launch_step(const SelArgs& a, hipStream_t s);
 
 namespace {
 
@@ -664,11 +666,33 @@ bool row16_path(const SelArgs& a) {
          row16_fits(a.D, a.N, a.L, sizeof(IN));
 }
 
+// Calls of at most 16 steps take the kernel of selective_step.hip, which moves
+// the states once and stages nothing.  Measured (us per call, the kernels of
+// longer calls / this one, every option): B=64, D=5120, N=16 bf16 488 / 11.7
+// at L=1, 213 / 57 at L=16, 212 / 134 at L=32, but fp32 124 / 66 at L=16 and
+// 131 / 341 at L=32; B=16, D=2048, N=64 fp32 79 / 11.3 at L=1, 73 / 19.5 at
+// L=16; small calls 12.5 / 11.7 up to L=16 and 12.5 / 16.5 at L=24.  A forced
+// layout or segment count keeps the other kernels.
+constexpr int64_t STEP_MAX_L = 16;
+bool step_path(const SelArgs& a) {
+  return a.L <= STEP_MAX_L && !a.ckpt && !a.s_out && env_int("SW_SS_LAYOUT", 0) == 0 &&
+         env_int("SW_SS_SEGMENTS", 0) == 0;
+}
+
 template <typename IN>
 int launch_selective(const SelArgs& a) {
   hipStream_t s = current_stream();
   const int64_t N = a.N;
   const bool v = vector_path<IN>(a);
+  if (step_path(a)) {
+    // as the kernel these calls took before: refused while capturing, except
+    // where the 16-lane layout takes them
+    if (!row16_path<IN>(a)) {
+      const int st = refuse_capture(s, "the per-stream scratch (tickets and carries)");
+      if (st != SW_OK) return st;
+    }
+    return launch_step<IN>(a, s);
+  }
   if (row16_path<IN>(a)) return launch_row16<IN>(a, s);
   if (N <= 8) return launch_npl<IN, 1>(a, v, s);
   if (N <= 16) return launch_npl<IN, 2>(a, v, s);
@@ -685,7 +709,7 @@ int selective_fwd(const SelArgs& a) {
 SelPlan selective_plan(const SelArgs& a, int cus) {
   SelPlan q;
   if (a.B * a.D == 0 || a.L == 0) return q;
-  if (a.bf16_in ? row16_path<uint16_t>(a) : row16_path<float>(a))
+  if (!step_path(a) && (a.bf16_in ? row16_path<uint16_t>(a) : row16_path<float>(a)))
     return a.bf16_in ? plan_row16<uint16_t>(a, cus) : plan_row16<float>(a, cus);
   q.layout = 8;
   q.nseg = 1;

@@ -386,6 +386,8 @@ void keep_pool_memory(int dev) {
   pool_ready[dev] = true;
 }
 
+}  // namespace
+
 // A call that needs the per-stream scratch or a workspace cannot be captured
 // into a HIP graph: a replay would repeat the ticket range and epoch the host
 // handed out (the tickets are spent, so the replayed kernel writes nothing),
@@ -404,8 +406,6 @@ int refuse_capture(hipStream_t s, const char* what) {
                 "is active)", what);
   return SW_OK;
 }
-
-}  // namespace
 
 ScratchSession::ScratchSession() {}
 

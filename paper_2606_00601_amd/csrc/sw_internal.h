@@ -27,6 +27,9 @@ void note_launch(const char* fmt, ...) __attribute__((format(printf, 1, 2)));
 // to *cus; returns SW_OK or SW_ERR_HIP with the message set.
 int device_cus(int* cus);
 
+// SW_ERR_UNSUPPORTED (naming `what`) while stream `s` is capturing, else SW_OK.
+int refuse_capture(hipStream_t s, const char* what);
+
 // Zero `words` 32-bit words with a plain kernel (no memset node).
 int zero_words(uint32_t* p, size_t words, hipStream_t s);
 
