@@ -658,12 +658,18 @@ bool vector_path(const SelArgs& a) {
   return a.vec && fits && ((uintptr_t)a.Bm % 16 == 0) && ((uintptr_t)a.Cm % 16 == 0);
 }
 
-// N = 16 on the vector path: one state per lane, 16-lane rows
-// (selective_scan16.hip); SW_SS_LAYOUT=8 keeps the 8-lane layout.
+// N = 16 with 16-byte aligned B and C: one state per lane, 16-lane rows
+// (selective_scan16.hip), whatever the rows' length and alignment;
+// SW_SS_LAYOUT=8 keeps the 8-lane layout.
 template <typename IN>
 bool row16_path(const SelArgs& a) {
-  return vector_path<IN>(a) && env_int("SW_SS_LAYOUT", 16) == 16 &&
-         row16_fits(a.D, a.N, a.L, sizeof(IN));
+  return (uintptr_t)a.Bm % 16 == 0 && (uintptr_t)a.Cm % 16 == 0 &&
+         env_int("SW_SS_LAYOUT", 16) == 16 && row16_fits(a.D, a.N, a.L, sizeof(IN));
+}
+// ... whose rows are whole aligned vectors
+template <typename IN>
+bool row16_whole_vectors(const SelArgs& a) {
+  return row16_path<IN>(a) && a.vec && a.L % (16 / (int64_t)sizeof(IN)) == 0;
 }
 
 // Calls of at most 16 steps take the kernel of selective_step.hip, which moves
@@ -684,16 +690,15 @@ int launch_selective(const SelArgs& a) {
   hipStream_t s = current_stream();
   const int64_t N = a.N;
   const bool v = vector_path<IN>(a);
-  if (step_path(a)) {
-    // as the kernel these calls took before: refused while capturing, except
-    // where the 16-lane layout takes them
-    if (!row16_path<IN>(a)) {
-      const int st = refuse_capture(s, "the per-stream scratch (tickets and carries)");
-      if (st != SW_OK) return st;
-    }
-    return launch_step<IN>(a, s);
+  const bool step = step_path(a), r16 = row16_path<IN>(a);
+  if ((step || r16) && !row16_whole_vectors<IN>(a)) {
+    // these calls are refused while a stream captures, like those of the
+    // 8-lane kernel (whose scratch a replay would find spent)
+    const int st = refuse_capture(s, "the per-stream scratch (tickets and carries)");
+    if (st != SW_OK) return st;
   }
-  if (row16_path<IN>(a)) return launch_row16<IN>(a, s);
+  if (step) return launch_step<IN>(a, s);
+  if (r16) return launch_row16<IN>(a, s);
   if (N <= 8) return launch_npl<IN, 1>(a, v, s);
   if (N <= 16) return launch_npl<IN, 2>(a, v, s);
   if (N <= 32) return launch_npl<IN, 4>(a, v, s);
@@ -720,7 +725,7 @@ SelPlan selective_plan(const SelArgs& a, int cus) {
 int selective_states_fwd(const SelArgs& a, bool* taken) {
   *taken = false;
   if (a.N != 16 || !a.ckpt || a.z || a.y_bf16 || a.s_out) return SW_OK;
-  if (a.bf16_in ? !row16_path<uint16_t>(a) : !row16_path<float>(a)) return SW_OK;
+  if (a.bf16_in ? !row16_whole_vectors<uint16_t>(a) : !row16_whole_vectors<float>(a)) return SW_OK;
   *taken = true;
   hipStream_t s = current_stream();
   return a.bf16_in ? launch_row16_states<uint16_t>(a, s) : launch_row16_states<float>(a, s);

@@ -79,12 +79,12 @@ constexpr int R16_LA = 2;                   // read-ahead, in 4-step blocks
 constexpr int R16_NS = 4;                   // rotating operand sets
 constexpr float R16_LOG2E = 1.4426950408889634f;
 // A byte offset past the end of every buffer resource of the kernel (their
-// sizes stay below 2^31 - 16): a load there returns zeros and moves no
+// sizes stay below 2^31 - 2^14): a load there returns zeros and moves no
 // memory.  The super-tile of delta and x run ahead of the walk takes it for
 // steps past the segment, so that no row reads the start of the next one
 // (6% of those bytes at L = 2048 in bf16).  The tiles of B, C and of x for
 // the D skip run ahead too, but only a tile, and mostly hit L2.
-constexpr int32_t R16_OOB = 0x7FFFFFF0;
+constexpr int32_t R16_OOB = 0x7FFFFF00;
 static_assert(R16_NB == 8 && R16_NB % R16_NS == 0 && R16_LA < R16_NS,
               "operand sets must rotate over a tile");
 
@@ -125,6 +125,79 @@ struct R16Ops {
   float4 b, c;
 };
 
+// Raw registers for COUNT consecutive elements at any element of a row, for
+// calls whose rows are not 16-byte aligned (RAG below).  fp32: the elements
+// from a 4-byte aligned address.  bf16: the COUNT / 2 + 1 dwords that cover
+// them.  A vector that would cross the row's end is read from COUNT elements
+// before it instead, so no load leaves the tensor; get() shifts it back by
+// `sh`: the elements stepped back, plus 1 (bf16) where the first element sits
+// in the high half of its dword.
+template <typename IN, int COUNT>
+struct RagVec {
+  static constexpr bool F32 = sizeof(IN) == 4;
+  static constexpr int NW = F32 ? COUNT : COUNT / 2 + 1;
+  uint32_t w[NW];
+  // from the (4-byte aligned) byte offset `off`
+  template <int POL = 0>
+  __device__ __forceinline__ void load_buf(__amdgpu_buffer_rsrc_t rs, int32_t off) {
+    if constexpr (COUNT == 4 && !F32) {
+      const uint2 v =
+          __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, POL));
+      w[0] = v.x;
+      w[1] = v.y;
+    } else {
+#pragma unroll
+      for (int q = 0; q < NW / 4; ++q) {
+        const uint4 v = __builtin_bit_cast(
+            uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * q, 0, POL));
+        w[4 * q] = v.x;
+        w[4 * q + 1] = v.y;
+        w[4 * q + 2] = v.z;
+        w[4 * q + 3] = v.w;
+      }
+    }
+    if constexpr (!F32)
+      w[NW - 1] = __builtin_bit_cast(
+          uint32_t, __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * (NW - 1), 0, POL));
+  }
+  // the elements as fp32; tail (wave-uniform): some lane's sh may exceed 1
+  __device__ __forceinline__ void get(float (&out)[COUNT], int sh, bool tail) const {
+    uint32_t v[NW];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) v[i] = w[i];
+    constexpr int UNIT = F32 ? 1 : 2;  // elements per dword
+    if (tail) {
+#pragma unroll
+      for (int m = 4; m >= 1; m /= 2) {  // dwords
+        const bool on = (sh & (m * UNIT)) != 0;
+#pragma unroll
+        for (int i = 0; i + m < NW; ++i) v[i] = on ? v[i + m] : v[i];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < COUNT / UNIT; ++i) {
+      if constexpr (F32) {
+        out[i] = __uint_as_float(v[i]);
+      } else {
+        const uint32_t o = __builtin_amdgcn_alignbit(v[i + 1], v[i], 16u * ((uint32_t)sh & 1u));
+        out[2 * i] = bf16_lo(o);
+        out[2 * i + 1] = bf16_hi(o);
+      }
+    }
+  }
+};
+
+// The resource over `bytes` bytes from `p` for RagVec loads: it starts and
+// ends on a dword (a dword that holds an element of the tensor is inside its
+// allocation); *h: the element `p` is at, from the resource's start.
+template <typename IN>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rag_rsrc(const IN* p, uint32_t bytes, int* h) {
+  const uintptr_t at = (uintptr_t)p;
+  *h = (int)((at & 3) / sizeof(IN));
+  return buffer_rsrc((const void*)(at & ~(uintptr_t)3),
+                     (bytes + (uint32_t)(at & 3) + 3u) & ~3u);
+}
+
 // Segment modes of the kernel (see the top of the file).
 //   R16_SEG_ENDS, R16_SEG_FWD: launches (1) and (3) of the records form;
 //   R16_SEG_ALL, R16_SEG_CORR: launches (1) and (3) of the correction form.
@@ -149,12 +222,24 @@ constexpr int R16_MAX_SEG = 16;  // segments per row at most
 // magnitude of the state, and of y (an fp32 walk rounds at 2^-24 of it).
 constexpr float R16_CORR_EPS = 1.4901161193847656e-08f;  // 2^-26
 
-// The record words of the segment starting at step t of a row, in y's memory
-// (fp32 or bf16 elements; t is a multiple of 64, so the words are aligned).
-__device__ __forceinline__ float* seg_words(void* yv, bool ybf, int64_t row, int64_t L,
-                                            int64_t t) {
-  return ybf ? reinterpret_cast<float*>(static_cast<uint16_t*>(yv) + row * L + t)
-             : static_cast<float*>(yv) + row * L + t;
+// Word i of the records of the segment starting at step t of a row, in y's
+// memory (fp32 or bf16 elements; a bf16 row of odd length starts at an odd
+// element, so there a word is two 2-byte accesses).
+__device__ __forceinline__ float rec_load(const void* yv, bool ybf, int64_t row, int64_t L,
+                                          int64_t t, int i) {
+  if (!ybf) return static_cast<const float*>(yv)[row * L + t + i];
+  const uint16_t* const p = static_cast<const uint16_t*>(yv) + row * L + t + 2 * i;
+  return __uint_as_float((uint32_t)p[0] | ((uint32_t)p[1] << 16));
+}
+__device__ __forceinline__ void rec_store(void* yv, bool ybf, int64_t row, int64_t L, int64_t t,
+                                          int i, float v) {
+  if (!ybf) {
+    static_cast<float*>(yv)[row * L + t + i] = v;
+  } else {
+    uint16_t* const p = static_cast<uint16_t*>(yv) + row * L + t + 2 * i;
+    p[0] = (uint16_t)(__float_as_uint(v) & 0xffffu);
+    p[1] = (uint16_t)(__float_as_uint(v) >> 16);
+  }
 }
 
 // OPT: the optional Mamba-block inputs (flags, z, delta bias) are read;
@@ -167,7 +252,10 @@ __device__ __forceinline__ float* seg_words(void* yv, bool ybf, int64_t row, int
 // segment (the logical order is spread over the XCDs in contiguous ranges);
 // a row has nseg segments of Lseg steps, the last one taking the rest
 // (shorter than Lseg, or up to a super-tile longer).
-template <typename IN, bool OPT, bool CK, int SEG>
+// RAG: rows of any length at any element alignment (L at least a lane's V
+// steps): loads through RagVec, steps past the row's end made identity steps
+// one by one, y stored by element in the last tile (bf16 y in every tile).
+template <typename IN, bool OPT, bool CK, int SEG, bool RAG>
 __global__ __launch_bounds__(256) void selective_row16_kernel(
     const IN* __restrict__ x, const IN* __restrict__ delta, const float* __restrict__ A,
     const IN* __restrict__ Bm, const IN* __restrict__ Cm, const float* __restrict__ Dskip,
@@ -213,15 +301,33 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
   // resources start at the segment's first step (row strides stay L)
   const uint32_t rows_bytes = (uint32_t)((rows * L - ts) * ES);
   const uint32_t bc_bytes = (uint32_t)((L - ts) * R16_N * ES);
-  const __amdgpu_buffer_rsrc_t rx = buffer_rsrc(x + row0 * L + ts, rows_bytes);
-  const __amdgpu_buffer_rsrc_t rd = buffer_rsrc(delta + row0 * L + ts, rows_bytes);
+  int hx = 0, hd = 0, hz = 0;  // RAG: where x, delta and z start in their resources
+  const __amdgpu_buffer_rsrc_t rx = RAG ? rag_rsrc(x + row0 * L + ts, rows_bytes, &hx)
+                                        : buffer_rsrc(x + row0 * L + ts, rows_bytes);
+  const __amdgpu_buffer_rsrc_t rd = RAG ? rag_rsrc(delta + row0 * L + ts, rows_bytes, &hd)
+                                        : buffer_rsrc(delta + row0 * L + ts, rows_bytes);
   const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(Bm + (b * L + ts) * R16_N, bc_bytes);
   const __amdgpu_buffer_rsrc_t rc = buffer_rsrc(Cm + (b * L + ts) * R16_N, bc_bytes);
   // the gate's input; without a gate (OPT set) the same loads read x (cached),
   // so that every path of one instantiation issues the same loads
+  const IN* const zsrc = ((flags & SEL_GATED) ? z : x) + row0 * L + ts;
   const __amdgpu_buffer_rsrc_t rz =
-      buffer_rsrc(((flags & SEL_GATED) ? z : x) + row0 * L + ts, rows_bytes);
+      RAG ? rag_rsrc(zsrc, rows_bytes, &hz) : buffer_rsrc(zsrc, rows_bytes);
   const int32_t lrow = (int32_t)((dcl - d0) * L * ES);  // byte offset of this lane's row
+  // RAG: the row's elements from the segment's start, and the byte offset and
+  // the shift of a vector of cnt elements at step t in an array that starts
+  // at element h of its resource
+  const int32_t Lr32 = (int32_t)(L - ts);
+  const int32_t lrow_e = (int32_t)((dcl - d0) * L);
+  auto rag_at = [&](int32_t t, int cnt, int h) { return lrow_e + h + (t < Lr32 - cnt ? t : Lr32 - cnt); };
+  auto rag_off = [&](int32_t t, int cnt, int h) {
+    const int32_t e = rag_at(t, cnt, h);
+    return ES == 4 ? e * 4 : (e & ~1) * 2;
+  };
+  auto rag_shift = [&](int32_t t, int cnt, int h) {
+    const int32_t back = t < Lr32 - cnt ? 0 : t - (Lr32 - cnt);
+    return back + (ES == 4 ? 0 : (rag_at(t, cnt, h) & 1));
+  };
 
   const float Al = A[dcl * R16_N + n] * R16_LOG2E;
   const float dsk = Dskip ? Dskip[dcl] : 0.0f;
@@ -230,7 +336,7 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
   float h = (h0 && sg == 0) ? h0[(b * D + dcl) * R16_N + n] : 0.0f;
   if constexpr (SEG == R16_SEG_FWD || CORR) {
     // the initial state the fold left in this segment's first words of y
-    if (sg > 0) h = seg_words(yv, ybf, b * D + dcl, L, ts)[n];
+    if (sg > 0) h = rec_load(yv, ybf, b * D + dcl, L, ts, n);
   }
   // CORR: the initial state, and the magnitude of the segment's own terms
   const float hin = h;
@@ -263,16 +369,22 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
   };
 
   // ---- delta / x of a super-tile: this lane's V steps starting at V*n
-  RawVec<IN, V> dlr, xr;  // raw bits of the next super-tile
+  // raw bits of the next super-tile
+  typename std::conditional<RAG, RagVec<IN, V>, RawVec<IN, V>>::type dlr, xr;
   float dl[V], dx[V];     // delta and delta*x of the current one
   auto fetch_dx = [&](int64_t sup) {
     // Ls is a multiple of V: a lane's V steps are all in or all out
     const int32_t t = (int32_t)(sup * ST) + V * n;
-    const int32_t off = t < Ls32 ? lrow + t * ES : R16_OOB;
     // delta is read once (non-temporal); x is read again for the y of its
     // tiles (fetch_yx), so this read keeps the default policy
-    dlr.template load_buf<SW_NT>(rd, off);
-    xr.load_buf(rx, off);
+    if constexpr (RAG) {
+      dlr.template load_buf<SW_NT>(rd, t < Ls32 ? rag_off(t, V, hd) : R16_OOB);
+      xr.load_buf(rx, t < Ls32 ? rag_off(t, V, hx) : R16_OOB);
+    } else {
+      const int32_t off = t < Ls32 ? lrow + t * ES : R16_OOB;
+      dlr.template load_buf<SW_NT>(rd, off);
+      xr.load_buf(rx, off);
+    }
   };
   auto widen_dx = [&](int64_t sup) {
     // steps past the segment are identity steps (a = 1, u = 0): the loads
@@ -280,14 +392,29 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
     // options turn delta = 0 into something else; Ls is a multiple of V, so
     // a lane's V steps are all inside or all past
     const bool past = OPT && (int32_t)(sup * ST) + V * n >= Ls32;
+    float draw[V], xraw[V];
+    if constexpr (RAG) {
+      const int32_t t = (int32_t)(sup * ST) + V * n;
+      const bool tail = (int32_t)(sup * ST) + ST > Lr32;
+      dlr.get(draw, rag_shift(t, V, hd), tail);
+      xr.get(xraw, rag_shift(t, V, hx), tail);
+    } else {
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        draw[k] = dlr.get(k);
+        xraw[k] = xr.get(k);
+      }
+    }
 #pragma unroll
     for (int k = 0; k < V; ++k) {
-      float dv = dlr.get(k), xv = xr.get(k);
+      float dv = draw[k], xv = xraw[k];
       if constexpr (OPT) {
         dv += dbv;
         if (flags & SEL_SOFTPLUS) dv = softplus_f32(dv);
         if (past) dv = xv = 0.0f;
       }
+      // a lane's steps may straddle the row's end here
+      if (RAG && (int32_t)(sup * ST) + V * n + k >= Ls32) dv = xv = 0.0f;
       dl[k] = dv;
       dx[k] = dv * xv;
       if constexpr (DSUM) dsum += dv;
@@ -298,12 +425,19 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
   // states 8*(n/8) .. +7 over steps 4*(n%8) .. +3 with 16-byte LDS reads,
   // the two halves meet through a row_ror:8 DPP add, and lanes n < 8 store.
   const int rq = n % 8, rh = n / 8;
-  RawVec<IN, 4> yxr, yzr;  // raw x and z of those four steps, for the tile awaiting its reduce
+  // raw x and z of those four steps, for the tile awaiting its reduce
+  typename std::conditional<RAG, RagVec<IN, 4>, RawVec<IN, 4>>::type yxr, yzr;
   auto fetch_yx = [&](int64_t kt) {
     if constexpr (NOY) return;
-    const int32_t off = lrow + (int32_t)((kt * R16_T + 4 * rq) * ES);
-    yxr.template load_buf<SW_NT>(rx, off);  // the last read of x
-    if constexpr (OPT) yzr.template load_buf<SW_NT>(rz, off);
+    const int32_t t = (int32_t)(kt * R16_T) + 4 * rq;
+    if constexpr (RAG) {
+      yxr.template load_buf<SW_NT>(rx, rag_off(t, 4, hx));
+      if constexpr (OPT) yzr.template load_buf<SW_NT>(rz, rag_off(t, 4, hz));
+    } else {
+      const int32_t off = lrow + t * ES;
+      yxr.template load_buf<SW_NT>(rx, off);  // the last read of x
+      if constexpr (OPT) yzr.template load_buf<SW_NT>(rz, off);
+    }
   };
   float* const p_w = &sm.p[w][r * R16_PRS + n * R16_TS];
   const float* const p_r = &sm.p[w][r * R16_PRS + 8 * rh * R16_TS + 4 * rq];
@@ -346,8 +480,17 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
     // ALL: the first super-tile of every segment but the first holds the
     // records until the correction walk writes its y
     const bool skip = ALL && sg > 0 && t < ST;
+    // RAG: the tile that holds the row's end stores by element, and so does
+    // bf16 y, whose rows may start at an odd element
+    const bool by_elem = RAG && (int32_t)(kt * R16_T) + R16_T > Ls32;
     if constexpr (OPT) {
-      if (s_out) {
+      if (s_out && by_elem) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          __builtin_amdgcn_raw_buffer_store_b32(
+              __float_as_uint(s4[q]), rs,
+              (int)(mine && t + q < Ls32 ? s_lrow + 4u * (uint32_t)(t + q) : s_bytes), 0, 0);
+      } else if (s_out) {
         const uint32_t so = mine ? s_lrow + 4u * (uint32_t)t : s_bytes;
         __builtin_amdgcn_raw_buffer_store_b128(
             __builtin_bit_cast(sw_u32x4, make_float4(s4[0], s4[1], s4[2], s4[3])), rs, (int)so,
@@ -357,7 +500,19 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
 #pragma unroll
     for (int q = 0; q < 4; ++q) s4[q] *= gt[q];
     const uint32_t yo = (mine && !skip) ? y_lrow + ys * (uint32_t)t : y_bytes;
-    if (ybf)
+    if (RAG && ybf) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        __builtin_amdgcn_raw_buffer_store_b16(
+            (short)bf16_rne(s4[q]), ry,
+            (int)(mine && t + q < Ls32 ? yo + 2u * (uint32_t)q : y_bytes), 0, 0);
+    } else if (by_elem) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        __builtin_amdgcn_raw_buffer_store_b32(
+            __float_as_uint(s4[q]), ry,
+            (int)(mine && !skip && t + q < Ls32 ? yo + 4u * (uint32_t)q : y_bytes), 0, 0);
+    } else if (ybf)
       __builtin_amdgcn_raw_buffer_store_b64(
           __builtin_bit_cast(sw_u32x2, make_uint2(bf16x2_rne(s4[0], s4[1]), bf16x2_rne(s4[2], s4[3]))),
           ry, (int)yo, 0, SW_NT);
@@ -397,11 +552,23 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
     const bool has_next = kt + 1 < ntile;
     stage_bc(sbr[(TT + 1) & 1], scr[(TT + 1) & 1], nbuf);
     fetch_bc(sbr[(TT + 1) & 1], scr[(TT + 1) & 1], kt + 3);
-    float yx[4], gt[4];
+    float yx[4], yz[4], gt[4];
+    if constexpr (RAG && !NOY) {
+      const int32_t t = (int32_t)(kt * R16_T) + 4 * rq;
+      const bool tail = (int32_t)(kt * R16_T) + R16_T > Lr32;
+      yxr.get(yx, rag_shift(t, 4, hx), tail);
+      if constexpr (OPT) yzr.get(yz, rag_shift(t, 4, hz), tail);
+    } else if constexpr (!RAG) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        yx[q] = yxr.get(q);
+        if constexpr (OPT) yz[q] = yzr.get(q);
+      }
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      yx[q] = yxr.get(q);
-      gt[q] = (OPT && (flags & SEL_GATED)) ? silu_f32(yzr.get(q)) : 1.0f;
+      if constexpr (RAG && NOY) yx[q] = 0.0f;
+      gt[q] = (OPT && !NOY && (flags & SEL_GATED)) ? silu_f32(yz[q]) : 1.0f;
     }
     fetch_yx(kt + 1);
     wg_barrier();
@@ -513,9 +680,8 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
 #pragma unroll
     for (int m = 8; m >= 1; m /= 2) dsum += __shfl_xor(dsum, m, R16_N);
     if (dok) {
-      float* wd = seg_words(yv, ybf, b * D + d, L, ts + Ls);
-      wd[n] = __builtin_amdgcn_exp2f(Al * dsum);
-      wd[R16_N + n] = h;
+      rec_store(yv, ybf, b * D + d, L, ts + Ls, n, __builtin_amdgcn_exp2f(Al * dsum));
+      rec_store(yv, ybf, b * D + d, L, ts + Ls, R16_N + n, h);
     }
   } else if constexpr (SEG == R16_STATES) {
     if (h_last && dok) h_last[(b * D + d) * R16_N + n] = h;
@@ -532,11 +698,10 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
       if (dok) {
         const float P = __builtin_amdgcn_exp2f(Al * dsum);
         if (sg < nseg - 1) {
-          float* wd = seg_words(yv, false, b * D + d, L, ts + Ls);
-          wd[n] = P;
-          wd[R16_N + n] = h;
+          rec_store(yv, false, b * D + d, L, ts + Ls, n, P);
+          rec_store(yv, false, b * D + d, L, ts + Ls, R16_N + n, h);
         } else {
-          seg_words(yv, false, b * D + d, L, ts)[2 * R16_N + n] = P;
+          rec_store(yv, false, b * D + d, L, ts, 2 * R16_N + n, P);
         }
       }
     }
@@ -563,9 +728,8 @@ __global__ __launch_bounds__(256) void row16_fold_kernel(void* __restrict__ yv, 
 #pragma unroll
   for (int sgi = 1; sgi < R16_MAX_SEG; ++sgi) {
     if (sgi < nseg) {
-      const float* wd = seg_words(yv, ybf, row, L, sgi * Lseg);
-      P[sgi] = wd[n];
-      U[sgi] = wd[R16_N + n];
+      P[sgi] = rec_load(yv, ybf, row, L, sgi * Lseg, n);
+      U[sgi] = rec_load(yv, ybf, row, L, sgi * Lseg, R16_N + n);
     }
   }
   float h = 0.0f;
@@ -573,7 +737,7 @@ __global__ __launch_bounds__(256) void row16_fold_kernel(void* __restrict__ yv, 
   for (int sgi = 1; sgi < R16_MAX_SEG; ++sgi) {
     if (sgi < nseg) {
       h = sgi == 1 ? U[sgi] : __builtin_fmaf(P[sgi], h, U[sgi]);
-      seg_words(yv, ybf, row, L, sgi * Lseg)[n] = h;
+      rec_store(yv, ybf, row, L, sgi * Lseg, n, h);
     }
   }
 }
@@ -594,9 +758,8 @@ __global__ __launch_bounds__(256) void row16_fold_corr_kernel(float* __restrict_
 #pragma unroll
   for (int sgi = 1; sgi < R16_MAX_SEG; ++sgi) {
     if (sgi < nseg) {
-      const float* wd = seg_words(y, false, row, L, sgi * Lseg);
-      P[sgi] = wd[n];  // of segment sgi - 1
-      U[sgi] = wd[R16_N + n];
+      P[sgi] = rec_load(y, false, row, L, sgi * Lseg, n);  // of segment sgi - 1
+      U[sgi] = rec_load(y, false, row, L, sgi * Lseg, R16_N + n);
     }
   }
   float h = 0.0f;
@@ -604,11 +767,11 @@ __global__ __launch_bounds__(256) void row16_fold_corr_kernel(float* __restrict_
   for (int sgi = 1; sgi < R16_MAX_SEG; ++sgi) {
     if (sgi < nseg) {
       h = sgi == 1 ? U[sgi] : __builtin_fmaf(P[sgi], h, U[sgi]);
-      seg_words(y, false, row, L, sgi * Lseg)[n] = h;
+      rec_store(y, false, row, L, sgi * Lseg, n, h);
     }
   }
   if (h_last) {
-    const float Pl = seg_words(y, false, row, L, (nseg - 1) * Lseg)[2 * R16_N + n];
+    const float Pl = rec_load(y, false, row, L, (nseg - 1) * Lseg, 2 * R16_N + n);
     h_last[row * R16_N + n] = __builtin_fmaf(Pl, h, h_last[row * R16_N + n]);
   }
 }
@@ -629,13 +792,13 @@ bool quad_fits(const SelArgs& a);
 template <typename IN>
 int launch_quad(const SelArgs& a, int64_t nseg, int64_t Lseg, hipStream_t s);
 
-// True when the N = 16 layout can take the call: vector-aligned rows, and
-// every byte offset of a workgroup (including loads run ahead past the end)
-// below 2^31.
+// True when the N = 16 layout can take the call: rows of at least a lane's
+// vector of steps, and every byte offset of a workgroup (including loads run
+// ahead past the end) below 2^31.
 bool row16_fits(int64_t D, int64_t N, int64_t L, size_t es) {
   if (N != R16_N) return false;
   const int64_t vstep = 16 / (int64_t)es;
-  if (L % vstep != 0) return false;
+  if (L < vstep) return false;
   const int64_t pad = 4 * R16_N * vstep;
   return R16_ROWS * (L + pad) * (int64_t)es < ((int64_t)1 << 31) &&
          (L + pad) * R16_N * (int64_t)es < ((int64_t)1 << 31) && D > 0;
@@ -733,7 +896,7 @@ N16Plan plan_n16(const SelArgs& a, int64_t ndb, int cus) {
   const int64_t L = a.L, st = R16_N * (16 / (int64_t)sizeof(IN));
   const int64_t quad_env = env_i64("SW_SS_QUAD"), seg_env = env_i64("SW_SS_SEGMENTS");
   const int64_t form_env = env_i64("SW_SS_SEGFORM");
-  const bool qfits = quad_fits<IN>(a);
+  const bool qfits = a.vec && quad_fits<IN>(a);
   const bool quad_only = quad_env == 1 && qfits;
   const bool with_quad = qfits && quad_env != 0 && (seg_env < 0 || quad_only);
   const bool corr_ok = !a.y_bf16;
@@ -798,12 +961,12 @@ N16Plan plan_n16(const SelArgs& a, int64_t ndb, int cus) {
   return best;
 }
 
-template <typename IN, bool OPT>
+template <typename IN, bool OPT, bool RAG>
 void launch_row16_segments(const SelArgs& a, int64_t ndb, uint32_t flags, int64_t nseg,
                            int64_t Lseg, hipStream_t s) {
   const int64_t R = a.B * a.D;
   const int64_t rblocks = a.B * ndb;
-  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_ENDS>),
+  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_ENDS, RAG>),
                      dim3((unsigned)(rblocks * (nseg - 1))), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,
                      static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
@@ -812,7 +975,7 @@ void launch_row16_segments(const SelArgs& a, int64_t ndb, uint32_t flags, int64_
   const int64_t lanes = R * R16_N;
   hipLaunchKernelGGL(row16_fold_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, s,
                      a.y, a.y_bf16, R, a.L, nseg, Lseg);
-  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_FWD>),
+  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_FWD, RAG>),
                      dim3((unsigned)(rblocks * nseg)), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,
                      static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
@@ -826,24 +989,56 @@ void launch_row16_segments(const SelArgs& a, int64_t ndb, uint32_t flags, int64_
 // state and corrects h_last; (3) every segment but the first walks again from
 // its initial state, rewriting y, until the part carried in from the start
 // is negligible against the segment's own terms (R16_CORR_EPS).
-template <typename IN, bool OPT>
+template <typename IN, bool OPT, bool RAG>
 void launch_row16_corr(const SelArgs& a, int64_t ndb, uint32_t flags, int64_t nseg,
                        int64_t Lseg, hipStream_t s) {
   const int64_t R = a.B * a.D;
   const int64_t rblocks = a.B * ndb;
-  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_ALL>),
+  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_ALL, RAG>),
                      dim3((unsigned)(rblocks * nseg)), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,
                      static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
                      static_cast<const IN*>(a.z), a.delta_bias, a.h0, a.y, a.h_last, a.D, a.L,
                      ndb, flags, nullptr, (int64_t)0, a.s_out, nseg, Lseg);
   launch_fold_corr(static_cast<float*>(a.y), a.h_last, R, a.L, nseg, Lseg, s);
-  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_CORR>),
+  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_CORR, RAG>),
                      dim3((unsigned)(rblocks * (nseg - 1))), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,
                      static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
                      static_cast<const IN*>(a.z), a.delta_bias, a.h0, a.y, nullptr, a.D, a.L,
                      ndb, flags, nullptr, (int64_t)0, a.s_out, nseg, Lseg);
+}
+
+// Whether the call's rows are whole 16-byte vectors: otherwise it takes the
+// RAG variant of the kernels.
+template <typename IN>
+bool row16_aligned(const SelArgs& a) {
+  return a.vec && a.L % (16 / (int64_t)sizeof(IN)) == 0;
+}
+
+template <typename IN, bool OPT, bool RAG>
+int launch_row16_t(const SelArgs& a, const N16Plan& p, int64_t ndb, hipStream_t s) {
+  const uint32_t flags = (a.softplus ? SEL_SOFTPLUS : 0u) | (a.y_bf16 ? SEL_Y_BF16 : 0u) |
+                         (a.z ? SEL_GATED : 0u);
+  const int64_t nseg = p.nseg, Lseg = p.Lseg;
+  if (nseg > 1) {
+    if (p.corr)
+      launch_row16_corr<IN, OPT, RAG>(a, ndb, flags, nseg, Lseg, s);
+    else
+      launch_row16_segments<IN, OPT, RAG>(a, ndb, flags, nseg, Lseg, s);
+    note_launch("selective_row16_kernel: %lld segments of %lld steps, %s form (3 launches)",
+                (long long)nseg, (long long)Lseg, p.corr ? "correction" : "records");
+    return check_launch("selective_row16_kernel (segments)");
+  }
+  auto kern = a.ckpt ? selective_row16_kernel<IN, OPT, true, R16_WHOLE, RAG>
+                     : selective_row16_kernel<IN, OPT, false, R16_WHOLE, RAG>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(a.B * ndb)), dim3(256), 0, s,
+                     static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,
+                     static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
+                     static_cast<const IN*>(a.z), a.delta_bias, a.h0, a.y, a.h_last, a.D, a.L,
+                     ndb, flags, a.ckpt, (a.L + 7) / 8, a.s_out, (int64_t)1, a.L);
+  note_launch("selective_row16_kernel: whole rows");
+  return check_launch("selective_row16_kernel");
 }
 
 template <typename IN>
@@ -857,44 +1052,17 @@ int launch_row16(const SelArgs& a, hipStream_t s) {
   if (device_cus(&cus) != SW_OK) cus = 256;  // a forced choice needs no device facts
   const N16Plan p = plan_n16<IN>(a, ndb, cus);
   if (p.quad) return launch_quad<IN>(a, p.nseg, p.Lseg, s);
-  const uint32_t flags = (a.softplus ? SEL_SOFTPLUS : 0u) | (a.y_bf16 ? SEL_Y_BF16 : 0u) |
-                         (a.z ? SEL_GATED : 0u);
-  const int64_t nseg = p.nseg, Lseg = p.Lseg;
-  if (nseg > 1 && p.corr) {
-    if (opt)
-      launch_row16_corr<IN, true>(a, ndb, flags, nseg, Lseg, s);
-    else
-      launch_row16_corr<IN, false>(a, ndb, flags, nseg, Lseg, s);
-    note_launch("selective_row16_kernel: %lld segments of %lld steps, correction form (3 launches)",
-                (long long)nseg, (long long)Lseg);
-    return check_launch("selective_row16_kernel (segments, correction form)");
-  }
-  if (nseg > 1) {
-    if (opt)
-      launch_row16_segments<IN, true>(a, ndb, flags, nseg, Lseg, s);
-    else
-      launch_row16_segments<IN, false>(a, ndb, flags, nseg, Lseg, s);
-    note_launch("selective_row16_kernel: %lld segments of %lld steps, records form (3 launches)",
-                (long long)nseg, (long long)Lseg);
-    return check_launch("selective_row16_kernel (segments)");
-  }
-  auto kern = opt ? (a.ckpt ? selective_row16_kernel<IN, true, true, R16_WHOLE>
-                            : selective_row16_kernel<IN, true, false, R16_WHOLE>)
-                  : (a.ckpt ? selective_row16_kernel<IN, false, true, R16_WHOLE>
-                            : selective_row16_kernel<IN, false, false, R16_WHOLE>);
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, s, static_cast<const IN*>(a.x),
-                     static_cast<const IN*>(a.delta), a.A, static_cast<const IN*>(a.Bm),
-                     static_cast<const IN*>(a.Cm), a.Dskip, static_cast<const IN*>(a.z),
-                     a.delta_bias, a.h0, a.y, a.h_last, a.D, a.L, ndb, flags, a.ckpt,
-                     (a.L + 7) / 8, a.s_out, (int64_t)1, a.L);
-  note_launch("selective_row16_kernel: whole rows");
-  return check_launch("selective_row16_kernel");
+  if (row16_aligned<IN>(a))
+    return opt ? launch_row16_t<IN, true, false>(a, p, ndb, s)
+               : launch_row16_t<IN, false, false>(a, p, ndb, s);
+  return opt ? launch_row16_t<IN, true, true>(a, p, ndb, s)
+             : launch_row16_t<IN, false, true>(a, p, ndb, s);
 }
 
 // The states of a whole-row walk without y (R16_STATES): the 8-step
 // checkpoints into a.ckpt and, if given, h_last; x, delta, B, A, h0 and the
 // delta options are read, C, Dskip, z and y are not.  The call must satisfy
-// row16_fits and the forward's vector-path conditions.
+// row16_fits and have whole, aligned vectors in its rows.
 template <typename IN>
 int launch_row16_states(const SelArgs& a, hipStream_t s) {
   const int64_t ndb = (a.D + R16_ROWS - 1) / R16_ROWS;
@@ -903,8 +1071,8 @@ int launch_row16_states(const SelArgs& a, hipStream_t s) {
     return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range", (long long)grid);
   const bool opt = a.delta_bias || a.softplus;
   const uint32_t flags = a.softplus ? SEL_SOFTPLUS : 0u;
-  auto kern = opt ? selective_row16_kernel<IN, true, true, R16_STATES>
-                  : selective_row16_kernel<IN, false, true, R16_STATES>;
+  auto kern = opt ? selective_row16_kernel<IN, true, true, R16_STATES, false>
+                  : selective_row16_kernel<IN, false, true, R16_STATES, false>;
   // y is never written in this mode: x stands in for its pointer
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, s, static_cast<const IN*>(a.x),
                      static_cast<const IN*>(a.delta), a.A, static_cast<const IN*>(a.Bm),
