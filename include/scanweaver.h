@@ -50,9 +50,9 @@
  *    fp32, 16-byte aligned arrays and a workgroup's byte offsets below 2^31;
  *    the bare scan and its projection form when a row fits one chunk
  *    (L <= 2048) or the rows alone fill the GPU (B*D >= 8 per compute unit);
- *    sw_affine_scan_noalloc on every path (its look-back words live in a
- *    static array that each call clears with a fill kernel and starts from
- *    the same epoch and ticket, so a replay repeats the call exactly); and
+ *    sw_affine_scan_noalloc on every path (its records live in a
+ *    static array that each call writes before it reads, so a replay repeats
+ *    the call exactly); and
  *    the Blelloch schedule entry points.  A call that uses the scratch
  *    is not replay-safe (a replay would repeat the ticket range and epoch the
  *    host gave the captured launch), and the backward allocates a workspace
@@ -107,19 +107,17 @@ int sw_affine_scan_i32(const int32_t* a, const int32_t* bx, const int32_t* h0, i
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments, layout, results (within fp32 rounding of the same
  * schedule) and errors as sw_affine_scan, but no hipMalloc, hipFree or
- * allocating library routine is called: the look-back tickets and chunk
- * carries live in a static array in the library's device code (256 bytes +
+ * allocating library routine is called: the records of rows cut into
+ * segments live in a static array in the library's device code (256 bytes +
  * 24 bytes per chunk, 1.5 MiB for SW_NOALLOC_MAX_CHUNKS chunks), one copy per
  * GPU, held until the process ends; its address is looked up on the first
  * call on each device (make that call before capturing one into a HIP
- * graph).  Each call clears the part it uses with a fill kernel on the
- * call's stream before the scan.
- *   - Calls whose chunk-parallel look-back kernel would need more than
- *     SW_NOALLOC_MAX_CHUNKS chunks return SW_ERR_UNSUPPORTED before enqueuing
- *     anything.  That kernel runs when L > 2048 and B*D < 8 * (compute
- *     units); its chunk count is B * D * ceil(L / 2048).  Other calls (one
- *     chunk per row, or enough rows to give each its own workgroup) use no
- *     scratch and have no limit beyond sw_affine_scan's.
+ * graph).
+ *   - Calls with L > 2048, B*D < 8 * (compute units) and more than
+ *     SW_NOALLOC_MAX_CHUNKS chunks, B * D * ceil(L / 2048), return
+ *     SW_ERR_UNSUPPORTED before enqueuing anything.  Other calls (one chunk
+ *     per row, or enough rows to give each its own workgroup) use no scratch
+ *     and have no limit beyond sw_affine_scan's.
  *   - Every call on one GPU shares that GPU's array: two calls that may run
  *     at the same time on one GPU (on different streams, or from different
  *     host threads without ordering) race and give wrong results.  Order
@@ -132,7 +130,8 @@ int sw_affine_scan_noalloc(const float* a, const float* bx, const float* h0, flo
 /* Scan schedules of sw_affine_scan_schedule. */
 enum {
   SW_SCHED_DEFAULT = 0,  /* the library's: lane-sequential composition, DPP wavefront scan,
-                            LDS combine, decoupled look-back (what sw_affine_scan runs) */
+                            LDS combine, rows walked chunk by chunk, few long rows in
+                            segments (what sw_affine_scan runs) */
   SW_SCHED_BLELLOCH = 1  /* the paper's (Sec. 3.3): a Blelloch upsweep / root / downsweep tree
                             over 2048-pair chunks in LDS, then affine-prefix reconstruction;
                             one workgroup per row, chunk carries in registers */

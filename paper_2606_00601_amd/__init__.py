@@ -163,8 +163,8 @@ def affine_scan(a, bx, h0=None, out=None):
 
 def affine_scan_noalloc(a, bx, h0=None, out=None):
     """:func:`affine_scan` through the entry point that allocates no device
-    memory (its look-back scratch is a fixed array in the library; calls with
-    more than ``SW_NOALLOC_MAX_CHUNKS`` look-back chunks are refused).  With
+    memory (its scratch is a fixed array in the library; calls on few rows with
+    more than ``SW_NOALLOC_MAX_CHUNKS`` chunks of 2048 steps are refused).  With
     ``out`` given, the call itself allocates nothing."""
     return _affine(fast().sw_affine_scan_noalloc, "sw_affine_scan_noalloc", torch.float32, a, bx,
                    h0, out)

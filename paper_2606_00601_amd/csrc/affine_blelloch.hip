@@ -1,7 +1,7 @@
 // affine_blelloch.hip -- the bare affine scan with the paper's schedule: a
 // Blelloch tree over the affine pairs of Eq. (6) in LDS (Sec. 3.3), kept as
 // the reference point of the schedule ablation against the lane-sequential /
-// DPP / look-back schedule of affine_scan.hip.
+// DPP schedule of affine_scan.hip.
 //
 // One workgroup (256 lanes) owns one (b,d) row and walks it in chunks of
 // 2048 steps, the carry held in registers (the hierarchical level above the

@@ -2,44 +2,55 @@
 // gfx950, as a prefix scan over the affine pairs of Eq. (6) under the
 // composition of Eq. (7), for fp32 and for the int32 wraparound ring.
 //
-// One workgroup (4 wavefronts, 256 lanes) owns one chunk of K*256 consecutive
-// steps of one (b,d) row:
-//   1. each lane loads K consecutive (a, bx) with 16-byte vector loads
-//      (consecutive lanes read consecutive 16-byte pieces: fully coalesced) and
-//      composes them sequentially into its local inclusive prefixes;
+// One workgroup (4 wavefronts, 256 lanes) walks a row in chunks of 256*K
+// consecutive steps:
+//   1. each lane loads K consecutive (a, bx) with 16-byte vector loads (a
+//      wavefront reads one contiguous run) and composes them sequentially
+//      into its local inclusive prefixes;
 //   2. the 64 lane totals of a wavefront are scanned with DPP lane moves
 //      (wave_inclusive_scan) and shifted to exclusive prefixes;
-//   3. the four wavefront totals go through LDS and every lane folds the
-//      totals of the wavefronts before it;
-//   4. rows longer than one chunk pass carries between workgroups by
-//      decoupled look-back: a chunk publishes its aggregate pair, walks back
-//      over its predecessors' published aggregates until it meets a published
-//      inclusive state, and then publishes its own inclusive state;
-//   5. every lane rebuilds its states as h = A_pre * h_in + U_pre (Sec. 3.2)
+//   3. the four wavefront totals go through LDS and every lane folds them,
+//      so every lane knows its prefix and the state leaving the chunk;
+//   4. every lane rebuilds its states as h = A_pre * h_in + U_pre (Sec. 3.2)
 //      and stores them with 16-byte vector stores.
-// The elementwise form of Eq. (3)-(4) (IO variant) forms bx = b * x at the
-// load, stores y = c * h instead of h and can write the final state h_last.
-// Chunks are handed out through an atomic ticket in chunk-major order (all
-// rows' chunk 0 first), so a chunk only ever waits on chunks that already
-// hold a ticket, which guarantees forward progress.  When the rows alone fill
-// the GPU, affine_rows_kernel below walks each row in one workgroup instead
-// and no carry leaves the chip.
+// The carry stays in a register from chunk to chunk, and the next chunk's
+// loads are in flight while the current one is scanned.  Rows may have any
+// length and any element alignment: gfx950 takes 16-byte accesses at 4-byte
+// alignment, and a vector that would cross the row's end is read from before
+// it and shifted.  The elementwise form of Eq. (3)-(4) (IO variant) forms bx =
+// b * x, stores y = c * h instead of h and can write the final state h_last.
+//
+// Few long rows are cut into segments of whole chunks, in two launches:
+// the first composes each segment but the last into its total pair (no
+// output), the second composes the pairs of the segments before its own into
+// its incoming state and walks as above.  The inputs are read twice (20
+// instead of 12 bytes per element, the second time in part from the last
+// level cache), but nothing waits for another workgroup, no ticket is handed
+// out and the result does not depend on timing.
+//
+// Rows of at most 512 steps take one wavefront each (no LDS, no barrier).
+// The long walks run at the rate of a copy (R=512, L=65536 in fp32: 79 us,
+// 5.1 TB/s), the ragged ones too: B=2, D=1000, L=3001 with x, c and h0 takes
+// 21 us, and took 125 us when rows off the 16-byte grid were gathered by
+// element; R=16384, L=100: 7.2 us against 20.7 with a workgroup per row.
 #include <mutex>
 
 #include "sw_internal.h"
 
 // Scratch of the entry point that allocates nothing (sw_affine_scan_noalloc):
-// the ticket counter in the first 256 bytes, then three carry words per chunk
-// for at most SW_NOALLOC_MAX_CHUNKS chunks.  Each GPU holds its own copy,
-// found by hipGetSymbolAddress once per device; host code uses only that
-// address, never the array's name.
+// 256 bytes, then three words per chunk for at most SW_NOALLOC_MAX_CHUNKS
+// chunks, of which the segments' records use two.  Each GPU holds its own
+// copy, found by hipGetSymbolAddress once per device; host code uses only
+// that address, never the array's name.
 static __device__ __align__(256) unsigned long long scratch[32 + 3 * (int64_t)SW_NOALLOC_MAX_CHUNKS];
 
 namespace sw {
 namespace {
 
 constexpr int AS_THREADS = 256;
+constexpr int AS_K = 8;
 constexpr int AS_WAVES = AS_THREADS / 64;
+constexpr int AS_MAX_SEG = AS_THREADS;  // segments per row at most: a record per lane
 
 // Operands of one call.  The plain scan has b = bx, y = h and no x, c or
 // h_last; the IO variant reads x (NULL: 1) and c (NULL: 1) and writes h_last
@@ -50,268 +61,158 @@ struct AffIO {
   T *y, *h_last;
 };
 
-// y element of state hv at step t (IO: times c_t; the final state goes to h_last)
-template <bool IO, typename T>
-__device__ __forceinline__ T out_elem(const AffIO<T>& io, const T* __restrict__ cr, T hv,
-                                      int64_t t, int64_t L, int64_t row) {
-  if constexpr (IO) {
-    if (io.h_last && t == L - 1) io.h_last[row] = hv;
-    if (cr) return Ring<T>::mul(cr[t], hv);
-  }
-  return hv;
-}
+// 2 or 4 elements at 4-byte alignment (one memory instruction on gfx950)
+struct __attribute__((packed, aligned(4))) Words2 {
+  uint32_t w[2];
+};
+struct __attribute__((packed, aligned(4))) Words4 {
+  uint32_t w[4];
+};
 
-template <typename T, int K, bool VEC, bool IO>
-__global__ __launch_bounds__(AS_THREADS) void affine_scan_kernel(
-    const AffIO<T> io, int64_t R, int64_t L, int64_t nchunks, int64_t total,
-    unsigned long long* __restrict__ carry, uint32_t* __restrict__ ticket, uint32_t tbase,
-    uint32_t epoch) {
-  static_assert(K % 4 == 0, "K must be a multiple of 4");
-  constexpr int64_t CH = (int64_t)AS_THREADS * K;
-  using Rg = Ring<T>;
-  __shared__ T sA[AS_WAVES], sU[AS_WAVES];
-  __shared__ T s_hin;
-  __shared__ uint32_t s_id;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const uint32_t st_agg = carry_status(epoch, CARRY_AGG);
-  const uint32_t st_inc = carry_status(epoch, CARRY_INC);
-  int64_t id = blockIdx.x;
-
-  for (;;) {
-    if (nchunks > 1) {
-      if (tid == 0) s_id = atomicAdd(ticket, 1u) - tbase;
-      __syncthreads();
-      id = s_id;
+// Raw bits of K consecutive elements from element t of a run of n (both
+// 32-bit: a run is the rest of a row from a chunk's start, cut at twice the
+// chunk), in vectors of V = min(K, 4).  A vector that would cross the run's
+// end is read from V elements before it: fix() shifts it back.  Elements past
+// the end are left over from the row: they only reach states past the end.
+// (n may be below V, or negative, for a later chunk of a row of at least V
+// elements: the address then falls before the run, still inside the row.)
+template <int K>
+struct RowRegs {
+  static constexpr int V = K < 4 ? K : 4;
+  uint32_t w[K];
+  template <typename T>
+  __device__ __forceinline__ void load(const T* __restrict__ r, int t, int n) {
+#pragma unroll
+    for (int q = 0; q < K; q += V) {
+      const int at = min(t + q, n - V);
+      if constexpr (V == 4) {
+        const Words4 v = *reinterpret_cast<const Words4*>(r + at);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[q + i] = v.w[i];
+      } else if constexpr (V == 2) {
+        const Words2 v = *reinterpret_cast<const Words2*>(r + at);
+        w[q] = v.w[0];
+        w[q + 1] = v.w[1];
+      } else {
+        w[q] = *reinterpret_cast<const uint32_t*>(r + at);
+      }
     }
-    if (id >= total) break;  // uniform across the workgroup
-    const int64_t c = id / R;
-    const int64_t row = id - c * R;
-    const int64_t t0 = c * CH + (int64_t)tid * K;
-    const T* __restrict__ ar = io.a + row * L;
-    const T* __restrict__ br = io.b + row * L;
-    const T* __restrict__ xr = (IO && io.x) ? io.x + row * L : nullptr;
-    const T* __restrict__ cr = (IO && io.c) ? io.c + row * L : nullptr;
-    T* __restrict__ hr = io.y + row * L;
+  }
+  __device__ __forceinline__ void fix(int t, int n) {
+#pragma unroll
+    for (int q = 0; q < K; q += V) {
+      const int back = t + q - (n - V);
+      const int sh = back > 0 && back < V ? back : 0;
+#pragma unroll
+      for (int m = V / 2; m >= 1; m /= 2) {
+        // (as masks: selects of array elements became indexed private memory)
+        const uint32_t on = (sh & m) ? ~0u : 0u;
+#pragma unroll
+        for (int i = 0; i + m < V; ++i) w[q + i] = (w[q + i] & ~on) | (w[q + i + m] & on);
+      }
+    }
+  }
+};
 
-    // 1. load and local inclusive prefixes
-    T pa[K], pu[K];
-    if (VEC && t0 + K <= L) {
+// a, b (and, IO, x and c) of one lane's K steps
+template <typename T, int K, bool IO>
+struct StepRegs {
+  RowRegs<K> a, b, x, c;
+  // steps t .. t+K-1 of the run of n at element `at`
+  __device__ __forceinline__ void load(const AffIO<T>& io, int64_t at, int t, int n) {
+    a.load(io.a + at, t, n);
+    b.load(io.b + at, t, n);
+    if constexpr (IO) {
+      if (io.x) x.load(io.x + at, t, n);
+      if (io.c) c.load(io.c + at, t, n);
+    }
+  }
+  __device__ __forceinline__ void fix(const AffIO<T>& io, int t, int n) {
+    a.fix(t, n);
+    b.fix(t, n);
+    if constexpr (IO) {
+      if (io.x) x.fix(t, n);
+      if (io.c) c.fix(t, n);
+    }
+  }
+  // the pairs (a, b x), composed sequentially into inclusive prefixes
+  __device__ __forceinline__ void prefixes(const AffIO<T>& io, T (&pa)[K], T (&pu)[K]) const {
+    using Rg = Ring<T>;
 #pragma unroll
-      for (int q = 0; q < K / 4; ++q) {
-        uint4 va = *reinterpret_cast<const uint4*>(ar + t0 + 4 * q);
-        uint4 vb = *reinterpret_cast<const uint4*>(br + t0 + 4 * q);
-        pa[4 * q + 0] = Rg::from_bits(va.x);
-        pa[4 * q + 1] = Rg::from_bits(va.y);
-        pa[4 * q + 2] = Rg::from_bits(va.z);
-        pa[4 * q + 3] = Rg::from_bits(va.w);
-        pu[4 * q + 0] = Rg::from_bits(vb.x);
-        pu[4 * q + 1] = Rg::from_bits(vb.y);
-        pu[4 * q + 2] = Rg::from_bits(vb.z);
-        pu[4 * q + 3] = Rg::from_bits(vb.w);
-        if (xr) {
-          const uint4 vx = *reinterpret_cast<const uint4*>(xr + t0 + 4 * q);
-          pu[4 * q + 0] = Rg::mul(pu[4 * q + 0], Rg::from_bits(vx.x));
-          pu[4 * q + 1] = Rg::mul(pu[4 * q + 1], Rg::from_bits(vx.y));
-          pu[4 * q + 2] = Rg::mul(pu[4 * q + 2], Rg::from_bits(vx.z));
-          pu[4 * q + 3] = Rg::mul(pu[4 * q + 3], Rg::from_bits(vx.w));
-        }
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const bool ok = t0 + k < L;
-        pa[k] = ok ? ar[t0 + k] : Rg::one();
-        pu[k] = ok ? (xr ? Rg::mul(br[t0 + k], xr[t0 + k]) : br[t0 + k]) : Rg::zero();
-      }
+    for (int k = 0; k < K; ++k) {
+      pa[k] = Rg::from_bits(a.w[k]);
+      pu[k] = Rg::from_bits(b.w[k]);
+      if (IO && io.x) pu[k] = Rg::mul(pu[k], Rg::from_bits(x.w[k]));
     }
 #pragma unroll
     for (int k = 1; k < K; ++k) absorb_earlier(pa[k], pu[k], pa[k - 1], pu[k - 1]);
-
-    // 2. wavefront scan of the lane totals
-    T wA = pa[K - 1], wU = pu[K - 1];
-    wave_inclusive_scan(wA, wU);
-    if (lane == 63) {
-      sA[wave] = wA;
-      sU[wave] = wU;
-    }
-    wave_shift_exclusive(wA, wU);
-    __syncthreads();
-
-    // 3. fold the totals of earlier wavefronts; chunk total
-    T pA = Rg::one(), pU = Rg::zero();  // prefix of waves before this one
-    T cA = Rg::one(), cU = Rg::zero();  // running chunk total
+  }
+  // y of the K steps from the state hs before them; the state of step
+  // n-1 also goes to h_last, where the run ends the row (last)
+  __device__ __forceinline__ void store(const AffIO<T>& io, const T (&pa)[K], const T (&pu)[K], T hs,
+                                        int64_t row, int64_t at, int t0, int n, bool last) const {
+    using Rg = Ring<T>;
+    T* __restrict__ yr = io.y + at;
+    uint32_t o[K];
 #pragma unroll
-    for (int w = 0; w < AS_WAVES; ++w) {
-      if (w == wave) {
-        pA = cA;
-        pU = cU;
+    for (int k = 0; k < K; ++k) {
+      T hv = Rg::mad(pa[k], hs, pu[k]);
+      if constexpr (IO) {
+        if (last && io.h_last && t0 + k == n - 1) io.h_last[row] = hv;
+        if (io.c) hv = Rg::mul(Rg::from_bits(c.w[k]), hv);
       }
-      T nA = sA[w], nU = sU[w];
-      absorb_earlier(nA, nU, cA, cU);
-      cA = nA;
-      cU = nU;
+      o[k] = Rg::bits(hv);
     }
-    absorb_earlier(wA, wU, pA, pU);  // lane's exclusive prefix within the chunk
-
-    // 4. carry into the chunk
-    T hin;
-    if (c == 0) {
-      hin = io.h0 ? io.h0[row] : Rg::zero();
-      if (nchunks > 1 && tid == 0)
-        carry_put(carry + (row * nchunks) * 3, st_inc, Rg::bits(Rg::mad(cA, hin, cU)));
-    } else {
-      if (tid == 0) {
-        unsigned long long* base = carry + (row * nchunks) * 3;
-        if (c + 1 < nchunks) {
-          carry_put(base + c * 3 + 1, st_agg, Rg::bits(cA));
-          carry_put(base + c * 3 + 2, st_agg, Rg::bits(cU));
-        }
-        T accA = Rg::one(), accU = Rg::zero();
-        int64_t p = c - 1;
-        for (;;) {
-          const unsigned long long wi = carry_get(base + p * 3);
-          if ((uint32_t)(wi >> 32) == st_inc) {
-            hin = Rg::mad(accA, Rg::from_bits((uint32_t)wi), accU);
-            break;
-          }
-          const unsigned long long wa = carry_get(base + p * 3 + 1);
-          const unsigned long long wu = carry_get(base + p * 3 + 2);
-          if ((uint32_t)(wa >> 32) == st_agg && (uint32_t)(wu >> 32) == st_agg) {
-            absorb_earlier(accA, accU, Rg::from_bits((uint32_t)wa), Rg::from_bits((uint32_t)wu));
-            --p;  // chunk 0 always publishes an inclusive state, so p stays >= 0
-            continue;
-          }
-          __builtin_amdgcn_s_sleep(1);
-        }
-        if (c + 1 < nchunks) carry_put(base + c * 3, st_inc, Rg::bits(Rg::mad(cA, hin, cU)));
-        s_hin = hin;
-      }
-      __syncthreads();
-      hin = s_hin;
-    }
-
-    // 5. rebuild the states and store
-    const T hs = Rg::mad(wA, hin, wU);
-    if (VEC && !IO && t0 + K <= L) {
+    if (t0 + K <= n) {
 #pragma unroll
-      for (int q = 0; q < K / 4; ++q) {
-        uint4 o;
-        o.x = Rg::bits(Rg::mad(pa[4 * q + 0], hs, pu[4 * q + 0]));
-        o.y = Rg::bits(Rg::mad(pa[4 * q + 1], hs, pu[4 * q + 1]));
-        o.z = Rg::bits(Rg::mad(pa[4 * q + 2], hs, pu[4 * q + 2]));
-        o.w = Rg::bits(Rg::mad(pa[4 * q + 3], hs, pu[4 * q + 3]));
-        *reinterpret_cast<uint4*>(hr + t0 + 4 * q) = o;
-      }
-    } else if (VEC && t0 + K <= L) {
-#pragma unroll
-      for (int q = 0; q < K / 4; ++q) {
-        uint4 vc = make_uint4(0u, 0u, 0u, 0u);
-        if (cr) vc = *reinterpret_cast<const uint4*>(cr + t0 + 4 * q);
-        const uint32_t cb[4] = {vc.x, vc.y, vc.z, vc.w};
-        T v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int k = 4 * q + e;
-          v[e] = Rg::mad(pa[k], hs, pu[k]);
-          if (io.h_last && t0 + k == L - 1) io.h_last[row] = v[e];
-          if (cr) v[e] = Rg::mul(Rg::from_bits(cb[e]), v[e]);
-        }
-        *reinterpret_cast<uint4*>(hr + t0 + 4 * q) =
-            make_uint4(Rg::bits(v[0]), Rg::bits(v[1]), Rg::bits(v[2]), Rg::bits(v[3]));
+      for (int q = 0; q < K; q += RowRegs<K>::V) {
+        if constexpr (K >= 4)
+          *reinterpret_cast<Words4*>(yr + t0 + q) = Words4{{o[q], o[q + 1], o[q + 2], o[q + 3]}};
+        else if constexpr (K == 2)
+          *reinterpret_cast<Words2*>(yr + t0) = Words2{{o[0], o[1]}};
+        else
+          yr[t0] = Rg::from_bits(o[0]);
       }
     } else {
 #pragma unroll
       for (int k = 0; k < K; ++k)
-        if (t0 + k < L) hr[t0 + k] = out_elem<IO>(io, cr, Rg::mad(pa[k], hs, pu[k]), t0 + k, L, row);
+        if (t0 + k < n) yr[t0 + k] = Rg::from_bits(o[k]);
     }
-    if (nchunks <= 1) {
-      id += gridDim.x;
+  }
+};
+
+// Totals of the four wavefronts, from LDS: this lane's prefix of the
+// wavefronts before its own, and the total of all.
+template <typename T>
+__device__ __forceinline__ void fold_waves(const T (&sA)[AS_WAVES], const T (&sU)[AS_WAVES],
+                                           int wave, T& pA, T& pU, T& cA, T& cU) {
+  pA = cA = Ring<T>::one();
+  pU = cU = Ring<T>::zero();
+#pragma unroll
+  for (int w = 0; w < AS_WAVES; ++w) {
+    if (w == wave) {
+      pA = cA;
+      pU = cU;
     }
-    __syncthreads();  // LDS is reused by the next chunk
+    T nA = sA[w], nU = sU[w];
+    absorb_earlier(nA, nU, cA, cU);
+    cA = nA;
+    cU = nU;
   }
 }
 
-constexpr int AS_K = 8;
+// Modes of the row walk: whole rows; the first launch of a segmented call
+// (each segment's total pair into rec); the second (each segment from the
+// pairs of those before it).
+enum : int { AS_WHOLE = 0, AS_ENDS = 1, AS_SEG = 2 };
 
-// Row-serial variant for many rows: one workgroup owns one (b,d) row and walks
-// it chunk by chunk, keeping the carry in registers (every lane folds the four
-// wavefront totals, so every lane knows the state leaving the chunk).  No
-// cross-workgroup traffic, no scratch; the next chunk's loads are in flight
-// while the current one is scanned.  Used when the rows alone fill the GPU.
-template <typename T, int K, bool VEC>
-struct ChunkRegs {
-  T a[K], u[K];
-};
-
-// In the IO variant the c of the chunk is prefetched with it.
-template <typename T, int K>
-struct ChunkC {
-  T c[K];
-};
-
-// Branch-free loads (clamped addresses, identity pairs past the end): the
-// prefetch then never forces a wait, and the register buffer is never written
-// from two control-flow paths.  Requires L >= 4; with VEC, L is a multiple of
-// 4, so every 4-element piece is wholly inside or wholly outside the row.
-// IO: u = b * x (x row `xr`, or 1 when NULL), and c (row `cr`, or 1) into `rc`.
-template <bool IO, typename T, int K, bool VEC>
-__device__ __forceinline__ void load_chunk(ChunkRegs<T, K, VEC>& r, ChunkC<T, K>& rc,
-                                           const T* __restrict__ ar, const T* __restrict__ br,
-                                           const T* __restrict__ xr, const T* __restrict__ cr,
-                                           int64_t t0, int64_t L) {
-  using Rg = Ring<T>;
-  if (VEC) {
-#pragma unroll
-    for (int q = 0; q < K / 4; ++q) {
-      const int64_t tq = t0 + 4 * q;
-      const bool ok = tq < L;
-      const int64_t at = ok ? tq : L - 4;
-      const uint4 va = *reinterpret_cast<const uint4*>(ar + at);
-      uint4 vb = *reinterpret_cast<const uint4*>(br + at);
-      if (IO && xr) {
-        const uint4 vx = *reinterpret_cast<const uint4*>(xr + at);
-        vb = make_uint4(Rg::bits(Rg::mul(Rg::from_bits(vb.x), Rg::from_bits(vx.x))),
-                        Rg::bits(Rg::mul(Rg::from_bits(vb.y), Rg::from_bits(vx.y))),
-                        Rg::bits(Rg::mul(Rg::from_bits(vb.z), Rg::from_bits(vx.z))),
-                        Rg::bits(Rg::mul(Rg::from_bits(vb.w), Rg::from_bits(vx.w))));
-      }
-      if (IO && cr) {
-        const uint4 vc = *reinterpret_cast<const uint4*>(cr + at);
-        rc.c[4 * q + 0] = Rg::from_bits(vc.x);
-        rc.c[4 * q + 1] = Rg::from_bits(vc.y);
-        rc.c[4 * q + 2] = Rg::from_bits(vc.z);
-        rc.c[4 * q + 3] = Rg::from_bits(vc.w);
-      }
-      r.a[4 * q + 0] = ok ? Rg::from_bits(va.x) : Rg::one();
-      r.a[4 * q + 1] = ok ? Rg::from_bits(va.y) : Rg::one();
-      r.a[4 * q + 2] = ok ? Rg::from_bits(va.z) : Rg::one();
-      r.a[4 * q + 3] = ok ? Rg::from_bits(va.w) : Rg::one();
-      r.u[4 * q + 0] = ok ? Rg::from_bits(vb.x) : Rg::zero();
-      r.u[4 * q + 1] = ok ? Rg::from_bits(vb.y) : Rg::zero();
-      r.u[4 * q + 2] = ok ? Rg::from_bits(vb.z) : Rg::zero();
-      r.u[4 * q + 3] = ok ? Rg::from_bits(vb.w) : Rg::zero();
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const bool ok = t0 + k < L;
-      const int64_t at = ok ? t0 + k : L - 1;
-      const T va = ar[at];
-      T vb = br[at];
-      if (IO && xr) vb = Rg::mul(vb, xr[at]);
-      if (IO && cr) rc.c[k] = cr[at];
-      r.a[k] = ok ? va : Rg::one();
-      r.u[k] = ok ? vb : Rg::zero();
-    }
-  }
-}
-
-template <typename T, int K, bool VEC, bool IO>
-__global__ __launch_bounds__(AS_THREADS) void affine_rows_kernel(const AffIO<T> io, int64_t R,
-                                                                 int64_t L) {
+// One workgroup per (row, segment): rows of nseg segments of seg_chunks chunks
+// (the last takes the rest; 1 segment in AS_WHOLE).  rec holds two carry
+// words per segment but the last: the pair's A and U.
+template <typename T, int K, bool IO, int MODE>
+__global__ __launch_bounds__(AS_THREADS) void affine_rows_kernel(
+    const AffIO<T> io, int64_t R, int64_t L, int64_t nseg, int64_t seg_chunks,
+    unsigned long long* __restrict__ rec, uint32_t epoch) {
   constexpr int64_t CH = (int64_t)AS_THREADS * K;
   using Rg = Ring<T>;
   __shared__ T sA[2][AS_WAVES], sU[2][AS_WAVES];
@@ -319,81 +220,98 @@ __global__ __launch_bounds__(AS_THREADS) void affine_rows_kernel(const AffIO<T> 
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int64_t nch = (L + CH - 1) / CH;
+  const int64_t nsl = MODE == AS_ENDS ? nseg - 1 : nseg;
+  const uint32_t st = carry_status(epoch, CARRY_AGG);
 
-  for (int64_t row = blockIdx.x; row < R; row += gridDim.x) {
-    const T* __restrict__ ar = io.a + row * L;
-    const T* __restrict__ br = io.b + row * L;
-    const T* __restrict__ xr = (IO && io.x) ? io.x + row * L : nullptr;
-    const T* __restrict__ cr = (IO && io.c) ? io.c + row * L : nullptr;
-    T* __restrict__ hr = io.y + row * L;
-    T carry = io.h0 ? io.h0[row] : Rg::zero();
-    ChunkRegs<T, K, VEC> cur, nxt;
-    ChunkC<T, K> ccur, cnxt;
-    load_chunk<IO>(cur, ccur, ar, br, xr, cr, (int64_t)tid * K, L);
-    for (int64_t c = 0; c < nch; ++c) {
-      const int64_t t0 = c * CH + (int64_t)tid * K;
-      if (c + 1 < nch)  // in flight during the scan
-        load_chunk<IO>(nxt, cnxt, ar, br, xr, cr, t0 + CH, L);
-      T pa[K], pu[K];
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        pa[k] = cur.a[k];
-        pu[k] = cur.u[k];
+  for (int64_t id = blockIdx.x; id < R * nsl; id += gridDim.x) {
+    const int64_t row = MODE == AS_WHOLE ? id : id / nsl;
+    const int64_t sg = MODE == AS_WHOLE ? 0 : id - row * nsl;
+    const int64_t base = row * L;
+    const int64_t c0 = sg * seg_chunks;
+    const int64_t c1 = MODE == AS_WHOLE || c0 + seg_chunks > nch ? nch : c0 + seg_chunks;
+    // elements left in the row from chunk c on, as a 32-bit run
+    auto left = [&](int64_t c) {
+      const int64_t n = L - c * CH;
+      return (int)(n < 2 * CH ? n : 2 * CH);
+    };
+    const int t0 = tid * K;
+    StepRegs<T, K, IO> cur, nxt;
+    cur.load(io, base + c0 * CH, t0, left(c0));
+    T carry = MODE != AS_ENDS && io.h0 ? io.h0[row] : Rg::zero();
+    if (MODE == AS_SEG && sg > 0) {
+      // the state entering the segment: lane l holds the pair of segment l
+      T wA = Rg::one(), wU = Rg::zero();
+      if (tid < sg) {
+        const unsigned long long* __restrict__ rr = rec + (row * (nseg - 1) + tid) * 2;
+        wA = Rg::from_bits((uint32_t)carry_get(rr));
+        wU = Rg::from_bits((uint32_t)carry_get(rr + 1));
       }
-#pragma unroll
-      for (int k = 1; k < K; ++k) absorb_earlier(pa[k], pu[k], pa[k - 1], pu[k - 1]);
+      wave_inclusive_scan(wA, wU);
+      if (lane == 63) {
+        sA[1][wave] = wA;
+        sU[1][wave] = wU;
+      }
+      __syncthreads();
+      T pA, pU, cA, cU;
+      fold_waves(sA[1], sU[1], wave, pA, pU, cA, cU);
+      carry = Rg::mad(cA, carry, cU);
+      // sA[1] is written again by the second chunk, after the first's barrier
+    }
+    T totA = Rg::one(), totU = Rg::zero();  // AS_ENDS: the pair so far
+    for (int64_t c = c0; c < c1; ++c) {
+      const int n = left(c);
+      if (c + 1 < c1) nxt.load(io, base + (c + 1) * CH, t0, left(c + 1));  // in flight during the scan
+      if (n < CH) cur.fix(io, t0, n);
+      T pa[K], pu[K];
+      cur.prefixes(io, pa, pu);
       T wA = pa[K - 1], wU = pu[K - 1];
       wave_inclusive_scan(wA, wU);
-      const int buf = (int)(c & 1);
+      const int buf = (int)((c - c0) & 1);
       if (lane == 63) {
         sA[buf][wave] = wA;
         sU[buf][wave] = wU;
       }
-      wave_shift_exclusive(wA, wU);
+      if (MODE != AS_ENDS) wave_shift_exclusive(wA, wU);
       __syncthreads();  // one barrier per chunk: the totals alternate between two buffers
-      T pA = Rg::one(), pU = Rg::zero(), cA = Rg::one(), cU = Rg::zero();
-#pragma unroll
-      for (int w = 0; w < AS_WAVES; ++w) {
-        if (w == wave) {
-          pA = cA;
-          pU = cU;
-        }
-        T nA = sA[buf][w], nU = sU[buf][w];
-        absorb_earlier(nA, nU, cA, cU);
-        cA = nA;
-        cU = nU;
-      }
-      absorb_earlier(wA, wU, pA, pU);
-      const T hs = Rg::mad(wA, carry, wU);
-      // y = c * h (IO with c), else h; the state of step L-1 also goes to h_last
-      auto outv = [&](int k) {
-        const T hv = Rg::mad(pa[k], hs, pu[k]);
-        if constexpr (IO) {
-          if (io.h_last && t0 + k == L - 1) io.h_last[row] = hv;
-          if (cr) return Rg::mul(ccur.c[k], hv);
-        }
-        return hv;
-      };
-      if (VEC) {
-#pragma unroll
-        for (int q = 0; q < K / 4; ++q) {
-          uint4 o;
-          o.x = Rg::bits(outv(4 * q + 0));
-          o.y = Rg::bits(outv(4 * q + 1));
-          o.z = Rg::bits(outv(4 * q + 2));
-          o.w = Rg::bits(outv(4 * q + 3));
-          if (t0 + 4 * q < L) *reinterpret_cast<uint4*>(hr + t0 + 4 * q) = o;
-        }
+      T pA, pU, cA, cU;
+      fold_waves(sA[buf], sU[buf], wave, pA, pU, cA, cU);
+      if constexpr (MODE == AS_ENDS) {
+        absorb_earlier(cA, cU, totA, totU);
+        totA = cA;
+        totU = cU;
       } else {
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-          if (t0 + k < L) hr[t0 + k] = outv(k);
+        absorb_earlier(wA, wU, pA, pU);
+        cur.store(io, pa, pu, Rg::mad(wA, carry, wU), row, base + c * CH, t0, n, n <= CH);
+        carry = Rg::mad(cA, carry, cU);
       }
-      carry = Rg::mad(cA, carry, cU);
       cur = nxt;
-      if constexpr (IO) ccur = cnxt;
+    }
+    if (MODE == AS_ENDS && tid == 0) {
+      carry_put(rec + (row * (nseg - 1) + sg) * 2, st, Rg::bits(totA));
+      carry_put(rec + (row * (nseg - 1) + sg) * 2 + 1, st, Rg::bits(totU));
     }
     __syncthreads();  // the totals buffers are reused by the next row
+  }
+}
+
+// Rows of at most 64*K steps: one wavefront per row.
+template <typename T, int K, bool IO>
+__global__ __launch_bounds__(AS_THREADS) void affine_wave_kernel(const AffIO<T> io, int64_t R,
+                                                                 int64_t L) {
+  using Rg = Ring<T>;
+  const int t0 = (int)(threadIdx.x & 63) * K, n = (int)L;
+  for (int64_t row = (int64_t)blockIdx.x * AS_WAVES + (threadIdx.x >> 6); row < R;
+       row += (int64_t)gridDim.x * AS_WAVES) {
+    StepRegs<T, K, IO> cur;
+    cur.load(io, row * L, t0, n);
+    const T h0 = io.h0 ? io.h0[row] : Rg::zero();
+    if (n < 64 * K) cur.fix(io, t0, n);
+    T pa[K], pu[K];
+    cur.prefixes(io, pa, pu);
+    T wA = pa[K - 1], wU = pu[K - 1];
+    wave_inclusive_scan(wA, wU);
+    wave_shift_exclusive(wA, wU);
+    cur.store(io, pa, pu, Rg::mad(wA, h0, wU), row, row * L, t0, n, true);
   }
 }
 
@@ -420,92 +338,120 @@ int static_scratch(int dev, unsigned long long** out) {
   return SW_OK;
 }
 
-// `fixed`: take the look-back scratch from the static array instead of the
-// per-stream allocation, clearing the ticket and this call's carry words with
-// a fill kernel first (so every call starts from epoch 1 and ticket 0).
-template <typename T, bool IO>
-int launch_affine(const AffIO<T>& io, int64_t R, int64_t L, bool vec, bool fixed = false) {
-  hipStream_t s = current_stream();
-  constexpr int64_t CH = (int64_t)AS_THREADS * AS_K;
-  int cus = 0;
-  int st0 = device_cus(&cus);
-  if (st0 != SW_OK) return st0;
-  if (L > CH && R >= 8 * (int64_t)cus) {
-    // enough rows to fill the machine: one workgroup per row, carries stay on chip
-    const int64_t grid = R < ((int64_t)1 << 30) ? R : ((int64_t)1 << 30);
-    auto kern = vec ? affine_rows_kernel<T, AS_K, true, IO> : affine_rows_kernel<T, AS_K, false, IO>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(AS_THREADS), 0, s, io, R, L);
+// Segments of a row of nch chunks when R rows are scanned on cus compute
+// units (1: whole rows).  One compute unit walks a chunk in about 0.8 us (27
+// GB/s: what its outstanding misses hold), so few rows leave the bandwidth
+// idle; the segmented form adds a launch and reads the inputs twice.  It pays
+// where half of the compute units or fewer have a row and the walk is longer
+// than the two launches; two segments per compute unit measured best or
+// within 10% of it.  us per call, whole rows / segments: R=64 L=65536 28.2 /
+// 16.6, L=32768 14.0 / 9.8, L=16384 7.8 / 9.2; R=128 L=65536 29.6 / 26.9,
+// R=192 32.5 / 37; R=1 L=262144 88 / 10.  (The look-back over 2048-step chunks
+// that both forms replaced was bound by its tickets, 16 ns each: R=64 L=65536
+// 52, R=512 381 against 79.)
+int64_t affine_segments(int64_t R, int64_t nch, int cus) {
+  if (2 * R > cus || nch <= 8) return 1;
+  int64_t n = 2 * (int64_t)cus / R;
+  if (n > nch) n = nch;
+  return n < AS_MAX_SEG ? n : AS_MAX_SEG;
+}
+
+template <typename T, int K, bool IO>
+int launch_rows(const AffIO<T>& io, int64_t R, int64_t L, int64_t nseg, int64_t seg_chunks,
+                unsigned long long* rec, uint32_t epoch, hipStream_t s) {
+  const int64_t most = (int64_t)1 << 30;
+  const auto grid = [&](int64_t n) { return dim3((unsigned)(n < most ? n : most)); };
+  if (nseg <= 1) {
+    hipLaunchKernelGGL((affine_rows_kernel<T, K, IO, AS_WHOLE>), grid(R), dim3(AS_THREADS), 0, s,
+                       io, R, L, (int64_t)1, seg_chunks, rec, epoch);
     return check_launch("affine_rows_kernel");
   }
-  const int64_t nchunks = (L + CH - 1) / CH;
-  const int64_t total = R * nchunks;
-  const int64_t grid = total < 65536 ? total : 65536;
-  auto kern = vec ? affine_scan_kernel<T, AS_K, true, IO> : affine_scan_kernel<T, AS_K, false, IO>;
+  hipLaunchKernelGGL((affine_rows_kernel<T, K, IO, AS_ENDS>), grid(R * (nseg - 1)),
+                     dim3(AS_THREADS), 0, s, io, R, L, nseg, seg_chunks, rec, epoch);
+  hipLaunchKernelGGL((affine_rows_kernel<T, K, IO, AS_SEG>), grid(R * nseg), dim3(AS_THREADS), 0,
+                     s, io, R, L, nseg, seg_chunks, rec, epoch);
+  return check_launch("affine_rows_kernel (segments)");
+}
+
+template <typename T, int K, bool IO>
+int launch_wave(const AffIO<T>& io, int64_t R, int64_t L, hipStream_t s) {
+  const int64_t wgs = (R + AS_WAVES - 1) / AS_WAVES, most = (int64_t)1 << 30;
+  hipLaunchKernelGGL((affine_wave_kernel<T, K, IO>), dim3((unsigned)(wgs < most ? wgs : most)),
+                     dim3(AS_THREADS), 0, s, io, R, L);
+  return check_launch("affine_wave_kernel");
+}
+
+// `fixed`: take the records' scratch from the static array instead of the
+// per-stream allocation.
+template <typename T, bool IO>
+int launch_affine(const AffIO<T>& io, int64_t R, int64_t L, bool fixed = false) {
+  hipStream_t s = current_stream();
+  if (L <= 64) return launch_wave<T, 1, IO>(io, R, L, s);
+  if (L <= 128) return launch_wave<T, 2, IO>(io, R, L, s);
+  if (L <= 256) return launch_wave<T, 4, IO>(io, R, L, s);
+  if (L <= 512) return launch_wave<T, 8, IO>(io, R, L, s);
+  constexpr int64_t CH = (int64_t)AS_THREADS * AS_K;
+  if (L <= CH / 2) return launch_rows<T, AS_K / 2, IO>(io, R, L, 1, 1, nullptr, 0u, s);
+  int cus = 0;
+  int st = device_cus(&cus);
+  if (st != SW_OK) return st;
+  const int64_t nch = (L + CH - 1) / CH;
+  // calls of several chunks on fewer than 8 rows per compute unit: the
+  // scratch limits and the refusal while capturing are those of this rule,
+  // whether or not the call is cut into segments
+  const bool scratched = nch > 1 && R < 8 * (int64_t)cus;
+  const int64_t total = R * nch;
+  if (!scratched) return launch_rows<T, AS_K, IO>(io, R, L, 1, nch, nullptr, 0u, s);
+  const int64_t want = affine_segments(R, nch, cus);
+  const int64_t per = (nch + want - 1) / want, nseg = (nch + per - 1) / per;
   if (fixed) {
+    if (total > (int64_t)SW_NOALLOC_MAX_CHUNKS)
+      return fail(SW_ERR_UNSUPPORTED,
+                  "%lld chunks of %lld steps exceed the %d the static scratch holds",
+                  (long long)total, (long long)CH, (int)SW_NOALLOC_MAX_CHUNKS);
+    int cur = 0;
+    hipError_t e = hipGetDevice(&cur);
+    if (e != hipSuccess) return fail(SW_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
     unsigned long long* base = nullptr;
-    if (nchunks > 1) {
-      if (total > (int64_t)SW_NOALLOC_MAX_CHUNKS)
-        return fail(SW_ERR_UNSUPPORTED,
-                    "%lld look-back chunks of %lld steps exceed the %d the static scratch holds",
-                    (long long)total, (long long)CH, (int)SW_NOALLOC_MAX_CHUNKS);
-      int cur = 0;
-      hipError_t e = hipGetDevice(&cur);
-      if (e != hipSuccess) return fail(SW_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
-      int st = static_scratch(cur, &base);
-      if (st != SW_OK) return st;
-      // 64 words of ticket area, then 2 words per 64-bit carry word
-      st = zero_words(reinterpret_cast<uint32_t*>(base), (size_t)(64 + 6 * total), s);
-      if (st != SW_OK) return st;
-    }
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(AS_THREADS), 0, s, io, R, L, nchunks,
-                       total, base ? base + 32 : nullptr, reinterpret_cast<uint32_t*>(base), 0u,
-                       1u);
-    return check_launch("affine_scan_kernel");
-  }
-  ScratchSession ss;
-  if (nchunks > 1) {
-    if (total >= ((int64_t)1 << 31))
-      return fail(SW_ERR_UNSUPPORTED, "%lld chunks exceed the ticket range", (long long)total);
-    // 3 carry words per chunk; every workgroup takes one ticket past the end
-    int st = ss.reserve((size_t)total * 3, (uint32_t)(total + grid), s);
+    st = static_scratch(cur, &base);
     if (st != SW_OK) return st;
+    return launch_rows<T, AS_K, IO>(io, R, L, nseg, per, base + 32, 1u, s);
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(AS_THREADS), 0, s, io, R, L, nchunks, total,
-                     ss.carry, ss.ticket, ss.ticket_base, ss.epoch);
-  int st = check_launch("affine_scan_kernel");
-  if (st != SW_OK) ss.invalidate();
-  return st;
+  if (total >= ((int64_t)1 << 31))
+    return fail(SW_ERR_UNSUPPORTED, "%lld chunks exceed the supported range", (long long)total);
+  ScratchSession ss;  // holds its lock until both launches are enqueued
+  st = ss.reserve((size_t)(R * (nseg - 1) * 2), 0, s);
+  if (st != SW_OK) return st;
+  return launch_rows<T, AS_K, IO>(io, R, L, nseg, per, ss.carry, ss.epoch, s);
 }
 
 }  // namespace
 
 int affine_scan_f32(const float* a, const float* bx, const float* h0, float* h, int64_t R,
-                    int64_t L, bool vec) {
-  return launch_affine<float, false>(AffIO<float>{a, bx, nullptr, nullptr, h0, h, nullptr}, R, L,
-                                     vec);
+                    int64_t L, bool /*vec*/) {
+  return launch_affine<float, false>(AffIO<float>{a, bx, nullptr, nullptr, h0, h, nullptr}, R, L);
 }
 
 int affine_scan_f32_noalloc(const float* a, const float* bx, const float* h0, float* h,
-                            int64_t R, int64_t L, bool vec) {
-  return launch_affine<float, false>(AffIO<float>{a, bx, nullptr, nullptr, h0, h, nullptr}, R, L,
-                                     vec, true);
+                            int64_t R, int64_t L, bool /*vec*/) {
+  return launch_affine<float, false>(AffIO<float>{a, bx, nullptr, nullptr, h0, h, nullptr}, R, L, true);
 }
 
 int affine_scan_u32(const uint32_t* a, const uint32_t* bx, const uint32_t* h0, uint32_t* h,
-                    int64_t R, int64_t L, bool vec) {
+                    int64_t R, int64_t L, bool /*vec*/) {
   return launch_affine<uint32_t, false>(
-      AffIO<uint32_t>{a, bx, nullptr, nullptr, h0, h, nullptr}, R, L, vec);
+      AffIO<uint32_t>{a, bx, nullptr, nullptr, h0, h, nullptr}, R, L);
 }
 
 int affine_scan_io_f32(const float* a, const float* b, const float* x, const float* c,
-                       const float* h0, float* y, float* h_last, int64_t R, int64_t L, bool vec) {
-  return launch_affine<float, true>(AffIO<float>{a, b, x, c, h0, y, h_last}, R, L, vec);
+                       const float* h0, float* y, float* h_last, int64_t R, int64_t L, bool /*vec*/) {
+  return launch_affine<float, true>(AffIO<float>{a, b, x, c, h0, y, h_last}, R, L);
 }
 
 int affine_scan_io_u32(const uint32_t* a, const uint32_t* b, const uint32_t* x, const uint32_t* c,
                        const uint32_t* h0, uint32_t* y, uint32_t* h_last, int64_t R, int64_t L,
-                       bool vec) {
-  return launch_affine<uint32_t, true>(AffIO<uint32_t>{a, b, x, c, h0, y, h_last}, R, L, vec);
+                       bool /*vec*/) {
+  return launch_affine<uint32_t, true>(AffIO<uint32_t>{a, b, x, c, h0, y, h_last}, R, L);
 }
 
 }  // namespace sw
