@@ -20,13 +20,15 @@
 // it and shifted.  The elementwise form of Eq. (3)-(4) (IO variant) forms bx =
 // b * x, stores y = c * h instead of h and can write the final state h_last.
 //
-// Few long rows are cut into segments of whole chunks, in two launches:
-// the first composes each segment but the last into its total pair (no
-// output), the second composes the pairs of the segments before its own into
-// its incoming state and walks as above.  The inputs are read twice (20
-// instead of 12 bytes per element, the second time in part from the last
-// level cache), but nothing waits for another workgroup, no ticket is handed
-// out and the result does not depend on timing.
+// Few long rows are cut into segments of whole chunks, one workgroup each: it
+// composes its segment into a total pair and publishes it, waits for the
+// pairs of the row's segments before it (a lane per segment), composes them
+// into its incoming state and walks the segment again as above, its inputs
+// still in the L2 (a segment of one chunk stays in registers).  Segments are
+// handed out by a ticket counter per row, so a workgroup only waits for
+// workgroups that already run, and the counters do not queue the rows behind
+// each other.  Pairs are composed in a fixed order: the result does not
+// depend on timing.
 //
 // Rows of at most 512 steps take one wavefront each (no LDS, no barrier).
 // The long walks run at the rate of a copy (R=512, L=65536 in fp32: 79 us,
@@ -38,11 +40,12 @@
 #include "sw_internal.h"
 
 // Scratch of the entry point that allocates nothing (sw_affine_scan_noalloc):
-// 256 bytes, then three words per chunk for at most SW_NOALLOC_MAX_CHUNKS
-// chunks, of which the segments' records use two.  Each GPU holds its own
+// the rows' ticket counters, then three words per chunk for at most
+// SW_NOALLOC_MAX_CHUNKS chunks, of which the segments' records use two.  Each GPU holds its own
 // copy, found by hipGetSymbolAddress once per device; host code uses only
 // that address, never the array's name.
-static __device__ __align__(256) unsigned long long scratch[32 + 3 * (int64_t)SW_NOALLOC_MAX_CHUNKS];
+static __device__ __align__(256) unsigned long long
+    scratch[sw::SW_ROW_TICKETS * sw::SW_TICKET_STRIDE / 2 + 3 * (int64_t)SW_NOALLOC_MAX_CHUNKS];
 
 namespace sw {
 namespace {
@@ -51,6 +54,7 @@ constexpr int AS_THREADS = 256;
 constexpr int AS_K = 8;
 constexpr int AS_WAVES = AS_THREADS / 64;
 constexpr int AS_MAX_SEG = AS_THREADS;  // segments per row at most: a record per lane
+constexpr int AS_TICKET_STRIDE = SW_TICKET_STRIDE;
 
 // Operands of one call.  The plain scan has b = bx, y = h and no x, c or
 // h_last; the IO variant reads x (NULL: 1) and c (NULL: 1) and writes h_last
@@ -201,94 +205,126 @@ __device__ __forceinline__ void fold_waves(const T (&sA)[AS_WAVES], const T (&sU
   }
 }
 
-// Modes of the row walk: whole rows; the first launch of a segmented call
-// (each segment's total pair into rec); the second (each segment from the
-// pairs of those before it).
-enum : int { AS_WHOLE = 0, AS_ENDS = 1, AS_SEG = 2 };
-
-// One workgroup per (row, segment): rows of nseg segments of seg_chunks chunks
-// (the last takes the rest; 1 segment in AS_WHOLE).  rec holds two carry
-// words per segment but the last: the pair's A and U.
-template <typename T, int K, bool IO, int MODE>
+// One workgroup per row, or (LOOK) per segment of a row: rows of nseg segments
+// of seg_chunks chunks, the last taking the rest.  rec holds two carry words
+// per segment but the last, its pair's A and U; ticket a counter per row,
+// AS_TICKET_STRIDE words apart, zero before and after the launch.
+template <typename T, int K, bool IO, bool LOOK>
 __global__ __launch_bounds__(AS_THREADS) void affine_rows_kernel(
     const AffIO<T> io, int64_t R, int64_t L, int64_t nseg, int64_t seg_chunks,
-    unsigned long long* __restrict__ rec, uint32_t epoch) {
+    unsigned long long* __restrict__ rec, uint32_t* __restrict__ ticket, uint32_t epoch) {
   constexpr int64_t CH = (int64_t)AS_THREADS * K;
   using Rg = Ring<T>;
   __shared__ T sA[2][AS_WAVES], sU[2][AS_WAVES];
+  __shared__ uint32_t s_seg;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int64_t nch = (L + CH - 1) / CH;
-  const int64_t nsl = MODE == AS_ENDS ? nseg - 1 : nseg;
-  const uint32_t st = carry_status(epoch, CARRY_AGG);
+  const int t0 = tid * K;
+  // elements left in the row from chunk c on, as a 32-bit run
+  auto left = [&](int64_t c) {
+    const int64_t n = L - c * CH;
+    return (int)(n < 2 * CH ? n : 2 * CH);
+  };
 
-  for (int64_t id = blockIdx.x; id < R * nsl; id += gridDim.x) {
-    const int64_t row = MODE == AS_WHOLE ? id : id / nsl;
-    const int64_t sg = MODE == AS_WHOLE ? 0 : id - row * nsl;
-    const int64_t base = row * L;
-    const int64_t c0 = sg * seg_chunks;
-    const int64_t c1 = MODE == AS_WHOLE || c0 + seg_chunks > nch ? nch : c0 + seg_chunks;
-    // elements left in the row from chunk c on, as a 32-bit run
-    auto left = [&](int64_t c) {
-      const int64_t n = L - c * CH;
-      return (int)(n < 2 * CH ? n : 2 * CH);
-    };
-    const int t0 = tid * K;
-    StepRegs<T, K, IO> cur, nxt;
-    cur.load(io, base + c0 * CH, t0, left(c0));
-    T carry = MODE != AS_ENDS && io.h0 ? io.h0[row] : Rg::zero();
-    if (MODE == AS_SEG && sg > 0) {
-      // the state entering the segment: lane l holds the pair of segment l
-      T wA = Rg::one(), wU = Rg::zero();
-      if (tid < sg) {
-        const unsigned long long* __restrict__ rr = rec + (row * (nseg - 1) + tid) * 2;
-        wA = Rg::from_bits((uint32_t)carry_get(rr));
-        wU = Rg::from_bits((uint32_t)carry_get(rr + 1));
-      }
-      wave_inclusive_scan(wA, wU);
-      if (lane == 63) {
-        sA[1][wave] = wA;
-        sU[1][wave] = wU;
+  for (int64_t id = blockIdx.x; id < (LOOK ? R * nseg : R); id += gridDim.x) {
+    const int64_t row = LOOK ? id % R : id;
+    int64_t sg = 0, c0 = 0, c1 = nch;
+    if constexpr (LOOK) {
+      // segments of a row are taken in order of its tickets, so a segment only
+      // waits for segments that running workgroups hold
+      if (tid == 0) {
+        uint32_t* const tk = ticket + row * AS_TICKET_STRIDE;
+        s_seg = atomicAdd(tk, 1u);
+        if (s_seg == (uint32_t)nseg - 1u)  // the row's last: ready for the next launch
+          __hip_atomic_store(tk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       __syncthreads();
-      T pA, pU, cA, cU;
-      fold_waves(sA[1], sU[1], wave, pA, pU, cA, cU);
-      carry = Rg::mad(cA, carry, cU);
-      // sA[1] is written again by the second chunk, after the first's barrier
+      sg = s_seg;
+      c0 = sg * seg_chunks;
+      if (c0 + seg_chunks < nch) c1 = c0 + seg_chunks;
     }
-    T totA = Rg::one(), totU = Rg::zero();  // AS_ENDS: the pair so far
-    for (int64_t c = c0; c < c1; ++c) {
-      const int n = left(c);
-      if (c + 1 < c1) nxt.load(io, base + (c + 1) * CH, t0, left(c + 1));  // in flight during the scan
-      if (n < CH) cur.fix(io, t0, n);
-      T pa[K], pu[K];
+    const int64_t base = row * L;
+    StepRegs<T, K, IO> cur, nxt;
+    cur.load(io, base + c0 * CH, t0, left(c0));
+    T carry = io.h0 ? io.h0[row] : Rg::zero();
+    T pa[K], pu[K];
+    // the wavefronts' totals of the chunk in cur into buffer buf; wA, wU: the
+    // lane's inclusive prefix
+    auto scan_chunk = [&](int buf, T& wA, T& wU) {
       cur.prefixes(io, pa, pu);
-      T wA = pa[K - 1], wU = pu[K - 1];
+      wA = pa[K - 1];
+      wU = pu[K - 1];
       wave_inclusive_scan(wA, wU);
-      const int buf = (int)((c - c0) & 1);
       if (lane == 63) {
         sA[buf][wave] = wA;
         sU[buf][wave] = wU;
       }
-      if (MODE != AS_ENDS) wave_shift_exclusive(wA, wU);
-      __syncthreads();  // one barrier per chunk: the totals alternate between two buffers
-      T pA, pU, cA, cU;
-      fold_waves(sA[buf], sU[buf], wave, pA, pU, cA, cU);
-      if constexpr (MODE == AS_ENDS) {
+    };
+    T wA, wU, pA, pU, cA, cU;
+    int buf = 0;  // one barrier per chunk: the totals alternate between two buffers
+    if (LOOK && sg + 1 < nseg) {
+      // the segment's total pair, for the segments after it
+      T totA = Rg::one(), totU = Rg::zero();
+      for (int64_t c = c0; c < c1; ++c) {
+        if (c + 1 < c1) nxt.load(io, base + (c + 1) * CH, t0, left(c + 1));
+        scan_chunk(buf, wA, wU);
+        __syncthreads();
+        fold_waves(sA[buf], sU[buf], wave, pA, pU, cA, cU);
         absorb_earlier(cA, cU, totA, totU);
         totA = cA;
         totU = cU;
-      } else {
-        absorb_earlier(wA, wU, pA, pU);
-        cur.store(io, pa, pu, Rg::mad(wA, carry, wU), row, base + c * CH, t0, n, n <= CH);
-        carry = Rg::mad(cA, carry, cU);
+        if (c + 1 < c1) cur = nxt;
+        buf ^= 1;
       }
-      cur = nxt;
+      if (tid == 0) {
+        unsigned long long* const w = rec + (row * (nseg - 1) + sg) * 2;
+        const uint32_t st = carry_status(epoch, CARRY_AGG);
+        carry_put(w, st, Rg::bits(totA));
+        carry_put(w + 1, st, Rg::bits(totU));
+      }
+      // a segment of one chunk is still in cur, a longer one is walked again
+      // (from the L2 this compute unit just filled)
+      if (c1 - c0 > 1) cur.load(io, base + c0 * CH, t0, left(c0));
     }
-    if (MODE == AS_ENDS && tid == 0) {
-      carry_put(rec + (row * (nseg - 1) + sg) * 2, st, Rg::bits(totA));
-      carry_put(rec + (row * (nseg - 1) + sg) * 2 + 1, st, Rg::bits(totU));
+    if (LOOK && sg > 0) {
+      // the state entering the segment: lane l holds the pair of segment l
+      wA = Rg::one();
+      wU = Rg::zero();
+      if (tid < sg) {
+        const unsigned long long* const w = rec + (row * (nseg - 1) + tid) * 2;
+        const uint32_t st = carry_status(epoch, CARRY_AGG);
+        unsigned long long a, u;
+        while (a = carry_get(w), u = carry_get(w + 1),
+               (uint32_t)(a >> 32) != st || (uint32_t)(u >> 32) != st)
+          __builtin_amdgcn_s_sleep(1);
+        wA = Rg::from_bits((uint32_t)a);
+        wU = Rg::from_bits((uint32_t)u);
+      }
+      wave_inclusive_scan(wA, wU);
+      if (lane == 63) {
+        sA[buf][wave] = wA;
+        sU[buf][wave] = wU;
+      }
+      __syncthreads();
+      fold_waves(sA[buf], sU[buf], wave, pA, pU, cA, cU);
+      carry = Rg::mad(cA, carry, cU);
+      buf ^= 1;
+    }
+    for (int64_t c = c0; c < c1; ++c) {
+      const int n = left(c);
+      if (c + 1 < c1) nxt.load(io, base + (c + 1) * CH, t0, left(c + 1));  // in flight during the scan
+      if (n < CH) cur.fix(io, t0, n);
+      scan_chunk(buf, wA, wU);
+      wave_shift_exclusive(wA, wU);
+      __syncthreads();
+      fold_waves(sA[buf], sU[buf], wave, pA, pU, cA, cU);
+      absorb_earlier(wA, wU, pA, pU);
+      cur.store(io, pa, pu, Rg::mad(wA, carry, wU), row, base + c * CH, t0, n, n <= CH);
+      carry = Rg::mad(cA, carry, cU);
+      cur = nxt;
+      buf ^= 1;
     }
     __syncthreads();  // the totals buffers are reused by the next row
   }
@@ -341,35 +377,34 @@ int static_scratch(int dev, unsigned long long** out) {
 // Segments of a row of nch chunks when R rows are scanned on cus compute
 // units (1: whole rows).  One compute unit walks a chunk in about 0.8 us (27
 // GB/s: what its outstanding misses hold), so few rows leave the bandwidth
-// idle; the segmented form adds a launch and reads the inputs twice.  It pays
-// where half of the compute units or fewer have a row and the walk is longer
-// than the two launches; two segments per compute unit measured best or
-// within 10% of it.  us per call, whole rows / segments: R=64 L=65536 28.2 /
-// 16.6, L=32768 14.0 / 9.8, L=16384 7.8 / 9.2; R=128 L=65536 29.6 / 26.9,
-// R=192 32.5 / 37; R=1 L=262144 88 / 10.  (The look-back over 2048-step chunks
-// that both forms replaced was bound by its tickets, 16 ns each: R=64 L=65536
+// idle; segments read the inputs a second time, from L2.  They pay where half
+// of the compute units or fewer have a row and a row has more than 5 chunks;
+// about three segments per compute unit measured best or within 10% of it.
+// us per call, whole rows / segments: R=64 L=65536 27.5 / 13, L=20000 9.0 /
+// 6.4, L=12288 6.1 / 6.4; R=128 L=65536 28.8 / 24, R=192 31.6 / 34; R=1
+// L=262144 83 / 6.5.  (The look-back over 2048-step chunks that both forms
+// replaced was bound by its one ticket counter, 16 ns a chunk: R=64 L=65536
 // 52, R=512 381 against 79.)
 int64_t affine_segments(int64_t R, int64_t nch, int cus) {
-  if (2 * R > cus || nch <= 8) return 1;
-  int64_t n = 2 * (int64_t)cus / R;
+  if (2 * R > cus || R > SW_ROW_TICKETS || nch <= 5) return 1;
+  int64_t n = 3 * (int64_t)cus / R;
   if (n > nch) n = nch;
   return n < AS_MAX_SEG ? n : AS_MAX_SEG;
 }
 
 template <typename T, int K, bool IO>
-int launch_rows(const AffIO<T>& io, int64_t R, int64_t L, int64_t nseg, int64_t seg_chunks,
-                unsigned long long* rec, uint32_t epoch, hipStream_t s) {
+int launch_rows(const AffIO<T>& io, int64_t R, int64_t L, hipStream_t s) {
   const int64_t most = (int64_t)1 << 30;
-  const auto grid = [&](int64_t n) { return dim3((unsigned)(n < most ? n : most)); };
-  if (nseg <= 1) {
-    hipLaunchKernelGGL((affine_rows_kernel<T, K, IO, AS_WHOLE>), grid(R), dim3(AS_THREADS), 0, s,
-                       io, R, L, (int64_t)1, seg_chunks, rec, epoch);
-    return check_launch("affine_rows_kernel");
-  }
-  hipLaunchKernelGGL((affine_rows_kernel<T, K, IO, AS_ENDS>), grid(R * (nseg - 1)),
-                     dim3(AS_THREADS), 0, s, io, R, L, nseg, seg_chunks, rec, epoch);
-  hipLaunchKernelGGL((affine_rows_kernel<T, K, IO, AS_SEG>), grid(R * nseg), dim3(AS_THREADS), 0,
-                     s, io, R, L, nseg, seg_chunks, rec, epoch);
+  hipLaunchKernelGGL((affine_rows_kernel<T, K, IO, false>), dim3((unsigned)(R < most ? R : most)),
+                     dim3(AS_THREADS), 0, s, io, R, L, (int64_t)1, (int64_t)0, nullptr, nullptr, 0u);
+  return check_launch("affine_rows_kernel");
+}
+
+template <typename T, bool IO>
+int launch_segments(const AffIO<T>& io, int64_t R, int64_t L, int64_t nseg, int64_t seg_chunks,
+                    unsigned long long* rec, uint32_t* ticket, uint32_t epoch, hipStream_t s) {
+  hipLaunchKernelGGL((affine_rows_kernel<T, AS_K, IO, true>), dim3((unsigned)(R * nseg)),
+                     dim3(AS_THREADS), 0, s, io, R, L, nseg, seg_chunks, rec, ticket, epoch);
   return check_launch("affine_rows_kernel (segments)");
 }
 
@@ -391,7 +426,7 @@ int launch_affine(const AffIO<T>& io, int64_t R, int64_t L, bool fixed = false) 
   if (L <= 256) return launch_wave<T, 4, IO>(io, R, L, s);
   if (L <= 512) return launch_wave<T, 8, IO>(io, R, L, s);
   constexpr int64_t CH = (int64_t)AS_THREADS * AS_K;
-  if (L <= CH / 2) return launch_rows<T, AS_K / 2, IO>(io, R, L, 1, 1, nullptr, 0u, s);
+  if (L <= CH / 2) return launch_rows<T, AS_K / 2, IO>(io, R, L, s);
   int cus = 0;
   int st = device_cus(&cus);
   if (st != SW_OK) return st;
@@ -401,28 +436,38 @@ int launch_affine(const AffIO<T>& io, int64_t R, int64_t L, bool fixed = false) 
   // whether or not the call is cut into segments
   const bool scratched = nch > 1 && R < 8 * (int64_t)cus;
   const int64_t total = R * nch;
-  if (!scratched) return launch_rows<T, AS_K, IO>(io, R, L, 1, nch, nullptr, 0u, s);
+  if (!scratched) return launch_rows<T, AS_K, IO>(io, R, L, s);
+  if (fixed && total > (int64_t)SW_NOALLOC_MAX_CHUNKS)
+    return fail(SW_ERR_UNSUPPORTED, "%lld chunks of %lld steps exceed the %d the static scratch holds",
+                (long long)total, (long long)CH, (int)SW_NOALLOC_MAX_CHUNKS);
+  if (!fixed) {
+    if (total >= ((int64_t)1 << 31))
+      return fail(SW_ERR_UNSUPPORTED, "%lld chunks exceed the supported range", (long long)total);
+    st = refuse_capture(s, "the per-stream scratch (tickets and carries)");
+    if (st != SW_OK) return st;
+  }
   const int64_t want = affine_segments(R, nch, cus);
   const int64_t per = (nch + want - 1) / want, nseg = (nch + per - 1) / per;
+  if (nseg <= 1) return launch_rows<T, AS_K, IO>(io, R, L, s);
   if (fixed) {
-    if (total > (int64_t)SW_NOALLOC_MAX_CHUNKS)
-      return fail(SW_ERR_UNSUPPORTED,
-                  "%lld chunks of %lld steps exceed the %d the static scratch holds",
-                  (long long)total, (long long)CH, (int)SW_NOALLOC_MAX_CHUNKS);
     int cur = 0;
     hipError_t e = hipGetDevice(&cur);
     if (e != hipSuccess) return fail(SW_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
     unsigned long long* base = nullptr;
     st = static_scratch(cur, &base);
     if (st != SW_OK) return st;
-    return launch_rows<T, AS_K, IO>(io, R, L, nseg, per, base + 32, 1u, s);
+    // the records of the call before carry the same epoch: clear this call's
+    unsigned long long* const rec = base + SW_ROW_TICKETS * SW_TICKET_STRIDE / 2;
+    st = zero_words(reinterpret_cast<uint32_t*>(rec), (size_t)(R * (nseg - 1) * 4), s);
+    if (st != SW_OK) return st;
+    return launch_segments<T, IO>(io, R, L, nseg, per, rec, reinterpret_cast<uint32_t*>(base), 1u, s);
   }
-  if (total >= ((int64_t)1 << 31))
-    return fail(SW_ERR_UNSUPPORTED, "%lld chunks exceed the supported range", (long long)total);
-  ScratchSession ss;  // holds its lock until both launches are enqueued
+  ScratchSession ss;
   st = ss.reserve((size_t)(R * (nseg - 1) * 2), 0, s);
   if (st != SW_OK) return st;
-  return launch_rows<T, AS_K, IO>(io, R, L, nseg, per, ss.carry, ss.epoch, s);
+  st = launch_segments<T, IO>(io, R, L, nseg, per, ss.carry, ss.row_tickets, ss.epoch, s);
+  if (st != SW_OK) ss.invalidate();
+  return st;
 }
 
 }  // namespace

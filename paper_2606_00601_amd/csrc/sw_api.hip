@@ -364,8 +364,10 @@ int check_launch(const char* what) {
 
 namespace {
 
+constexpr size_t HEAD = 256 + (size_t)SW_ROW_TICKETS * SW_TICKET_STRIDE * 4;
+
 struct StreamScratch {
-  void* base = nullptr;   // [0, 256): ticket counter; [256, bytes): carry words
+  void* base = nullptr;   // [0, 256): ticket counter; [256, HEAD): row tickets; then carry words
   size_t bytes = 0;
   uint32_t next_ticket = 0;
   uint32_t epoch = 0;
@@ -432,7 +434,7 @@ int ScratchSession::reserve(size_t carry_words, uint32_t tickets, hipStream_t s)
   dev_ = dev;
   stream_ = s;
   StreamScratch& ws = scratch_map[std::make_pair(dev, s)];
-  const size_t need = 256 + carry_words * 8;
+  const size_t need = HEAD + carry_words * 8;
   if (ws.bytes < need || ws.epoch + 1 >= (1u << 30)) {
     if (ws.base) (void)hipFreeAsync(ws.base, s);
     ws = StreamScratch();
@@ -451,9 +453,10 @@ int ScratchSession::reserve(size_t carry_words, uint32_t tickets, hipStream_t s)
   ws.epoch += 1;
   epoch = ws.epoch;
   ticket = reinterpret_cast<uint32_t*>(ws.base);
+  row_tickets = ticket + 64;
   ticket_base = ws.next_ticket;
   ws.next_ticket += tickets;  // wraps modulo 2^32 together with the device counter
-  carry = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(ws.base) + 256);
+  carry = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(ws.base) + HEAD);
   return SW_OK;
 }
 

@@ -41,6 +41,9 @@ int zero_words(uint32_t* p, size_t words, hipStream_t s);
 // holds a lock from reserve() until it is destroyed, so the order in which
 // launches are enqueued on the stream is the order in which epochs and ticket
 // ranges were handed out.
+// Counters of the launches that hand out the segments of each row by a ticket
+// of its own: each leaves the counters it used at zero.
+constexpr int SW_ROW_TICKETS = 512, SW_TICKET_STRIDE = 16;  // 64 bytes apart
 struct ScratchSession {
   ScratchSession();
   ~ScratchSession();
@@ -55,6 +58,7 @@ struct ScratchSession {
   void invalidate();
   unsigned long long* carry = nullptr;
   uint32_t* ticket = nullptr;
+  uint32_t* row_tickets = nullptr;  // SW_ROW_TICKETS counters, zero between launches
   uint32_t ticket_base = 0;
   uint32_t epoch = 0;  // in [1, 2^30)
  private:
