@@ -360,6 +360,21 @@ int sw_selective_scan_bwd(const void* x, const void* delta, const float* A, cons
                           int64_t B, int64_t D, int64_t N, int64_t L, int in_dtype, int dy_dtype,
                           int flags);
 
+/*
+ * sw_selective_scan_bwd with the type of the gradients that follow the inputs'
+ * type: dx, ddelta, dB, dC and dz are of grad_dtype (bf16: the fp32 gradient
+ * rounded once to nearest even; bf16 inputs, fp32 dy and N <= 16 only, else
+ * SW_ERR_UNSUPPORTED); dA, dDskip, ddelta_bias and dh0 stay fp32.
+ */
+int sw_selective_scan_bwd_ex(const void* x, const void* delta, const float* A, const void* Bm,
+                             const void* Cm, const float* Dskip, const void* z,
+                             const float* delta_bias, const float* h0, const void* dy,
+                             const float* dh_last, const float* ckpt, const float* s_pre,
+                             void* dx, void* ddelta, float* dA, void* dB, void* dC,
+                             float* dDskip, void* dz, float* ddelta_bias, float* dh0, int64_t B,
+                             int64_t D, int64_t N, int64_t L, int in_dtype, int dy_dtype,
+                             int grad_dtype, int flags);
+
 /* Stream used by the calling thread's subsequent calls (a hipStream_t;
  * NULL = the null stream).  Always SW_OK. */
 int sw_set_stream(void* hip_stream);

@@ -358,6 +358,13 @@ def selective_scan_bwd(x, delta, A, Bm, Cm, Dskip, dy, dh_last=None, *, z=None, 
     ``ddelta_bias`` (D,) when Dskip / delta_bias are given, ``dz`` (B, D, L)
     when z is given, and ``dh0`` (B, D, N) when ``want_dh0``.
     """
+    return _bwd(x, delta, A, Bm, Cm, Dskip, dy, dh_last, z, delta_bias, h0, delta_softplus,
+                want_dh0, ckpt, s_pre, torch.float32)
+
+
+def _bwd(x, delta, A, Bm, Cm, Dskip, dy, dh_last, z, delta_bias, h0, delta_softplus, want_dh0,
+         ckpt, s_pre, gdt):
+    """selective_scan_bwd with dx, ddelta, dB, dC and dz in ``gdt``."""
     if not isinstance(x, torch.Tensor) or x.dim() != 3:
         raise ValueError("x must be a (B, D, L) tensor")
     dt = x.dtype
@@ -391,23 +398,25 @@ def selective_scan_bwd(x, delta, A, Bm, Cm, Dskip, dy, dh_last=None, *, z=None, 
         _need(s_pre, "s_pre", torch.float32, (B, D, L))
     dev = x.device
     f32 = dict(dtype=torch.float32, device=dev)
-    out = {"dx": torch.empty((B, D, L), **f32), "ddelta": torch.empty((B, D, L), **f32),
-           "dA": torch.empty((D, N), **f32), "dB": torch.empty((B, L, N), **f32),
-           "dC": torch.empty((B, L, N), **f32)}
+    gr = dict(dtype=gdt, device=dev)
+    out = {"dx": torch.empty((B, D, L), **gr), "ddelta": torch.empty((B, D, L), **gr),
+           "dA": torch.empty((D, N), **f32), "dB": torch.empty((B, L, N), **gr),
+           "dC": torch.empty((B, L, N), **gr)}
     out["dDskip"] = torch.empty((D,), **f32) if Dskip is not None else None
     out["ddelta_bias"] = torch.empty((D,), **f32) if delta_bias is not None else None
-    out["dz"] = torch.empty((B, D, L), **f32) if z is not None else None
+    out["dz"] = torch.empty((B, D, L), **gr) if z is not None else None
     out["dh0"] = torch.empty((B, D, N), **f32) if want_dh0 else None
     in_dt = SW_DTYPE_F32 if dt == torch.float32 else SW_DTYPE_BF16
     dy_dt = SW_DTYPE_F32 if dy.dtype == torch.float32 else SW_DTYPE_BF16
+    gr_dt = SW_DTYPE_F32 if gdt == torch.float32 else SW_DTYPE_BF16
     with _on(dev):
-        check(fast().sw_selective_scan_bwd(
+        check(fast().sw_selective_scan_bwd_ex(
             _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(z),
             _ptr(delta_bias), _ptr(h0), _ptr(dy), _ptr(dh_last), _ptr(ckpt), _ptr(s_pre),
             _ptr(out["dx"]),
             _ptr(out["ddelta"]), _ptr(out["dA"]), _ptr(out["dB"]), _ptr(out["dC"]),
             _ptr(out["dDskip"]), _ptr(out["dz"]), _ptr(out["ddelta_bias"]), _ptr(out["dh0"]),
-            B, D, N, L, in_dt, dy_dt, SW_DELTA_SOFTPLUS if delta_softplus else 0),
+            B, D, N, L, in_dt, dy_dt, gr_dt, SW_DELTA_SOFTPLUS if delta_softplus else 0),
             "sw_selective_scan_bwd")
     return {k: v for k, v in out.items() if v is not None}
 
@@ -439,10 +448,10 @@ class _SelectiveScanFn(torch.autograd.Function):
         dy = dy.contiguous().to(torch.float32)
         if dh_last is not None:
             dh_last = dh_last.contiguous().to(torch.float32)
-        g = selective_scan_bwd(x, delta, A, Bm, Cm, Dskip, dy, dh_last, z=z, delta_bias=delta_bias,
-                               h0=h0, delta_softplus=ctx.delta_softplus,
-                               want_dh0=h0 is not None and h0.requires_grad, ckpt=ck,
-                               s_pre=sp)
+        # the library rounds the gradients of bf16 inputs itself (N <= 16)
+        gdt = x.dtype if A.shape[1] <= 16 else torch.float32
+        g = _bwd(x, delta, A, Bm, Cm, Dskip, dy, dh_last, z, delta_bias, h0, ctx.delta_softplus,
+                 h0 is not None and h0.requires_grad, ck, sp, gdt)
         cast = lambda t, like: None if t is None else t.to(like.dtype)  # noqa: E731
         return (cast(g["dx"], x), cast(g["ddelta"], delta), g["dA"], cast(g["dB"], Bm),
                 cast(g["dC"], Cm), g.get("dDskip"), cast(g.get("dz"), z) if z is not None else None,

@@ -13,81 +13,68 @@
 //   dC_{t,n} += ds_t h_t                        (over d)
 //   dh0 = a_0 lam_0,  dDskip += ds x,  dz = dy s silu'(z) with s the pre-gate y.
 //
-// One workgroup (4 wavefronts) owns 16 (b,d) rows of one batch; lane n of a
-// 16-lane row owns state n (N <= 16; states past N are identity steps).
-//   1. A forward sweep over the sequence stores the state at the start of
-//      every 8-step tile (a checkpoint per lane per tile, in a workspace).
-//   2. A reverse sweep over the tiles: the tile's delta, delta*x, ds and
-//      B, C are staged in LDS; every lane reloads its checkpoint, recomputes
-//      the tile's a_t and q_t forward into registers, then walks the tile
-//      backwards carrying lam.  Per step it forms four partial products:
-//      lam q A and lam B (summed over n, per row and step, into ddelta and
-//      dx) go to LDS; lam delta x and ds h (summed over the 16 rows, per step
-//      and state, into this workgroup's share of dB and dC) are first summed
-//      over the wavefront's four rows by lane-half exchanges, and only those
-//      sums go to LDS.
-//   3. Half of the workgroup sums the first pair per (row, step), the other
-//      half adds the four wavefronts' row sums per (step, state); the shares
-//      of dB / dC, dA, dDskip and ddelta_bias go to a workspace, and a second
-//      kernel adds the shares in a fixed order (no atomics: the result is
-//      reproducible).
-// The pre-gate output s needed by dz comes from the forward kernel run
-// without the gate.
+// The state before every 8th step (a checkpoint per row, state and tile)
+// comes from the forward, from its walk without y, or from
+// selective_sweep_kernel below.  selective_bwd_kernel walks the tiles of its
+// rows backwards:
+//   * a workgroup (4 wavefronts) owns 64 rows of one batch, a wavefront 16 of
+//     them: lane (rl, nl) = (lane / 8, lane % 8) owns states 2nl, 2nl+1 of
+//     rows rl and rl+8.  Four chains per lane share the loads of their row and
+//     state operands, the sums over the states and over the rows are half
+//     done in registers, and each wavefront has four independent chains to
+//     issue from while one waits;
+//   * a wavefront stages its rows' delta, delta*x and ds of the next tile in
+//     its own LDS, one lane per (row, two steps); the workgroup stages B and C
+//     (one element per lane);
+//   * every lane reloads its checkpoints, recomputes the tile's a_t and q_t
+//     forward into registers, forming ds h on the way, then walks the tile
+//     backwards carrying lam;
+//   * lam q A and lam B, summed over the lane's two states, meet in the
+//     wavefront's LDS, and the lane that staged (row, two steps) adds the
+//     eight partials and stores ddelta and dx one tile later;
+//   * lam delta x and ds h, summed over the lane's two rows, are summed over
+//     the wavefront's rows by lane-half exchanges (v_permlane32_swap,
+//     v_permlane16_swap); one lane per (dB or dC, step, state) adds the four
+//     wavefronts' sums into this workgroup's share.  One barrier per tile.
+// Few rows are cut into segments of tiles: a first launch walks each segment
+// but the first from a zero adjoint (the last from dh_last) without gradients
+// and records its end value and the product of its a_t (as exp of A times the
+// sum of delta); the main launch composes the records of the segments after
+// its own into its incoming lam.  A second kernel adds the shares of dB and
+// dC (over the workgroups of a batch) and of dA, dDskip and ddelta_bias (over
+// batch and segments) in a fixed order: no atomics, reproducible bit for bit.
+//
+// Bound by instruction issue: about 12 operations and an exp2 per element
+// and state (45 cycles per wavefront and SIMD), the sums over rows (9) and
+// states (4) and the staging with softplus and gate (9), against the HBM
+// time of the checkpoints and the (B, D, L) arrays.
 #include "selective_common.h"
 
 namespace sw {
 namespace {
 
-constexpr int BW_N = 16;                 // state lanes per row
-constexpr int BW_T = 8;                  // steps per tile
-constexpr int BW_TS = 8;                 // LDS stride of one [t] run (16-byte aligned)
-constexpr int BW_ROWS = 16;              // (b,d) rows per workgroup
-// stride of one row's [n][t] block: 8 mod 64 banks, so that the 64 lanes of a
-// role-a reduce (8 rows x 8 steps) read 64 different banks
-constexpr int BW_RS = BW_N * BW_TS + 8;
-constexpr int BW_RING = 4;               // raw tile registers: loads run 3 tiles ahead
+constexpr int BW_N = 16;      // states per launch (groups of 16 for N > 16)
+constexpr int BW_T = 8;       // steps per tile
+constexpr int BW_WROWS = 16;  // rows per wavefront
+constexpr int BW_ROWS = 64;   // rows per workgroup
+constexpr int BW_MAX_SEG = 32;
+// LDS words of one row's [n][t] partials, and of one quantity's 16 rows: as
+// 16-byte groups, 18 a row (writes: two rows of 16 lanes fill the 64 banks,
+// one on the even groups, one on the odd) and 8 more for the second quantity
+// (reads: 4 rows x 2 quantities x 2 halves fill them)
+constexpr int BW_SPR = 72;
+constexpr int BW_SPQ = BW_WROWS * BW_SPR + 32;
 constexpr float BW_LOG2E = 1.4426950408889634f;
 
-// Position of step t of state n inside its 8-step run: the two 4-step halves
-// trade places for n >= 8, so that the 16 states of a row (float4 accesses)
-// and the 16 x 4 (state, step) lanes of the reduces fall on 64 different banks.
-__device__ __forceinline__ int swz(int n, int t) { return t ^ ((n >> 1) & 4); }
-
+// (the adjoint's walk without gradients uses rv and bc only, and keeps more
+// workgroups on a compute unit)
+template <bool ENDS>
 struct BwSmem {
-  float rv[2][3][BW_ROWS][BW_TS];  // two tile buffers; per row and step: delta, delta*x, ds
-  float bc[2][2][BW_N][BW_TS];     // two tile buffers; B, C of the tile as [n][t]
-  // partials, two buffers (tile k uses k & 1): the sums of tile k+1 are read
-  // while tile k's are written, so one barrier per tile orders both
-  float sp[2][2][BW_ROWS * BW_RS];  // per row [n][t]: lam q A, lam B      (sum over n)
-  float pw[2][4][64 * 4];           // per wavefront and lane: four row sums (rows4_sum)
+  float rv[4][2][3][BW_WROWS][BW_T];     // per wavefront, two tiles: delta, delta*x, ds
+  float bc[2][2][BW_N][BW_T];            // two tiles: B, C as [n][t], halves swapped for n >= 8
+  float sp[4][ENDS ? 4 : 2 * BW_SPQ];    // per wavefront: lam q A, lam B (summed over n next)
+  float pw[2][4][2][ENDS ? 4 : 64 * 4];  // two tiles, per wavefront and 4 steps: row sums
 };
-
-// Sums over the four 16-lane rows of a wavefront, by the two lane-half
-// exchanges of gfx950: v_permlane32_swap trades lanes 32-63 of its first
-// operand with lanes 0-31 of its second, v_permlane16_swap the odd 16-lane
-// rows of the first with the even rows of the second.  In: a lane's
-// lam delta x (dx) and ds h (dh) at the tile's 8 steps.  Out: lane l holds,
-// for state l % 16, the sums over the four rows of dx (l < 32) or dh
-// (l >= 32) at steps 4 ((l / 16) & 1) + 0..3.
-__device__ __forceinline__ void rows4_sum(const float (&dx)[8], const float (&dh)[8],
-                                          float (&out)[4]) {
-  float r[8];
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    // lanes 0-31 get dx of lanes l and l+32, lanes 32-63 dh of l-32 and l
-    const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(dx[t]),
-                                                    __float_as_uint(dh[t]), false, false);
-    r[t] = __uint_as_float(v[0]) + __uint_as_float(v[1]);
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    // row 0 of the wavefront gets rows 0 + 1 of r[t], row 1 rows 0 + 1 of
-    // r[t+4], rows 2 and 3 likewise from rows 2 + 3
-    const auto v = __builtin_amdgcn_permlane16_swap(__float_as_uint(r[t]),
-                                                    __float_as_uint(r[t + 4]), false, false);
-    out[t] = __uint_as_float(v[0]) + __uint_as_float(v[1]);
-  }
-}
 
 __device__ __forceinline__ float sigmoid_f32(float v) {
   return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-v * BW_LOG2E));
@@ -99,19 +86,31 @@ __device__ __forceinline__ void bw_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
+// LDS writes of this wavefront are seen by its later reads in every lane.
+__device__ __forceinline__ void bw_wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Value of `v` in the lane whose index differs in bit 0.
+__device__ __forceinline__ float lane_xor1(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1,
+                                                               0xf, 0xf, false));
+}
+
 struct BwWork {
   float* ck;       // (B*D, ntile, 16) states at tile starts
   const float* s;  // (B*D, L) pre-gate output (gated calls)
-  float* dA_p;     // (B*D, 16)
-  float* dD_p;     // (B*D)
-  float* db_p;     // (B*D)
+  float* rec;      // (nseg - 1, 2, B*D, 16): P and end adjoint of segments 1 ..
+  float* dA_p;     // (nseg, B*D, 16)
+  float* dD_p;     // (nseg, B*D)
+  float* db_p;     // (nseg, B*D)
   float* dB_p;     // (B, G, L, 16)
   float* dC_p;     // (B, G, L, 16)
-  float* trash;    // 256 floats: the target of stores a lane does not need
+  float* trash;    // 1024 floats: the target of stores a lane does not need
 };
 
-// Raw bits of one element as loaded; widened to fp32 only when used, so that
-// the load is not waited for until then.
 template <typename T>
 __device__ __forceinline__ float widen(T r) {
   if constexpr (sizeof(T) == 4)
@@ -119,18 +118,6 @@ __device__ __forceinline__ float widen(T r) {
   else
     return __uint_as_float((uint32_t)r << 16);
 }
-
-// One staging thread's raw inputs of one tile.  Waves 0-1 read x, delta, dy
-// (and z, s) of (row, step); waves 2-3 read B, C of (step, state) through the
-// same two slots r0, r1, so that every thread runs the same straight-line
-// loads (their dy, z, s slots read a valid, unused element).
-template <typename IN, typename DYT>
-struct TileRaw {
-  IN r0, r1, z;
-  DYT dy;
-  float s;
-  bool ok;  // role a: a step of a real row inside the sequence; role b: t < L, n < N
-};
 
 // One element of type T at byte offset voff + soff of a raw buffer resource
 // (zero past the resource's end).
@@ -142,197 +129,636 @@ __device__ __forceinline__ T buf_ld(__amdgpu_buffer_rsrc_t r, int32_t voff, int3
     return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0));
 }
 
+template <typename T>
+struct Bits {
+  using type = uint32_t;
+};
+template <>
+struct Bits<uint16_t> {
+  using type = uint16_t;
+};
+
+// Two consecutive elements as loaded (widened when used, so that the load is
+// not waited for until then).  PAIR: one access (rows of even length, bf16
+// rows on a dword).
+template <typename T, bool PAIR>
+struct Two {
+  static constexpr int W = sizeof(T) == 2 && PAIR ? 1 : 2;
+  uint32_t w[W];
+  __device__ __forceinline__ void load_buf(__amdgpu_buffer_rsrc_t r, int32_t voff, int32_t soff) {
+    if constexpr (!PAIR) {
+      w[0] = __builtin_bit_cast(typename Bits<T>::type, buf_ld<T>(r, voff, soff));
+      w[1] = __builtin_bit_cast(typename Bits<T>::type, buf_ld<T>(r, voff + (int)sizeof(T), soff));
+    } else if constexpr (W == 1) {
+      w[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+    } else {
+      const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+      w[0] = v.x;
+      w[1] = v.y;
+    }
+  }
+  __device__ __forceinline__ void set(T a, T b) {
+    const uint32_t u = __builtin_bit_cast(typename Bits<T>::type, a);
+    const uint32_t v = __builtin_bit_cast(typename Bits<T>::type, b);
+    if constexpr (W == 1) {
+      w[0] = u | (v << 16);
+    } else {
+      w[0] = u;
+      w[1] = v;
+    }
+  }
+  __device__ __forceinline__ float get(int i) const {
+    if constexpr (sizeof(T) == 4)
+      return __uint_as_float(w[i]);
+    else if constexpr (W == 1)
+      return i ? bf16_hi(w[0]) : bf16_lo(w[0]);
+    else
+      return __uint_as_float(w[i] << 16);
+  }
+};
+
+// One gradient value as stored: fp32, or bf16 rounded to nearest even.
+template <typename OUT>
+__device__ __forceinline__ void st1(OUT* p, float v) {
+  if constexpr (sizeof(OUT) == 4)
+    *p = v;
+  else
+    *p = (OUT)bf16_rne(v);
+}
+
+// Launch modes: the gradients; the adjoint's walk without gradients (segments
+// 1 .. nseg-1), which records each segment's end value.
+enum : int { BW_MAIN = 0, BW_ENDS = 1 };
+
 // All global loads below are unconditional, from valid addresses, with the
-// unwanted values replaced afterwards: the loads of the next tile then stay in
-// flight across the current one instead of being waited for inside a branch.
-// BUF: the loads go through raw buffer resources over the workgroup's rows
-// (and its batch's B, C), so that a tile's address is a per-lane offset fixed
-// for the whole kernel plus a scalar one (every offset below 2^31, checked by
-// the host); without it, 64-bit addresses clamped into range.
-template <typename IN, typename DYT, bool GATED, bool BUF>
-__global__ __launch_bounds__(256) void selective_bwd_kernel(const BwdArgs a, const BwWork w,
-                                                            int64_t G, int64_t ntile, int n0) {
-  __shared__ __align__(16) BwSmem sm;
+// unwanted values replaced afterwards, and all stores the same instructions
+// for every lane: the loads of the next tile then stay in flight across the
+// current one instead of being waited for inside a branch.  BUF: loads and
+// stores go through raw buffer resources over the wavefront's rows (and its
+// batch's B, C), a per-lane offset fixed for the whole kernel plus a scalar
+// one (every offset below 2^31, checked by the host; a lane with nothing to
+// store aims at the resource's end, where the store is dropped); without it,
+// 64-bit addresses clamped into range, and stores aimed at trash slots.
+// OUT: the type of dx, ddelta, dz (and dB, dC).
+template <typename IN, typename DYT, typename OUT, bool GATED, bool PAIR, bool BUF, int MODE>
+__global__ __launch_bounds__(256, MODE == BW_ENDS ? 4 : 2) void selective_bwd_kernel(const BwdArgs a, const BwWork w,
+                                                               int64_t G, int64_t ntile, int n0,
+                                                               int nseg, int64_t seg_tiles) {
+  constexpr bool ENDS = MODE == BW_ENDS;
+  constexpr int ES = (int)sizeof(IN), OS = (int)sizeof(OUT);
+  __shared__ __align__(16) BwSmem<ENDS> sm;
+  const IN* __restrict__ X = static_cast<const IN*>(a.x);
+  const IN* __restrict__ DL = static_cast<const IN*>(a.delta);
+  const IN* __restrict__ Z = static_cast<const IN*>(a.z);
+  const DYT* __restrict__ DY = static_cast<const DYT*>(a.dy);
+  const int64_t D = a.D, L = a.L, N = a.N, R = a.B * a.D;
+
+  const int tid = threadIdx.x;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int lane = tid % 64;
+  const int nsl = ENDS ? nseg - 1 : nseg;
+  const int64_t rblk = blockIdx.x / (unsigned)nsl;
+  const int sg = (int)(blockIdx.x - rblk * nsl) + (ENDS ? 1 : 0);
+  const int64_t b = rblk / G, g = rblk - b * G;
+  const int64_t k_lo = sg * seg_tiles;
+  const int64_t k_hi = sg == nseg - 1 ? ntile : k_lo + seg_tiles;
+
+  // the wavefront's rows: nrows of them from row0 (a wavefront past D works on
+  // a copy of row D-1 and stores nothing)
+  const int64_t d0w = g * BW_ROWS + wv * BW_WROWS;
+  const int64_t d0 = d0w < D ? d0w : D - 1;
+  const int nrows = d0w < D ? (int)imin(BW_WROWS, D - d0w) : 0;
+  const int64_t row0 = b * D + d0;
+  const int vrows = nrows > 0 ? nrows : 1;  // rows the resources cover
+
+  // ---- walking role: states n0 + 2nl + i of rows rl + 8j
+  const int nl = lane & 7, rl = lane >> 3;
+  bool dok[2], nok[2];
+  int rj[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    dok[j] = rl + 8 * j < nrows;
+    rj[j] = dok[j] ? rl + 8 * j : vrows - 1;
+    nok[j] = n0 + 2 * nl + j < N;
+  }
+  float Ar[2][2], Al[2][2], lam[2][2], dA_acc[2][2];  // [state][row]
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int ns = n0 + 2 * nl + i;
+      const float v = a.A[(d0 + rj[j]) * N + (nok[i] ? ns : 0)];
+      Ar[i][j] = nok[i] ? v : 0.0f;
+      Al[i][j] = Ar[i][j] * BW_LOG2E;
+      dA_acc[i][j] = 0.0f;
+      const bool ok = dok[j] && nok[i];
+      lam[i][j] = 0.0f;
+      if (sg == nseg - 1) {
+        if (a.dh_last && ok) lam[i][j] = a.dh_last[(row0 + rj[j]) * N + ns];
+      } else if constexpr (!ENDS) {
+        // the adjoint entering from the segments after this one
+        const int64_t st = R * BW_N;
+        const float* const rp = w.rec + (row0 + rj[j]) * BW_N + 2 * nl + i;
+        float v2 = rp[(int64_t)(2 * (nseg - 2) + 1) * st];
+#pragma unroll 8
+        for (int q = nseg - 3; q >= sg; --q)
+          v2 = __builtin_fmaf(rp[(int64_t)(2 * q) * st], v2, rp[(int64_t)(2 * q + 1) * st]);
+        lam[i][j] = ok ? v2 : 0.0f;
+      }
+    }
+  // records are of segments 1 .., so segment q's are rec[q - 1]
+
+  // ---- staging role: steps 2p, 2p+1 of row sr
+  const int sr = lane >> 2, pr = lane & 3;
+  const bool sdok = sr < nrows;
+  const int src = sdok ? sr : vrows - 1;
+  const float dbias = a.delta_bias ? a.delta_bias[d0 + src] : 0.0f;
+  const bool first = n0 == 0;  // the terms that do not depend on the state come with the first group
+  const float Dsk = a.Dskip && first ? a.Dskip[d0 + src] : 0.0f;
+  // ---- B/C role: element (step bt, state bn) of B (wavefronts 0, 1) or C
+  const bool isC = wv >= 2;  // wave-uniform: it picks buffer resources
+  const int bt = (tid >> 4) & 7, bn = tid & 15;
+  const bool bnok = n0 + bn < N;
+
+  const int32_t ea = src * (int32_t)(BUF ? L : 0) + 2 * pr;
+  const int32_t eb = bt * (int32_t)N + (bnok ? n0 + bn : (int32_t)N - 1);
+  const uint32_t rows_e = (uint32_t)(vrows * L);  // elements (BUF: below 2^29)
+  const __amdgpu_buffer_rsrc_t rx = buffer_rsrc(X + row0 * L, rows_e * ES);
+  const __amdgpu_buffer_rsrc_t rd = buffer_rsrc(DL + row0 * L, rows_e * ES);
+  const __amdgpu_buffer_rsrc_t rz = buffer_rsrc(GATED ? Z + row0 * L : X, GATED ? rows_e * ES : 0u);
+  const __amdgpu_buffer_rsrc_t rdy = buffer_rsrc(DY + row0 * L, rows_e * (uint32_t)sizeof(DYT));
+  const __amdgpu_buffer_rsrc_t rs =
+      buffer_rsrc(GATED ? w.s + row0 * L : w.trash, GATED ? rows_e * 4u : 0u);
+  const IN* const bcp = static_cast<const IN*>(isC ? a.Cm : a.Bm) + b * L * N;
+  const __amdgpu_buffer_rsrc_t rbc = buffer_rsrc(bcp, (uint32_t)(L * N * ES));
+  const __amdgpu_buffer_rsrc_t rck =
+      buffer_rsrc(w.ck + row0 * ntile * BW_N, (uint32_t)(vrows * ntile * BW_N * 4));
+  OUT* const ddp = static_cast<OUT*>(a.ddelta) + row0 * L;
+  OUT* const dxp = static_cast<OUT*>(a.dx) + row0 * L;
+  OUT* const dzp = static_cast<OUT*>(GATED && a.dz ? a.dz : a.dx) + row0 * L;
+  const bool want_dz = GATED && a.dz && first;
+  const uint32_t out_b = rows_e * OS;
+  const __amdgpu_buffer_rsrc_t rodd = buffer_rsrc(ddp, out_b);
+  const __amdgpu_buffer_rsrc_t rodx = buffer_rsrc(dxp, out_b);
+  const __amdgpu_buffer_rsrc_t rodz = buffer_rsrc(dzp, want_dz ? out_b : 0u);
+  const uint32_t sh_b = (uint32_t)(L * BW_N * 4);
+  float* const shp = (isC ? w.dC_p : w.dB_p) + (b * G + g) * L * BW_N;
+  const __amdgpu_buffer_rsrc_t rsh = buffer_rsrc(shp, sh_b);
+
+  struct Raw {
+    Two<IN, PAIR> x, dl, z;
+    Two<DYT, PAIR> dy;
+    Two<float, PAIR> s;
+    IN bc;
+  };
+  auto at2 = [&](auto* p, int64_t t, auto& v) {  // !BUF: steps t, t+1 of the staging row
+    const int64_t t1 = t < L ? t : L - 1, t2 = t + 1 < L ? t + 1 : L - 1;
+    v.set(p[(row0 + src) * L + t1], p[(row0 + src) * L + t2]);
+  };
+  auto load_tile = [&](int64_t k, Raw& v) {
+    const int64_t kc = k < 0 ? 0 : k;  // a tile before the start: tile 0, unused
+    if constexpr (BUF) {
+      const int32_t tk = (int32_t)kc * BW_T;
+      if constexpr (!ENDS) v.x.load_buf(rx, ea * ES, tk * ES);
+      v.dl.load_buf(rd, ea * ES, tk * ES);
+      v.dy.load_buf(rdy, ea * (int)sizeof(DYT), tk * (int)sizeof(DYT));
+      if constexpr (GATED) {
+        v.z.load_buf(rz, ea * ES, tk * ES);
+        if constexpr (!ENDS) v.s.load_buf(rs, ea * 4, tk * 4);
+      }
+      v.bc = buf_ld<IN>(rbc, eb * ES, tk * (int32_t)N * ES);
+    } else {
+      const int64_t t = kc * BW_T + 2 * pr;
+      if constexpr (!ENDS) at2(X, t, v.x);
+      at2(DL, t, v.dl);
+      at2(DY, t, v.dy);
+      if constexpr (GATED) {
+        at2(Z, t, v.z);
+        if constexpr (!ENDS) at2(w.s, t, v.s);
+      }
+      const int64_t tb = kc * BW_T + bt;
+      v.bc = bcp[(tb < L ? tb : L - 1) * N + (bnok ? n0 + bn : N - 1)];
+    }
+  };
+  // both steps' values of an output row; lv: which of them are stored
+  auto st2 = [&](__amdgpu_buffer_rsrc_t r, OUT* p, int64_t k, const bool (&lv)[2], float v0,
+                 float v1) {
+    if constexpr (BUF) {
+      const int32_t o = (ea + (int32_t)k * BW_T) * OS;
+      if constexpr (PAIR && OS == 4) {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(sw_u32x2, make_float2(v0, v1)), r,
+                                              lv[0] ? o : (int32_t)out_b, 0, 0);
+      } else if constexpr (PAIR) {
+        __builtin_amdgcn_raw_buffer_store_b32(bf16x2_rne(v0, v1), r, lv[0] ? o : (int32_t)out_b, 0, 0);
+      } else if constexpr (OS == 4) {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v0), r, lv[0] ? o : (int32_t)out_b, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v1), r, lv[1] ? o + OS : (int32_t)out_b,
+                                              0, 0);
+      } else {
+        const uint32_t v = bf16x2_rne(v0, v1);
+        __builtin_amdgcn_raw_buffer_store_b16((short)(v & 0xffffu), r, lv[0] ? o : (int32_t)out_b, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b16((short)(v >> 16), r, lv[1] ? o + OS : (int32_t)out_b, 0, 0);
+      }
+    } else {
+      OUT* const q = p + src * L + k * BW_T + 2 * pr;  // formed, not used, where lv is false
+      OUT* const tr = reinterpret_cast<OUT*>(w.trash + tid);
+      st1<OUT>(lv[0] ? q : tr, v0);
+      st1<OUT>(lv[1] ? q + 1 : tr, v1);
+    }
+  };
+
+  // ---- checkpoints of tile k: states 2nl, 2nl+1 of both rows
+  auto load_ck = [&](int64_t k, float (&h)[2][2]) {
+    const int64_t kc = k < 0 ? 0 : k;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      float2 v;
+      if constexpr (BUF)
+        v = __builtin_bit_cast(
+            float2, __builtin_amdgcn_raw_buffer_load_b64(
+                        rck, (rj[j] * (int32_t)ntile * BW_N + 2 * nl) * 4, (int32_t)kc * (BW_N * 4), 0));
+      else
+        v = *reinterpret_cast<const float2*>(w.ck + ((row0 + rj[j]) * ntile + kc) * BW_N + 2 * nl);
+      h[0][j] = v.x;
+      h[1][j] = v.y;
+    }
+  };
+
+  // ---- stage tile k from `v`; keeps what its ddelta and dx need
+  struct Keep {
+    float dl[2], sg[2], xv[2], dsD[2];
+    bool lv[2];
+  };
+  float dD_acc = 0.0f, db_acc = 0.0f;
+  auto stage = [&](int64_t k, bool live, const Raw& v, int buf, Keep& kp) {
+    float dlv[2], dxv[2], dsv[2], zv2[2] = {0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      kp.lv[i] = live && sdok && k * BW_T + 2 * pr + i < L;
+      const bool lv = kp.lv[i];
+      float dv = v.dl.get(i) + dbias;
+      kp.sg[i] = 1.0f;
+      if (a.softplus) {
+        kp.sg[i] = sigmoid_f32(dv);
+        dv = softplus_f32(dv);
+      }
+      dlv[i] = lv ? dv : 0.0f;
+      const float dyv = lv ? v.dy.get(i) : 0.0f;
+      float gt = 1.0f;
+      if constexpr (GATED) {
+        const float zv = lv ? v.z.get(i) : 0.0f;
+        const float sz = sigmoid_f32(zv);
+        gt = zv * sz;
+        if constexpr (!ENDS)
+          zv2[i] = dyv * (lv ? v.s.get(i) : 0.0f) * (sz * (1.0f + zv * (1.0f - sz)));
+      }
+      dsv[i] = dyv * gt;
+      if constexpr (!ENDS) {
+        const float xv = lv ? v.x.get(i) : 0.0f;
+        dxv[i] = dlv[i] * xv;
+        kp.dl[i] = dlv[i];
+        kp.xv[i] = xv;
+        kp.dsD[i] = dsv[i] * Dsk;
+        dD_acc = __builtin_fmaf(dsv[i], xv, dD_acc);
+      }
+    }
+    *reinterpret_cast<float2*>(&sm.rv[wv][buf][0][sr][2 * pr]) = make_float2(dlv[0], dlv[1]);
+    if constexpr (!ENDS)
+      *reinterpret_cast<float2*>(&sm.rv[wv][buf][1][sr][2 * pr]) = make_float2(dxv[0], dxv[1]);
+    *reinterpret_cast<float2*>(&sm.rv[wv][buf][2][sr][2 * pr]) = make_float2(dsv[0], dsv[1]);
+    const float bcv = bnok && k * BW_T + bt < L ? widen<IN>(v.bc) : 0.0f;
+    sm.bc[buf][isC ? 1 : 0][bn][4 * ((bt >> 2) ^ (bn >> 3)) + (bt & 3)] = bcv;
+    if constexpr (GATED && !ENDS) {
+      if (BUF || want_dz) st2(rodz, dzp, k, kp.lv, zv2[0], zv2[1]);
+    }
+  };
+
+  auto row4 = [&](int buf, int q, int j, int blk) {
+    return *reinterpret_cast<const float4*>(&sm.rv[wv][buf][q][rl + 8 * j][4 * blk]);
+  };
+  auto bc4 = [&](int buf, int q, int i, int blk) {
+    return *reinterpret_cast<const float4*>(&sm.bc[buf][q][2 * nl + i][4 * (blk ^ (nl >> 2))]);
+  };
+  float* const spw = sm.sp[wv];
+
+  // ---- ddelta, dx of tile k (staging role) from the wavefront's partials
+  auto finish_rows = [&](int64_t k, const Keep& kp) {
+    const int q = pr & 1, tq = pr >> 1;
+    const float* const p = spw + q * BW_SPQ + sr * BW_SPR + 4 * (tq ^ (sr & 1));
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float4 f = *reinterpret_cast<const float4*>(p + 8 * i);
+      v[0] += f.x;
+      v[1] += f.y;
+      v[2] += f.z;
+      v[3] += f.w;
+    }
+    // lane q = 0 holds lam q A of steps 4tq .. +3, q = 1 lam B: each keeps its
+    // two steps (2 pr, 2 pr + 1) and takes the other quantity's from its peer
+    const float r0 = lane_xor1(q ? v[0] : v[2]), r1 = lane_xor1(q ? v[1] : v[3]);
+    const float sa[2] = {q ? r0 : v[0], q ? r1 : v[1]};
+    const float sb[2] = {q ? v[2] : r0, q ? v[3] : r1};
+    float dd[2], dx[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      dd[i] = kp.lv[i] ? __builtin_fmaf(kp.xv[i], sb[i], sa[i]) * kp.sg[i] : 0.0f;
+      dx[i] = __builtin_fmaf(kp.dl[i], sb[i], kp.dsD[i]);
+      db_acc += dd[i];
+    }
+    if constexpr (OS == 4) {
+      if (!first) {  // later state groups add to the sums over the states
+        const int64_t o = (int64_t)src * L + k * BW_T + 2 * pr;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          if (kp.lv[i]) {
+            dd[i] += ddp[o + i];
+            dx[i] += dxp[o + i];
+          }
+        }
+      }
+    }
+    st2(rodd, ddp, k, kp.lv, dd[0], dd[1]);
+    st2(rodx, dxp, k, kp.lv, dx[0], dx[1]);
+  };
+  // ---- this workgroup's share of dB (tid < 128) or dC at step bt, state bn
+  auto finish_share = [&](int64_t k, bool live, int buf) {
+    const int l = (isC ? 32 : 0) + (bn & 1) * 8 + (bn >> 1);
+    float s = 0.0f;
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) s += sm.pw[buf][m][bt >> 2][(l + 16 * hh) * 4 + (bt & 3)];
+    const int64_t t = k * BW_T + bt;
+    if constexpr (BUF)
+      __builtin_amdgcn_raw_buffer_store_b32(
+          __float_as_uint(s), rsh, live && t < L ? ((int32_t)t * BW_N + bn) * 4 : (int32_t)sh_b, 0, 0);
+    else
+      *(live && t < L ? shp + t * BW_N + bn : w.trash + tid) = s;
+  };
+
+  // ---- prologue: the last tile staged, the one before in flight
+  Raw raw;
+  Keep kn, kc{};  // of the tile staged, and of the tile walked
+  float hc[2][2], hn[2][2];
+  float dsum[2] = {0.f, 0.f};
+  load_tile(k_hi - 1, raw);
+  if constexpr (!ENDS) load_ck(k_hi - 1, hn);
+  stage(k_hi - 1, true, raw, (int)((k_hi - 1) & 1), kn);
+  load_tile(k_hi - 2, raw);
+
+  for (int64_t k = k_hi - 1; k >= k_lo; --k) {
+    const int buf = (int)(k & 1);
+    bw_barrier();  // tile k is staged, tile k+1's row sums are complete
+    if constexpr (!ENDS) {
+      finish_rows(k + 1, kc);  // (nothing to store in the first round)
+      finish_share(k + 1, k + 1 < k_hi, buf ^ 1);
+      kc = kn;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) hc[i][j] = dok[j] && nok[i] ? hn[i][j] : 0.0f;
+      load_ck(k - 1, hn);
+    }
+    stage(k - 1, k > k_lo, raw, buf ^ 1, kn);  // (past the segment: nothing kept or stored)
+    load_tile(k - 2, raw);
+    if constexpr (ENDS) {
+#pragma unroll
+      for (int blk = 1; blk >= 0; --blk) {
+        float dl[2][4], ds[2][4], c[2][4];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const float4 f = row4(buf, 0, j, blk), e = row4(buf, 2, j, blk), q = bc4(buf, 1, j, blk);
+          dl[j][0] = f.x, dl[j][1] = f.y, dl[j][2] = f.z, dl[j][3] = f.w;
+          ds[j][0] = e.x, ds[j][1] = e.y, ds[j][2] = e.z, ds[j][3] = e.w;
+          c[j][0] = q.x, c[j][1] = q.y, c[j][2] = q.z, c[j][3] = q.w;
+        }
+#pragma unroll
+        for (int t = 3; t >= 0; --t) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            dsum[j] += dl[j][t];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+              lam[i][j] = __builtin_amdgcn_exp2f(dl[j][t] * Al[i][j]) *
+                          __builtin_fmaf(ds[j][t], c[i][t], lam[i][j]);
+          }
+        }
+      }
+    } else {
+      // recompute a_t, q_t = a_t h_{t-1}; ds h of both states, over the two rows
+      float av[2][2][BW_T], qv[2][2][BW_T], ph[2][BW_T];
+#pragma unroll
+      for (int blk = 0; blk < 2; ++blk) {
+        float dl[2][4], dx[2][4], ds[2][4], bb[2][4];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const float4 f = row4(buf, 0, j, blk), e = row4(buf, 1, j, blk), d = row4(buf, 2, j, blk);
+          const float4 q = bc4(buf, 0, j, blk);
+          dl[j][0] = f.x, dl[j][1] = f.y, dl[j][2] = f.z, dl[j][3] = f.w;
+          dx[j][0] = e.x, dx[j][1] = e.y, dx[j][2] = e.z, dx[j][3] = e.w;
+          ds[j][0] = d.x, ds[j][1] = d.y, ds[j][2] = d.z, ds[j][3] = d.w;
+          bb[j][0] = q.x, bb[j][1] = q.y, bb[j][2] = q.z, bb[j][3] = q.w;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int t = 4 * blk + u;
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+              av[i][j][t] = __builtin_amdgcn_exp2f(dl[j][u] * Al[i][j]);
+              qv[i][j][t] = av[i][j][t] * hc[i][j];
+              hc[i][j] = __builtin_fmaf(dx[j][u], bb[i][u], qv[i][j][t]);
+            }
+            ph[i][t] = __builtin_fmaf(ds[1][u], hc[i][1], ds[0][u] * hc[i][0]);
+          }
+        }
+      }
+      // walk the tile backwards
+#pragma unroll
+      for (int blk = 1; blk >= 0; --blk) {
+        float dl[2][4], dx[2][4], ds[2][4], bb[2][4], cc[2][4];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const float4 f = row4(buf, 0, j, blk), e = row4(buf, 1, j, blk), d = row4(buf, 2, j, blk);
+          const float4 q = bc4(buf, 0, j, blk), p = bc4(buf, 1, j, blk);
+          dl[j][0] = f.x, dl[j][1] = f.y, dl[j][2] = f.z, dl[j][3] = f.w;
+          dx[j][0] = e.x, dx[j][1] = e.y, dx[j][2] = e.z, dx[j][3] = e.w;
+          ds[j][0] = d.x, ds[j][1] = d.y, ds[j][2] = d.z, ds[j][3] = d.w;
+          bb[j][0] = q.x, bb[j][1] = q.y, bb[j][2] = q.z, bb[j][3] = q.w;
+          cc[j][0] = p.x, cc[j][1] = p.y, cc[j][2] = p.z, cc[j][3] = p.w;
+        }
+        float sa[2][4], sb[2][4], px[2][4];
+#pragma unroll
+        for (int u = 3; u >= 0; --u) {
+          const int t = 4 * blk + u;
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              const float l = __builtin_fmaf(ds[j][u], cc[i][u], lam[i][j]);
+              const float p = l * qv[i][j][t];
+              dA_acc[i][j] = __builtin_fmaf(p, dl[j][u], dA_acc[i][j]);
+              sa[j][u] = i == 0 ? p * Ar[0][j] : __builtin_fmaf(p, Ar[1][j], sa[j][u]);
+              sb[j][u] = i == 0 ? l * bb[0][u] : __builtin_fmaf(l, bb[1][u], sb[j][u]);
+              px[i][u] = j == 0 ? l * dx[0][u] : __builtin_fmaf(l, dx[1][u], px[i][u]);
+              lam[i][j] = av[i][j][t] * l;
+            }
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int r = rl + 8 * j;
+          float* const p = spw + r * BW_SPR + 8 * nl + 4 * (blk ^ (r & 1));
+          *reinterpret_cast<float4*>(p) = make_float4(sa[j][0], sa[j][1], sa[j][2], sa[j][3]);
+          *reinterpret_cast<float4*>(p + BW_SPQ) = make_float4(sb[j][0], sb[j][1], sb[j][2], sb[j][3]);
+        }
+        // sums over the wavefront's rows but for lane bit 3: lanes 0-31 keep
+        // lam delta x, lanes 32-63 ds h (v_permlane32_swap trades the upper
+        // half of its first operand with the lower of its second), then even
+        // 16-lane rows state 2nl, odd rows state 2nl+1
+        float o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          float r2[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const auto v = __builtin_amdgcn_permlane32_swap(
+                __float_as_uint(px[i][u]), __float_as_uint(ph[i][4 * blk + u]), false, false);
+            r2[i] = __uint_as_float(v[0]) + __uint_as_float(v[1]);
+          }
+          const auto v = __builtin_amdgcn_permlane16_swap(__float_as_uint(r2[0]),
+                                                          __float_as_uint(r2[1]), false, false);
+          o[u] = __uint_as_float(v[0]) + __uint_as_float(v[1]);
+        }
+        // slot (quantity: bit 5, row half: bit 3, state: bit 4, nl), so that the
+        // 16 states of a sum are contiguous
+        const int slot = (lane & 32) | ((lane & 8) << 1) | ((lane & 16) >> 1) | nl;
+        *reinterpret_cast<float4*>(&sm.pw[buf][wv][blk][slot * 4]) = make_float4(o[0], o[1], o[2], o[3]);
+      }
+    }
+    bw_wave_order();  // this wavefront's partials are written before their reads
+  }
+
+  if constexpr (ENDS) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (dok[j]) {
+          float* const rp = w.rec + (int64_t)(2 * (sg - 1)) * R * BW_N + (row0 + rj[j]) * BW_N + 2 * nl + i;
+          rp[0] = __builtin_amdgcn_exp2f(Al[i][j] * dsum[j]);
+          rp[R * BW_N] = nok[i] ? lam[i][j] : 0.0f;
+        }
+      }
+  } else {
+    bw_barrier();  // the first tile's row sums are complete
+    finish_rows(k_lo, kc);
+    finish_share(k_lo, true, (int)(k_lo & 1));
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (dok[j]) {
+          if (sg == 0 && a.dh0 && nok[i]) a.dh0[(row0 + rj[j]) * N + n0 + 2 * nl + i] = lam[i][j];
+          w.dA_p[((int64_t)sg * R + row0 + rj[j]) * BW_N + 2 * nl + i] = dA_acc[i][j];
+        }
+      }
+#pragma unroll
+    for (int off = 1; off < 4; off *= 2) {
+      dD_acc += __shfl_xor(dD_acc, off);
+      db_acc += __shfl_xor(db_acc, off);
+    }
+    if (pr == 0 && sdok) {
+      const int64_t o = (int64_t)sg * R + row0 + sr;
+      if (first) {
+        w.dD_p[o] = dD_acc;
+        w.db_p[o] = db_acc;
+      } else {
+        w.db_p[o] += db_acc;
+      }
+    }
+  }
+}
+
+// The states before every 8th step, for calls without checkpoints: one lane
+// per state, 16 rows of one batch per workgroup, whole rows forward.  Raw
+// inputs of tile j live in ring[j % SW_RING]: loads run SW_RING - 1 tiles
+// ahead of their use, from clamped addresses.
+constexpr int SW_ROWS = 16, SW_RING = 4;
+
+struct SweepSmem {
+  float rv[2][2][SW_ROWS][BW_T];  // two tile buffers: delta, delta*x
+  float b[2][BW_N][BW_T];         // B as [n][t], halves swapped for n >= 8
+};
+
+template <typename IN>
+__global__ __launch_bounds__(256) void selective_sweep_kernel(const BwdArgs a, float* __restrict__ ck,
+                                                              int64_t G, int64_t ntile, int n0) {
+  __shared__ __align__(16) SweepSmem sm;
   const IN* __restrict__ X = static_cast<const IN*>(a.x);
   const IN* __restrict__ DL = static_cast<const IN*>(a.delta);
   const IN* __restrict__ BM = static_cast<const IN*>(a.Bm);
-  const IN* __restrict__ CM = static_cast<const IN*>(a.Cm);
-  const IN* __restrict__ Z = static_cast<const IN*>(a.z);
-  const DYT* __restrict__ DY = static_cast<const DYT*>(a.dy);
   const int64_t D = a.D, L = a.L, N = a.N;
-
   const int tid = threadIdx.x;
-  const int wv = __builtin_amdgcn_readfirstlane(tid / 64);  // wave-uniform
-  const int lane = tid % 64;
-  const int rr = 4 * wv + lane / 16;  // compute role: row within the workgroup
-  const int n = lane % 16;            // ... and state
+  const int wv = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int rr = 4 * wv + (tid % 64) / 16;  // row within the workgroup
+  const int n = tid % 16, ns = n0 + n;
   const int64_t b = blockIdx.x / G;
-  const int64_t g = blockIdx.x - b * G;
-  const int64_t d0 = g * BW_ROWS;
+  const int64_t d0 = (blockIdx.x - b * G) * SW_ROWS;
   const int64_t d = d0 + rr;
-  const bool dok = d < D;
-  // this launch's states are n0 .. n0+15 (groups of 16 for N > 16); the
-  // first group also adds the terms that do not depend on the state
-  const int ns = n0 + n;  // the lane's state
-  const bool nok = ns < N;
-  const bool first = n0 == 0;
+  const bool dok = d < D, nok = ns < N;
   const int64_t row = b * D + (dok ? d : D - 1);
-
-  // staging / reduce roles (by wavefront): waves 0-1 own (row sr, step st),
-  // waves 2-3 own (step bt, state bn)
+  // staging: wavefronts 0-1 own (row sr, step st), 2-3 (step bt, state bn)
   const bool role_a = wv < 2;
   const int sr = (tid % 128) / BW_T, st = tid % BW_T;
   const int bt = (tid % 128) / BW_N, bn = tid % BW_N;
   const int64_t sd = d0 + sr;
   const bool sdok = sd < D;
   const int64_t srow = b * D + (sdok ? sd : D - 1);
-
-  const float Ar = a.A[(dok ? d : D - 1) * N + (nok ? ns : 0)] * (nok ? 1.0f : 0.0f);
-  const float Al = Ar * BW_LOG2E;
+  const float Al = nok ? a.A[(dok ? d : D - 1) * N + ns] * BW_LOG2E : 0.0f;
   const float dbias = a.delta_bias ? a.delta_bias[sdok ? sd : D - 1] : 0.0f;
-  const float Dsk = a.Dskip ? a.Dskip[sdok ? sd : D - 1] : 0.0f;
-
-  // --- staging helpers -----------------------------------------------------
-  const IN* __restrict__ P0 = role_a ? X : BM;
-  const IN* __restrict__ P1 = role_a ? DL : CM;
-  using Raw = TileRaw<IN, DYT>;
-  // BUF: resources and per-lane element offsets.  Role a (and the dy, z, s
-  // loads of every lane) index (row - d0) * L + t of the workgroup's rows,
-  // role b (t * N + n) of the batch's B, C.
-  const int64_t row0 = b * D + d0;
-  const int64_t nrows = imin(BW_ROWS, D - d0);
-  const int32_t ea = (int32_t)(((sdok ? sd : D - 1) - d0) * L) + st;
-  const int32_t eb = bt * (int32_t)N + (n0 + bn < N ? n0 + bn : (int32_t)N - 1);
-  const int32_t e01 = role_a ? ea : eb;
-  const int32_t ts01 = role_a ? BW_T : BW_T * (int32_t)N;  // elements per tile
-  // (built in both variants; only BUF uses them)
-  const uint32_t rows_b = (uint32_t)(nrows * L * (int64_t)sizeof(IN));
-  const uint32_t bc_b = (uint32_t)(L * N * (int64_t)sizeof(IN));
-  const __amdgpu_buffer_rsrc_t r0s =
-      buffer_rsrc(role_a ? (const void*)(X + row0 * L) : (const void*)(BM + b * L * N),
-                  role_a ? rows_b : bc_b);
-  const __amdgpu_buffer_rsrc_t r1s =
-      buffer_rsrc(role_a ? (const void*)(DL + row0 * L) : (const void*)(CM + b * L * N),
-                  role_a ? rows_b : bc_b);
-  const __amdgpu_buffer_rsrc_t rdy =
-      buffer_rsrc(DY + row0 * L, (uint32_t)(nrows * L * (int64_t)sizeof(DYT)));
-  const __amdgpu_buffer_rsrc_t rz = buffer_rsrc(GATED ? Z + row0 * L : X, GATED ? rows_b : 0u);
-  const __amdgpu_buffer_rsrc_t rs =
-      buffer_rsrc(GATED ? w.s + row0 * L : w.trash, GATED ? (uint32_t)(nrows * L * 4) : 0u);
-  const __amdgpu_buffer_rsrc_t rck =
-      buffer_rsrc(w.ck + row0 * ntile * BW_N, (uint32_t)(nrows * ntile * BW_N * 4));
-  const int32_t eck = (int32_t)(((dok ? d : D - 1) - d0) * ntile * BW_N) + n;
-  const uint32_t ck_b = (uint32_t)(nrows * ntile * BW_N * 4);
-  // BUF: the reduce's outputs through resources too, picked by the
-  // wavefront's role: role a the workgroup's rows of ddelta, dx (and dz),
-  // role b this workgroup's share of dB, dC; a lane with nothing to store
-  // aims at the resource's end, where the store is dropped (and a load
-  // returns zero)
-  const uint32_t out_b = role_a ? (uint32_t)(nrows * L * 4) : (uint32_t)(L * BW_N * 4);
-  const __amdgpu_buffer_rsrc_t ro0 =
-      buffer_rsrc(role_a ? a.ddelta + row0 * L : w.dB_p + (b * G + g) * L * BW_N, out_b);
-  const __amdgpu_buffer_rsrc_t ro1 =
-      buffer_rsrc(role_a ? a.dx + row0 * L : w.dC_p + (b * G + g) * L * BW_N, out_b);
-  const __amdgpu_buffer_rsrc_t roz =
-      buffer_rsrc(GATED ? a.dz + row0 * L : a.dx, GATED && role_a ? out_b : 0u);
-  auto load_tile = [&](int64_t k, Raw& v) {
-    if constexpr (BUF) {
-      // a tile before the start reads tile 0 (unused); past the end, the
-      // offsets run out of the resources or into other rows (unused)
-      const int64_t kc = k < 0 ? 0 : k;
-      const int64_t rem = L - k * BW_T;
-      const int32_t lim = k < 0 ? 0 : (int32_t)(rem < 0 ? 0 : (rem < BW_T ? rem : BW_T));
-      v.ok = role_a ? (sdok && st < lim) : (bt < lim && n0 + bn < N);
-      const int32_t tk = (int32_t)kc * BW_T;  // first step of the tile
-      v.r0 = buf_ld<IN>(r0s, e01 * (int32_t)sizeof(IN), tk * (ts01 / BW_T) * (int32_t)sizeof(IN));
-      v.r1 = buf_ld<IN>(r1s, e01 * (int32_t)sizeof(IN), tk * (ts01 / BW_T) * (int32_t)sizeof(IN));
-      v.dy = buf_ld<DYT>(rdy, ea * (int32_t)sizeof(DYT), tk * (int32_t)sizeof(DYT));
-      if constexpr (GATED) {
-        v.z = buf_ld<IN>(rz, ea * (int32_t)sizeof(IN), tk * (int32_t)sizeof(IN));
-        v.s = buf_ld<float>(rs, ea * 4, tk * 4);
-      }
-      return;
-    }
-    // every address is clamped into range, so tiles past either end (the
-    // read-ahead) load valid, unused elements
-    const int64_t ta = k * BW_T + st;
-    const int64_t tca = ta < 0 ? 0 : (ta < L ? ta : L - 1);
-    const int64_t ia = srow * L + tca;
-    const int64_t tb = k * BW_T + bt;
-    const int64_t tcb = tb < 0 ? 0 : (tb < L ? tb : L - 1);
+  struct Raw {
+    IN r0, r1;
+    bool ok;
+  };
+  auto load = [&](int64_t k, Raw& v) {
+    const int64_t ta = k * BW_T + st, tb = k * BW_T + bt;
+    const int64_t tca = ta < L ? ta : L - 1, tcb = tb < L ? tb : L - 1;
     const int64_t ib = (b * L + tcb) * N + (n0 + bn < N ? n0 + bn : N - 1);
-    v.ok = role_a ? (sdok && ta >= 0 && ta < L) : (tb >= 0 && tb < L && n0 + bn < N);
-    const int64_t i01 = role_a ? ia : ib;
-    v.r0 = P0[i01];
-    v.r1 = P1[i01];
-    v.dy = DY[ia];
-    if constexpr (GATED) {
-      v.z = Z[ia];
-      v.s = w.s[ia];
-    }
+    v.ok = role_a ? sdok && ta < L : tb < L && n0 + bn < N;
+    v.r0 = role_a ? X[srow * L + tca] : BM[ib];
+    v.r1 = role_a ? DL[srow * L + tca] : v.r0;
   };
-  // delta after bias and softplus, and d delta / d raw (1 without softplus)
-  auto widen_delta = [&](float raw, bool live, float& dlv, float& sg) {
-    float v = raw + dbias;
-    sg = 1.0f;
-    if (a.softplus) {
-      sg = sigmoid_f32(v);
-      v = softplus_f32(v);
-    }
-    dlv = live ? v : 0.0f;
-  };
-  auto bc_val = [&](IN r, bool ok) { return ok ? widen<IN>(r) : 0.0f; };
-  const int64_t ck_row = row * ntile;
-  auto ck_at = [&](int64_t k) {
-    const int64_t kc = k < 0 ? 0 : (k < ntile ? k : ntile - 1);
-    return w.ck + (ck_row + kc) * BW_N + n;
-  };
-  // the checkpoint of tile k (clamped into range; the ones outside are unused)
-  auto ck_load = [&](int64_t k) {
-    if constexpr (BUF) {
-      const int64_t kc = k < 0 ? 0 : (k < ntile ? k : ntile - 1);
-      return buf_ld<float>(rck, eck * 4, (int32_t)kc * (BW_N * 4));
-    } else {
-      return *ck_at(k);
-    }
-  };
-
-  // Raw inputs of tile j live in ring[j % BW_RING]: loads run BW_RING - 1
-  // tiles ahead of their use.
-  Raw ring[BW_RING];
-
-  // --- 1. forward sweep: checkpoints (unless the forward pass supplied them)
+  Raw ring[SW_RING];
   float h = (a.h0 && dok && nok) ? a.h0[row * N + ns] : 0.0f;
-  const int64_t ntile1 = a.ckpt ? 0 : ntile;
 #pragma unroll
-  for (int u = 0; u < BW_RING - 1; ++u) load_tile(u, ring[u]);
-  for (int64_t k0 = 0; k0 < ntile1; k0 += BW_RING) {
+  for (int u = 0; u < SW_RING - 1; ++u) load(u, ring[u]);
+  for (int64_t k0 = 0; k0 < ntile; k0 += SW_RING) {
 #pragma unroll
-    for (int u = 0; u < BW_RING; ++u) {
+    for (int u = 0; u < SW_RING; ++u) {
       const int64_t k = k0 + u;
-      if (k >= ntile1) break;
-      const int buf = u & 1;  // BW_RING is even, so this is k & 1
-      Raw& cur = ring[u];
+      if (k >= ntile) break;
+      const int buf = u & 1;  // SW_RING is even, so this is k & 1
+      const Raw& cur = ring[u];
       if (role_a) {
-        float dlv, sg;
-        widen_delta(widen<IN>(cur.r1), cur.ok, dlv, sg);
-        sm.rv[buf][0][sr][st] = dlv;
-        sm.rv[buf][1][sr][st] = cur.ok ? dlv * widen<IN>(cur.r0) : 0.0f;
+        float dv = widen<IN>(cur.r1) + dbias;
+        if (a.softplus) dv = softplus_f32(dv);
+        dv = cur.ok ? dv : 0.0f;
+        sm.rv[buf][0][sr][st] = dv;
+        sm.rv[buf][1][sr][st] = cur.ok ? dv * widen<IN>(cur.r0) : 0.0f;
       } else {
-        sm.bc[buf][0][bn][swz(bn, bt)] = bc_val(cur.r0, cur.ok);
+        sm.b[buf][bn][bt ^ ((bn >> 1) & 4)] = cur.ok ? widen<IN>(cur.r0) : 0.0f;
       }
-      load_tile(k + BW_RING - 1, ring[(u + BW_RING - 1) % BW_RING]);
+      load(k + SW_RING - 1, ring[(u + SW_RING - 1) % SW_RING]);
       bw_barrier();  // one per tile: the other buffer is the one staged next
-      if constexpr (BUF)
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(h), rck, dok ? eck * 4 : (int32_t)ck_b,
-                                              (int32_t)k * (BW_N * 4), 0);
-      else
-        *(dok ? w.ck + (ck_row + k) * BW_N + n : w.trash + tid) = h;
+      if (dok) ck[(row * ntile + k) * BW_N + n] = h;
 #pragma unroll
       for (int q = 0; q < BW_T; q += 4) {
         const float4 dl4 = *reinterpret_cast<const float4*>(&sm.rv[buf][0][rr][q]);
         const float4 dx4 = *reinterpret_cast<const float4*>(&sm.rv[buf][1][rr][q]);
-        const float4 b4 = *reinterpret_cast<const float4*>(&sm.bc[buf][0][n][swz(n, q)]);
+        const float4 b4 = *reinterpret_cast<const float4*>(&sm.b[buf][n][q ^ ((n >> 1) & 4)]);
         const float dlq[4] = {dl4.x, dl4.y, dl4.z, dl4.w};
         const float dxq[4] = {dx4.x, dx4.y, dx4.z, dx4.w};
         const float bq[4] = {b4.x, b4.y, b4.z, b4.w};
@@ -342,235 +768,19 @@ __global__ __launch_bounds__(256) void selective_bwd_kernel(const BwdArgs a, con
       }
     }
   }
-  bw_barrier();  // the reverse sweep restages the buffers of the last tiles
-
-  // --- 2./3. reverse sweep ---------------------------------------------------
-  float lam = (a.dh_last && dok && nok) ? a.dh_last[row * N + ns] : 0.0f;
-  float dA_acc = 0.0f;
-  float dD_acc = 0.0f, db_acc = 0.0f;  // role a: this thread's (row, step slot)
-  float hring[BW_RING];
-#pragma unroll
-  for (int u = 0; u < BW_RING - 1; ++u) {
-    load_tile(ntile - 1 - u, ring[u]);
-    hring[u] = ck_load(ntile - 1 - u);
-  }
-  // Sums of tile k from partial buffer pb (role a: over the states, ddelta
-  // and dx of row sr, step st; role b: over the four wavefronts' row sums,
-  // this workgroup's share of dB, dC at step bt, state bn), with the
-  // role-a values saved from that tile's staging.  The stores are the same
-  // instructions for every lane, aimed at the trash slots where a lane has
-  // nothing to store.
-  float p_dlv = 0.f, p_sg = 1.f, p_ds = 0.f, p_gp = 0.f, p_xv = 0.f, p_dyv = 0.f, p_sv = 0.f;
-  bool p_live = false;
-  auto reduce_tile = [&](int64_t k, int pb) {
-    float v0, v1, v2 = 0.f;
-    float *p0, *p1, *p2 = w.trash + tid;
-    uint32_t o = out_b;  // BUF: the byte offset of both outputs
-    if (role_a) {
-      float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-      for (int m = 0; m < BW_N; ++m) {
-        s1 += sm.sp[pb][0][sr * BW_RS + m * BW_TS + swz(m, st)];
-        s2 += sm.sp[pb][1][sr * BW_RS + m * BW_TS + swz(m, st)];
-      }
-      const float ddl = p_live ? (s1 + p_xv * s2) * p_sg : 0.0f;
-      v0 = ddl;
-      v1 = __builtin_fmaf(p_dlv, s2, first ? p_ds * Dsk : 0.0f);
-      if constexpr (BUF) {
-        if (p_live) o = (uint32_t)(ea + (int32_t)k * BW_T) * 4u;
-      } else {
-        const int64_t i = srow * L + (p_live ? k * BW_T + st : 0);
-        p0 = p_live ? a.ddelta + i : w.trash + tid;
-        p1 = p_live ? a.dx + i : w.trash + tid;
-        if constexpr (GATED) p2 = p_live ? a.dz + i : w.trash + tid;
-      }
-      if constexpr (GATED) v2 = p_dyv * p_sv * p_gp;
-      if (first) dD_acc = __builtin_fmaf(p_ds, p_xv, dD_acc);
-      db_acc += ddl;
-    } else {
-      // lane (bt / 4) * 16 + bn of each wavefront holds the dB sums of
-      // steps 4 (bt / 4) .. +3 at state bn, lane 32 more the dC sums
-      const int lb = (bt >> 2) * 16 + bn, tb = bt & 3;
-      float sb = 0.f, sc = 0.f;
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        sb += sm.pw[pb][m][lb * 4 + tb];
-        sc += sm.pw[pb][m][(32 + lb) * 4 + tb];
-      }
-      const int64_t t = k * BW_T + bt;
-      v0 = sb;
-      v1 = sc;
-      if constexpr (BUF) {
-        if (t < L) o = (uint32_t)((int32_t)t * BW_N + bn) * 4u;
-      } else {
-        const int64_t i = ((b * G + g) * L + (t < L ? t : 0)) * BW_N + bn;
-        p0 = t < L ? w.dB_p + i : w.trash + tid;
-        p1 = t < L ? w.dC_p + i : w.trash + tid;
-      }
-    }
-    if constexpr (BUF) {
-      if (role_a && !first) {  // later state groups add to the sums over the states
-        v0 += buf_ld<float>(ro0, (int32_t)o, 0);
-        v1 += buf_ld<float>(ro1, (int32_t)o, 0);
-      }
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v0), ro0, (int32_t)o, 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v1), ro1, (int32_t)o, 0, 0);
-      if constexpr (GATED) {
-        if (first) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v2), roz, (int32_t)o, 0, 0);
-      }
-    } else {
-      if (role_a && !first) {  // later state groups add to the sums over the states
-        v0 += *p0;
-        v1 += *p1;
-      }
-      *p0 = v0;
-      *p1 = v1;
-      if constexpr (GATED) {
-        if (first) *p2 = v2;
-      }
-    }
-  };
-
-  for (int64_t k0 = ntile - 1; k0 >= 0; k0 -= BW_RING) {
-#pragma unroll
-    for (int u = 0; u < BW_RING; ++u) {
-      const int64_t k = k0 - u;
-      if (k < 0) break;
-      // tile k is in ring[u] (its index counted down from the last tile)
-      const int buf = (int)(k & 1);
-      Raw& cur = ring[u];
-      float dlv = 0.f, sg = 1.f, ds = 0.f, gp = 0.f, xv = 0.f, dyv = 0.f, sv = 0.f;
-      const bool live = role_a && cur.ok;
-      if (role_a) {
-        widen_delta(widen<IN>(cur.r1), live, dlv, sg);
-        xv = widen<IN>(cur.r0);
-        dyv = widen<DYT>(cur.dy);
-        float gt = 1.0f;
-        if constexpr (GATED) {
-          const float zv = widen<IN>(cur.z);
-          const float sz = sigmoid_f32(zv);
-          gt = zv * sz;
-          gp = sz * (1.0f + zv * (1.0f - sz));
-          sv = cur.s;
-        }
-        ds = live ? dyv * gt : 0.0f;
-        sm.rv[buf][0][sr][st] = dlv;
-        sm.rv[buf][1][sr][st] = live ? dlv * xv : 0.0f;
-        sm.rv[buf][2][sr][st] = ds;
-      } else {
-        sm.bc[buf][0][bn][swz(bn, bt)] = bc_val(cur.r0, cur.ok);
-        sm.bc[buf][1][bn][swz(bn, bt)] = bc_val(cur.r1, cur.ok);
-      }
-      const float hstart = dok ? hring[u] : 0.0f;
-      load_tile(k - (BW_RING - 1), ring[(u + BW_RING - 1) % BW_RING]);
-      hring[(u + BW_RING - 1) % BW_RING] = ck_load(k - (BW_RING - 1));
-      bw_barrier();  // tile k is staged, tile k+1's partials are complete
-
-      if (k + 1 < ntile) reduce_tile(k + 1, (int)((k + 1) & 1));
-      p_dlv = dlv;
-      p_sg = sg;
-      p_ds = ds;
-      p_gp = gp;
-      p_xv = xv;
-      p_dyv = dyv;
-      p_sv = sv;
-      p_live = live;
-
-      // recompute a_t, q_t = a_t h_{t-1} and h_t of the tile; delta, delta*x
-      // and B stay in registers for the backward walk
-      float av[BW_T], qv[BW_T], hv[BW_T], dlr[BW_T], dxr[BW_T], br[BW_T];
-      {
-        float hh = hstart;
-#pragma unroll
-        for (int q = 0; q < BW_T; q += 4) {
-          const float4 dl4 = *reinterpret_cast<const float4*>(&sm.rv[buf][0][rr][q]);
-          const float4 dx4 = *reinterpret_cast<const float4*>(&sm.rv[buf][1][rr][q]);
-          const float4 b4 = *reinterpret_cast<const float4*>(&sm.bc[buf][0][n][swz(n, q)]);
-          const float dlq[4] = {dl4.x, dl4.y, dl4.z, dl4.w};
-          const float dxq[4] = {dx4.x, dx4.y, dx4.z, dx4.w};
-          const float bq[4] = {b4.x, b4.y, b4.z, b4.w};
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            dlr[q + j] = dlq[j];
-            dxr[q + j] = dxq[j];
-            br[q + j] = bq[j];
-            av[q + j] = __builtin_amdgcn_exp2f(dlq[j] * Al);
-            qv[q + j] = av[q + j] * hh;
-            hh = __builtin_fmaf(dxq[j], bq[j], qv[q + j]);
-            hv[q + j] = hh;
-          }
-        }
-      }
-      // walk the tile backwards
-      float* const sp0 = &sm.sp[buf][0][rr * BW_RS + n * BW_TS];
-      float* const sp1 = &sm.sp[buf][1][rr * BW_RS + n * BW_TS];
-      float pdx[BW_T], pdh[BW_T];  // lam delta x and ds h, summed over rows below
-#pragma unroll
-      for (int q = BW_T - 4; q >= 0; q -= 4) {
-        const float4 ds4 = *reinterpret_cast<const float4*>(&sm.rv[buf][2][rr][q]);
-        const float4 c4 = *reinterpret_cast<const float4*>(&sm.bc[buf][1][n][swz(n, q)]);
-        const float dsq[4] = {ds4.x, ds4.y, ds4.z, ds4.w};
-        const float cq[4] = {c4.x, c4.y, c4.z, c4.w};
-        float o0[4], o1[4];
-#pragma unroll
-        for (int j = 3; j >= 0; --j) {
-          const int t = q + j;
-          const float l = __builtin_fmaf(dsq[j], cq[j], lam);
-          const float p = l * qv[t];
-          dA_acc = __builtin_fmaf(p, dlr[t], dA_acc);
-          o0[j] = p * Ar;
-          o1[j] = l * br[t];
-          pdx[t] = l * dxr[t];
-          pdh[t] = dsq[j] * hv[t];
-          lam = av[t] * l;
-        }
-        const int qs = swz(n, q);
-        *reinterpret_cast<float4*>(sp0 + qs) = make_float4(o0[0], o0[1], o0[2], o0[3]);
-        *reinterpret_cast<float4*>(sp1 + qs) = make_float4(o1[0], o1[1], o1[2], o1[3]);
-      }
-      {
-        float o[4];
-        rows4_sum(pdx, pdh, o);
-        *reinterpret_cast<float4*>(&sm.pw[buf][wv][lane * 4]) =
-            make_float4(o[0], o[1], o[2], o[3]);
-      }
-    }
-  }
-  bw_barrier();  // tile 0's partials are complete
-  reduce_tile(0, 0);
-
-  if (dok && nok) {
-    if (a.dh0) a.dh0[row * N + ns] = lam;
-    w.dA_p[row * BW_N + n] = dA_acc;
-  }
-  // per-row sums of the step slots (8 consecutive lanes of role a)
-  if (role_a) {
-#pragma unroll
-    for (int off = 1; off < BW_T; off *= 2) {
-      dD_acc += __shfl_xor(dD_acc, off);
-      db_acc += __shfl_xor(db_acc, off);
-    }
-    if (st == 0 && sdok) {
-      if (first) {
-        w.dD_p[srow] = dD_acc;
-        w.db_p[srow] = db_acc;
-      } else {
-        w.db_p[srow] += db_acc;
-      }
-    }
-  }
 }
 
 // Adds the shares in a fixed order: dB, dC over the workgroups of a batch
 // (one thread per 4 states of one (b, t) and one of dB / dC, float4 loads,
 // eight in flight, summed in workgroup order); dA, dDskip, ddelta_bias over
-// the batch.
+// batch and segments.
 // With state groups (N > 16) it runs after each group's main kernel and
 // writes that group's states n0 .. n0+15; dDskip and ddelta_bias after the
 // last group (last = true).
+template <typename OUT>
 __global__ __launch_bounds__(256) void selective_bwd_reduce_kernel(const BwdArgs a,
                                                                    const BwWork w, int64_t G,
-                                                                   int n0, bool last) {
+                                                                   int n0, bool last, int nseg) {
   const int64_t B = a.B, D = a.D, N = a.N, L = a.L;
   const int64_t ng = N - n0 < BW_N ? N - n0 : BW_N;  // states of this group
   const int64_t nq = B * L * (BW_N / 4);  // float4 chunks of one of dB / dC
@@ -604,26 +814,32 @@ __global__ __launch_bounds__(256) void selective_bwd_reduce_kernel(const BwdArgs
       acc.z += v.z;
       acc.w += v.w;
     }
-    float* const dst = (isC ? a.dC : a.dB) + bt * N + n0;
+    OUT* const dst = static_cast<OUT*>(isC ? a.dC : a.dB) + bt * N + n0;
     const float av[4] = {acc.x, acc.y, acc.z, acc.w};
     if (N == BW_N && (((uintptr_t)a.dB | (uintptr_t)a.dC) & 15) == 0) {
-      *reinterpret_cast<float4*>(dst + 4 * c) = acc;
+      if constexpr (sizeof(OUT) == 4)
+        *reinterpret_cast<float4*>(dst + 4 * c) = acc;
+      else
+        *reinterpret_cast<uint2*>(dst + 4 * c) =
+            make_uint2(bf16x2_rne(acc.x, acc.y), bf16x2_rne(acc.z, acc.w));
     } else {
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (4 * c + u < ng) dst[4 * c + u] = av[u];
+        if (4 * c + u < ng) st1<OUT>(dst + 4 * c + u, av[u]);
     }
   }
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < D * ng; i += stride) {
     const int64_t d = i / ng, nn = i - d * ng;
     float s = 0.f;
-    for (int64_t b = 0; b < B; ++b) s += w.dA_p[(b * D + d) * BW_N + nn];
+#pragma unroll 8
+    for (int64_t b = 0; b < B * nseg; ++b) s += w.dA_p[(b * D + d) * BW_N + nn];
     a.dA[d * N + n0 + nn] = s;
   }
   if (!last) return;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < D; i += stride) {
     float sd = 0.f, sbias = 0.f;
-    for (int64_t b = 0; b < B; ++b) {
+#pragma unroll 8
+    for (int64_t b = 0; b < B * nseg; ++b) {
       sd += w.dD_p[b * D + i];
       sbias += w.db_p[b * D + i];
     }
@@ -633,39 +849,111 @@ __global__ __launch_bounds__(256) void selective_bwd_reduce_kernel(const BwdArgs
 }
 
 // True when every byte offset of the buffer-resource path stays below 2^31:
-// a workgroup's rows of x, delta, dy, z and s, a batch's B and C, and a
-// workgroup's checkpoints, with the read-ahead tiles past the end.
+// a wavefront's rows of x, delta, dy, z, s and its checkpoints, and a batch's
+// B, C and shares, with the tiles past the end.
 bool bwd_buf_fits(const BwdArgs& a, int64_t ntile) {
   const int64_t lim = (int64_t)1 << 31;
-  const int64_t Lp = a.L + 4 * BW_RING * BW_T;
-  return BW_ROWS * Lp * 4 < lim && Lp * a.N * 4 < lim && Lp * BW_N * 4 < lim &&
-         BW_ROWS * (ntile + 2 * BW_RING) * BW_N * 4 < lim;
+  const int64_t Lp = a.L + 4 * BW_T;
+  return BW_WROWS * Lp * 4 < lim && Lp * a.N * 4 < lim && Lp * BW_N * 4 < lim &&
+         BW_WROWS * (ntile + 2) * BW_N * 4 < lim;
 }
 
-template <typename IN, typename DYT>
-void launch_bwd_dy(const BwdArgs& a, const BwWork& w, int64_t G, int64_t ntile, int64_t grid,
-                   int n0, hipStream_t s) {
-  const bool buf = bwd_buf_fits(a, ntile);
-  auto kern = a.z ? (buf ? selective_bwd_kernel<IN, DYT, true, true>
-                         : selective_bwd_kernel<IN, DYT, true, false>)
-                  : (buf ? selective_bwd_kernel<IN, DYT, false, true>
-                         : selective_bwd_kernel<IN, DYT, false, false>);
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, s, a, w, G, ntile, n0);
+// Rows whose pairs of steps are one access: even length, bf16 on a dword.
+bool bwd_pairs(const BwdArgs& a) {
+  uintptr_t p = 0;
+  if (a.bf16_in) p |= (uintptr_t)a.x | (uintptr_t)a.delta | (uintptr_t)a.z;
+  if (a.dy_bf16) p |= (uintptr_t)a.dy;
+  if (a.grads_bf16) p |= (uintptr_t)a.dx | (uintptr_t)a.ddelta | (uintptr_t)a.dz;
+  return a.L % 2 == 0 && p % 4 == 0;
 }
 
-void launch_bwd(const BwdArgs& a, const BwWork& w, int64_t G, int64_t ntile, int64_t grid,
-                int n0, hipStream_t s) {
-  if (a.bf16_in) {
-    if (a.dy_bf16)
-      launch_bwd_dy<uint16_t, uint16_t>(a, w, G, ntile, grid, n0, s);
+struct BwdPlan {
+  int nseg;
+  int64_t seg_tiles;
+};
+
+template <typename IN, typename DYT, typename OUT, bool GATED, bool PAIR, bool BUF>
+void launch_bwd_k(const BwdArgs& a, const BwWork& w, int64_t G, int64_t ntile, const BwdPlan& p,
+                  int n0, hipStream_t s) {
+  if (p.nseg > 1)
+    hipLaunchKernelGGL((selective_bwd_kernel<IN, DYT, OUT, GATED, PAIR, BUF, BW_ENDS>),
+                       dim3((unsigned)(a.B * G * (p.nseg - 1))), dim3(256), 0, s, a, w, G, ntile,
+                       n0, p.nseg, p.seg_tiles);
+  hipLaunchKernelGGL((selective_bwd_kernel<IN, DYT, OUT, GATED, PAIR, BUF, BW_MAIN>),
+                     dim3((unsigned)(a.B * G * p.nseg)), dim3(256), 0, s, a, w, G, ntile, n0,
+                     p.nseg, p.seg_tiles);
+}
+
+template <typename IN, typename DYT, typename OUT>
+void launch_bwd_t(const BwdArgs& a, const BwWork& w, int64_t G, int64_t ntile, const BwdPlan& p,
+                  int n0, hipStream_t s) {
+  const bool buf = bwd_buf_fits(a, ntile), pair = buf && bwd_pairs(a);
+  if (a.z) {
+    if (pair)
+      launch_bwd_k<IN, DYT, OUT, true, true, true>(a, w, G, ntile, p, n0, s);
+    else if (buf)
+      launch_bwd_k<IN, DYT, OUT, true, false, true>(a, w, G, ntile, p, n0, s);
     else
-      launch_bwd_dy<uint16_t, float>(a, w, G, ntile, grid, n0, s);
+      launch_bwd_k<IN, DYT, OUT, true, false, false>(a, w, G, ntile, p, n0, s);
+  } else {
+    if (pair)
+      launch_bwd_k<IN, DYT, OUT, false, true, true>(a, w, G, ntile, p, n0, s);
+    else if (buf)
+      launch_bwd_k<IN, DYT, OUT, false, false, true>(a, w, G, ntile, p, n0, s);
+    else
+      launch_bwd_k<IN, DYT, OUT, false, false, false>(a, w, G, ntile, p, n0, s);
+  }
+}
+
+void launch_bwd(const BwdArgs& a, const BwWork& w, int64_t G, int64_t ntile, const BwdPlan& p,
+                int n0, hipStream_t s) {
+  if (!a.bf16_in) {  // fp32 gradients
+    if (a.dy_bf16)
+      launch_bwd_t<float, uint16_t, float>(a, w, G, ntile, p, n0, s);
+    else
+      launch_bwd_t<float, float, float>(a, w, G, ntile, p, n0, s);
+  } else if (a.grads_bf16) {  // fp32 dy
+    launch_bwd_t<uint16_t, float, uint16_t>(a, w, G, ntile, p, n0, s);
   } else {
     if (a.dy_bf16)
-      launch_bwd_dy<float, uint16_t>(a, w, G, ntile, grid, n0, s);
+      launch_bwd_t<uint16_t, uint16_t, float>(a, w, G, ntile, p, n0, s);
     else
-      launch_bwd_dy<float, float>(a, w, G, ntile, grid, n0, s);
+      launch_bwd_t<uint16_t, float, float>(a, w, G, ntile, p, n0, s);
   }
+}
+
+// How many segments the sequence is cut into, priced like the forward's plan:
+// a launch of n workgroups runs in rounds of at most two per compute unit (by
+// LDS and registers), a tile of a round takes 2.1 us with one workgroup on
+// the busiest compute unit and 3.5 us with two (measured, gate and softplus
+// included), and starting and ending a segment about two tiles more.  Cut
+// calls add the adjoint's walk, 0.5 + 0.45 us per tile and workgroup resident
+// (up to seven), and 8 us for its launch and the records.  us per call,
+// whole rows / cut, against one state per lane on whole rows before: B=8,
+// D=1536, L=2048 (bf16, gate, softplus) 641 / 508 (5 or 8 segments), 561
+// before; B=1, D=1000, L=1501 (fp32) 398 / 71 (16), 200 before; B=16, D=5120,
+// L=256 345 / 393 (2), 455 before.
+BwdPlan plan_bwd(const BwdArgs& a, int64_t G, int64_t ntile, int cus) {
+  BwdPlan best{1, ntile};
+  const int64_t W = a.B * G;
+  const auto per_cu = [&](int64_t n) { return (n + cus - 1) / cus; };
+  const auto main_us = [&](int64_t n, int64_t tiles) {
+    const int64_t p = per_cu(n);
+    return (double)(tiles + 2) * ((double)(p / 2) * 3.5 + (double)(p % 2) * 2.1);
+  };
+  double best_us = main_us(W, ntile);
+  for (int64_t k = 2; k <= BW_MAX_SEG && k <= ntile; ++k) {
+    const int64_t tiles = (ntile + k - 1) / k, n = (ntile + tiles - 1) / tiles;
+    if (n < 2 || W * n >= ((int64_t)1 << 31)) continue;
+    const int64_t e = per_cu(W * (n - 1));
+    const double walk = (double)(e / 7) * (0.5 + 0.45 * 7) + (e % 7 ? 0.5 + 0.45 * (double)(e % 7) : 0.0);
+    const double us = main_us(W * n, tiles) + (double)(tiles + 2) * walk + 8.0;
+    if (us < best_us) {
+      best_us = us;
+      best = BwdPlan{(int)n, tiles};
+    }
+  }
+  return best;
 }
 
 }  // namespace
@@ -677,15 +965,20 @@ int selective_bwd(const BwdArgs& a) {
   const int64_t B = a.B, D = a.D, L = a.L;
   const int64_t G = (D + BW_ROWS - 1) / BW_ROWS;
   const int64_t ntile = (L + BW_T - 1) / BW_T;
-  const int64_t grid = B * G;
-  if (grid >= ((int64_t)1 << 31))
-    return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range", (long long)grid);
+  const int64_t G16 = (D + SW_ROWS - 1) / SW_ROWS;
+  if (B * G16 >= ((int64_t)1 << 31))
+    return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range", (long long)(B * G16));
+  int cus = 0;
+  if (device_cus(&cus) != SW_OK) cus = 256;
+  const BwdPlan plan = plan_bwd(a, G, ntile, cus);
   const size_t R = (size_t)(B * D);
   // without the forward's checkpoints the kernel rebuilds them in a workspace
   const size_t n_ck = a.ckpt ? 0 : R * (size_t)ntile * BW_N;
   const size_t n_s = (a.z && !a.s_pre) ? R * (size_t)L : 0;
-  const size_t n_dA = R * BW_N, n_bc = (size_t)(B * G) * (size_t)L * BW_N;
-  const size_t total = n_ck + n_s + n_dA + 2 * R + 2 * n_bc + 256;
+  const size_t n_dA = R * BW_N * plan.nseg, n_rec = 2 * R * BW_N * (plan.nseg - 1), n_bc = (size_t)(B * G) * (size_t)L * BW_N;
+  const size_t n_d = R * plan.nseg;
+  // 16-byte groups first: shares and checkpoints are read as vectors
+  const size_t total = n_ck + 2 * n_bc + n_rec + n_dA + n_s + 2 * n_d + 1024;
   void* base = nullptr;
   int st = workspace_alloc(&base, total * sizeof(float), s);
   if (st != SW_OK) return st;
@@ -693,19 +986,21 @@ int selective_bwd(const BwdArgs& a) {
   BwWork w;
   w.ck = a.ckpt ? const_cast<float*>(a.ckpt) : f;  // read-only when given
   f += n_ck;
-  float* s_pre = (a.z && !a.s_pre) ? f : nullptr;
-  w.s = a.s_pre ? a.s_pre : s_pre;
-  f += n_s;
-  w.dA_p = f;
-  f += n_dA;
-  w.dD_p = f;
-  f += R;
-  w.db_p = f;
-  f += R;
   w.dB_p = f;
   f += n_bc;
   w.dC_p = f;
   f += n_bc;
+  w.rec = f;
+  f += n_rec;
+  w.dA_p = f;
+  f += n_dA;
+  float* s_pre = (a.z && !a.s_pre) ? f : nullptr;
+  w.s = a.s_pre ? a.s_pre : s_pre;
+  f += n_s;
+  w.dD_p = f;
+  f += n_d;
+  w.db_p = f;
+  f += n_d;
   w.trash = f;
   // with a gate, the forward without the gate runs anyway (for the pre-gate
   // output); for N <= 16 it also writes the tile checkpoints, so the backward
@@ -772,11 +1067,18 @@ int selective_bwd(const BwdArgs& a) {
       ck_from = "from the forward's walk without y";
     }
   }
-  if (!ck_from) ck_from = "rebuilt by the backward kernel";
+  const bool sweep = !ab.ckpt;
+  if (!ck_from) ck_from = "rebuilt by a sweep";
   // the states in groups of 16: each group's main kernel, then its reduction
   // (dA, dB, dC of its states; the sums over the states accumulate)
   for (int n0 = 0; n0 < a.N && st == SW_OK; n0 += BW_N) {
-    launch_bwd(ab, w, G, ntile, grid, n0, s);
+    if (sweep) {
+      auto kern = a.bf16_in ? selective_sweep_kernel<uint16_t> : selective_sweep_kernel<float>;
+      hipLaunchKernelGGL(kern, dim3((unsigned)(B * G16)), dim3(256), 0, s, a, w.ck, G16, ntile, n0);
+      st = check_launch("selective_sweep_kernel");
+      if (st != SW_OK) break;
+    }
+    launch_bwd(ab, w, G, ntile, plan, n0, s);
     st = check_launch("selective_bwd_kernel");
     if (st != SW_OK) break;
     int64_t work = 2 * B * L * (BW_N / 4);
@@ -784,15 +1086,17 @@ int selective_bwd(const BwdArgs& a) {
     int64_t blocks = (work + 255) / 256;
     if (blocks > 8192) blocks = 8192;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(selective_bwd_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a, w,
-                       G, n0, n0 + BW_N >= a.N);
+    auto red = a.grads_bf16 ? selective_bwd_reduce_kernel<uint16_t> : selective_bwd_reduce_kernel<float>;
+    hipLaunchKernelGGL(red, dim3((unsigned)blocks), dim3(256), 0, s, a, w, G, n0, n0 + BW_N >= a.N,
+                       plan.nseg);
     st = check_launch("selective_bwd_reduce_kernel");
   }
   workspace_free(base, s);
   if (st == SW_OK)
-    note_launch("selective_bwd_kernel + selective_bwd_reduce_kernel (%lld state group%s), "
-                "checkpoints %s",
-                (long long)((a.N + BW_N - 1) / BW_N), a.N > BW_N ? "s" : "", ck_from);
+    note_launch("selective_bwd_kernel + selective_bwd_reduce_kernel (%lld state group%s, %d "
+                "segment%s), checkpoints %s",
+                (long long)((a.N + BW_N - 1) / BW_N), a.N > BW_N ? "s" : "", plan.nseg,
+                plan.nseg > 1 ? "s" : "", ck_from);
   return st;
 }
 

@@ -253,9 +253,11 @@ int selective_bwd_common(BwdArgs a) {
   if (a.s_pre && !a.z) return fail(SW_ERR_INVALID_ARG, "s_pre requires z");
   if (a.ckpt && N > 16)
     return fail(SW_ERR_UNSUPPORTED, "checkpoints hold 16 states (got N=%lld)", (long long)N);
+  if (a.grads_bf16 && (N > 16 || !a.bf16_in || a.dy_bf16))
+    return fail(SW_ERR_UNSUPPORTED, "bf16 gradients need bf16 inputs, fp32 dy and N <= 16");
   int dev, st;
   if ((st = current_device(&dev)) != SW_OK) return st;
-  const size_t es = a.bf16_in ? 2 : 4, dys = a.dy_bf16 ? 2 : 4;
+  const size_t es = a.bf16_in ? 2 : 4, dys = a.dy_bf16 ? 2 : 4, gs = a.grads_bf16 ? 2 : 4;
   const bool empty = R == 0 || L == 0;
   // inputs
   if ((st = check_ptr(a.x, es, "x", !empty, dev)) != SW_OK) return st;
@@ -272,19 +274,19 @@ int selective_bwd_common(BwdArgs a) {
   if ((st = check_ptr(a.ckpt, 4, "ckpt", false, dev)) != SW_OK) return st;
   if ((st = check_ptr(a.s_pre, 4, "s_pre", false, dev)) != SW_OK) return st;
   // outputs
-  if ((st = check_ptr(a.dx, 4, "dx", nx > 0, dev)) != SW_OK) return st;
-  if ((st = check_ptr(a.ddelta, 4, "ddelta", nx > 0, dev)) != SW_OK) return st;
+  if ((st = check_ptr(a.dx, gs, "dx", nx > 0, dev)) != SW_OK) return st;
+  if ((st = check_ptr(a.ddelta, gs, "ddelta", nx > 0, dev)) != SW_OK) return st;
   if ((st = check_ptr(a.dA, 4, "dA", nan > 0, dev)) != SW_OK) return st;
-  if ((st = check_ptr(a.dB, 4, "dB", nbc > 0, dev)) != SW_OK) return st;
-  if ((st = check_ptr(a.dC, 4, "dC", nbc > 0, dev)) != SW_OK) return st;
+  if ((st = check_ptr(a.dB, gs, "dB", nbc > 0, dev)) != SW_OK) return st;
+  if ((st = check_ptr(a.dC, gs, "dC", nbc > 0, dev)) != SW_OK) return st;
   if ((st = check_ptr(a.dDskip, 4, "dDskip", false, dev)) != SW_OK) return st;
-  if ((st = check_ptr(a.dz, 4, "dz", false, dev)) != SW_OK) return st;
+  if ((st = check_ptr(a.dz, gs, "dz", false, dev)) != SW_OK) return st;
   if ((st = check_ptr(a.ddelta_bias, 4, "ddelta_bias", false, dev)) != SW_OK) return st;
   if ((st = check_ptr(a.dh0, 4, "dh0", false, dev)) != SW_OK) return st;
-  Span outs[] = {{a.dx, (size_t)nx * 4, "dx"},         {a.ddelta, (size_t)nx * 4, "ddelta"},
-                 {a.dA, (size_t)nan * 4, "dA"},        {a.dB, (size_t)nbc * 4, "dB"},
-                 {a.dC, (size_t)nbc * 4, "dC"},        {a.dDskip, (size_t)D * 4, "dDskip"},
-                 {a.dz, (size_t)nx * 4, "dz"},         {a.ddelta_bias, (size_t)D * 4, "ddelta_bias"},
+  Span outs[] = {{a.dx, (size_t)nx * gs, "dx"},         {a.ddelta, (size_t)nx * gs, "ddelta"},
+                 {a.dA, (size_t)nan * 4, "dA"},        {a.dB, (size_t)nbc * gs, "dB"},
+                 {a.dC, (size_t)nbc * gs, "dC"},        {a.dDskip, (size_t)D * 4, "dDskip"},
+                 {a.dz, (size_t)nx * gs, "dz"},         {a.ddelta_bias, (size_t)D * 4, "ddelta_bias"},
                  {a.dh0, (size_t)nh * 4, "dh0"}};
   Span ins[] = {{a.x, (size_t)nx * es, "x"},           {a.delta, (size_t)nx * es, "delta"},
                 {a.A, (size_t)nan * 4, "A"},            {a.Bm, (size_t)nbc * es, "Bm"},
@@ -298,10 +300,11 @@ int selective_bwd_common(BwdArgs a) {
   hipStream_t s = current_stream();
   if (empty) {
     // no step: every sum is empty, and the initial state's gradient is dh_last
-    uint32_t* zs[] = {reinterpret_cast<uint32_t*>(a.dA), reinterpret_cast<uint32_t*>(a.dB),
-                      reinterpret_cast<uint32_t*>(a.dC), reinterpret_cast<uint32_t*>(a.dDskip),
+    // (dB and dC have elements only when L > 0, B > 0 and D == 0)
+    uint32_t* zs[] = {reinterpret_cast<uint32_t*>(a.dA), static_cast<uint32_t*>(a.dB),
+                      static_cast<uint32_t*>(a.dC), reinterpret_cast<uint32_t*>(a.dDskip),
                       reinterpret_cast<uint32_t*>(a.ddelta_bias)};
-    const size_t nw[] = {(size_t)nan, (size_t)nbc, (size_t)nbc, (size_t)D, (size_t)D};
+    const size_t nw[] = {(size_t)nan, (size_t)nbc * gs / 4, (size_t)nbc * gs / 4, (size_t)D, (size_t)D};
     for (int i = 0; i < 5; ++i)
       if (zs[i] && (st = zero_words(zs[i], nw[i], s)) != SW_OK) return st;
     if (a.dh0 && nh > 0) {
@@ -591,17 +594,20 @@ SW_API int sw_affine_scan_proj_i32(const int32_t* a, const int32_t* b, const int
                                           sw::affine_scan_io_u32);
 }
 
-SW_API int sw_selective_scan_bwd(const void* x, const void* delta, const float* A,
+SW_API int sw_selective_scan_bwd_ex(const void* x, const void* delta, const float* A,
                                  const void* Bm, const void* Cm, const float* Dskip,
                                  const void* z, const float* delta_bias, const float* h0,
                                  const void* dy, const float* dh_last, const float* ckpt,
-                                 const float* s_pre, float* dx, float* ddelta,
-                                 float* dA, float* dB, float* dC, float* dDskip, float* dz,
+                                 const float* s_pre, void* dx, void* ddelta,
+                                 float* dA, void* dB, void* dC, float* dDskip, void* dz,
                                  float* ddelta_bias, float* dh0, int64_t B, int64_t D, int64_t N,
-                                 int64_t L, int in_dtype, int dy_dtype, int flags) {
+                                 int64_t L, int in_dtype, int dy_dtype, int grad_dtype,
+                                    int flags) {
   if ((in_dtype != SW_DTYPE_F32 && in_dtype != SW_DTYPE_BF16) ||
-      (dy_dtype != SW_DTYPE_F32 && dy_dtype != SW_DTYPE_BF16))
-    return sw::fail(SW_ERR_INVALID_ARG, "unknown dtype (in %d, dy %d)", in_dtype, dy_dtype);
+      (dy_dtype != SW_DTYPE_F32 && dy_dtype != SW_DTYPE_BF16) ||
+      (grad_dtype != SW_DTYPE_F32 && grad_dtype != SW_DTYPE_BF16))
+    return sw::fail(SW_ERR_INVALID_ARG, "unknown dtype (in %d, dy %d, gradients %d)", in_dtype,
+                    dy_dtype, grad_dtype);
   if (flags & ~(int)SW_DELTA_SOFTPLUS)
     return sw::fail(SW_ERR_INVALID_ARG, "unknown flags 0x%x", (unsigned)flags);
   sw::BwdArgs a{};
@@ -633,8 +639,22 @@ SW_API int sw_selective_scan_bwd(const void* x, const void* delta, const float* 
   a.L = L;
   a.bf16_in = in_dtype == SW_DTYPE_BF16;
   a.dy_bf16 = dy_dtype == SW_DTYPE_BF16;
+  a.grads_bf16 = grad_dtype == SW_DTYPE_BF16;
   a.softplus = (flags & SW_DELTA_SOFTPLUS) != 0;
   return sw::selective_bwd_common(a);
+}
+
+SW_API int sw_selective_scan_bwd(const void* x, const void* delta, const float* A,
+                                 const void* Bm, const void* Cm, const float* Dskip,
+                                 const void* z, const float* delta_bias, const float* h0,
+                                 const void* dy, const float* dh_last, const float* ckpt,
+                                 const float* s_pre, float* dx, float* ddelta,
+                                 float* dA, float* dB, float* dC, float* dDskip, float* dz,
+                                 float* ddelta_bias, float* dh0, int64_t B, int64_t D, int64_t N,
+                                 int64_t L, int in_dtype, int dy_dtype, int flags) {
+  return sw_selective_scan_bwd_ex(x, delta, A, Bm, Cm, Dskip, z, delta_bias, h0, dy, dh_last, ckpt,
+                                  s_pre, dx, ddelta, dA, dB, dC, dDskip, dz, ddelta_bias, dh0, B, D,
+                                  N, L, in_dtype, dy_dtype, SW_DTYPE_F32, flags);
 }
 
 SW_API int sw_selective_scan_fwd(const float* x, const float* delta, const float* A,

@@ -105,7 +105,7 @@ int selective_states_fwd(const SelArgs& a, bool* taken);
 
 // Arguments of one backward call of the fused form, already validated.
 // x, delta, Bm, Cm, z are fp32 or bf16 as `bf16_in` says, dy as `dy_bf16`
-// says; gradients are fp32.  Optional inputs (NULL: absent): Dskip, z,
+// says; gradients are fp32 unless grads_bf16.  Optional inputs (NULL: absent): Dskip, z,
 // delta_bias, h0, dh_last; optional outputs: dDskip (with Dskip), dz (with z),
 // ddelta_bias (with delta_bias), dh0.
 struct BwdArgs {
@@ -113,9 +113,11 @@ struct BwdArgs {
   const float *A, *Dskip, *delta_bias, *h0, *dh_last;
   const float* ckpt;  // the forward's states at 8-step boundaries, or NULL (recomputed)
   const float* s_pre;  // the forward's output before the gate, or NULL (recomputed)
-  float *dx, *ddelta, *dA, *dB, *dC, *dDskip, *dz, *ddelta_bias, *dh0;
+  void *dx, *ddelta, *dB, *dC, *dz;  // fp32, or bf16 bits (grads_bf16)
+  float *dA, *dDskip, *ddelta_bias, *dh0;
   int64_t B, D, N, L;
   bool bf16_in, dy_bf16, softplus, vec;  // vec: x and delta allow the forward's vector path
+  bool grads_bf16;  // dx, ddelta, dB, dC, dz in bf16 (bf16 inputs, fp32 dy, N <= 16)
 };
 int selective_bwd(const BwdArgs& a);
 

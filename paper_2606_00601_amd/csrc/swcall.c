@@ -117,6 +117,12 @@ SW_CALL(sw_selective_scan_bwd, "PPPPPPPPPPPPPPPPPPPPPPLLLLIII", 29,
                               AP(11), AP(12), AP(13), AP(14), AP(15), AP(16), AP(17), AP(18), AP(19),
                               AP(20), AP(21), AL(22), AL(23), AL(24), AL(25), AI(26), AI(27), AI(28)))
 
+SW_CALL(sw_selective_scan_bwd_ex, "PPPPPPPPPPPPPPPPPPPPPPLLLLIIII", 30,
+        sw_selective_scan_bwd_ex(AP(0), AP(1), AP(2), AP(3), AP(4), AP(5), AP(6), AP(7), AP(8), AP(9), AP(10),
+                              AP(11), AP(12), AP(13), AP(14), AP(15), AP(16), AP(17), AP(18), AP(19),
+                              AP(20), AP(21), AL(22), AL(23), AL(24), AL(25), AI(26), AI(27), AI(28),
+                                 AI(29)))
+
 static PyObject* py_sw_set_stream(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   (void)self;
   Arg v[1];
@@ -180,6 +186,7 @@ static PyMethodDef methods[] = {
     FAST(sw_selective_scan_fwd_ex),
     FAST(sw_selective_scan_fwd_train),
     FAST(sw_selective_scan_bwd),
+    FAST(sw_selective_scan_bwd_ex),
     FAST(sw_selective_scan_plan),
     FAST(sw_set_stream),
     NOARG(sw_get_stream),
