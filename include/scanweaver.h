@@ -312,6 +312,20 @@ int sw_selective_scan_fwd_train(const void* x, const void* delta, const float* A
                                 int64_t L, int in_dtype, int out_dtype, int flags);
 
 /*
+ * sw_selective_scan_fwd_train that may cut each row into segments where its
+ * rows leave the GPU idle (N = 16; the records form of sw_selective_scan_fwd,
+ * whose last launch walks every segment from its composed state and writes
+ * its checkpoints): y, s_pre, h_last and ckpt agree with those of
+ * sw_selective_scan_fwd_train within fp32 rounding, not bit for bit.
+ */
+int sw_selective_scan_fwd_train_seg(const void* x, const void* delta, const float* A,
+                                    const void* Bm, const void* Cm, const float* Dskip,
+                                    const void* z, const float* delta_bias, const float* h0,
+                                    void* y, float* h_last, float* ckpt, float* s_pre, int64_t B,
+                                    int64_t D, int64_t N, int64_t L, int in_dtype, int out_dtype,
+                                    int flags);
+
+/*
  * Backward of sw_selective_scan_fwd_ex: the gradients of
  *   sum_{b,d,t} dy[b,d,t] y[b,d,t] + sum_{b,d,n} dh_last[b,d,n] h_last[b,d,n]
  * with respect to every input, by the chain rule through Eq. (3).  The

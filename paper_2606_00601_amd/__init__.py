@@ -243,6 +243,13 @@ def selective_scan_fwd(x, delta, A, Bm, Cm, Dskip=None, *, y=None, h_last=None,
     ``s_pre`` (B, D, L) fp32 (with ckpt) the output before the gate, both for
     :func:`selective_scan_bwd`.
     """
+    return _fwd(x, delta, A, Bm, Cm, Dskip, y, h_last, want_h_last, z, delta_bias, h0,
+                delta_softplus, y_dtype, ckpt, s_pre, False)
+
+
+def _fwd(x, delta, A, Bm, Cm, Dskip, y, h_last, want_h_last, z, delta_bias, h0, delta_softplus,
+         y_dtype, ckpt, s_pre, segments):
+    """selective_scan_fwd; ``segments``: a call with ckpt may cut its rows."""
     if not isinstance(x, torch.Tensor) or x.dim() != 3:
         raise ValueError("x must be a (B, D, L) tensor")
     dt = x.dtype
@@ -289,7 +296,9 @@ def selective_scan_fwd(x, delta, A, Bm, Cm, Dskip=None, *, y=None, h_last=None,
         _need(s_pre, "s_pre", torch.float32, (B, D, L))
     with _on(x.device):
         if ckpt is not None:
-            check(fast().sw_selective_scan_fwd_train(
+            train = fast().sw_selective_scan_fwd_train_seg if segments \
+                else fast().sw_selective_scan_fwd_train
+            check(train(
                 _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(z),
                 _ptr(delta_bias), _ptr(h0), _ptr(y), _ptr(h_last), _ptr(ckpt), _ptr(s_pre),
                 B, D, N, L, in_dt, out_dt, flags), "sw_selective_scan_fwd_train")
@@ -432,9 +441,8 @@ class _SelectiveScanFn(torch.autograd.Function):
         ck = new_ckpt(x, N) if N <= 16 else None
         sp = (torch.empty(x.shape, dtype=torch.float32, device=x.device)
               if ck is not None and z is not None else None)
-        y, h_last = selective_scan_fwd(x, delta, A, Bm, Cm, Dskip, z=z, delta_bias=delta_bias,
-                                       h0=h0, delta_softplus=delta_softplus, ckpt=ck,
-                                       s_pre=sp, y_dtype=torch.float32)
+        y, h_last = _fwd(x, delta, A, Bm, Cm, Dskip, None, None, True, z, delta_bias, h0,
+                         delta_softplus, torch.float32, ck, sp, True)
         ctx.save_for_backward(x, delta, A, Bm, Cm, Dskip, z, delta_bias, h0, ck, sp)
         ctx.delta_softplus = delta_softplus
         ctx.set_materialize_grads(False)

@@ -264,7 +264,7 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
     uint32_t flags_in, float* __restrict__ ck, int64_t nT8, float* __restrict__ s_out,
     int64_t nseg, int64_t Lseg) {
   constexpr bool WHOLE = SEG == R16_WHOLE || SEG == R16_STATES;  // one walk per row
-  static_assert(!(CK && !WHOLE), "checkpoints are written by whole-row walks only");
+  static_assert(!CK || WHOLE || SEG == R16_SEG_FWD, "checkpoints come from walks from the true state");
   constexpr bool ENDS = SEG == R16_SEG_ENDS;  // no y: the segment's P and end state
   constexpr bool NOY = ENDS || SEG == R16_STATES;  // no C, no y
   constexpr bool ALL = SEG == R16_SEG_ALL;    // y from a zero state, and the segment's records
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
       if constexpr (CK) {
         // the state before step kt*T + 4*bi; rows past D write the same
         // values as row D-1 to row D-1's slots
-        const int64_t t8 = (kt * R16_T + 4 * bi) / 8;
+        const int64_t t8 = (ts + kt * R16_T + 4 * bi) / 8;
         if ((bi & 1) == 0 && t8 < nT8) ck[((b * D + dcl) * nT8 + t8) * R16_N + n] = h;
       }
       const R16Ops& o = ops[bi % R16_NS];
@@ -892,14 +892,17 @@ void quad_geometry(int64_t L, int64_t k, int64_t* Lseg, int64_t* last) {
 template <typename IN>
 N16Plan plan_n16(const SelArgs& a, int64_t ndb, int cus) {
   N16Plan best;
-  if (a.ckpt) return best;  // checkpoints are written by whole-row walks
+  // checkpoints come from whole-row walks, or where the caller allows
+  // segments, from the records form (whose last launch walks every segment
+  // from its composed state)
+  if (a.ckpt && !a.ckpt_seg) return best;
   const int64_t L = a.L, st = R16_N * (16 / (int64_t)sizeof(IN));
   const int64_t quad_env = env_i64("SW_SS_QUAD"), seg_env = env_i64("SW_SS_SEGMENTS");
   const int64_t form_env = env_i64("SW_SS_SEGFORM");
   const bool qfits = a.vec && quad_fits<IN>(a);
   const bool quad_only = quad_env == 1 && qfits;
   const bool with_quad = qfits && quad_env != 0 && (seg_env < 0 || quad_only);
-  const bool corr_ok = !a.y_bf16;
+  const bool corr_ok = !a.y_bf16 && !a.ckpt;
   const double qscale = sizeof(IN) == 2 ? 0.92 : 1.0;
   const int64_t G16 = a.B * ndb, Gq = a.B * ((a.D + 63) / 64);
   double best_us = 1e300;
@@ -975,12 +978,13 @@ void launch_row16_segments(const SelArgs& a, int64_t ndb, uint32_t flags, int64_
   const int64_t lanes = R * R16_N;
   hipLaunchKernelGGL(row16_fold_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, s,
                      a.y, a.y_bf16, R, a.L, nseg, Lseg);
-  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_FWD, RAG>),
-                     dim3((unsigned)(rblocks * nseg)), dim3(256), 0, s,
+  auto kern = a.ckpt ? selective_row16_kernel<IN, OPT, true, R16_SEG_FWD, RAG>
+                     : selective_row16_kernel<IN, OPT, false, R16_SEG_FWD, RAG>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(rblocks * nseg)), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,
                      static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
                      static_cast<const IN*>(a.z), a.delta_bias, a.h0, a.y, a.h_last, a.D, a.L,
-                     ndb, flags, nullptr, (int64_t)0, a.s_out, nseg, Lseg);
+                     ndb, flags, a.ckpt, (a.L + 7) / 8, a.s_out, nseg, Lseg);
 }
 
 // The correction form: (1) every segment walks from a zero state (the first

@@ -734,12 +734,13 @@ SW_API int sw_selective_scan_plan(int64_t B, int64_t D, int64_t N, int64_t L, in
   return SW_OK;
 }
 
-SW_API int sw_selective_scan_fwd_train(const void* x, const void* delta, const float* A,
-                                       const void* Bm, const void* Cm, const float* Dskip,
-                                       const void* z, const float* delta_bias, const float* h0,
-                                       void* y, float* h_last, float* ckpt, float* s_pre,
-                                       int64_t B, int64_t D, int64_t N, int64_t L, int in_dtype,
-                                       int out_dtype, int flags) {
+namespace {
+int train_forward(const void* x, const void* delta, const float* A,
+                  const void* Bm, const void* Cm, const float* Dskip,
+                  const void* z, const float* delta_bias, const float* h0,
+                  void* y, float* h_last, float* ckpt, float* s_pre,
+                  int64_t B, int64_t D, int64_t N, int64_t L, int in_dtype,
+                  int out_dtype, int flags, bool segments) {
   if (!ckpt) return sw::fail(SW_ERR_INVALID_ARG, "ckpt is NULL");
   if ((in_dtype != SW_DTYPE_F32 && in_dtype != SW_DTYPE_BF16) ||
       (out_dtype != SW_DTYPE_F32 && out_dtype != SW_DTYPE_BF16))
@@ -754,8 +755,30 @@ SW_API int sw_selective_scan_fwd_train(const void* x, const void* delta, const f
   a.y_bf16 = out_dtype == SW_DTYPE_BF16;
   a.softplus = (flags & SW_DELTA_SOFTPLUS) != 0;
   a.ckpt = ckpt;
+  a.ckpt_seg = segments;
   a.s_out = s_pre;
   return sw::selective_common(a);
+}
+}  // namespace
+
+SW_API int sw_selective_scan_fwd_train(const void* x, const void* delta, const float* A,
+                                       const void* Bm, const void* Cm, const float* Dskip,
+                                       const void* z, const float* delta_bias, const float* h0,
+                                       void* y, float* h_last, float* ckpt, float* s_pre,
+                                       int64_t B, int64_t D, int64_t N, int64_t L, int in_dtype,
+                                       int out_dtype, int flags) {
+  return train_forward(x, delta, A, Bm, Cm, Dskip, z, delta_bias, h0, y, h_last, ckpt, s_pre, B, D, N,
+                       L, in_dtype, out_dtype, flags, false);
+}
+
+SW_API int sw_selective_scan_fwd_train_seg(const void* x, const void* delta, const float* A,
+                                           const void* Bm, const void* Cm, const float* Dskip,
+                                           const void* z, const float* delta_bias, const float* h0,
+                                           void* y, float* h_last, float* ckpt, float* s_pre,
+                                           int64_t B, int64_t D, int64_t N, int64_t L, int in_dtype,
+                                           int out_dtype, int flags) {
+  return train_forward(x, delta, A, Bm, Cm, Dskip, z, delta_bias, h0, y, h_last, ckpt, s_pre, B, D, N,
+                       L, in_dtype, out_dtype, flags, true);
 }
 
 SW_API int sw_set_stream(void* hip_stream) {

@@ -79,6 +79,7 @@ struct SelArgs {
   bool bf16_in, y_bf16, softplus, vec;
   bool blelloch = false;  // the paper's schedule (plain form only)
   float* ckpt = nullptr;  // (B*D, ceil(L/8), 16): states at 8-step boundaries (N <= 16)
+  bool ckpt_seg = false;  // a call with checkpoints may cut its rows into segments (N = 16)
   float* s_out = nullptr;  // (B, D, L) fp32: y before the output gate (with the options)
 };
 int selective_fwd(const SelArgs& a);

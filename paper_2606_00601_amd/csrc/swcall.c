@@ -109,6 +109,10 @@ SW_CALL(sw_selective_scan_fwd_train, "PPPPPPPPPPPPPLLLLIII", 20,
         sw_selective_scan_fwd_train(AP(0), AP(1), AP(2), AP(3), AP(4), AP(5), AP(6), AP(7), AP(8), AP(9),
                                     AP(10), AP(11), AP(12), AL(13), AL(14), AL(15), AL(16), AI(17),
                                     AI(18), AI(19)))
+SW_CALL(sw_selective_scan_fwd_train_seg, "PPPPPPPPPPPPPLLLLIII", 20,
+        sw_selective_scan_fwd_train_seg(AP(0), AP(1), AP(2), AP(3), AP(4), AP(5), AP(6), AP(7), AP(8), AP(9),
+                                    AP(10), AP(11), AP(12), AL(13), AL(14), AL(15), AL(16), AI(17),
+                                    AI(18), AI(19)))
 SW_CALL(sw_selective_scan_plan, "LLLLIIIIPPPP", 12,
         sw_selective_scan_plan(AL(0), AL(1), AL(2), AL(3), AI(4), AI(5), AI(6), AI(7), AP(8), AP(9),
                                AP(10), AP(11)))
@@ -185,6 +189,7 @@ static PyMethodDef methods[] = {
     FAST(sw_selective_scan_fwd_schedule),
     FAST(sw_selective_scan_fwd_ex),
     FAST(sw_selective_scan_fwd_train),
+    FAST(sw_selective_scan_fwd_train_seg),
     FAST(sw_selective_scan_bwd),
     FAST(sw_selective_scan_bwd_ex),
     FAST(sw_selective_scan_plan),

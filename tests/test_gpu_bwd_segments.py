@@ -72,3 +72,42 @@ def test_autograd_bf16_gradients_are_the_fp32_ones_rounded(sw, shape):  # noqa: 
     names = dict(zip(leaves, ("dx", "ddelta", "dA", "dB", "dC", "dDskip", "dz", "ddelta_bias")))
     for (k, leaf), v in zip(leaves.items(), got):
         assert v.dtype == leaf.dtype and torch.equal(v, g[names[k]].to(leaf.dtype)), k
+
+
+@pytest.mark.parametrize("L,segs", [(1024, "4"), (1003, "3")])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_segmented_training_forward(sw, monkeypatch, L, segs, dtype):  # noqa: F811
+    """Under autograd the forward may cut its rows: its checkpoints, pre-gate
+    output and y are those of the whole-row walk within fp32 rounding (the
+    composed state is one more rounding per segment of terms that the walk
+    rounds at every step: 2^-18 of the largest, against 2^-24 a step), and the
+    gradients are the oracle's."""
+    B, D, N = 1, 21, 16
+    opts = ("z", "bias", "softplus", "h0")
+    inp, ex = _inputs(B, D, N, L, 2600 + L, dtype, opts)
+    conv = (lambda k: _bf16_dev(inp[k + "_bf16"])) if dtype == "bf16" else (lambda k: _dev(inp[k]))
+    x, dl, Bm, Cm = (conv(k) for k in ("x", "delta", "Bm", "Cm"))
+    z = _bf16_dev(ex["z_bits"]) if dtype == "bf16" else _dev(ex["z"])
+    A, Dk = _dev(inp["A"]), _dev(inp["Dskip"])
+    rest = (z, _dev(ex["delta_bias"]), _dev(ex["h0"]), True, torch.float32)
+    got = []
+    for count, seg in (("1", False), (segs, True)):
+        monkeypatch.setenv("SW_SS_SEGMENTS", count)
+        ck = sw.new_ckpt(x, N).fill_(float("nan"))
+        sp = torch.full((B, D, L), float("nan"), device="cuda")
+        y, hl = sw._fwd(x, dl, A, Bm, Cm, Dk, None, None, True, *rest, ck, sp, seg)
+        assert (f"{segs} segments" in sw.last_launch()) == seg, sw.last_launch()
+        got.append((y, hl, ck, sp))
+    for a, b in zip(*got):
+        assert bool(torch.isfinite(b).all())
+        assert (a - b).abs().max() <= 2 ** -18 * a.abs().max()
+    leaves = [t.requires_grad_() for t in (x, dl, A, Bm, Cm, Dk, z)]
+    y = sw.selective_scan_fn(*leaves, delta_bias=rest[1], h0=rest[2], delta_softplus=True)
+    g = torch.autograd.grad(y, leaves, _dev(ex["dy"]))
+    o = _ref(inp, ex, opts)
+    for v, k in zip(g, ("dx", "ddelta", "dA", "dB", "dC", "dDskip", "dz")):
+        if v.dtype == torch.float32:
+            assert_gate(fp_gate(v.cpu().numpy(), o[k], o["m_" + k]), f"segmented {k}")
+        else:  # rounded once more, half a unit of 8 bits
+            err = np.abs(v.float().cpu().numpy() - o[k])
+            assert (err <= 2.0 ** -8 * np.abs(o[k]) + 1.01e-4 * o["m_" + k]).all(), k
