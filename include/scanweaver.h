@@ -379,6 +379,10 @@ int sw_selective_scan_bwd(const void* x, const void* delta, const float* A, cons
  * type: dx, ddelta, dB, dC and dz are of grad_dtype (bf16: the fp32 gradient
  * rounded once to nearest even; bf16 inputs, fp32 dy and N <= 16 only, else
  * SW_ERR_UNSUPPORTED); dA, dDskip, ddelta_bias and dh0 stay fp32.
+ * workspace: 16-byte aligned device memory of at least
+ * sw_selective_scan_bwd_workspace bytes that nothing else uses until the call
+ * completes on its stream (SW_ERR_INVALID_ARG if smaller), or NULL: taken
+ * from the device's stream-ordered pool for the call.
  */
 int sw_selective_scan_bwd_ex(const void* x, const void* delta, const float* A, const void* Bm,
                              const void* Cm, const float* Dskip, const void* z,
@@ -387,7 +391,16 @@ int sw_selective_scan_bwd_ex(const void* x, const void* delta, const float* A, c
                              void* dx, void* ddelta, float* dA, void* dB, void* dC,
                              float* dDskip, void* dz, float* ddelta_bias, float* dh0, int64_t B,
                              int64_t D, int64_t N, int64_t L, int in_dtype, int dy_dtype,
-                             int grad_dtype, int flags);
+                             int grad_dtype, int flags, void* workspace,
+                             int64_t workspace_bytes);
+
+/*
+ * Bytes of the workspace of a backward call of these sizes on the current
+ * device, with (nonzero) or without ckpt, z and s_pre (0 for an empty or
+ * invalid call).
+ */
+int64_t sw_selective_scan_bwd_workspace(int64_t B, int64_t D, int64_t N, int64_t L, int ckpt,
+                                        int z, int s_pre);
 
 /* Stream used by the calling thread's subsequent calls (a hipStream_t;
  * NULL = the null stream).  Always SW_OK. */

@@ -419,14 +419,19 @@ def _bwd(x, delta, A, Bm, Cm, Dskip, dy, dh_last, z, delta_bias, h0, delta_softp
     dy_dt = SW_DTYPE_F32 if dy.dtype == torch.float32 else SW_DTYPE_BF16
     gr_dt = SW_DTYPE_F32 if gdt == torch.float32 else SW_DTYPE_BF16
     with _on(dev):
+        # from torch's allocator, on the stream the call runs on: a block of the
+        # library's own pool costs the host more per call than it saves
+        nws = fast().sw_selective_scan_bwd_workspace(B, D, N, L, ckpt is not None, z is not None,
+                                                     s_pre is not None)
+        ws = torch.empty((nws,), dtype=torch.uint8, device=dev) if nws else None
         check(fast().sw_selective_scan_bwd_ex(
             _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(z),
             _ptr(delta_bias), _ptr(h0), _ptr(dy), _ptr(dh_last), _ptr(ckpt), _ptr(s_pre),
             _ptr(out["dx"]),
             _ptr(out["ddelta"]), _ptr(out["dA"]), _ptr(out["dB"]), _ptr(out["dC"]),
             _ptr(out["dDskip"]), _ptr(out["dz"]), _ptr(out["ddelta_bias"]), _ptr(out["dh0"]),
-            B, D, N, L, in_dt, dy_dt, gr_dt, SW_DELTA_SOFTPLUS if delta_softplus else 0),
-            "sw_selective_scan_bwd")
+            B, D, N, L, in_dt, dy_dt, gr_dt, SW_DELTA_SOFTPLUS if delta_softplus else 0,
+            _ptr(ws), nws), "sw_selective_scan_bwd")
     return {k: v for k, v in out.items() if v is not None}
 
 

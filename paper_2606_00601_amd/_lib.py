@@ -34,7 +34,8 @@ SIGNATURES = {
     "sw_affine_scan_schedule_i32": (_int, [_vp] * 4 + [_i64] * 3 + [_int]),
     "sw_affine_scan_proj": (_int, [_vp] * 7 + [_i64] * 3),
     "sw_selective_scan_bwd": (_int, [_vp] * 22 + [_i64] * 4 + [_int] * 3),
-    "sw_selective_scan_bwd_ex": (_int, [_vp] * 22 + [_i64] * 4 + [_int] * 4),
+    "sw_selective_scan_bwd_ex": (_int, [_vp] * 22 + [_i64] * 4 + [_int] * 4 + [_vp, _i64]),
+    "sw_selective_scan_bwd_workspace": (_i64, [_i64] * 4 + [_int] * 3),
     "sw_selective_scan_fwd_train": (_int, [_vp] * 13 + [_i64] * 4 + [_int] * 3),
     "sw_selective_scan_fwd_train_seg": (_int, [_vp] * 13 + [_i64] * 4 + [_int] * 3),
     "sw_selective_scan_plan": (_int, [_i64] * 4 + [_int] * 4 + [_vp] * 4),

@@ -378,7 +378,8 @@ __global__ __launch_bounds__(256, MODE == BW_ENDS ? 4 : 2) void selective_bwd_ke
             float2, __builtin_amdgcn_raw_buffer_load_b64(
                         rck, (rj[j] * (int32_t)ntile * BW_N + 2 * nl) * 4, (int32_t)kc * (BW_N * 4), 0));
       else
-        v = *reinterpret_cast<const float2*>(w.ck + ((row0 + rj[j]) * ntile + kc) * BW_N + 2 * nl);
+        v = make_float2(w.ck[((row0 + rj[j]) * ntile + kc) * BW_N + 2 * nl],
+                        w.ck[((row0 + rj[j]) * ntile + kc) * BW_N + 2 * nl + 1]);
       h[0][j] = v.x;
       h[1][j] = v.y;
     }
@@ -933,9 +934,9 @@ void launch_bwd(const BwdArgs& a, const BwWork& w, int64_t G, int64_t ntile, con
 // D=1536, L=2048 (bf16, gate, softplus) 641 / 508 (5 or 8 segments), 561
 // before; B=1, D=1000, L=1501 (fp32) 398 / 71 (16), 200 before; B=16, D=5120,
 // L=256 345 / 393 (2), 455 before.
-BwdPlan plan_bwd(const BwdArgs& a, int64_t G, int64_t ntile, int cus) {
+BwdPlan plan_bwd(int64_t B, int64_t G, int64_t ntile, int cus) {
   BwdPlan best{1, ntile};
-  const int64_t W = a.B * G;
+  const int64_t W = B * G;
   const auto per_cu = [&](int64_t n) { return (n + cus - 1) / cus; };
   const auto main_us = [&](int64_t n, int64_t tiles) {
     const int64_t p = per_cu(n);
@@ -956,51 +957,85 @@ BwdPlan plan_bwd(const BwdArgs& a, int64_t G, int64_t ntile, int cus) {
   return best;
 }
 
+// The call's sizes: workgroups per batch, tiles, segments, and the floats of
+// each part of the workspace.
+struct BwdSizes {
+  int64_t G, ntile;
+  BwdPlan plan;
+  size_t ck, bc, rec, dA, s, d, total;
+};
+
+BwdSizes bwd_sizes(int64_t B, int64_t D, int64_t N, int64_t L, bool ckpt, bool pre) {
+  BwdSizes z;
+  z.G = (D + BW_ROWS - 1) / BW_ROWS;
+  z.ntile = (L + BW_T - 1) / BW_T;
+  int cus = 0;
+  if (device_cus(&cus) != SW_OK) cus = 256;
+  z.plan = plan_bwd(B, z.G, z.ntile, cus);
+  const size_t R = (size_t)(B * D), nseg = (size_t)z.plan.nseg;
+  // without the forward's checkpoints the call rebuilds them in the workspace
+  z.ck = ckpt ? 0 : R * (size_t)z.ntile * BW_N;
+  z.bc = (size_t)(B * z.G) * (size_t)L * BW_N;
+  z.rec = 2 * R * BW_N * (nseg - 1);
+  z.dA = R * BW_N * nseg;
+  z.s = pre ? R * (size_t)L : 0;
+  z.d = R * nseg;
+  // 16-byte groups first: shares and checkpoints are read as vectors
+  z.total = z.ck + 2 * z.bc + z.rec + z.dA + z.s + 2 * z.d + 1024;
+  return z;
+}
+
 }  // namespace
+
+int64_t selective_bwd_workspace(int64_t B, int64_t D, int64_t N, int64_t L, bool ckpt, bool z,
+                                bool s_pre) {
+  return (int64_t)(bwd_sizes(B, D, N, L, ckpt, z && !s_pre).total * sizeof(float));
+}
 
 int selective_bwd(const BwdArgs& a) {
   if (a.ckpt && a.N > BW_N)
     return fail(SW_ERR_UNSUPPORTED, "checkpoints hold 16 states (N=%lld)", (long long)a.N);
   hipStream_t s = current_stream();
   const int64_t B = a.B, D = a.D, L = a.L;
-  const int64_t G = (D + BW_ROWS - 1) / BW_ROWS;
-  const int64_t ntile = (L + BW_T - 1) / BW_T;
   const int64_t G16 = (D + SW_ROWS - 1) / SW_ROWS;
   if (B * G16 >= ((int64_t)1 << 31))
     return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range", (long long)(B * G16));
-  int cus = 0;
-  if (device_cus(&cus) != SW_OK) cus = 256;
-  const BwdPlan plan = plan_bwd(a, G, ntile, cus);
-  const size_t R = (size_t)(B * D);
-  // without the forward's checkpoints the kernel rebuilds them in a workspace
-  const size_t n_ck = a.ckpt ? 0 : R * (size_t)ntile * BW_N;
-  const size_t n_s = (a.z && !a.s_pre) ? R * (size_t)L : 0;
-  const size_t n_dA = R * BW_N * plan.nseg, n_rec = 2 * R * BW_N * (plan.nseg - 1), n_bc = (size_t)(B * G) * (size_t)L * BW_N;
-  const size_t n_d = R * plan.nseg;
-  // 16-byte groups first: shares and checkpoints are read as vectors
-  const size_t total = n_ck + 2 * n_bc + n_rec + n_dA + n_s + 2 * n_d + 1024;
-  void* base = nullptr;
-  int st = workspace_alloc(&base, total * sizeof(float), s);
+  const BwdSizes z = bwd_sizes(B, D, a.N, L, a.ckpt != nullptr, a.z && !a.s_pre);
+  const int64_t G = z.G, ntile = z.ntile;
+  const BwdPlan plan = z.plan;
+  void* base = a.ws;
+  int st;
+  if (base) {
+    if (a.ws_bytes < z.total * sizeof(float))
+      return fail(SW_ERR_INVALID_ARG, "workspace of %zu bytes, %zu needed", a.ws_bytes,
+                  z.total * sizeof(float));
+    st = refuse_capture(s, "a workspace allocated per call");
+  } else {
+    st = workspace_alloc(&base, z.total * sizeof(float), s);
+  }
   if (st != SW_OK) return st;
+  const auto done = [&] {
+    if (!a.ws) workspace_free(base, s);
+  };
   float* f = static_cast<float*>(base);
   BwWork w;
   w.ck = a.ckpt ? const_cast<float*>(a.ckpt) : f;  // read-only when given
-  f += n_ck;
+  f += z.ck;
   w.dB_p = f;
-  f += n_bc;
+  f += z.bc;
   w.dC_p = f;
-  f += n_bc;
+  f += z.bc;
   w.rec = f;
-  f += n_rec;
+  f += z.rec;
   w.dA_p = f;
-  f += n_dA;
+  f += z.dA;
   float* s_pre = (a.z && !a.s_pre) ? f : nullptr;
   w.s = a.s_pre ? a.s_pre : s_pre;
-  f += n_s;
+  f += z.s;
   w.dD_p = f;
-  f += n_d;
+  f += z.d;
   w.db_p = f;
-  f += n_d;
+  f += z.d;
   w.trash = f;
   // with a gate, the forward without the gate runs anyway (for the pre-gate
   // output); for N <= 16 it also writes the tile checkpoints, so the backward
@@ -1031,7 +1066,7 @@ int selective_bwd(const BwdArgs& a) {
     }
     st = selective_fwd(fa);
     if (st != SW_OK) {
-      workspace_free(base, s);
+      done();
       return st;
     }
   }
@@ -1059,7 +1094,7 @@ int selective_bwd(const BwdArgs& a) {
     bool taken = false;
     st = selective_states_fwd(fa, &taken);
     if (st != SW_OK) {
-      workspace_free(base, s);
+      done();
       return st;
     }
     if (taken) {
@@ -1091,7 +1126,7 @@ int selective_bwd(const BwdArgs& a) {
                        plan.nseg);
     st = check_launch("selective_bwd_reduce_kernel");
   }
-  workspace_free(base, s);
+  done();
   if (st == SW_OK)
     note_launch("selective_bwd_kernel + selective_bwd_reduce_kernel (%lld state group%s, %d "
                 "segment%s), checkpoints %s",

@@ -283,11 +283,12 @@ int selective_bwd_common(BwdArgs a) {
   if ((st = check_ptr(a.dz, gs, "dz", false, dev)) != SW_OK) return st;
   if ((st = check_ptr(a.ddelta_bias, 4, "ddelta_bias", false, dev)) != SW_OK) return st;
   if ((st = check_ptr(a.dh0, 4, "dh0", false, dev)) != SW_OK) return st;
+  if ((st = check_ptr(a.ws, 16, "workspace", false, dev)) != SW_OK) return st;
   Span outs[] = {{a.dx, (size_t)nx * gs, "dx"},         {a.ddelta, (size_t)nx * gs, "ddelta"},
                  {a.dA, (size_t)nan * 4, "dA"},        {a.dB, (size_t)nbc * gs, "dB"},
                  {a.dC, (size_t)nbc * gs, "dC"},        {a.dDskip, (size_t)D * 4, "dDskip"},
                  {a.dz, (size_t)nx * gs, "dz"},         {a.ddelta_bias, (size_t)D * 4, "ddelta_bias"},
-                 {a.dh0, (size_t)nh * 4, "dh0"}};
+                 {a.dh0, (size_t)nh * 4, "dh0"},       {a.ws, a.ws_bytes, "workspace"}};
   Span ins[] = {{a.x, (size_t)nx * es, "x"},           {a.delta, (size_t)nx * es, "delta"},
                 {a.A, (size_t)nan * 4, "A"},            {a.Bm, (size_t)nbc * es, "Bm"},
                 {a.Cm, (size_t)nbc * es, "Cm"},         {a.Dskip, (size_t)D * 4, "Dskip"},
@@ -296,7 +297,7 @@ int selective_bwd_common(BwdArgs a) {
                 {a.dh_last, (size_t)nh * 4, "dh_last"},
                 {a.ckpt, (size_t)R * (size_t)((L + 7) / 8) * 64, "ckpt"},
                 {a.s_pre, (size_t)nx * 4, "s_pre"}};
-  if ((st = check_spans(outs, 9, ins, 13)) != SW_OK) return st;
+  if ((st = check_spans(outs, 10, ins, 13)) != SW_OK) return st;
   hipStream_t s = current_stream();
   if (empty) {
     // no step: every sum is empty, and the initial state's gradient is dh_last
@@ -602,7 +603,7 @@ SW_API int sw_selective_scan_bwd_ex(const void* x, const void* delta, const floa
                                  float* dA, void* dB, void* dC, float* dDskip, void* dz,
                                  float* ddelta_bias, float* dh0, int64_t B, int64_t D, int64_t N,
                                  int64_t L, int in_dtype, int dy_dtype, int grad_dtype,
-                                    int flags) {
+                                    int flags, void* workspace, int64_t workspace_bytes) {
   if ((in_dtype != SW_DTYPE_F32 && in_dtype != SW_DTYPE_BF16) ||
       (dy_dtype != SW_DTYPE_F32 && dy_dtype != SW_DTYPE_BF16) ||
       (grad_dtype != SW_DTYPE_F32 && grad_dtype != SW_DTYPE_BF16))
@@ -610,7 +611,10 @@ SW_API int sw_selective_scan_bwd_ex(const void* x, const void* delta, const floa
                     dy_dtype, grad_dtype);
   if (flags & ~(int)SW_DELTA_SOFTPLUS)
     return sw::fail(SW_ERR_INVALID_ARG, "unknown flags 0x%x", (unsigned)flags);
+  if (workspace_bytes < 0) return sw::fail(SW_ERR_INVALID_ARG, "negative workspace size");
   sw::BwdArgs a{};
+  a.ws = workspace;
+  a.ws_bytes = (size_t)workspace_bytes;
   a.x = x;
   a.delta = delta;
   a.Bm = Bm;
@@ -644,6 +648,15 @@ SW_API int sw_selective_scan_bwd_ex(const void* x, const void* delta, const floa
   return sw::selective_bwd_common(a);
 }
 
+SW_API int64_t sw_selective_scan_bwd_workspace(int64_t B, int64_t D, int64_t N, int64_t L, int ckpt,
+                                               int z, int s_pre) {
+  int64_t n;
+  if (B <= 0 || D <= 0 || N < 1 || N > 64 || L <= 0 || !sw::mul_ok(B, D, &n) || !sw::mul_ok(n, L, &n) ||
+      !sw::mul_ok(n, 64, &n))
+    return 0;
+  return sw::selective_bwd_workspace(B, D, N, L, ckpt != 0, z != 0, s_pre != 0);
+}
+
 SW_API int sw_selective_scan_bwd(const void* x, const void* delta, const float* A,
                                  const void* Bm, const void* Cm, const float* Dskip,
                                  const void* z, const float* delta_bias, const float* h0,
@@ -654,7 +667,7 @@ SW_API int sw_selective_scan_bwd(const void* x, const void* delta, const float* 
                                  int64_t L, int in_dtype, int dy_dtype, int flags) {
   return sw_selective_scan_bwd_ex(x, delta, A, Bm, Cm, Dskip, z, delta_bias, h0, dy, dh_last, ckpt,
                                   s_pre, dx, ddelta, dA, dB, dC, dDskip, dz, ddelta_bias, dh0, B, D,
-                                  N, L, in_dtype, dy_dtype, SW_DTYPE_F32, flags);
+                                  N, L, in_dtype, dy_dtype, SW_DTYPE_F32, flags, nullptr, 0);
 }
 
 SW_API int sw_selective_scan_fwd(const float* x, const float* delta, const float* A,

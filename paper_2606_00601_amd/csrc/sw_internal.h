@@ -118,9 +118,14 @@ struct BwdArgs {
   float *dA, *dDskip, *ddelta_bias, *dh0;
   int64_t B, D, N, L;
   bool bf16_in, dy_bf16, softplus, vec;  // vec: x and delta allow the forward's vector path
+  void* ws = nullptr;  // the caller's workspace (NULL: allocated per call)
+  size_t ws_bytes = 0;
   bool grads_bf16;  // dx, ddelta, dB, dC, dz in bf16 (bf16 inputs, fp32 dy, N <= 16)
 };
 int selective_bwd(const BwdArgs& a);
+// Bytes of its workspace (given: checkpoints; z, s_pre: the call has them).
+int64_t selective_bwd_workspace(int64_t B, int64_t D, int64_t N, int64_t L, bool ckpt, bool z,
+                                bool s_pre);
 
 // Stream-ordered workspace (hipMallocAsync / hipFreeAsync on `s`; freed
 // blocks stay in the device's pool).

@@ -121,11 +121,20 @@ SW_CALL(sw_selective_scan_bwd, "PPPPPPPPPPPPPPPPPPPPPPLLLLIII", 29,
                               AP(11), AP(12), AP(13), AP(14), AP(15), AP(16), AP(17), AP(18), AP(19),
                               AP(20), AP(21), AL(22), AL(23), AL(24), AL(25), AI(26), AI(27), AI(28)))
 
-SW_CALL(sw_selective_scan_bwd_ex, "PPPPPPPPPPPPPPPPPPPPPPLLLLIIII", 30,
+SW_CALL(sw_selective_scan_bwd_ex, "PPPPPPPPPPPPPPPPPPPPPPLLLLIIIIPL", 32,
         sw_selective_scan_bwd_ex(AP(0), AP(1), AP(2), AP(3), AP(4), AP(5), AP(6), AP(7), AP(8), AP(9), AP(10),
                               AP(11), AP(12), AP(13), AP(14), AP(15), AP(16), AP(17), AP(18), AP(19),
                               AP(20), AP(21), AL(22), AL(23), AL(24), AL(25), AI(26), AI(27), AI(28),
-                                 AI(29)))
+                                 AI(29), AP(30), AL(31)))
+
+static PyObject* py_sw_selective_scan_bwd_workspace(PyObject* self, PyObject* const* args,
+                                                    Py_ssize_t nargs) {
+  (void)self;
+  Arg v[7];
+  if (!parse(args, nargs, "LLLLIII", v, "sw_selective_scan_bwd_workspace")) return NULL;
+  return PyLong_FromLongLong(
+      sw_selective_scan_bwd_workspace(AL(0), AL(1), AL(2), AL(3), AI(4), AI(5), AI(6)));
+}
 
 static PyObject* py_sw_set_stream(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   (void)self;
@@ -192,6 +201,7 @@ static PyMethodDef methods[] = {
     FAST(sw_selective_scan_fwd_train_seg),
     FAST(sw_selective_scan_bwd),
     FAST(sw_selective_scan_bwd_ex),
+    FAST(sw_selective_scan_bwd_workspace),
     FAST(sw_selective_scan_plan),
     FAST(sw_set_stream),
     NOARG(sw_get_stream),
