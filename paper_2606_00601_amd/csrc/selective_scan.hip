@@ -639,6 +639,8 @@ bool row16_fits(int64_t D, int64_t N, int64_t L, size_t es);
 template <typename IN>
 int launch_row16(const SelArgs& a, hipStream_t s);
 template <typename IN>
+int launch_row16_groups(const SelArgs& a, hipStream_t s);
+template <typename IN>
 int launch_row16_states(const SelArgs& a, hipStream_t s);
 template <typename IN>
 SelPlan plan_row16(const SelArgs& a, int cus);
@@ -658,18 +660,55 @@ bool vector_path(const SelArgs& a) {
   return a.vec && fits && ((uintptr_t)a.Bm % 16 == 0) && ((uintptr_t)a.Cm % 16 == 0);
 }
 
-// N = 16 with 16-byte aligned B and C: one state per lane, 16-lane rows
-// (selective_scan16.hip), whatever the rows' length and alignment;
+// 16-byte aligned B and C and an even N above 8: one state per lane, 16-lane
+// rows (selective_scan16.hip), whatever the rows' length and alignment;
 // SW_SS_LAYOUT=8 keeps the 8-lane layout.
 template <typename IN>
-bool row16_path(const SelArgs& a) {
+bool lanes16_path(const SelArgs& a) {
   return (uintptr_t)a.Bm % 16 == 0 && (uintptr_t)a.Cm % 16 == 0 &&
          env_int("SW_SS_LAYOUT", 16) == 16 && row16_fits(a.D, a.N, a.L, sizeof(IN));
+}
+template <typename IN>
+bool row16_path(const SelArgs& a) {
+  return a.N == 16 && lanes16_path<IN>(a);
 }
 // ... whose rows are whole aligned vectors
 template <typename IN>
 bool row16_whole_vectors(const SelArgs& a) {
   return row16_path<IN>(a) && a.vec && a.L % (16 / (int64_t)sizeof(IN)) == 0;
+}
+
+// Whether a call that lanes16_path admits takes the 16-lane kernels rather
+// than the 8-lane one.  Up to 16 states always: us per call, 8-lane / 16-lane,
+// B=1 D=1000 N=12 L=1000 57 / 23, B=8 D=1536 N=12 L=2048 184 / 124 (fp32).
+// Above, both are priced.  The groups: their walk on whole rows (the per-step
+// times of the 16-lane plan), the traffic of the planes at the rate of a copy,
+// and at least 35 us, the host's time for the planes' workspace and the
+// launches.  The 8-lane kernel: its measured time per step with w wavefronts
+// on a compute unit, 6 (N <= 32) or 3 (by LDS) of them at a time, 1.15 times
+// that where N is padded.  Measured: B=2 D=1024 N=64 L=1024 128 / 70, B=16
+// D=2560 N=48 L=200 373 / 219, B=1 D=768 N=24 L=500 48 / 43, but B=2 D=512 N=48
+// L=100 29 / 35, B=1 D=256 N=32 L=64 14 / 35, B=8 D=2048 N=32 L=1024 180 / 224.
+template <typename IN>
+bool groups_pay(const SelArgs& a) {
+  if (a.N <= 16) return true;
+  int cus = 0;
+  if (device_cus(&cus) != SW_OK) cus = 256;
+  const int64_t R = a.B * a.D, ngrp = (a.N + 15) / 16;
+  const int64_t per = (a.B * ((a.D + 15) / 16) * ngrp + cus - 1) / cus;
+  const double rest[3] = {0.0, 28.8, 42.3};
+  const double walk = (double)a.L * ((double)(per / 3) * 57.1 + rest[per % 3]) * 1e-3;
+  const int passes = (int)(2 * ngrp + 1) + (a.z ? 2 : 0);
+  const double planes = (double)R * (double)a.L * 4.0 * passes / 5.0e6;
+  double groups = walk + planes + 5.0;
+  if (groups < 35.0) groups = 35.0;
+  const double w = (double)R / (8.0 * cus);
+  const double wc = w < 1.0 ? 1.0 : w;
+  double step = a.N > 32 ? (w <= 1.0 ? 0.125 : 0.15 * (wc > 3.0 ? wc / 3.0 : 1.0))
+                         : 0.09 + 0.012 * ((wc < 6.0 ? wc : 6.0) - 1.0);
+  if (a.N <= 32 && wc > 6.0) step *= wc / 6.0;
+  if ((a.N != 32 && a.N != 64) || !vector_path<IN>(a)) step *= 1.15;
+  return groups < step * (double)a.L;
 }
 
 // Calls of at most 16 steps take the kernel of selective_step.hip, which moves
@@ -699,6 +738,8 @@ int launch_selective(const SelArgs& a) {
   }
   if (step) return launch_step<IN>(a, s);
   if (r16) return launch_row16<IN>(a, s);
+  if (lanes16_path<IN>(a) && !(a.ckpt && N > 16) && groups_pay<IN>(a))
+    return launch_row16_groups<IN>(a, s);
   if (N <= 8) return launch_npl<IN, 1>(a, v, s);
   if (N <= 16) return launch_npl<IN, 2>(a, v, s);
   if (N <= 32) return launch_npl<IN, 4>(a, v, s);

@@ -255,14 +255,21 @@ __device__ __forceinline__ void rec_store(void* yv, bool ybf, int64_t row, int64
 // RAG: rows of any length at any element alignment (L at least a lane's V
 // steps): loads through RagVec, steps past the row's end made identity steps
 // one by one, y stored by element in the last tile (bf16 y in every tile).
-template <typename IN, bool OPT, bool CK, int SEG, bool RAG>
+// KIND: R16_VEC whole aligned vectors, R16_RAG as above, R16_GRP as R16_RAG for
+// N other than 16 (even, above 8): the states in ngrp groups of 16, a
+// workgroup per (row block, group), states past N masked to identity steps.
+// With several groups each writes its part of y (no skip, no gate, fp32) to
+// its own plane of B*D*L elements from yv, added up by row16_groups_kernel.
+enum : int { R16_VEC = 0, R16_RAG = 1, R16_GRP = 2 };
+template <typename IN, bool OPT, bool CK, int SEG, int KIND>
 __global__ __launch_bounds__(256) void selective_row16_kernel(
     const IN* __restrict__ x, const IN* __restrict__ delta, const float* __restrict__ A,
     const IN* __restrict__ Bm, const IN* __restrict__ Cm, const float* __restrict__ Dskip,
     const IN* __restrict__ z, const float* __restrict__ dbias, const float* __restrict__ h0,
-    void* __restrict__ yv, float* __restrict__ h_last, int64_t D, int64_t L, int64_t ndb,
+    void* __restrict__ yv_in, float* __restrict__ h_last, int64_t D, int64_t L, int64_t ndb,
     uint32_t flags_in, float* __restrict__ ck, int64_t nT8, float* __restrict__ s_out,
-    int64_t nseg, int64_t Lseg) {
+    int64_t nseg, int64_t Lseg, int Nst, int ngrp, int64_t plane) {
+  constexpr bool RAG = KIND != R16_VEC, GRP = KIND == R16_GRP;
   constexpr bool WHOLE = SEG == R16_WHOLE || SEG == R16_STATES;  // one walk per row
   static_assert(!CK || WHOLE || SEG == R16_SEG_FWD, "checkpoints come from walks from the true state");
   constexpr bool ENDS = SEG == R16_SEG_ENDS;  // no y: the segment's P and end state
@@ -286,7 +293,11 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
   const int64_t nsl = (ENDS || CORR) ? nseg - 1 : nseg;
   const int64_t bid = xcd_contiguous(blockIdx.x, gridDim.x);
   const int64_t sg = !WHOLE ? bid % nsl + (CORR ? 1 : 0) : 0;
-  const int64_t rblk = !WHOLE ? bid / nsl : bid;
+  const int64_t rblk_g = !WHOLE ? bid / nsl : bid;
+  const int64_t rblk = GRP ? rblk_g / ngrp : rblk_g;
+  const int grp = GRP ? (int)(rblk_g - rblk * ngrp) : 0;
+  const int N = GRP ? Nst : R16_N, n0 = R16_N * grp;
+  void* const yv = GRP ? static_cast<void*>(static_cast<float*>(yv_in) + grp * plane) : yv_in;
   const int64_t ts = !WHOLE ? sg * Lseg : 0;  // first step of the segment
   const int64_t Ls = !WHOLE ? (sg == nseg - 1 ? L - ts : Lseg) : L;  // its steps
   const int32_t Ls32 = (int32_t)Ls;  // below 2^31 / 16 (row16_fits)
@@ -300,14 +311,14 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
 
   // resources start at the segment's first step (row strides stay L)
   const uint32_t rows_bytes = (uint32_t)((rows * L - ts) * ES);
-  const uint32_t bc_bytes = (uint32_t)((L - ts) * R16_N * ES);
+  const uint32_t bc_bytes = (uint32_t)((L - ts) * N * ES);
   int hx = 0, hd = 0, hz = 0;  // RAG: where x, delta and z start in their resources
   const __amdgpu_buffer_rsrc_t rx = RAG ? rag_rsrc(x + row0 * L + ts, rows_bytes, &hx)
                                         : buffer_rsrc(x + row0 * L + ts, rows_bytes);
   const __amdgpu_buffer_rsrc_t rd = RAG ? rag_rsrc(delta + row0 * L + ts, rows_bytes, &hd)
                                         : buffer_rsrc(delta + row0 * L + ts, rows_bytes);
-  const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(Bm + (b * L + ts) * R16_N, bc_bytes);
-  const __amdgpu_buffer_rsrc_t rc = buffer_rsrc(Cm + (b * L + ts) * R16_N, bc_bytes);
+  const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(Bm + (b * L + ts) * N, bc_bytes);
+  const __amdgpu_buffer_rsrc_t rc = buffer_rsrc(Cm + (b * L + ts) * N, bc_bytes);
   // the gate's input; without a gate (OPT set) the same loads read x (cached),
   // so that every path of one instantiation issues the same loads
   const IN* const zsrc = ((flags & SEL_GATED) ? z : x) + row0 * L + ts;
@@ -329,11 +340,12 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
     return back + (ES == 4 ? 0 : (rag_at(t, cnt, h) & 1));
   };
 
-  const float Al = A[dcl * R16_N + n] * R16_LOG2E;
+  const bool nok = !GRP || n0 + n < N;
+  const float Al = nok ? A[dcl * N + n0 + n] * R16_LOG2E : 0.0f;
   const float dsk = Dskip ? Dskip[dcl] : 0.0f;
   const float dbv = (OPT && dbias) ? dbias[dcl] : 0.0f;
   const bool ybf = (flags & SEL_Y_BF16) != 0;
-  float h = (h0 && sg == 0) ? h0[(b * D + dcl) * R16_N + n] : 0.0f;
+  float h = (h0 && sg == 0 && nok) ? h0[(b * D + dcl) * N + n0 + n] : 0.0f;
   if constexpr (SEG == R16_SEG_FWD || CORR) {
     // the initial state the fold left in this segment's first words of y
     if (sg > 0) h = rec_load(yv, ybf, b * D + dcl, L, ts, n);
@@ -353,18 +365,19 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
   const int stt = tid / 8, sn = 2 * (tid % 8);
   RawVec<IN, 2> sbr[2], scr[2];  // raw pairs of tiles kt+1 and kt+2 (by tile parity)
   auto fetch_bc = [&](RawVec<IN, 2>& rbv, RawVec<IN, 2>& rcv, int64_t kt) {
-    const int32_t off = (int32_t)(((kt * R16_T + stt) * R16_N + sn) * ES);
+    const int32_t off = (int32_t)(((kt * R16_T + stt) * N + n0 + sn) * ES);
     rbv.load_buf(rb, off);
     if constexpr (!NOY) rcv.load_buf(rc, off);  // NOY: C is not read
   };
   auto stage_bc = [&](const RawVec<IN, 2>& rbv, const RawVec<IN, 2>& rcv, int buf) {
     float* bb = &sm.bc[buf][0][sn * R16_TS + stt];
     float* cc = &sm.bc[buf][1][sn * R16_TS + stt];
-    bb[0] = rbv.get(0);
-    bb[R16_TS] = rbv.get(1);
+    const bool ok = !GRP || n0 + sn < N;  // N is even: both states or neither
+    bb[0] = ok ? rbv.get(0) : 0.0f;
+    bb[R16_TS] = ok ? rbv.get(1) : 0.0f;
     if constexpr (!NOY) {
-      cc[0] = rcv.get(0);
-      cc[R16_TS] = rcv.get(1);
+      cc[0] = ok ? rcv.get(0) : 0.0f;
+      cc[R16_TS] = ok ? rcv.get(1) : 0.0f;
     }
   };
 
@@ -684,7 +697,7 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
       rec_store(yv, ybf, b * D + d, L, ts + Ls, R16_N + n, h);
     }
   } else if constexpr (SEG == R16_STATES) {
-    if (h_last && dok) h_last[(b * D + d) * R16_N + n] = h;
+    if (h_last && dok && nok) h_last[(b * D + d) * N + n0 + n] = h;
   } else {
     float4 pr[8];
     read_partials(pr);
@@ -706,8 +719,8 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
       }
     }
     if constexpr (!CORR) {
-      if (h_last && dok && (WHOLE || sg == nseg - 1))
-        h_last[(b * D + d) * R16_N + n] = h;
+      if (h_last && dok && nok && (WHOLE || sg == nseg - 1))
+        h_last[(b * D + d) * N + n0 + n] = h;
     }
   }
 }
@@ -749,7 +762,7 @@ __global__ __launch_bounds__(256) void row16_fold_kernel(void* __restrict__ yv, 
 __global__ __launch_bounds__(256) void row16_fold_corr_kernel(float* __restrict__ y,
                                                               float* __restrict__ h_last,
                                                               int64_t R, int64_t L, int64_t nseg,
-                                                              int64_t Lseg) {
+                                                              int64_t Lseg, int N, int64_t Rg) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= R * R16_N) return;
   const int64_t row = i / R16_N;
@@ -770,9 +783,39 @@ __global__ __launch_bounds__(256) void row16_fold_corr_kernel(float* __restrict_
       rec_store(y, false, row, L, sgi * Lseg, n, h);
     }
   }
-  if (h_last) {
+  // row r of plane g (Rg rows a plane) holds states 16g .. of the call's row r
+  const int64_t g = row / Rg, ns = R16_N * g + n, at = (row - g * Rg) * N + ns;
+  if (h_last && ns < N) {
     const float Pl = rec_load(y, false, row, L, (nseg - 1) * Lseg, 2 * R16_N + n);
-    h_last[row * R16_N + n] = __builtin_fmaf(Pl, h, h_last[row * R16_N + n]);
+    h_last[at] = __builtin_fmaf(Pl, h, h_last[at]);
+  }
+}
+
+// y of a call whose states were walked in groups: the groups' planes added in
+// order, Dskip x, the pre-gate output, the gate, and y in its type.  One
+// workgroup per row and 1024 steps; bound by HBM (the planes, x, z and y).
+template <typename IN>
+__global__ __launch_bounds__(256) void row16_groups_kernel(
+    const float* __restrict__ planes, int ngrp, const IN* __restrict__ x,
+    const IN* __restrict__ z, const float* __restrict__ Dskip, void* __restrict__ y,
+    float* __restrict__ s_out, int64_t R, int64_t D, int64_t L, int64_t nch, bool ybf) {
+  const int64_t row = blockIdx.x / nch;
+  const int64_t t0 = (blockIdx.x - row * nch) * 1024 + threadIdx.x;
+  const float dsk = Dskip ? Dskip[row % D] : 0.0f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t t = t0 + 256 * q;
+    if (t >= L) break;
+    const int64_t i = row * L + t;
+    float s = planes[i];
+    for (int g = 1; g < ngrp; ++g) s += planes[g * R * L + i];
+    if (Dskip) s = __builtin_fmaf(dsk, __uint_as_float(Elt<IN>::raw(x, i) << (sizeof(IN) == 2 ? 16 : 0)), s);
+    if (s_out) s_out[i] = s;
+    if (z) s *= silu_f32(__uint_as_float(Elt<IN>::raw(z, i) << (sizeof(IN) == 2 ? 16 : 0)));
+    if (ybf)
+      static_cast<uint16_t*>(y)[i] = (uint16_t)bf16_rne(s);
+    else
+      static_cast<float*>(y)[i] = s;
   }
 }
 
@@ -784,7 +827,7 @@ void launch_fold_corr(float* y, float* h_last, int64_t R, int64_t L, int64_t nse
                       hipStream_t s) {
   const int64_t lanes = R * R16_N;
   hipLaunchKernelGGL(row16_fold_corr_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0,
-                     s, y, h_last, R, L, nseg, Lseg);
+                     s, y, h_last, R, L, nseg, Lseg, R16_N, R);
 }
 
 template <typename IN>
@@ -795,13 +838,14 @@ int launch_quad(const SelArgs& a, int64_t nseg, int64_t Lseg, hipStream_t s);
 // True when the N = 16 layout can take the call: rows of at least a lane's
 // vector of steps, and every byte offset of a workgroup (including loads run
 // ahead past the end) below 2^31.
+// (N other than 16: the state groups of R16_GRP, which read B and C in pairs.)
 bool row16_fits(int64_t D, int64_t N, int64_t L, size_t es) {
-  if (N != R16_N) return false;
+  if (N <= 8 || N % 2 != 0) return false;
   const int64_t vstep = 16 / (int64_t)es;
   if (L < vstep) return false;
   const int64_t pad = 4 * R16_N * vstep;
   return R16_ROWS * (L + pad) * (int64_t)es < ((int64_t)1 << 31) &&
-         (L + pad) * R16_N * (int64_t)es < ((int64_t)1 << 31) && D > 0;
+         (L + pad) * (N > R16_N ? N : R16_N) * (int64_t)es < ((int64_t)1 << 31) && D > 0;
 }
 
 // ---- which layout, how many segments and which form an N = 16 call takes
@@ -964,27 +1008,34 @@ N16Plan plan_n16(const SelArgs& a, int64_t ndb, int cus) {
   return best;
 }
 
-template <typename IN, bool OPT, bool RAG>
+// Groups of 16 states of a call of that kind.
+template <int KIND>
+int r16_groups(int64_t N) {
+  return KIND == R16_GRP ? (int)((N + R16_N - 1) / R16_N) : 1;
+}
+
+template <typename IN, bool OPT, int KIND>
 void launch_row16_segments(const SelArgs& a, int64_t ndb, uint32_t flags, int64_t nseg,
                            int64_t Lseg, hipStream_t s) {
   const int64_t R = a.B * a.D;
-  const int64_t rblocks = a.B * ndb;
-  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_ENDS, RAG>),
+  const int ngrp = r16_groups<KIND>(a.N);
+  const int64_t rblocks = a.B * ndb * ngrp;
+  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_ENDS, KIND>),
                      dim3((unsigned)(rblocks * (nseg - 1))), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,
                      static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
                      static_cast<const IN*>(a.z), a.delta_bias, a.h0, a.y, nullptr, a.D, a.L,
-                     ndb, flags, nullptr, (int64_t)0, nullptr, nseg, Lseg);
-  const int64_t lanes = R * R16_N;
+                     ndb, flags, nullptr, (int64_t)0, nullptr, nseg, Lseg, (int)a.N, ngrp, R * a.L);
+  const int64_t lanes = R * ngrp * R16_N;
   hipLaunchKernelGGL(row16_fold_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, s,
-                     a.y, a.y_bf16, R, a.L, nseg, Lseg);
-  auto kern = a.ckpt ? selective_row16_kernel<IN, OPT, true, R16_SEG_FWD, RAG>
-                     : selective_row16_kernel<IN, OPT, false, R16_SEG_FWD, RAG>;
+                     a.y, a.y_bf16, R * ngrp, a.L, nseg, Lseg);
+  auto kern = a.ckpt ? selective_row16_kernel<IN, OPT, true, R16_SEG_FWD, KIND>
+                     : selective_row16_kernel<IN, OPT, false, R16_SEG_FWD, KIND>;
   hipLaunchKernelGGL(kern, dim3((unsigned)(rblocks * nseg)), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,
                      static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
                      static_cast<const IN*>(a.z), a.delta_bias, a.h0, a.y, a.h_last, a.D, a.L,
-                     ndb, flags, a.ckpt, (a.L + 7) / 8, a.s_out, nseg, Lseg);
+                     ndb, flags, a.ckpt, (a.L + 7) / 8, a.s_out, nseg, Lseg, (int)a.N, ngrp, R * a.L);
 }
 
 // The correction form: (1) every segment walks from a zero state (the first
@@ -993,24 +1044,27 @@ void launch_row16_segments(const SelArgs& a, int64_t ndb, uint32_t flags, int64_
 // state and corrects h_last; (3) every segment but the first walks again from
 // its initial state, rewriting y, until the part carried in from the start
 // is negligible against the segment's own terms (R16_CORR_EPS).
-template <typename IN, bool OPT, bool RAG>
+template <typename IN, bool OPT, int KIND>
 void launch_row16_corr(const SelArgs& a, int64_t ndb, uint32_t flags, int64_t nseg,
                        int64_t Lseg, hipStream_t s) {
   const int64_t R = a.B * a.D;
-  const int64_t rblocks = a.B * ndb;
-  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_ALL, RAG>),
+  const int ngrp = r16_groups<KIND>(a.N);
+  const int64_t rblocks = a.B * ndb * ngrp;
+  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_ALL, KIND>),
                      dim3((unsigned)(rblocks * nseg)), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,
                      static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
                      static_cast<const IN*>(a.z), a.delta_bias, a.h0, a.y, a.h_last, a.D, a.L,
-                     ndb, flags, nullptr, (int64_t)0, a.s_out, nseg, Lseg);
-  launch_fold_corr(static_cast<float*>(a.y), a.h_last, R, a.L, nseg, Lseg, s);
-  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_CORR, RAG>),
+                     ndb, flags, nullptr, (int64_t)0, a.s_out, nseg, Lseg, (int)a.N, ngrp, R * a.L);
+  const int64_t lanes = R * ngrp * R16_N;
+  hipLaunchKernelGGL(row16_fold_corr_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0,
+                     s, static_cast<float*>(a.y), a.h_last, R * ngrp, a.L, nseg, Lseg, (int)a.N, R);
+  hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_CORR, KIND>),
                      dim3((unsigned)(rblocks * (nseg - 1))), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,
                      static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
                      static_cast<const IN*>(a.z), a.delta_bias, a.h0, a.y, nullptr, a.D, a.L,
-                     ndb, flags, nullptr, (int64_t)0, a.s_out, nseg, Lseg);
+                     ndb, flags, nullptr, (int64_t)0, a.s_out, nseg, Lseg, (int)a.N, ngrp, R * a.L);
 }
 
 // Whether the call's rows are whole 16-byte vectors: otherwise it takes the
@@ -1020,27 +1074,29 @@ bool row16_aligned(const SelArgs& a) {
   return a.vec && a.L % (16 / (int64_t)sizeof(IN)) == 0;
 }
 
-template <typename IN, bool OPT, bool RAG>
+template <typename IN, bool OPT, int KIND>
 int launch_row16_t(const SelArgs& a, const N16Plan& p, int64_t ndb, hipStream_t s) {
   const uint32_t flags = (a.softplus ? SEL_SOFTPLUS : 0u) | (a.y_bf16 ? SEL_Y_BF16 : 0u) |
                          (a.z ? SEL_GATED : 0u);
   const int64_t nseg = p.nseg, Lseg = p.Lseg;
   if (nseg > 1) {
     if (p.corr)
-      launch_row16_corr<IN, OPT, RAG>(a, ndb, flags, nseg, Lseg, s);
+      launch_row16_corr<IN, OPT, KIND>(a, ndb, flags, nseg, Lseg, s);
     else
-      launch_row16_segments<IN, OPT, RAG>(a, ndb, flags, nseg, Lseg, s);
+      launch_row16_segments<IN, OPT, KIND>(a, ndb, flags, nseg, Lseg, s);
     note_launch("selective_row16_kernel: %lld segments of %lld steps, %s form (3 launches)",
                 (long long)nseg, (long long)Lseg, p.corr ? "correction" : "records");
     return check_launch("selective_row16_kernel (segments)");
   }
-  auto kern = a.ckpt ? selective_row16_kernel<IN, OPT, true, R16_WHOLE, RAG>
-                     : selective_row16_kernel<IN, OPT, false, R16_WHOLE, RAG>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(a.B * ndb)), dim3(256), 0, s,
+  const int ngrp = r16_groups<KIND>(a.N);
+  auto kern = a.ckpt ? selective_row16_kernel<IN, OPT, true, R16_WHOLE, KIND>
+                     : selective_row16_kernel<IN, OPT, false, R16_WHOLE, KIND>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(a.B * ndb * ngrp)), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,
                      static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
                      static_cast<const IN*>(a.z), a.delta_bias, a.h0, a.y, a.h_last, a.D, a.L,
-                     ndb, flags, a.ckpt, (a.L + 7) / 8, a.s_out, (int64_t)1, a.L);
+                     ndb, flags, a.ckpt, (a.L + 7) / 8, a.s_out, (int64_t)1, a.L, (int)a.N, ngrp,
+                     a.B * a.D * a.L);
   note_launch("selective_row16_kernel: whole rows");
   return check_launch("selective_row16_kernel");
 }
@@ -1057,10 +1113,51 @@ int launch_row16(const SelArgs& a, hipStream_t s) {
   const N16Plan p = plan_n16<IN>(a, ndb, cus);
   if (p.quad) return launch_quad<IN>(a, p.nseg, p.Lseg, s);
   if (row16_aligned<IN>(a))
-    return opt ? launch_row16_t<IN, true, false>(a, p, ndb, s)
-               : launch_row16_t<IN, false, false>(a, p, ndb, s);
-  return opt ? launch_row16_t<IN, true, true>(a, p, ndb, s)
-             : launch_row16_t<IN, false, true>(a, p, ndb, s);
+    return opt ? launch_row16_t<IN, true, R16_VEC>(a, p, ndb, s)
+               : launch_row16_t<IN, false, R16_VEC>(a, p, ndb, s);
+  return opt ? launch_row16_t<IN, true, R16_RAG>(a, p, ndb, s)
+             : launch_row16_t<IN, false, R16_RAG>(a, p, ndb, s);
+}
+
+// N other than 16 (row16_fits): one group of up to 16 states writes y itself;
+// several write planes of a per-call workspace that a last kernel adds up.
+// At B=2, D=1024, N=64, L=1024 (fp32) the 8-lane kernel, with 256 wavefronts
+// for the GPU's 1024 SIMDs, took 125 us.
+template <typename IN>
+int launch_row16_groups(const SelArgs& a, hipStream_t s) {
+  const int64_t ndb = (a.D + R16_ROWS - 1) / R16_ROWS, R = a.B * a.D;
+  const int ngrp = r16_groups<R16_GRP>(a.N);
+  if (a.B * ndb * ngrp >= ((int64_t)1 << 31) || R * ((a.L + 1023) / 1024) >= ((int64_t)1 << 31))
+    return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range",
+                (long long)(a.B * ndb * ngrp));
+  int cus = 0;
+  if (device_cus(&cus) != SW_OK) cus = 256;
+  int st = refuse_capture(s, "the per-stream scratch (tickets and carries)");
+  if (st != SW_OK) return st;
+  SelArgs g = a;
+  if (ngrp > 1) {
+    st = workspace_alloc(&g.y, (size_t)ngrp * (size_t)R * (size_t)a.L * sizeof(float), s);
+    if (st != SW_OK) return st;
+    g.Dskip = nullptr;
+    g.z = nullptr;
+    g.s_out = nullptr;
+    g.y_bf16 = false;
+  }
+  const N16Plan p = plan_n16<IN>(g, ndb * ngrp, cus);
+  const bool opt = g.z || g.delta_bias || g.softplus || g.y_bf16 || g.s_out;
+  st = opt ? launch_row16_t<IN, true, R16_GRP>(g, p, ndb, s)
+           : launch_row16_t<IN, false, R16_GRP>(g, p, ndb, s);
+  if (ngrp > 1) {
+    if (st == SW_OK) {
+      const int64_t nch = (a.L + 1023) / 1024;
+      hipLaunchKernelGGL((row16_groups_kernel<IN>), dim3((unsigned)(R * nch)), dim3(256), 0, s,
+                         static_cast<const float*>(g.y), ngrp, static_cast<const IN*>(a.x),
+                         static_cast<const IN*>(a.z), a.Dskip, a.y, a.s_out, R, a.D, a.L, nch, a.y_bf16);
+      st = check_launch("row16_groups_kernel");
+    }
+    workspace_free(g.y, s);
+  }
+  return st;
 }
 
 // The states of a whole-row walk without y (R16_STATES): the 8-step
@@ -1075,14 +1172,15 @@ int launch_row16_states(const SelArgs& a, hipStream_t s) {
     return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range", (long long)grid);
   const bool opt = a.delta_bias || a.softplus;
   const uint32_t flags = a.softplus ? SEL_SOFTPLUS : 0u;
-  auto kern = opt ? selective_row16_kernel<IN, true, true, R16_STATES, false>
-                  : selective_row16_kernel<IN, false, true, R16_STATES, false>;
+  auto kern = opt ? selective_row16_kernel<IN, true, true, R16_STATES, R16_VEC>
+                  : selective_row16_kernel<IN, false, true, R16_STATES, R16_VEC>;
   // y is never written in this mode: x stands in for its pointer
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, s, static_cast<const IN*>(a.x),
                      static_cast<const IN*>(a.delta), a.A, static_cast<const IN*>(a.Bm),
                      static_cast<const IN*>(a.Cm), a.Dskip, static_cast<const IN*>(nullptr),
                      a.delta_bias, a.h0, const_cast<void*>(a.x), a.h_last, a.D, a.L, ndb, flags,
-                     a.ckpt, (a.L + 7) / 8, static_cast<float*>(nullptr), (int64_t)1, a.L);
+                     a.ckpt, (a.L + 7) / 8, static_cast<float*>(nullptr), (int64_t)1, a.L, (int)a.N, 1,
+                     (int64_t)0);
   return check_launch("selective_row16_kernel (states)");
 }
 
@@ -1100,6 +1198,8 @@ SelPlan plan_row16(const SelArgs& a, int cus) {
 
 template int launch_row16<float>(const SelArgs&, hipStream_t);
 template int launch_row16<uint16_t>(const SelArgs&, hipStream_t);
+template int launch_row16_groups<float>(const SelArgs&, hipStream_t);
+template int launch_row16_groups<uint16_t>(const SelArgs&, hipStream_t);
 template SelPlan plan_row16<float>(const SelArgs&, int);
 template SelPlan plan_row16<uint16_t>(const SelArgs&, int);
 template int launch_row16_states<float>(const SelArgs&, hipStream_t);
