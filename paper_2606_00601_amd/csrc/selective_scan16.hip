@@ -852,8 +852,10 @@ bool row16_fits(int64_t D, int64_t N, int64_t L, size_t es) {
 //
 // The candidates: the 16-lane layout walking whole rows; the 16-lane layout
 // with 2..16 segments per row, in the records or the correction form; the
-// quad layout (four lanes per row, selective_scan_quad.hip) with 2..16
-// segments, correction form.  Each is priced with a model of its launches
+// quad layout (four lanes per row, selective_scan_quad.hip) on whole rows or
+// with 2..16 segments, correction form.  (Whole rows of the quad layout win
+// from about 32768 rows on: B=16, D=5120, L=256 110 / 81 us, 16-lane / quad,
+// B=32, D=1024, L=512 76 / 65, but B=4, D=5120, L=1024 95 / 117.)  Each is priced with a model of its launches
 // and the cheapest is taken.  A launch of G workgroups on `cus` CUs runs in
 // rounds: its busiest CU holds ceil(G / cus) workgroups, at most `cap` at a
 // time (three of the 16-lane layout, four of the quad layout, by LDS), and a
@@ -987,10 +989,11 @@ N16Plan plan_n16(const SelArgs& a, int64_t ndb, int cus) {
   if (with_quad) {
     // a forced count is capped at one segment per QUAD_SKIP steps
     const int64_t kcap = L / QUAD_SKIP;
-    if (quad_only && (kmin == 1 || (seg_env > 0 && kcap < 2)))
+    if (kmin == 1 || (quad_only && seg_env > 0 && kcap < 2))
       consider(launch_us(Gq, L, cus, QUAD_COST, qscale), true, 1, L, false);
     const int64_t qmin = seg_env > 0 && kmin > kcap ? kcap : kmin;
-    const int64_t qmax = seg_env > 0 && kmax > kcap ? kcap : kmax;
+    // bf16 y has no room for the segments' records of the correction form
+    const int64_t qmax = a.y_bf16 ? 1 : seg_env > 0 && kmax > kcap ? kcap : kmax;
     for (int64_t k = (qmin > 2 ? qmin : 2); k <= qmax; ++k) {
       int64_t Lseg, last;
       quad_geometry(L, k, &Lseg, &last);

@@ -183,9 +183,14 @@ __global__ __launch_bounds__(256) void selective_quad_kernel(
   // wavefront's rows from the segment's start; a lane with nothing to store
   // aims at the resource's end, where the store is dropped (16 rows of
   // L < 2^26 fp32 steps fit 32 bits)
-  const uint32_t ybytes = (uint32_t)(((int64_t)rows * L - ts) * 4);
-  const __amdgpu_buffer_rsrc_t ry = buffer_rsrc(y + row0 * L + ts, ybytes);
-  const __amdgpu_buffer_rsrc_t rso = buffer_rsrc(OPT && s_out ? s_out + row0 * L + ts : y, ybytes);
+  // (bf16 y: whole rows only, so the records' words are always fp32)
+  const bool ybf = OPT && (flags & SEL_Y_BF16) != 0;
+  const uint32_t yelems = (uint32_t)((int64_t)rows * L - ts), ys = ybf ? 2u : 4u;
+  const uint32_t ybytes = yelems * ys;
+  const __amdgpu_buffer_rsrc_t ry =
+      ybf ? buffer_rsrc(reinterpret_cast<uint16_t*>(y) + row0 * L + ts, ybytes)
+          : buffer_rsrc(y + row0 * L + ts, ybytes);
+  const __amdgpu_buffer_rsrc_t rso = buffer_rsrc(OPT && s_out ? s_out + row0 * L + ts : y, yelems * 4u);
   struct Raw {
     RawVec<IN, 4> d[2], x[2], z[2], b[2], c[2];
   };
@@ -309,18 +314,24 @@ __global__ __launch_bounds__(256) void selective_quad_kernel(
       s.w = __builtin_fmaf(idsk[k], xc[k][3], s.w);
       const int t = kt * Q_T + 4 * ij;
       const bool store = iok[k] && !(!CORR && sg > 0 && t < Q_SKIP);
-      const uint32_t at = store ? (uint32_t)(iro[k] * L + t) * 4u : ybytes;
+      const uint32_t at = store ? (uint32_t)(iro[k] * L + t) * ys : ybytes;
       if constexpr (OPT) {
         if (s_out)
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(sw_u32x4, s), rso, (int)at, 0,
-                                                 SW_NT);
+          __builtin_amdgcn_raw_buffer_store_b128(
+              __builtin_bit_cast(sw_u32x4, s), rso,
+              (int)(store ? (uint32_t)(iro[k] * L + t) * 4u : yelems * 4u), 0, SW_NT);
         s.x *= zc[k][0];
         s.y *= zc[k][1];
         s.z *= zc[k][2];
         s.w *= zc[k][3];
       }
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(sw_u32x4, s), ry, (int)at, 0,
-                                             SW_NT);
+      if (ybf)  // half a line of a row per tile: the default policy
+        __builtin_amdgcn_raw_buffer_store_b64(
+            __builtin_bit_cast(sw_u32x2, make_uint2(bf16x2_rne(s.x, s.y), bf16x2_rne(s.z, s.w))), ry,
+            (int)at, 0, 0);
+      else
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(sw_u32x4, s), ry, (int)at, 0,
+                                               SW_NT);
     }
   };
 
@@ -421,13 +432,13 @@ void launch_quad_t(const SelArgs& a, uint32_t flags, int64_t nseg, int64_t Lseg,
 
 }  // namespace
 
-// True when the quad layout can take the call: fp32 y, no checkpoints,
+// True when the quad layout can take the call (bf16 y: on whole rows only): no checkpoints,
 // N = 16, whole tiles, 32-bit offsets over a wavefront's rows and a batch's
 // B and C.  (Which layout and how many segments a call takes is decided with
 // the 16-lane layout's choices, in selective_scan16.hip.)
 template <typename IN>
 bool quad_fits(const SelArgs& a) {
-  if (a.N != Q_N || a.y_bf16 || a.ckpt || a.L <= 0 || a.B * a.D <= 0) return false;
+  if (a.N != Q_N || a.ckpt || a.L <= 0 || a.B * a.D <= 0) return false;
   if (a.L % Q_T != 0 || a.D >= ((int64_t)1 << 30) || a.L >= ((int64_t)1 << 26)) return false;
   if ((Q_RPW * (a.L + 4 * Q_T)) * (int64_t)sizeof(IN) >= ((int64_t)1 << 31)) return false;
   if ((a.L + 4 * Q_T) * Q_N * (int64_t)sizeof(IN) >= ((int64_t)1 << 31)) return false;
@@ -445,8 +456,10 @@ int launch_quad(const SelArgs& a, int64_t nseg, int64_t Lseg, hipStream_t s) {
     return fail(SW_ERR_UNSUPPORTED, "quad layout: %lld segments of %lld steps for L=%lld",
                 (long long)nseg, (long long)Lseg, (long long)a.L);
   if (nseg == 1) Lseg = a.L;
-  const bool opt = a.z || a.delta_bias || a.softplus || a.s_out;
-  const uint32_t flags = (a.softplus ? SEL_SOFTPLUS : 0u) | (a.z ? SEL_GATED : 0u);
+  if (a.y_bf16 && nseg > 1) return fail(SW_ERR_UNSUPPORTED, "quad layout: bf16 y takes whole rows");
+  const bool opt = a.z || a.delta_bias || a.softplus || a.s_out || a.y_bf16;
+  const uint32_t flags = (a.softplus ? SEL_SOFTPLUS : 0u) | (a.z ? SEL_GATED : 0u) |
+                         (a.y_bf16 ? SEL_Y_BF16 : 0u);
   if (opt)
     launch_quad_t<IN, true>(a, flags, nseg, Lseg, s);
   else

@@ -105,3 +105,18 @@ def test_ragged_checkpoints(sw, dtype, L):  # noqa: F811
         assert torch.equal(g0[k], g1[k]), k
     for k in n0:
         assert torch.equal(n0[k], n1[k]), k
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(2, 70, 64), (1, 33, 1056)])
+def test_quad_whole_rows_in_bf16(sw, monkeypatch, dtype, shape):  # noqa: F811
+    """bf16 y of the quad layout on whole rows: the fp32 y rounded once."""
+    B, D, L = shape
+    monkeypatch.setenv("SW_SS_QUAD", "1")
+    monkeypatch.setenv("SW_SS_SEGMENTS", "1")
+    inp, ex = _ex_inputs(B, D, 16, L, 5700 + L, dtype, ("h0", "bias", "softplus", "z"))
+    y32, h32 = _run_ex(sw, inp, ex, dtype, True, False)
+    assert sw.last_launch() == "selective_quad_kernel: whole rows", sw.last_launch()
+    y16, h16 = _run_ex(sw, inp, ex, dtype, True, True)
+    assert sw.last_launch() == "selective_quad_kernel: whole rows", sw.last_launch()
+    assert torch.equal(y16, y32.to(torch.bfloat16)) and torch.equal(h16, h32)
