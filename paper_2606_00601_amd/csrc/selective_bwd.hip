@@ -1070,48 +1070,40 @@ int selective_bwd(const BwdArgs& a) {
       return st;
     }
   }
-  // still without checkpoints: where the forward takes its 16-lane layout,
-  // its walk without y writes them (the states do not depend on the gate),
-  // cheaper than the backward kernel's own sweep and bit-identical to it
+  // still without checkpoints: where the 16-lane kernels can walk the call,
+  // their walk without y writes them (the states do not depend on the gate),
+  // cheaper than the sweep and bit-identical to it
+  SelArgs sa{};
+  sa.x = a.x;
+  sa.delta = a.delta;
+  sa.Bm = a.Bm;
+  sa.Cm = a.Cm;
+  sa.A = a.A;
+  sa.delta_bias = a.delta_bias;
+  sa.h0 = a.h0;
+  sa.B = B;
+  sa.D = D;
+  sa.N = a.N;
+  sa.L = L;
+  sa.bf16_in = a.bf16_in;
+  sa.softplus = a.softplus;
+  sa.vec = a.vec;
+  sa.ckpt = w.ck;
   const char* ck_from = a.ckpt ? "given" : ab.ckpt ? "from the ungated forward" : nullptr;
-  if (!ab.ckpt && a.N == BW_N) {
-    SelArgs fa{};
-    fa.x = a.x;
-    fa.delta = a.delta;
-    fa.Bm = a.Bm;
-    fa.Cm = a.Cm;
-    fa.A = a.A;
-    fa.delta_bias = a.delta_bias;
-    fa.h0 = a.h0;
-    fa.B = B;
-    fa.D = D;
-    fa.N = a.N;
-    fa.L = L;
-    fa.bf16_in = a.bf16_in;
-    fa.softplus = a.softplus;
-    fa.vec = a.vec;
-    fa.ckpt = w.ck;
-    bool taken = false;
-    st = selective_states_fwd(fa, &taken);
-    if (st != SW_OK) {
-      done();
-      return st;
-    }
-    if (taken) {
-      ab.ckpt = w.ck;
-      ck_from = "from the forward's walk without y";
-    }
-  }
-  const bool sweep = !ab.ckpt;
-  if (!ck_from) ck_from = "rebuilt by a sweep";
   // the states in groups of 16: each group's main kernel, then its reduction
   // (dA, dB, dC of its states; the sums over the states accumulate)
   for (int n0 = 0; n0 < a.N && st == SW_OK; n0 += BW_N) {
-    if (sweep) {
-      auto kern = a.bf16_in ? selective_sweep_kernel<uint16_t> : selective_sweep_kernel<float>;
-      hipLaunchKernelGGL(kern, dim3((unsigned)(B * G16)), dim3(256), 0, s, a, w.ck, G16, ntile, n0);
-      st = check_launch("selective_sweep_kernel");
+    if (!ab.ckpt) {
+      bool taken = false;
+      st = selective_states_fwd(sa, n0 / BW_N, &taken);
       if (st != SW_OK) break;
+      ck_from = taken ? "from the forward's walk without y" : "rebuilt by a sweep";
+      if (!taken) {
+        auto kern = a.bf16_in ? selective_sweep_kernel<uint16_t> : selective_sweep_kernel<float>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(B * G16)), dim3(256), 0, s, a, w.ck, G16, ntile, n0);
+        st = check_launch("selective_sweep_kernel");
+        if (st != SW_OK) break;
+      }
     }
     launch_bwd(ab, w, G, ntile, plan, n0, s);
     st = check_launch("selective_bwd_kernel");

@@ -641,7 +641,7 @@ int launch_row16(const SelArgs& a, hipStream_t s);
 template <typename IN>
 int launch_row16_groups(const SelArgs& a, hipStream_t s);
 template <typename IN>
-int launch_row16_states(const SelArgs& a, hipStream_t s);
+int launch_row16_states(const SelArgs& a, int grp, hipStream_t s);
 template <typename IN>
 SelPlan plan_row16(const SelArgs& a, int cus);
 template <typename IN>
@@ -763,13 +763,15 @@ SelPlan selective_plan(const SelArgs& a, int cus) {
   return q;
 }
 
-int selective_states_fwd(const SelArgs& a, bool* taken) {
+int selective_states_fwd(const SelArgs& a, int grp, bool* taken) {
   *taken = false;
-  if (a.N != 16 || !a.ckpt || a.z || a.y_bf16 || a.s_out) return SW_OK;
-  if (a.bf16_in ? !row16_whole_vectors<uint16_t>(a) : !row16_whole_vectors<float>(a)) return SW_OK;
+  if (!a.ckpt || a.z || a.y_bf16 || a.s_out) return SW_OK;
+  const bool fits = a.N == 16 ? (a.bf16_in ? row16_whole_vectors<uint16_t>(a) : row16_whole_vectors<float>(a))
+                              : (a.bf16_in ? lanes16_path<uint16_t>(a) : lanes16_path<float>(a));
+  if (!fits) return SW_OK;
   *taken = true;
   hipStream_t s = current_stream();
-  return a.bf16_in ? launch_row16_states<uint16_t>(a, s) : launch_row16_states<float>(a, s);
+  return a.bf16_in ? launch_row16_states<uint16_t>(a, grp, s) : launch_row16_states<float>(a, grp, s);
 }
 
 }  // namespace sw

@@ -294,10 +294,12 @@ __global__ __launch_bounds__(256) void selective_row16_kernel(
   const int64_t bid = xcd_contiguous(blockIdx.x, gridDim.x);
   const int64_t sg = !WHOLE ? bid % nsl + (CORR ? 1 : 0) : 0;
   const int64_t rblk_g = !WHOLE ? bid / nsl : bid;
-  const int64_t rblk = GRP ? rblk_g / ngrp : rblk_g;
-  const int grp = GRP ? (int)(rblk_g - rblk * ngrp) : 0;
+  // (R16_STATES walks one group, whose number is ngrp)
+  constexpr bool ONE = SEG == R16_STATES;
+  const int64_t rblk = GRP && !ONE ? rblk_g / ngrp : rblk_g;
+  const int grp = GRP ? (ONE ? ngrp : (int)(rblk_g - rblk * ngrp)) : 0;
   const int N = GRP ? Nst : R16_N, n0 = R16_N * grp;
-  void* const yv = GRP ? static_cast<void*>(static_cast<float*>(yv_in) + grp * plane) : yv_in;
+  void* const yv = GRP && !ONE ? static_cast<void*>(static_cast<float*>(yv_in) + grp * plane) : yv_in;
   const int64_t ts = !WHOLE ? sg * Lseg : 0;  // first step of the segment
   const int64_t Ls = !WHOLE ? (sg == nseg - 1 ? L - ts : Lseg) : L;  // its steps
   const int32_t Ls32 = (int32_t)Ls;  // below 2^31 / 16 (row16_fits)
@@ -1164,25 +1166,27 @@ int launch_row16_groups(const SelArgs& a, hipStream_t s) {
 }
 
 // The states of a whole-row walk without y (R16_STATES): the 8-step
-// checkpoints into a.ckpt and, if given, h_last; x, delta, B, A, h0 and the
+// checkpoints of state group grp (16 states, 0 for N = 16) into a.ckpt and, if given, h_last; x, delta, B, A, h0 and the
 // delta options are read, C, Dskip, z and y are not.  The call must satisfy
-// row16_fits and have whole, aligned vectors in its rows.
+// row16_fits and, for N = 16, have whole, aligned vectors in its rows.
 template <typename IN>
-int launch_row16_states(const SelArgs& a, hipStream_t s) {
+int launch_row16_states(const SelArgs& a, int grp, hipStream_t s) {
   const int64_t ndb = (a.D + R16_ROWS - 1) / R16_ROWS;
   const int64_t grid = a.B * ndb;
   if (grid >= ((int64_t)1 << 31))
     return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range", (long long)grid);
   const bool opt = a.delta_bias || a.softplus;
   const uint32_t flags = a.softplus ? SEL_SOFTPLUS : 0u;
-  auto kern = opt ? selective_row16_kernel<IN, true, true, R16_STATES, R16_VEC>
-                  : selective_row16_kernel<IN, false, true, R16_STATES, R16_VEC>;
+  auto kern = a.N == R16_N ? (opt ? selective_row16_kernel<IN, true, true, R16_STATES, R16_VEC>
+                                  : selective_row16_kernel<IN, false, true, R16_STATES, R16_VEC>)
+                           : (opt ? selective_row16_kernel<IN, true, true, R16_STATES, R16_GRP>
+                                  : selective_row16_kernel<IN, false, true, R16_STATES, R16_GRP>);
   // y is never written in this mode: x stands in for its pointer
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, s, static_cast<const IN*>(a.x),
                      static_cast<const IN*>(a.delta), a.A, static_cast<const IN*>(a.Bm),
                      static_cast<const IN*>(a.Cm), a.Dskip, static_cast<const IN*>(nullptr),
                      a.delta_bias, a.h0, const_cast<void*>(a.x), a.h_last, a.D, a.L, ndb, flags,
-                     a.ckpt, (a.L + 7) / 8, static_cast<float*>(nullptr), (int64_t)1, a.L, (int)a.N, 1,
+                     a.ckpt, (a.L + 7) / 8, static_cast<float*>(nullptr), (int64_t)1, a.L, (int)a.N, grp,
                      (int64_t)0);
   return check_launch("selective_row16_kernel (states)");
 }
@@ -1205,7 +1209,7 @@ template int launch_row16_groups<float>(const SelArgs&, hipStream_t);
 template int launch_row16_groups<uint16_t>(const SelArgs&, hipStream_t);
 template SelPlan plan_row16<float>(const SelArgs&, int);
 template SelPlan plan_row16<uint16_t>(const SelArgs&, int);
-template int launch_row16_states<float>(const SelArgs&, hipStream_t);
-template int launch_row16_states<uint16_t>(const SelArgs&, hipStream_t);
+template int launch_row16_states<float>(const SelArgs&, int, hipStream_t);
+template int launch_row16_states<uint16_t>(const SelArgs&, int, hipStream_t);
 
 }  // namespace sw

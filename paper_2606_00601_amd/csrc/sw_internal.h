@@ -97,12 +97,13 @@ struct SelPlan {
 // The plan of selective_fwd for `a` priced for `cus` compute units (the
 // pointers of `a` are only tested for alignment; nothing is launched).
 SelPlan selective_plan(const SelArgs& a, int cus);
-// The states of the forward walk without y: the 8-step checkpoints (a.ckpt,
-// required) and h_last if given, for a backward call without the forward's
-// checkpoints.  Enqueues (*taken = true) only where the forward takes its
-// 16-lane layout and no gate, bf16 y or pre-gate output is asked for;
+// The states of the forward walk without y: the 8-step checkpoints of state
+// group grp (states 16 grp .. +15; a.ckpt, required) and h_last if given, for
+// a backward call without the forward's checkpoints.  Enqueues (*taken =
+// true) only where the 16-lane kernels can walk the call (at N = 16, rows of
+// whole vectors) and no gate, bf16 y or pre-gate output is asked for;
 // otherwise returns SW_OK with nothing enqueued.
-int selective_states_fwd(const SelArgs& a, bool* taken);
+int selective_states_fwd(const SelArgs& a, int grp, bool* taken);
 
 // Arguments of one backward call of the fused form, already validated.
 // x, delta, Bm, Cm, z are fp32 or bf16 as `bf16_in` says, dy as `dy_bf16`
