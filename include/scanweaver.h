@@ -421,8 +421,9 @@ const char* sw_last_error(void);
  * nothing is launched and no device memory is touched, so with cus > 0 it
  * needs no GPU.  Outputs (all required):
  *   layout : 16 (one lane per state), 4 (four lanes per row, four states
- *            each), 8 (the kernels for any N: one for at most 16 steps, and
- *            one that chains its own sequence chunks), or 0 when there is nothing to launch (B*D or L zero)
+ *            each), 8 (the kernels for any N, whose segments are not planned
+ *            here: one for at most 16 steps, one that chains its own sequence
+ *            chunks, and the 16-lane kernels on groups of states), or 0 when there is nothing to launch (B*D or L zero)
  *   nseg, lseg : the row is walked as nseg segments of lseg steps, the last
  *            taking the rest (1 and L: whole rows; 0 and 0 with layout 0)
  *   form   : 0 whole rows, 1 records form, 2 correction form (see

@@ -641,6 +641,8 @@ int launch_row16(const SelArgs& a, hipStream_t s);
 template <typename IN>
 int launch_row16_groups(const SelArgs& a, hipStream_t s);
 template <typename IN>
+double row16_groups_us(const SelArgs& a, int cus);
+template <typename IN>
 int launch_row16_states(const SelArgs& a, int grp, hipStream_t s);
 template <typename IN>
 SelPlan plan_row16(const SelArgs& a, int cus);
@@ -660,7 +662,7 @@ bool vector_path(const SelArgs& a) {
   return a.vec && fits && ((uintptr_t)a.Bm % 16 == 0) && ((uintptr_t)a.Cm % 16 == 0);
 }
 
-// 16-byte aligned B and C and an even N above 8: one state per lane, 16-lane
+// 16-byte aligned B and C and an even N: one state per lane, 16-lane
 // rows (selective_scan16.hip), whatever the rows' length and alignment;
 // SW_SS_LAYOUT=8 keeps the 8-lane layout.
 template <typename IN>
@@ -689,11 +691,20 @@ bool row16_whole_vectors(const SelArgs& a) {
 // that where N is padded.  Measured: B=2 D=1024 N=64 L=1024 128 / 70, B=16
 // D=2560 N=48 L=200 373 / 219, B=1 D=768 N=24 L=500 48 / 43, but B=2 D=512 N=48
 // L=100 29 / 35, B=1 D=256 N=32 L=64 14 / 35, B=8 D=2048 N=32 L=1024 180 / 224.
+// Up to 8 states the 8-lane kernel has one per lane and half the lanes of a
+// group idle: the groups take long calls on few rows, where their segments
+// win: B=1 D=768 N=4 L=3000 116 / 40, B=1 D=256 N=4 L=16000 584 / 72, but B=2
+// D=1536 N=8 L=2000 71 / 69.
 template <typename IN>
 bool groups_pay(const SelArgs& a) {
-  if (a.N <= 16) return true;
   int cus = 0;
   if (device_cus(&cus) != SW_OK) cus = 256;
+  if (a.N <= 8) {
+    const double w = (double)(a.B * a.D) / (8.0 * cus);
+    const double lanes8 = 0.043 * (double)a.L * (w > 6.0 ? w / 6.0 : 1.0);
+    return lanes8 > 60.0 && row16_groups_us<IN>(a, cus) < 0.8 * lanes8;
+  }
+  if (a.N <= 16) return true;
   const int64_t R = a.B * a.D, ngrp = (a.N + 15) / 16;
   const int64_t per = (a.B * ((a.D + 15) / 16) * ngrp + cus - 1) / cus;
   const double rest[3] = {0.0, 28.8, 42.3};

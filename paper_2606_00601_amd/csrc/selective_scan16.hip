@@ -256,7 +256,7 @@ __device__ __forceinline__ void rec_store(void* yv, bool ybf, int64_t row, int64
 // steps): loads through RagVec, steps past the row's end made identity steps
 // one by one, y stored by element in the last tile (bf16 y in every tile).
 // KIND: R16_VEC whole aligned vectors, R16_RAG as above, R16_GRP as R16_RAG for
-// N other than 16 (even, above 8): the states in ngrp groups of 16, a
+// N other than 16 (even): the states in ngrp groups of 16, a
 // workgroup per (row block, group), states past N masked to identity steps.
 // With several groups each writes its part of y (no skip, no gate, fp32) to
 // its own plane of B*D*L elements from yv, added up by row16_groups_kernel.
@@ -842,7 +842,7 @@ int launch_quad(const SelArgs& a, int64_t nseg, int64_t Lseg, hipStream_t s);
 // ahead past the end) below 2^31.
 // (N other than 16: the state groups of R16_GRP, which read B and C in pairs.)
 bool row16_fits(int64_t D, int64_t N, int64_t L, size_t es) {
-  if (N <= 8 || N % 2 != 0) return false;
+  if (N % 2 != 0) return false;
   const int64_t vstep = 16 / (int64_t)es;
   if (L < vstep) return false;
   const int64_t pad = 4 * R16_N * vstep;
@@ -907,6 +907,7 @@ struct N16Plan {
   int64_t nseg = 1;  // 1: whole rows
   int64_t Lseg = 0;
   bool corr = false;
+  double us = 0.0;  // its price
 };
 
 // Segments of the 16-lane layout for a count k: L / k rounded up to whole
@@ -943,6 +944,8 @@ N16Plan plan_n16(const SelArgs& a, int64_t ndb, int cus) {
   // checkpoints come from whole-row walks, or where the caller allows
   // segments, from the records form (whose last launch walks every segment
   // from its composed state)
+  const int64_t G16 = a.B * ndb;
+  best.us = launch_us(G16, a.L, cus, R16_COST, 1.0);
   if (a.ckpt && !a.ckpt_seg) return best;
   const int64_t L = a.L, st = R16_N * (16 / (int64_t)sizeof(IN));
   const int64_t quad_env = env_i64("SW_SS_QUAD"), seg_env = env_i64("SW_SS_SEGMENTS");
@@ -952,7 +955,7 @@ N16Plan plan_n16(const SelArgs& a, int64_t ndb, int cus) {
   const bool with_quad = qfits && quad_env != 0 && (seg_env < 0 || quad_only);
   const bool corr_ok = !a.y_bf16 && !a.ckpt;
   const double qscale = sizeof(IN) == 2 ? 0.92 : 1.0;
-  const int64_t G16 = a.B * ndb, Gq = a.B * ((a.D + 63) / 64);
+  const int64_t Gq = a.B * ((a.D + 63) / 64);
   double best_us = 1e300;
   auto consider = [&](double us, bool quad, int64_t nseg, int64_t Lseg, bool corr) {
     if (us < best_us) {
@@ -961,6 +964,7 @@ N16Plan plan_n16(const SelArgs& a, int64_t ndb, int cus) {
       best.nseg = nseg;
       best.Lseg = Lseg;
       best.corr = corr;
+      best.us = us;
     }
   };
   const int64_t kmin = seg_env > 0 ? (seg_env < 16 ? seg_env : 16) : 1;
@@ -1124,6 +1128,12 @@ int launch_row16(const SelArgs& a, hipStream_t s) {
              : launch_row16_t<IN, false, R16_RAG>(a, p, ndb, s);
 }
 
+// The planned price of the groups' walk on `cus` compute units.
+template <typename IN>
+double row16_groups_us(const SelArgs& a, int cus) {
+  return plan_n16<IN>(a, (a.D + R16_ROWS - 1) / R16_ROWS * r16_groups<R16_GRP>(a.N), cus).us;
+}
+
 // N other than 16 (row16_fits): one group of up to 16 states writes y itself;
 // several write planes of a per-call workspace that a last kernel adds up.
 // At B=2, D=1024, N=64, L=1024 (fp32) the 8-lane kernel, with 256 wavefronts
@@ -1205,6 +1215,8 @@ SelPlan plan_row16(const SelArgs& a, int cus) {
 
 template int launch_row16<float>(const SelArgs&, hipStream_t);
 template int launch_row16<uint16_t>(const SelArgs&, hipStream_t);
+template double row16_groups_us<float>(const SelArgs&, int);
+template double row16_groups_us<uint16_t>(const SelArgs&, int);
 template int launch_row16_groups<float>(const SelArgs&, hipStream_t);
 template int launch_row16_groups<uint16_t>(const SelArgs&, hipStream_t);
 template SelPlan plan_row16<float>(const SelArgs&, int);

@@ -1,5 +1,6 @@
-"""The forward on an even N above 8 other than 16: states in groups of 16 lanes,
-one group (N = 10, 14) writing y itself and several adding up planes of y (the
+"""The forward on an even N other than 16: states in groups of 16 lanes,
+one group (N = 10, 14; N = 4, 8 on long
+calls of few rows) writing y itself and several adding up planes of y (the
 last group full or not), whole rows and segments of either form, at aligned
 and ragged lengths, against the oracle."""
 import numpy as np
@@ -14,7 +15,7 @@ pytestmark = pytest.mark.gpu
 # (B, D, N, L), forced segments, form
 _CASES = [((2, 19, 10, 100), "", ""), ((1, 33, 14, 517), "3", "1"), ((1, 17, 24, 1000), "1", ""),
           ((2, 16, 32, 515), "", ""), ((1, 21, 48, 777), "3", "2"), ((1, 16, 64, 640), "4", "1"),
-          ((1, 5, 34, 367), "", ""), ((1, 18, 62, 2049), "5", "2")]
+          ((1, 5, 34, 367), "", ""), ((1, 20, 4, 1500), "", ""), ((2, 9, 8, 1601), "", ""), ((1, 18, 62, 2049), "5", "2")]
 
 
 @pytest.mark.parametrize("case", _CASES)
