@@ -80,6 +80,21 @@ __device__ __forceinline__ float sigmoid_f32(float v) {
   return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-v * BW_LOG2E));
 }
 
+// softplus(v) and its derivative sigmoid(v) from one exp2: e = e^-|v| and w =
+// 1 + e give sigmoid(|v|) = 1 / w and log1p(e) = log(w) e / (w - 1) (e where w
+// rounds to 1), and softplus(v) = max(v, 0) + log1p(e).  The staging of a tile
+// is bound by instruction issue and an exp2 takes 8.5 cycles of it: two
+// separate ones took the B=8 D=1536 L=2048 bf16 call 602 us, this 577 together
+// with the segment rule's five tiles.
+__device__ __forceinline__ void softplus_sigmoid_f32(float v, float& sp, float& sg) {
+  const float e = __builtin_amdgcn_exp2f(-__builtin_fabsf(v) * BW_LOG2E);
+  const float w = 1.0f + e, d = w - 1.0f;
+  const float l = __builtin_amdgcn_logf(w) * 0.6931471805599453f * (e * __builtin_amdgcn_rcpf(d));
+  sp = (v > 0.0f ? v : 0.0f) + (d == 0.0f ? e : l);
+  const float r = __builtin_amdgcn_rcpf(w);
+  sg = v > 0.0f ? r : e * r;
+}
+
 __device__ __forceinline__ void bw_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_s_barrier();
@@ -399,10 +414,7 @@ __global__ __launch_bounds__(256, MODE == BW_ENDS ? 4 : 2) void selective_bwd_ke
       const bool lv = kp.lv[i];
       float dv = v.dl.get(i) + dbias;
       kp.sg[i] = 1.0f;
-      if (a.softplus) {
-        kp.sg[i] = sigmoid_f32(dv);
-        dv = softplus_f32(dv);
-      }
+      if (a.softplus) softplus_sigmoid_f32(dv, dv, kp.sg[i]);
       dlv[i] = lv ? dv : 0.0f;
       const float dyv = lv ? v.dy.get(i) : 0.0f;
       float gt = 1.0f;
@@ -927,7 +939,7 @@ void launch_bwd(const BwdArgs& a, const BwWork& w, int64_t G, int64_t ntile, con
 // a launch of n workgroups runs in rounds of at most two per compute unit (by
 // LDS and registers), a tile of a round takes 2.1 us with one workgroup on
 // the busiest compute unit and 3.5 us with two (measured, gate and softplus
-// included), and starting and ending a segment about two tiles more.  Cut
+// included), and starting and ending a segment about five tiles more.  Cut
 // calls add the adjoint's walk, 0.5 + 0.45 us per tile and workgroup resident
 // (up to seven), and 8 us for its launch and the records.  us per call,
 // whole rows / cut, against one state per lane on whole rows before: B=8,
@@ -940,7 +952,7 @@ BwdPlan plan_bwd(int64_t B, int64_t G, int64_t ntile, int cus) {
   const auto per_cu = [&](int64_t n) { return (n + cus - 1) / cus; };
   const auto main_us = [&](int64_t n, int64_t tiles) {
     const int64_t p = per_cu(n);
-    return (double)(tiles + 2) * ((double)(p / 2) * 3.5 + (double)(p % 2) * 2.1);
+    return (double)(tiles + 5) * ((double)(p / 2) * 3.5 + (double)(p % 2) * 2.1);
   };
   double best_us = main_us(W, ntile);
   for (int64_t k = 2; k <= BW_MAX_SEG && k <= ntile; ++k) {
@@ -948,7 +960,7 @@ BwdPlan plan_bwd(int64_t B, int64_t G, int64_t ntile, int cus) {
     if (n < 2 || W * n >= ((int64_t)1 << 31)) continue;
     const int64_t e = per_cu(W * (n - 1));
     const double walk = (double)(e / 7) * (0.5 + 0.45 * 7) + (e % 7 ? 0.5 + 0.45 * (double)(e % 7) : 0.0);
-    const double us = main_us(W * n, tiles) + (double)(tiles + 2) * walk + 8.0;
+    const double us = main_us(W * n, tiles) + (double)(tiles + 5) * walk + 8.0;
     if (us < best_us) {
       best_us = us;
       best = BwdPlan{(int)n, tiles};

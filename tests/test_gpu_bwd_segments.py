@@ -111,3 +111,19 @@ def test_segmented_training_forward(sw, monkeypatch, L, segs, dtype):  # noqa: F
         else:  # rounded once more, half a unit of 8 bits
             err = np.abs(v.float().cpu().numpy() - o[k])
             assert (err <= 2.0 ** -8 * np.abs(o[k]) + 1.01e-4 * o["m_" + k]).all(), k
+
+
+@pytest.mark.parametrize("lo,hi", [(-60.0, -15.0), (-20.0, 20.0), (15.0, 90.0)])
+def test_bwd_softplus_over_its_range(sw, lo, hi):  # noqa: F811
+    """softplus and its derivative where 1 + e^-|v| rounds to 1, around 0 and
+    where softplus(v) is v, zero of either sign included."""
+    B, D, N, L = 2, 19, 16, 70
+    opts = ("softplus", "z", "h0")
+    inp, ex = _inputs(B, D, N, L, 2700 + int(hi), "f32", opts)
+    v = np.random.Generator(np.random.PCG64(27)).uniform(lo, hi, (B, D, L))
+    inp["delta"] = v.astype(np.float32)
+    inp["delta"][:, :2, ::7] = np.float32([0.0, -0.0])[:, None]
+    inp["A"] = inp["A"] * np.float32(1.0 / 64)
+    g = _run(sw, inp, ex, "f32", opts)
+    _check_all(g, _ref(inp, ex, opts), f"softplus {lo} {hi}",
+               ["dx", "ddelta", "dA", "dB", "dC", "dDskip", "dz", "dh0"])
