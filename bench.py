@@ -406,11 +406,9 @@ def bench_affine(w, args):
 
     wall, kern, per = run_timed(step, args)
     gbs = abytes / kern / 1e9
-    # the library walks each row in one workgroup once the rows alone fill the
-    # GPU (>= 8 per CU) and a row is longer than one 2048-step chunk
-    cus = torch.cuda.get_device_properties(dev).multi_processor_count
-    kname = ("affine_rows_kernel" if w.L > 2048 and w.B * w.D >= 8 * cus
-             else "affine_scan_kernel")
+    # rows of at most 512 steps take a wavefront each, longer ones a workgroup
+    # (or several, each a segment)
+    kname = "affine_wave_kernel" if w.L <= 512 else "affine_rows_kernel"
     if args.schedule == "blelloch":
         kname = "affine_blelloch_kernel"
     if proj:

@@ -680,6 +680,11 @@ bool row16_whole_vectors(const SelArgs& a) {
   return row16_path<IN>(a) && a.vec && a.L % (16 / (int64_t)sizeof(IN)) == 0;
 }
 
+// The planes of a call stay in the stream-ordered pool after it, so they are
+// bounded: calls that need more than 1 GiB (over 4e9 states
+// times steps at N = 64) keep the 8-lane kernel, which needs none.
+constexpr int64_t GROUPS_MAX_BYTES = (int64_t)1 << 30;
+
 // Whether a call that lanes16_path admits takes the 16-lane kernels rather
 // than the 8-lane one.  Up to 16 states always: us per call, 8-lane / 16-lane,
 // B=1 D=1000 N=12 L=1000 57 / 23, B=8 D=1536 N=12 L=2048 184 / 124 (fp32).
@@ -706,6 +711,7 @@ bool groups_pay(const SelArgs& a) {
   }
   if (a.N <= 16) return true;
   const int64_t R = a.B * a.D, ngrp = (a.N + 15) / 16;
+  if (R > GROUPS_MAX_BYTES / 4 / ngrp / a.L) return false;
   const int64_t per = (a.B * ((a.D + 15) / 16) * ngrp + cus - 1) / cus;
   const double rest[3] = {0.0, 28.8, 42.3};
   const double walk = (double)a.L * ((double)(per / 3) * 57.1 + rest[per % 3]) * 1e-3;
@@ -749,8 +755,12 @@ int launch_selective(const SelArgs& a) {
   }
   if (step) return launch_step<IN>(a, s);
   if (r16) return launch_row16<IN>(a, s);
-  if (lanes16_path<IN>(a) && !(a.ckpt && N > 16) && groups_pay<IN>(a))
-    return launch_row16_groups<IN>(a, s);
+  if (lanes16_path<IN>(a) && !(a.ckpt && N > 16) && groups_pay<IN>(a)) {
+    // without memory for the planes (nothing is launched then) the 8-lane
+    // kernel takes the call
+    const int st = launch_row16_groups<IN>(a, s);
+    if (st != SW_ERR_ALLOC) return st;
+  }
   if (N <= 8) return launch_npl<IN, 1>(a, v, s);
   if (N <= 16) return launch_npl<IN, 2>(a, v, s);
   if (N <= 32) return launch_npl<IN, 4>(a, v, s);
