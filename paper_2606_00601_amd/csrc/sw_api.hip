@@ -36,10 +36,21 @@ thread_local char tls_msg[512] = "";
 thread_local char tls_launch[256] = "";
 bool pool_ready[64] = {};  // guarded by scratch_mu
 
-__global__ void fill_zero_kernel(uint32_t* __restrict__ p, size_t n) {
+template <typename T>
+__global__ void fill_zero_kernel(T* __restrict__ p, size_t n) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) p[i] = 0u;
+  for (; i < n; i += stride) p[i] = 0;
+}
+
+// Zero n elements of T at p, which is aligned for T.
+template <typename T>
+int zero_elems(T* p, size_t n, hipStream_t s) {
+  if (n == 0) return SW_OK;
+  size_t blocks = (n + 255) / 256;
+  if (blocks > 4096) blocks = 4096;
+  hipLaunchKernelGGL(fill_zero_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, s, p, n);
+  return check_launch("fill_zero_kernel");
 }
 
 // ------------------------------------------------------------ validation
@@ -302,12 +313,17 @@ int selective_bwd_common(BwdArgs a) {
   if (empty) {
     // no step: every sum is empty, and the initial state's gradient is dh_last
     // (dB and dC have elements only when L > 0, B > 0 and D == 0)
-    uint32_t* zs[] = {reinterpret_cast<uint32_t*>(a.dA), static_cast<uint32_t*>(a.dB),
-                      static_cast<uint32_t*>(a.dC), reinterpret_cast<uint32_t*>(a.dDskip),
-                      reinterpret_cast<uint32_t*>(a.ddelta_bias)};
-    const size_t nw[] = {(size_t)nan, (size_t)nbc * gs / 4, (size_t)nbc * gs / 4, (size_t)D, (size_t)D};
-    for (int i = 0; i < 5; ++i)
-      if (zs[i] && (st = zero_words(zs[i], nw[i], s)) != SW_OK) return st;
+    float* zs[] = {a.dA, a.dDskip, a.ddelta_bias};
+    const size_t nw[] = {(size_t)nan, (size_t)D, (size_t)D};
+    for (int i = 0; i < 3; ++i)
+      if (zs[i] && (st = zero_elems(zs[i], nw[i], s)) != SW_OK) return st;
+    for (void* p : {a.dB, a.dC}) {
+      if (!p) continue;
+      // (bf16: by element, any number of them at any element alignment)
+      st = a.grads_bf16 ? zero_elems(static_cast<uint16_t*>(p), (size_t)nbc, s)
+                        : zero_elems(static_cast<float*>(p), (size_t)nbc, s);
+      if (st != SW_OK) return st;
+    }
     if (a.dh0 && nh > 0) {
       if (!a.dh_last) return zero_words(reinterpret_cast<uint32_t*>(a.dh0), (size_t)nh, s);
       hipError_t e = hipMemcpyAsync(a.dh0, a.dh_last, (size_t)nh * 4, hipMemcpyDeviceToDevice, s);
@@ -511,13 +527,7 @@ int device_cus(int* cus) {
   return SW_OK;
 }
 
-int zero_words(uint32_t* p, size_t words, hipStream_t s) {
-  if (words == 0) return SW_OK;
-  size_t blocks = (words + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p, words);
-  return check_launch("fill_zero_kernel");
-}
+int zero_words(uint32_t* p, size_t words, hipStream_t s) { return zero_elems(p, words, s); }
 
 }  // namespace sw
 

@@ -127,3 +127,21 @@ def test_bwd_softplus_over_its_range(sw, lo, hi):  # noqa: F811
     g = _run(sw, inp, ex, "f32", opts)
     _check_all(g, _ref(inp, ex, opts), f"softplus {lo} {hi}",
                ["dx", "ddelta", "dA", "dB", "dC", "dDskip", "dz", "dh0"])
+
+
+@pytest.mark.parametrize("N,L,k", [(5, 3, 0), (5, 3, 1), (4, 2, 1)])
+def test_bwd_of_no_rows_clears_odd_bf16_gradients(sw, N, L, k):  # noqa: F811
+    """No rows (D = 0): dB and dC are sums of nothing, cleared whole, in bf16
+    also where their number is odd or they start off a 4-byte boundary, and
+    nothing beside them is."""
+    n = L * N
+    bufs = [torch.full((n + 8,), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    B16, F32 = 1, 0
+    ptr = [b.data_ptr() + 2 * k for b in bufs]
+    args = [None] * 16 + [ptr[0], ptr[1]] + [None] * 4
+    with sw._on(bufs[0].device):
+        st = sw.lib().sw_selective_scan_bwd_ex(*args, 1, 0, N, L, B16, F32, B16, 0, None, 0)
+    assert st == 0, sw.lib().sw_last_error()
+    for b in bufs:
+        assert torch.count_nonzero(b[k:k + n]) == 0 and bool(torch.isnan(b[:k]).all())
+        assert bool(torch.isnan(b[k + n:]).all())
