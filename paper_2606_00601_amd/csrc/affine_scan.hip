@@ -394,9 +394,9 @@ int64_t affine_segments(int64_t R, int64_t nch, int cus) {
 
 template <typename T, int K, bool IO>
 int launch_rows(const AffIO<T>& io, int64_t R, int64_t L, hipStream_t s) {
-  const int64_t most = (int64_t)1 << 30;
-  hipLaunchKernelGGL((affine_rows_kernel<T, K, IO, false>), dim3((unsigned)(R < most ? R : most)),
-                     dim3(AS_THREADS), 0, s, io, R, L, (int64_t)1, (int64_t)0, nullptr, nullptr, 0u);
+  hipLaunchKernelGGL((affine_rows_kernel<T, K, IO, false>),
+                     dim3((unsigned)(R < SW_MAX_WGS ? R : SW_MAX_WGS)), dim3(AS_THREADS), 0, s, io, R, L,
+                     (int64_t)1, (int64_t)0, nullptr, nullptr, 0u);
   return check_launch("affine_rows_kernel");
 }
 
@@ -410,9 +410,10 @@ int launch_segments(const AffIO<T>& io, int64_t R, int64_t L, int64_t nseg, int6
 
 template <typename T, int K, bool IO>
 int launch_wave(const AffIO<T>& io, int64_t R, int64_t L, hipStream_t s) {
-  const int64_t wgs = (R + AS_WAVES - 1) / AS_WAVES, most = (int64_t)1 << 30;
-  hipLaunchKernelGGL((affine_wave_kernel<T, K, IO>), dim3((unsigned)(wgs < most ? wgs : most)),
-                     dim3(AS_THREADS), 0, s, io, R, L);
+  const int64_t wgs = (R + AS_WAVES - 1) / AS_WAVES;
+  hipLaunchKernelGGL((affine_wave_kernel<T, K, IO>),
+                     dim3((unsigned)(wgs < SW_MAX_WGS ? wgs : SW_MAX_WGS)), dim3(AS_THREADS), 0, s, io, R,
+                     L);
   return check_launch("affine_wave_kernel");
 }
 

@@ -959,7 +959,7 @@ BwdPlan plan_bwd(int64_t B, int64_t G, int64_t ntile, int cus) {
   double best_us = main_us(W, ntile);
   for (int64_t k = 2; k <= BW_MAX_SEG && k <= ntile; ++k) {
     const int64_t tiles = (ntile + k - 1) / k, n = (ntile + tiles - 1) / tiles;
-    if (n < 2 || W * n >= ((int64_t)1 << 31)) continue;
+    if (n < 2 || W * n > SW_MAX_WGS) continue;
     const int64_t e = per_cu(W * (n - 1));
     const double walk = (double)(e / 7) * (0.5 + 0.45 * 7) + (e % 7 ? 0.5 + 0.45 * (double)(e % 7) : 0.0);
     const double us = main_us(W * n, tiles) + (double)(tiles + 5) * walk + 8.0;
@@ -1012,8 +1012,10 @@ int selective_bwd(const BwdArgs& a) {
   hipStream_t s = current_stream();
   const int64_t B = a.B, D = a.D, L = a.L;
   const int64_t G16 = (D + SW_ROWS - 1) / SW_ROWS;
-  if (B * G16 >= ((int64_t)1 << 31))
-    return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range", (long long)(B * G16));
+  // (the sweep that rebuilds checkpoints takes 16 rows a workgroup)
+  const int64_t wgs = B * (a.ckpt ? (D + BW_ROWS - 1) / BW_ROWS : G16);
+  if (wgs > SW_MAX_WGS)
+    return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range", (long long)wgs);
   const BwdSizes z = bwd_sizes(B, D, a.N, L, a.ckpt != nullptr, a.z && !a.s_pre);
   const int64_t G = z.G, ntile = z.ntile;
   const BwdPlan plan = z.plan;

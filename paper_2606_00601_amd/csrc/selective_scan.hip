@@ -663,11 +663,14 @@ bool vector_path(const SelArgs& a) {
 }
 
 // 16-byte aligned B and C and an even N: one state per lane, 16-lane
-// rows (selective_scan16.hip), whatever the rows' length and alignment;
-// SW_SS_LAYOUT=8 keeps the 8-lane layout.
+// rows (selective_scan16.hip), whatever the rows' length and alignment, where
+// one launch takes a workgroup per 16 rows and group of states (the 8-lane
+// kernel's grid is persistent and takes any number of rows); SW_SS_LAYOUT=8
+// keeps the 8-lane layout.
 template <typename IN>
 bool lanes16_path(const SelArgs& a) {
   return (uintptr_t)a.Bm % 16 == 0 && (uintptr_t)a.Cm % 16 == 0 &&
+         a.B * ((a.D + 15) / 16) * ((a.N + 15) / 16) <= SW_MAX_WGS &&
          env_int("SW_SS_LAYOUT", 16) == 16 && row16_fits(a.D, a.N, a.L, sizeof(IN));
 }
 template <typename IN>

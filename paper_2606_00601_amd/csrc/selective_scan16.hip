@@ -974,7 +974,7 @@ N16Plan plan_n16(const SelArgs& a, int64_t ndb, int cus) {
     for (int64_t k = (kmin > 2 ? kmin : 2); k <= kmax; ++k) {
       int64_t n, Lseg;
       r16_geometry(L, st, k, &n, &Lseg);
-      if (n < 2 || G16 * n >= ((int64_t)1 << 31)) continue;
+      if (n < 2 || G16 * n > SW_MAX_WGS) continue;
       // every segment walks at once: the longest sets the launch's time
       const int64_t last = L - (n - 1) * Lseg;
       const int64_t longest = last > Lseg ? last : Lseg;
@@ -1003,7 +1003,7 @@ N16Plan plan_n16(const SelArgs& a, int64_t ndb, int cus) {
     for (int64_t k = (qmin > 2 ? qmin : 2); k <= qmax; ++k) {
       int64_t Lseg, last;
       quad_geometry(L, k, &Lseg, &last);
-      if (Lseg < QUAD_SKIP) continue;
+      if (Lseg < QUAD_SKIP || Gq * k > SW_MAX_WGS) continue;
       // every segment walks at once: the longest sets the launch's time
       const int64_t longest = last > Lseg ? last : Lseg;
       const int64_t walk =
@@ -1115,7 +1115,7 @@ int launch_row16(const SelArgs& a, hipStream_t s) {
   const bool opt = a.z || a.delta_bias || a.softplus || a.y_bf16 || a.s_out;
   const int64_t ndb = (a.D + R16_ROWS - 1) / R16_ROWS;
   const int64_t grid = a.B * ndb;
-  if (grid >= ((int64_t)1 << 31))
+  if (grid > SW_MAX_WGS)
     return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range", (long long)grid);
   int cus = 0;
   if (device_cus(&cus) != SW_OK) cus = 256;  // a forced choice needs no device facts
@@ -1142,7 +1142,7 @@ template <typename IN>
 int launch_row16_groups(const SelArgs& a, hipStream_t s) {
   const int64_t ndb = (a.D + R16_ROWS - 1) / R16_ROWS, R = a.B * a.D;
   const int ngrp = r16_groups<R16_GRP>(a.N);
-  if (a.B * ndb * ngrp >= ((int64_t)1 << 31) || R * ((a.L + 1023) / 1024) >= ((int64_t)1 << 31))
+  if (a.B * ndb * ngrp > SW_MAX_WGS || (ngrp > 1 && R * ((a.L + 1023) / 1024) > SW_MAX_WGS))
     return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range",
                 (long long)(a.B * ndb * ngrp));
   int cus = 0;
@@ -1183,7 +1183,7 @@ template <typename IN>
 int launch_row16_states(const SelArgs& a, int grp, hipStream_t s) {
   const int64_t ndb = (a.D + R16_ROWS - 1) / R16_ROWS;
   const int64_t grid = a.B * ndb;
-  if (grid >= ((int64_t)1 << 31))
+  if (grid > SW_MAX_WGS)
     return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range", (long long)grid);
   const bool opt = a.delta_bias || a.softplus;
   const uint32_t flags = a.softplus ? SEL_SOFTPLUS : 0u;

@@ -442,7 +442,7 @@ bool quad_fits(const SelArgs& a) {
   if (a.L % Q_T != 0 || a.D >= ((int64_t)1 << 30) || a.L >= ((int64_t)1 << 26)) return false;
   if ((Q_RPW * (a.L + 4 * Q_T)) * (int64_t)sizeof(IN) >= ((int64_t)1 << 31)) return false;
   if ((a.L + 4 * Q_T) * Q_N * (int64_t)sizeof(IN) >= ((int64_t)1 << 31)) return false;
-  return a.B * ((a.D + Q_WAVES * Q_RPW - 1) / (Q_WAVES * Q_RPW)) * Q_MAX_SEG < ((int64_t)1 << 31);
+  return a.B * ((a.D + Q_WAVES * Q_RPW - 1) / (Q_WAVES * Q_RPW)) <= SW_MAX_WGS;
 }
 
 // Launches the quad layout with nseg segments of Lseg steps (the last takes

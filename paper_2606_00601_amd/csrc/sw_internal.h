@@ -30,6 +30,12 @@ int device_cus(int* cus);
 // SW_ERR_UNSUPPORTED (naming `what`) while stream `s` is capturing, else SW_OK.
 int refuse_capture(hipStream_t s, const char* what);
 
+// Workgroups of 256 threads one launch may have: the runtime refuses a grid of
+// 2^32 threads or more.  Kernels that walk their rows with the grid's stride
+// are launched with at most this many; the others refuse, or leave the call to
+// a kernel that does.
+constexpr int64_t SW_MAX_WGS = ((int64_t)1 << 24) - 1;
+
 // Zero `words` 32-bit words with a plain kernel (no memset node).
 int zero_words(uint32_t* p, size_t words, hipStream_t s);
 

@@ -63,3 +63,15 @@ def test_f32_segments_are_reproducible(sw):  # noqa: F811
     for _ in range(5):
         assert torch.equal(sw.affine_scan(a, bx, h0), h)
     assert torch.equal(sw.affine_scan_noalloc(a, bx, h0), h)
+
+
+def test_more_rows_than_a_grid_holds(sw):  # noqa: F811
+    """2^26 rows of one step, one more than a launch of a workgroup per four
+    rows may have (2^32 threads): the workgroups take several each."""
+    R = 2 ** 26 + 5
+    bx = torch.arange(R, dtype=torch.int32, device="cuda").view(1, R, 1)
+    a = torch.full_like(bx, 3)
+    assert torch.equal(sw.affine_scan_i32(a, bx), bx)
+    h0 = bx.view(1, R)
+    y, hl = sw.affine_scan_proj_i32(a, bx, None, a, h0)
+    assert torch.equal(hl, 4 * h0) and torch.equal(y, 12 * bx)

@@ -125,3 +125,14 @@ def test_plan_errors():
     assert e.value.status == 1  # SW_ERR_INVALID_ARG
     with pytest.raises(ScanWeaverError):
         sw.selective_scan_plan(1 << 20, 1 << 20, 16, 64, cus=256)
+
+
+@pytest.mark.parametrize("L", [32, 33, 64])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_more_rows_than_a_grid_holds(L, dtype):
+    """A workgroup per 16 rows is at most 2^24 - 1 workgroups of 256 threads
+    (2^32 threads is the launch limit): calls of more rows take the 8-lane
+    kernel, whose grid is persistent."""
+    for B, layout in ((2 ** 23 - 1, (4, 16)), (2 ** 23, (8,))):
+        p = sw.selective_scan_plan(B, 17, 16, L, dtype, "f32", False, 256)
+        assert p["layout"] in layout and p["segments"] == 1, (B, p)
