@@ -50,9 +50,9 @@
  *    fp32, 16-byte aligned arrays and a workgroup's byte offsets below 2^31;
  *    the bare scan and its projection form when a row fits one chunk
  *    (L <= 2048) or the rows alone fill the GPU (B*D >= 8 per compute unit);
- *    sw_affine_scan_noalloc on every path (its records live in a
- *    static array that each call clears with a fill kernel, so a replay
- *    repeats the call exactly); and
+ *    sw_affine_scan_noalloc on every path (its tickets and records live in
+ *    a static array, of which each call first clears what it uses with a fill
+ *    kernel, so a replay repeats the call exactly); and
  *    the Blelloch schedule entry points.  A call that uses the scratch
  *    is not replay-safe (a replay would repeat the ticket range and epoch the
  *    host gave the captured launch), and the backward allocates a workspace
@@ -107,13 +107,14 @@ int sw_affine_scan_i32(const int32_t* a, const int32_t* bx, const int32_t* h0, i
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments, layout, results (within fp32 rounding of the same
  * schedule) and errors as sw_affine_scan, but no hipMalloc, hipFree or
- * allocating library routine is called: the records of rows cut into
- * segments live in a static array in the library's device code (32 KiB +
+ * allocating library routine is called: the tickets and records of rows cut
+ * into segments live in a static array in the library's device code (32 KiB +
  * 24 bytes per chunk, 1.5 MiB for SW_NOALLOC_MAX_CHUNKS chunks), one copy per
  * GPU, held until the process ends; its address is looked up on the first
  * call on each device (make that call before capturing one into a HIP
- * graph).  Each call clears the part it uses with a fill kernel on the
- * call's stream before the scan.
+ * graph).  Each call clears the part it uses, tickets and records, with a fill
+ * kernel on the call's stream before the scan: what an earlier call left there
+ * does not matter.
  *   - Calls with L > 2048, B*D < 8 * (compute units) and more than
  *     SW_NOALLOC_MAX_CHUNKS chunks, B * D * ceil(L / 2048), return
  *     SW_ERR_UNSUPPORTED before enqueuing anything.  Other calls (one chunk

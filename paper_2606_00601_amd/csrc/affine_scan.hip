@@ -40,10 +40,12 @@
 #include "sw_internal.h"
 
 // Scratch of the entry point that allocates nothing (sw_affine_scan_noalloc):
-// the rows' ticket counters, then three words per chunk for at most
-// SW_NOALLOC_MAX_CHUNKS chunks, of which the segments' records use two.  Each GPU holds its own
-// copy, found by hipGetSymbolAddress once per device; host code uses only
-// that address, never the array's name.
+// the ticket counters of a call's rows, directly followed by its segments'
+// records (two words each, at most AS_MAX_SEG segments of SW_ROW_TICKETS rows;
+// room for three words per chunk of SW_NOALLOC_MAX_CHUNKS chunks).  Each call
+// clears what it uses of both.  Each GPU holds its own copy, found by
+// hipGetSymbolAddress once per device; host code uses only that address,
+// never the array's name.
 static __device__ __align__(256) unsigned long long
     scratch[sw::SW_ROW_TICKETS * sw::SW_TICKET_STRIDE / 2 + 3 * (int64_t)SW_NOALLOC_MAX_CHUNKS];
 
@@ -457,9 +459,13 @@ int launch_affine(const AffIO<T>& io, int64_t R, int64_t L, bool fixed = false) 
     unsigned long long* base = nullptr;
     st = static_scratch(cur, &base);
     if (st != SW_OK) return st;
-    // the records of the call before carry the same epoch: clear this call's
-    unsigned long long* const rec = base + SW_ROW_TICKETS * SW_TICKET_STRIDE / 2;
-    st = zero_words(reinterpret_cast<uint32_t*>(rec), (size_t)(R * (nseg - 1) * 4), s);
+    // The records of the call before carry the same epoch, and its counters
+    // may hold anything if it did not run alone: a segment that no workgroup
+    // ever takes would be waited for forever.  So each call starts from
+    // cleared counters and records, whatever came before it.
+    unsigned long long* const rec = base + R * SW_TICKET_STRIDE / 2;
+    st = zero_words(reinterpret_cast<uint32_t*>(base),
+                    (size_t)(R * SW_TICKET_STRIDE + R * (nseg - 1) * 4), s);
     if (st != SW_OK) return st;
     return launch_segments<T, IO>(io, R, L, nseg, per, rec, reinterpret_cast<uint32_t*>(base), 1u, s);
   }

@@ -132,3 +132,15 @@ def test_largest_call_and_one_chunk_more(sw):
     assert "65568" in msg and "65536" in msg, msg
     torch.cuda.synchronize()
     assert bool((out == 7.0).all())  # nothing was enqueued
+
+
+def test_a_call_starts_from_cleared_tickets_and_records(sw):
+    """Calls of few and many rows in turn: a call's records lie where the next
+    one keeps its tickets (R counters of 64 bytes, the records behind them), so
+    each must clear both before its scan.  Exact inputs, bit for bit."""
+    cases = [(1, 60_000), (100, 14_000), (3, 40_000), (128, 20_000), (2, 600_000), (64, 12_300)]
+    for D, L in cases + cases[::-1]:
+        _say("case noalloc cleared", D, L)
+        a, bx = _exact_inputs(1, D, L, 8100 + D, 4)
+        got, ref = _both(sw, torch.from_numpy(a).cuda(), torch.from_numpy(bx).cuda())
+        assert torch.equal(got, ref)
