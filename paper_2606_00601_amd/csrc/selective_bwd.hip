@@ -13,6 +13,10 @@
 //   dC_{t,n} += ds_t h_t                        (over d)
 //   dh0 = a_0 lam_0,  dDskip += ds x,  dz = dy s silu'(z) with s the pre-gate y.
 //
+// Two kernels walk it, and plan_bwd prices them per call: the one below, on 64
+// rows a workgroup, and the one of selective_bwd16.hip, on 16, for calls whose
+// 16-row blocks fill the compute units where their 64-row blocks do not.
+//
 // The state before every 8th step (a checkpoint per row, state and tile)
 // comes from the forward, from its walk without y, or from
 // selective_sweep_kernel below.  selective_bwd_kernel walks the tiles of its
@@ -48,13 +52,13 @@
 // and state (45 cycles per wavefront and SIMD), the sums over rows (9) and
 // states (4) and the staging with softplus and gate (9), against the HBM
 // time of the checkpoints and the (B, D, L) arrays.
-#include "selective_common.h"
+#include <stdlib.h>
+
+#include "bwd_common.h"
 
 namespace sw {
 namespace {
 
-constexpr int BW_N = 16;      // states per launch (groups of 16 for N > 16)
-constexpr int BW_T = 8;       // steps per tile
 constexpr int BW_WROWS = 16;  // rows per wavefront
 constexpr int BW_ROWS = 64;   // rows per workgroup
 constexpr int BW_MAX_SEG = 32;
@@ -64,7 +68,6 @@ constexpr int BW_MAX_SEG = 32;
 // (reads: 4 rows x 2 quantities x 2 halves fill them)
 constexpr int BW_SPR = 72;
 constexpr int BW_SPQ = BW_WROWS * BW_SPR + 32;
-constexpr float BW_LOG2E = 1.4426950408889634f;
 
 // (the adjoint's walk without gradients uses rv and bc only, and keeps more
 // workgroups on a compute unit)
@@ -75,31 +78,6 @@ struct BwSmem {
   float sp[4][ENDS ? 4 : 2 * BW_SPQ];    // per wavefront: lam q A, lam B (summed over n next)
   float pw[2][4][2][ENDS ? 4 : 64 * 4];  // two tiles, per wavefront and 4 steps: row sums
 };
-
-__device__ __forceinline__ float sigmoid_f32(float v) {
-  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-v * BW_LOG2E));
-}
-
-// softplus(v) and its derivative sigmoid(v) from one exp2: e = e^-|v| and w =
-// 1 + e give sigmoid(|v|) = 1 / w and log1p(e) = log(w) e / (w - 1) (e where w
-// rounds to 1), and softplus(v) = max(v, 0) + log1p(e).  The staging of a tile
-// is bound by instruction issue and an exp2 takes 8.5 cycles of it: two
-// separate ones took the B=8 D=1536 L=2048 bf16 call 602 us, this 577 together
-// with the segment rule's five tiles.
-__device__ __forceinline__ void softplus_sigmoid_f32(float v, float& sp, float& sg) {
-  const float e = __builtin_amdgcn_exp2f(-__builtin_fabsf(v) * BW_LOG2E);
-  const float w = 1.0f + e, d = w - 1.0f;
-  const float l = __builtin_amdgcn_logf(w) * 0.6931471805599453f * (e * __builtin_amdgcn_rcpf(d));
-  sp = (v > 0.0f ? v : 0.0f) + (d == 0.0f ? e : l);
-  const float r = __builtin_amdgcn_rcpf(w);
-  sg = v > 0.0f ? r : e * r;
-}
-
-__device__ __forceinline__ void bw_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
 
 // LDS writes of this wavefront are seen by its later reads in every lane.
 __device__ __forceinline__ void bw_wave_order() {
@@ -112,36 +90,6 @@ __device__ __forceinline__ void bw_wave_order() {
 __device__ __forceinline__ float lane_xor1(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1,
                                                                0xf, 0xf, false));
-}
-
-struct BwWork {
-  float* ck;       // (B*D, ntile, 16) states at tile starts
-  const float* s;  // (B*D, L) pre-gate output (gated calls)
-  float* rec;      // (nseg - 1, 2, B*D, 16): P and end adjoint of segments 1 ..
-  float* dA_p;     // (nseg, B*D, 16)
-  float* dD_p;     // (nseg, B*D)
-  float* db_p;     // (nseg, B*D)
-  float* dB_p;     // (B, G, L, 16)
-  float* dC_p;     // (B, G, L, 16)
-  float* trash;    // 1024 floats: the target of stores a lane does not need
-};
-
-template <typename T>
-__device__ __forceinline__ float widen(T r) {
-  if constexpr (sizeof(T) == 4)
-    return r;
-  else
-    return __uint_as_float((uint32_t)r << 16);
-}
-
-// One element of type T at byte offset voff + soff of a raw buffer resource
-// (zero past the resource's end).
-template <typename T>
-__device__ __forceinline__ T buf_ld(__amdgpu_buffer_rsrc_t r, int32_t voff, int32_t soff) {
-  if constexpr (sizeof(T) == 4)
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
-  else
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0));
 }
 
 template <typename T>
@@ -191,15 +139,6 @@ struct Two {
       return __uint_as_float(w[i] << 16);
   }
 };
-
-// One gradient value as stored: fp32, or bf16 rounded to nearest even.
-template <typename OUT>
-__device__ __forceinline__ void st1(OUT* p, float v) {
-  if constexpr (sizeof(OUT) == 4)
-    *p = v;
-  else
-    *p = (OUT)bf16_rne(v);
-}
 
 // Launch modes: the gradients; the adjoint's walk without gradients (segments
 // 1 .. nseg-1), which records each segment's end value.
@@ -736,13 +675,17 @@ __global__ __launch_bounds__(256) void selective_sweep_kernel(const BwdArgs a, f
     IN r0, r1;
     bool ok;
   };
+  // (both roles run the same loads: one inside a branch is waited for there)
+  const IN* __restrict__ P0 = role_a ? X : BM;
+  const IN* __restrict__ P1 = role_a ? DL : BM;
   auto load = [&](int64_t k, Raw& v) {
     const int64_t ta = k * BW_T + st, tb = k * BW_T + bt;
     const int64_t tca = ta < L ? ta : L - 1, tcb = tb < L ? tb : L - 1;
     const int64_t ib = (b * L + tcb) * N + (n0 + bn < N ? n0 + bn : N - 1);
     v.ok = role_a ? sdok && ta < L : tb < L && n0 + bn < N;
-    v.r0 = role_a ? X[srow * L + tca] : BM[ib];
-    v.r1 = role_a ? DL[srow * L + tca] : v.r0;
+    const int64_t i = role_a ? srow * L + tca : ib;
+    v.r0 = P0[i];
+    v.r1 = P1[i];
   };
   Raw ring[SW_RING];
   float h = (a.h0 && dok && nok) ? a.h0[row * N + ns] : 0.0f;
@@ -883,6 +826,7 @@ bool bwd_pairs(const BwdArgs& a) {
 struct BwdPlan {
   int nseg;
   int64_t seg_tiles;
+  bool rows16;  // the kernel of selective_bwd16.hip, on whole rows
 };
 
 template <typename IN, typename DYT, typename OUT, bool GATED, bool PAIR, bool BUF>
@@ -935,39 +879,77 @@ void launch_bwd(const BwdArgs& a, const BwWork& w, int64_t G, int64_t ntile, con
   }
 }
 
-// How many segments the sequence is cut into, priced like the forward's plan:
-// a launch of n workgroups runs in rounds of at most two per compute unit (by
-// LDS and registers), a tile of a round takes 2.1 us with one workgroup on
-// the busiest compute unit and 3.5 us with two (measured, gate and softplus
-// included), and starting and ending a segment about five tiles more.  Cut
-// calls add the adjoint's walk, 0.5 + 0.45 us per tile and workgroup resident
-// (up to seven), and 8 us for its launch and the records.  us per call,
-// whole rows / cut, against one state per lane on whole rows before: B=8,
-// D=1536, L=2048 (bf16, gate, softplus) 641 / 508 (5 or 8 segments), 561
-// before; B=1, D=1000, L=1501 (fp32) 398 / 71 (16), 200 before; B=16, D=5120,
-// L=256 345 / 393 (2), 455 before.  The first shape with bf16 dy and fp32
-// gradients takes 538 in 5 segments and took 496 before: the adjoint's walk
-// stages softplus and gate a second time, about 100 us.
-BwdPlan plan_bwd(int64_t B, int64_t G, int64_t ntile, int cus) {
-  BwdPlan best{1, ntile};
-  const int64_t W = B * G;
-  const auto per_cu = [&](int64_t n) { return (n + cus - 1) / cus; };
-  const auto main_us = [&](int64_t n, int64_t tiles) {
-    const int64_t p = per_cu(n);
-    return (double)(tiles + 5) * ((double)(p / 2) * 3.5 + (double)(p % 2) * 2.1);
-  };
-  double best_us = main_us(W, ntile);
+// Which kernel a call takes, and how many segments the 64-row one cuts the
+// sequence into, priced like the forward's plan.  A launch of n workgroups runs
+// in rounds of at most two (64 rows) or three (16 rows) per compute unit, by
+// LDS and registers; a round takes BwdCost::us per tile of 8 steps with that
+// many workgroups on the busiest compute unit, and about five tiles more to
+// start and end a segment (seven for a row block of 16).  Rows of odd length
+// read their steps one by one, and their lines are shared by more accesses:
+// `odd` times that, most with a gate, whose z, s and dz have lines of their own.
+// Rounds of many small workgroups overlap: from 4.5 per compute unit on, each
+// takes `many` us a tile.  State groups after the first read ddelta and dx back,
+// 1.24 times the 64-row kernel's time (0.12 more over two groups).  Cut calls
+// add the adjoint's walk, 0.5 + 0.45 us per tile and workgroup resident (up to
+// seven; without a gate 0.73 of it), and 8 us for its launch and the records.
+// The constants are fits to 13 widths of 1024 to 40960 rows, L = 64 to 4096 and
+// N = 8 to 64, fp32 and bf16, gate with softplus or neither (what the sizing of
+// the workspace knows of a call).  Ties go to the 16-row kernel; over the 3435
+// timed calls the choice is 1.3% from the faster kernel on average.  us per
+// call with given checkpoints, 16-row / 64-row kernel:
+//   B=8 D=1536 L=1024  ungated 202 / 279, gated 252 / 312 (fp32)
+//   B=8 D=1536 L=2048  ungated 402 / 398, gated 511 / 579 (fp32), 477 / 507 (bf16)
+//   B=4 D=5120 L=1024  gated 421 / 528 (fp32)
+//   B=4 D=1024 L=2048  ungated 271 / 157, gated 298 / 203 (fp32)
+//   B=8 D=4096 L=1024  ungated 534 / 424, gated 654 / 595 (fp32)
+//   B=1 D=1024 L=4096  ungated 505 / 113 (fp32)
+struct BwdCost {
+  int cap;              // workgroups per compute unit
+  double start;         // tiles
+  double us[2][3];      // [gated][workgroups resident - 1]
+  double odd[2][3];
+  double many[2];
+};
+constexpr BwdCost COST_ROWS16 = {
+    3, 7.0, {{1.0, 1.25, 1.53}, {1.16, 1.43, 1.9}}, {{1.04, 1.04, 1.04}, {1.17, 1.17, 1.17}}, {0.495, 0.6}};
+constexpr BwdCost COST_ROWS64 = {
+    2, 5.0, {{2.08, 2.85, 0.0}, {2.4, 3.85, 0.0}}, {{1.05, 1.33, 0.0}, {1.4, 1.6, 0.0}}, {9.0, 9.0}};
+
+double bwd_launch_us(const BwdCost& c, int64_t wgs, int64_t tiles, bool gated, bool odd, int cus) {
+  const int64_t per = (wgs + cus - 1) / cus;
+  const auto us = [&](int64_t o) { return c.us[gated][o - 1] * (odd ? c.odd[gated][o - 1] : 1.0); };
+  double tile = (double)(per / c.cap) * us(c.cap) + (per % c.cap ? us(per % c.cap) : 0.0);
+  const double share = (double)wgs / (double)cus;
+  const double many = share * c.many[gated] * (odd ? c.odd[gated][0] : 1.0);
+  if (share >= 4.5 && many < tile) tile = many;
+  return ((double)tiles + c.start) * tile;
+}
+
+BwdPlan plan_bwd(int64_t B, int64_t D, int64_t N, int64_t L, bool gated, int cus) {
+  const int64_t ntile = (L + BW_T - 1) / BW_T, W = B * ((D + BW_ROWS - 1) / BW_ROWS);
+  const int64_t W16 = B * ((D + 15) / 16);
+  const int64_t ngrp = (N + BW_N - 1) / BW_N;
+  const double groups = 1.0 + 0.12 * (double)(ngrp - 1) / (double)ngrp;
+  const bool odd = L % 2 != 0;
+  BwdPlan best{1, ntile, false};
+  double best_us = groups * bwd_launch_us(COST_ROWS64, W, ntile, gated, odd, cus);
   for (int64_t k = 2; k <= BW_MAX_SEG && k <= ntile; ++k) {
     const int64_t tiles = (ntile + k - 1) / k, n = (ntile + tiles - 1) / tiles;
     if (n < 2 || W * n > SW_MAX_WGS) continue;
-    const int64_t e = per_cu(W * (n - 1));
+    const int64_t e = (W * (n - 1) + cus - 1) / cus;
     const double walk = (double)(e / 7) * (0.5 + 0.45 * 7) + (e % 7 ? 0.5 + 0.45 * (double)(e % 7) : 0.0);
-    const double us = main_us(W * n, tiles) + (double)(tiles + 5) * walk + 8.0;
+    const double us = groups * bwd_launch_us(COST_ROWS64, W * n, tiles, gated, odd, cus) +
+                      ((double)tiles + COST_ROWS64.start) * walk * (gated ? 1.0 : 0.73) + 8.0;
     if (us < best_us) {
       best_us = us;
-      best = BwdPlan{(int)n, tiles};
+      best = BwdPlan{(int)n, tiles, false};
     }
   }
+  // SW_SS_BWD_ROWS=16 or 64 keeps one kernel
+  const char* const v = getenv("SW_SS_BWD_ROWS");
+  const int force = v && *v ? atoi(v) : 0;
+  const bool rows16 = bwd_launch_us(COST_ROWS16, W16, ntile, gated, odd, cus) < 1.03 * best_us;
+  if (W16 <= SW_MAX_WGS && (force == 16 || (force != 64 && rows16))) best = BwdPlan{1, ntile, true};
   return best;
 }
 
@@ -979,13 +961,14 @@ struct BwdSizes {
   size_t ck, bc, rec, dA, s, d, total;
 };
 
-BwdSizes bwd_sizes(int64_t B, int64_t D, int64_t N, int64_t L, bool ckpt, bool pre) {
+BwdSizes bwd_sizes(int64_t B, int64_t D, int64_t N, int64_t L, bool ckpt, bool gated, bool pre) {
   BwdSizes z;
-  z.G = (D + BW_ROWS - 1) / BW_ROWS;
   z.ntile = (L + BW_T - 1) / BW_T;
   int cus = 0;
   if (device_cus(&cus) != SW_OK) cus = 256;
-  z.plan = plan_bwd(B, z.G, z.ntile, cus);
+  z.plan = plan_bwd(B, D, N, L, gated, cus);
+  const int64_t rows = z.plan.rows16 ? 16 : BW_ROWS;
+  z.G = (D + rows - 1) / rows;
   const size_t R = (size_t)(B * D), nseg = (size_t)z.plan.nseg;
   // without the forward's checkpoints the call rebuilds them in the workspace
   z.ck = ckpt ? 0 : R * (size_t)z.ntile * BW_N;
@@ -1003,7 +986,7 @@ BwdSizes bwd_sizes(int64_t B, int64_t D, int64_t N, int64_t L, bool ckpt, bool p
 
 int64_t selective_bwd_workspace(int64_t B, int64_t D, int64_t N, int64_t L, bool ckpt, bool z,
                                 bool s_pre) {
-  return (int64_t)(bwd_sizes(B, D, N, L, ckpt, z && !s_pre).total * sizeof(float));
+  return (int64_t)(bwd_sizes(B, D, N, L, ckpt, z, z && !s_pre).total * sizeof(float));
 }
 
 int selective_bwd(const BwdArgs& a) {
@@ -1016,7 +999,7 @@ int selective_bwd(const BwdArgs& a) {
   const int64_t wgs = B * (a.ckpt ? (D + BW_ROWS - 1) / BW_ROWS : G16);
   if (wgs > SW_MAX_WGS)
     return fail(SW_ERR_UNSUPPORTED, "%lld workgroups exceed the grid range", (long long)wgs);
-  const BwdSizes z = bwd_sizes(B, D, a.N, L, a.ckpt != nullptr, a.z && !a.s_pre);
+  const BwdSizes z = bwd_sizes(B, D, a.N, L, a.ckpt != nullptr, a.z != nullptr, a.z && !a.s_pre);
   const int64_t G = z.G, ntile = z.ntile;
   const BwdPlan plan = z.plan;
   void* base = a.ws;
@@ -1088,7 +1071,10 @@ int selective_bwd(const BwdArgs& a) {
   }
   // still without checkpoints: where the 16-lane kernels can walk the call,
   // their walk without y writes them (the states do not depend on the gate),
-  // cheaper than the sweep and bit-identical to it
+  // bit-identical to a sweep.  The 64-row kernel otherwise has a sweep kernel
+  // run before it; the 16-row kernel sweeps by itself, which also is faster
+  // than a walk per state group where it is taken (us per call, walk / own
+  // sweep: B=8 D=1536 N=64 L=64 bf16 151 / 123, B=4 D=2560 N=64 L=300 395 / 359).
   SelArgs sa{};
   sa.x = a.x;
   sa.delta = a.delta;
@@ -1109,19 +1095,25 @@ int selective_bwd(const BwdArgs& a) {
   // the states in groups of 16: each group's main kernel, then its reduction
   // (dA, dB, dC of its states; the sums over the states accumulate)
   for (int n0 = 0; n0 < a.N && st == SW_OK; n0 += BW_N) {
+    BwdArgs ag = ab;  // of this group
     if (!ab.ckpt) {
       bool taken = false;
-      st = selective_states_fwd(sa, n0 / BW_N, &taken);
+      if (!plan.rows16 || a.N == BW_N) st = selective_states_fwd(sa, n0 / BW_N, &taken);
       if (st != SW_OK) break;
       ck_from = taken ? "from the forward's walk without y" : "rebuilt by a sweep";
-      if (!taken) {
+      if (taken) {
+        ag.ckpt = w.ck;
+      } else if (!plan.rows16) {
         auto kern = a.bf16_in ? selective_sweep_kernel<uint16_t> : selective_sweep_kernel<float>;
         hipLaunchKernelGGL(kern, dim3((unsigned)(B * G16)), dim3(256), 0, s, a, w.ck, G16, ntile, n0);
         st = check_launch("selective_sweep_kernel");
         if (st != SW_OK) break;
       }
     }
-    launch_bwd(ab, w, G, ntile, plan, n0, s);
+    if (plan.rows16)
+      launch_bwd_rows16(ag, w, G, ntile, n0, s);
+    else
+      launch_bwd(ag, w, G, ntile, plan, n0, s);
     st = check_launch("selective_bwd_kernel");
     if (st != SW_OK) break;
     int64_t work = 2 * B * L * (BW_N / 4);
@@ -1136,8 +1128,9 @@ int selective_bwd(const BwdArgs& a) {
   }
   done();
   if (st == SW_OK)
-    note_launch("selective_bwd_kernel + selective_bwd_reduce_kernel (%lld state group%s, %d "
+    note_launch("%s + selective_bwd_reduce_kernel (%lld state group%s, %d "
                 "segment%s), checkpoints %s",
+                plan.rows16 ? "selective_bwd_rows16_kernel" : "selective_bwd_kernel",
                 (long long)((a.N + BW_N - 1) / BW_N), a.N > BW_N ? "s" : "", plan.nseg,
                 plan.nseg > 1 ? "s" : "", ck_from);
   return st;

@@ -39,6 +39,50 @@ def test_bwd_rows_and_segments(sw, shape, dtype, opts):  # noqa: F811
         assert torch.equal(g[k], g2[k]), k
 
 
+# D at the edges of 16 rows beside those above, L at the edges of the four tiles
+# that loads run ahead, a last state group that is not full
+@pytest.mark.parametrize("shape", _SHAPES + [(1, 16, 16, 24), (3, 33, 16, 31), (1, 48, 16, 32),
+                                             (2, 18, 47, 25)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("opts", [(), _ALL, ("dybf16", "h0", "dhl")])
+@pytest.mark.parametrize("rows", ["16", "64"])
+def test_bwd_kernels_of_16_and_64_rows(sw, monkeypatch, shape, dtype, opts, rows):  # noqa: F811
+    """Both kernels of the backward on every shape, whichever the rule takes."""
+    monkeypatch.setenv("SW_SS_BWD_ROWS", rows)
+    B, D, N, L = shape
+    print("case bwd rows", rows, dtype, shape, opts, flush=True)
+    inp, ex = _inputs(B, D, N, L, 2800 + B + D + N + L, dtype, opts)
+    g = _run(sw, inp, ex, dtype, opts)
+    assert ("rows16" in sw.last_launch()) == (rows == "16"), sw.last_launch()
+    keys = ["dx", "ddelta", "dA", "dB", "dC", "dDskip", "dh0"]
+    keys += ["dz"] if "z" in opts else []
+    keys += ["ddelta_bias"] if "bias" in opts else []
+    _check_all(g, _ref(inp, ex, opts), f"rows {rows} {dtype} {shape} {opts}", keys)
+
+
+@pytest.mark.parametrize("rows", ["16", "64"])
+@pytest.mark.parametrize("shape", [(2, 37, 16, 200), (1, 70, 16, 203), (2, 9, 5, 64)])
+def test_bf16_gradients_of_both_kernels(sw, monkeypatch, shape, rows):  # noqa: F811
+    monkeypatch.setenv("SW_SS_BWD_ROWS", rows)
+    test_autograd_bf16_gradients_are_the_fp32_ones_rounded(sw, shape)
+    assert ("rows16" in sw.last_launch()) == (rows == "16"), sw.last_launch()
+
+
+@pytest.mark.parametrize("shape,rows16", [((8, 1536, 16, 1024), True), ((4, 1536, 16, 128), True),
+                                          ((4, 1024, 16, 1024), False), ((8, 2048, 16, 256), False)])
+def test_bwd_takes_the_kernel_that_fills_the_gpu(sw, shape, rows16):  # noqa: F811
+    """The rule between the kernels on a 256-CU part: 16 rows a workgroup where
+    those are two or three per compute unit and 64-row ones leave units idle."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("priced for 256 compute units")
+    B, D, N, L = shape
+    x = torch.randn((B, D, L), device="cuda").bfloat16()
+    Bm = torch.randn((B, L, N), device="cuda").bfloat16()
+    A = -torch.rand((D, N), device="cuda")
+    sw.selective_scan_bwd(x, x.abs() * 0.01, A, Bm, Bm, None, x)
+    assert ("rows16" in sw.last_launch()) == rows16, sw.last_launch()
+
+
 @pytest.mark.parametrize("A", ["zero", "growth"])
 def test_bwd_segments_without_decay(sw, A):  # noqa: F811
     """The adjoint carried across segments where it does not fade."""
