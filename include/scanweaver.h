@@ -37,12 +37,15 @@
  *    a small scratch per (device, stream) -- carry words and a ticket
  *    counter -- allocated from the device's default stream-ordered pool on
  *    the first such call on that stream, kept for later calls (grown when a
- *    call needs more) and never freed by the library.  The backward pass
- *    takes a per-call workspace from the same pool on the same stream and
- *    releases it, stream-ordered, before returning.  The library raises that
- *    pool's release threshold so freed blocks stay cached for the next call
- *    (a process-wide setting of the device's default pool).  SW_ERR_ALLOC if
- *    an allocation fails.
+ *    call needs more) and never freed by the library.  Where the caller hands
+ *    none over, the backward pass takes a per-call workspace, and a forward
+ *    with N > 16 its planes of y (ceil(N/16) B*D*L fp32, at most 1 GiB), from
+ *    the same pool on the same stream and releases it, stream-ordered, before
+ *    returning.  The library raises that pool's release threshold so freed
+ *    blocks stay cached for the next call (a process-wide setting of the
+ *    device's default pool).  SW_ERR_ALLOC if an allocation fails, except that
+ *    of the planes: the call then takes a kernel that needs none, whose y
+ *    agrees within fp32 rounding.
  *  - Threads using distinct streams may call concurrently.
  *  - HIP graph capture: a call that uses neither the scratch nor a workspace
  *    can be captured and replayed: it launches kernels only.  Such calls are
@@ -292,6 +295,27 @@ int sw_selective_scan_fwd_ex(const void* x, const void* delta, const float* A, c
                              const float* delta_bias, const float* h0, void* y, float* h_last,
                              int64_t B, int64_t D, int64_t N, int64_t L, int in_dtype,
                              int out_dtype, int flags);
+
+/*
+ * sw_selective_scan_fwd_ex with workspace, 16-byte aligned device memory of at
+ * least sw_selective_scan_fwd_workspace bytes that nothing else uses until the
+ * call completes on its stream (SW_ERR_INVALID_ARG if the call needs more), or
+ * NULL: taken from the device's stream-ordered pool for the call.
+ */
+int sw_selective_scan_fwd_ws(const void* x, const void* delta, const float* A, const void* Bm,
+                             const void* Cm, const float* Dskip, const void* z,
+                             const float* delta_bias, const float* h0, void* y, float* h_last,
+                             int64_t B, int64_t D, int64_t N, int64_t L, int in_dtype,
+                             int out_dtype, int flags, void* workspace, int64_t workspace_bytes);
+
+/*
+ * Bytes of the workspace of a forward of these sizes on the current device,
+ * with (nonzero) or without z, with all arrays 16-byte aligned (nonzero) or not
+ * (then what the call may need at most).  0 for N <= 16, for calls that need
+ * none and for an empty or invalid call.
+ */
+int64_t sw_selective_scan_fwd_workspace(int64_t B, int64_t D, int64_t N, int64_t L, int in_dtype,
+                                        int z, int aligned);
 
 /*
  * sw_selective_scan_fwd_ex that also keeps what the backward pass needs

@@ -302,6 +302,11 @@ def _fwd(x, delta, A, Bm, Cm, Dskip, y, h_last, want_h_last, z, delta_bias, h0, 
                 _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(z),
                 _ptr(delta_bias), _ptr(h0), _ptr(y), _ptr(h_last), _ptr(ckpt), _ptr(s_pre),
                 B, D, N, L, in_dt, out_dt, flags), "sw_selective_scan_fwd_train")
+        elif (ws := _fwd_workspace(x, delta, Bm, Cm, z, y, N, in_dt)) is not None:
+            check(fast().sw_selective_scan_fwd_ws(
+                _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(z),
+                _ptr(delta_bias), _ptr(h0), _ptr(y), _ptr(h_last), B, D, N, L, in_dt, out_dt,
+                flags, _ptr(ws), ws.numel()), "sw_selective_scan_fwd_ex")
         elif z is None and delta_bias is None and h0 is None and not flags \
                 and out_dt == SW_DTYPE_F32:
             fn = fast().sw_selective_scan_fwd if dt == torch.float32 \
@@ -316,6 +321,26 @@ def _fwd(x, delta, A, Bm, Cm, Dskip, y, h_last, want_h_last, z, delta_bias, h0, 
                 _ptr(delta_bias), _ptr(h0), _ptr(y), _ptr(h_last), B, D, N, L, in_dt, out_dt,
                 flags), "sw_selective_scan_fwd_ex")
     return y, h_last
+
+
+def _fwd_workspace(x, delta, Bm, Cm, z, y, N, in_dt):
+    """The planes of y of a forward with N > 16 from torch's allocator, which
+    takes them back after the call (None: none needed, or no memory for them;
+    the library then asks its own pool and, failing that, takes the kernel that
+    needs none)."""
+    if N <= 16:
+        return None
+    B, D, L = x.shape
+    at = x.data_ptr() | delta.data_ptr() | Bm.data_ptr() | Cm.data_ptr() | y.data_ptr()
+    if z is not None:
+        at |= z.data_ptr()
+    nws = fast().sw_selective_scan_fwd_workspace(B, D, N, L, in_dt, z is not None, at % 16 == 0)
+    if nws == 0:
+        return None
+    try:
+        return torch.empty((nws,), dtype=torch.uint8, device=x.device)
+    except torch.OutOfMemoryError:
+        return None
 
 
 def selective_scan_fwd_schedule(x, delta, A, Bm, Cm, Dskip=None, *, schedule="default",

@@ -43,6 +43,8 @@ SIGNATURES = {
     "sw_selective_scan_fwd": (_int, [_vp] * 8 + [_i64] * 4),
     "sw_selective_scan_fwd_bf16": (_int, [_vp] * 8 + [_i64] * 4),
     "sw_selective_scan_fwd_ex": (_int, [_vp] * 11 + [_i64] * 4 + [_int] * 3),
+    "sw_selective_scan_fwd_ws": (_int, [_vp] * 11 + [_i64] * 4 + [_int] * 3 + [_vp, _i64]),
+    "sw_selective_scan_fwd_workspace": (_i64, [_i64] * 4 + [_int] * 3),
     "sw_set_stream": (_int, [_vp]),
     "sw_get_stream": (_vp, []),
     "sw_status_string": (ctypes.c_char_p, [_int]),

@@ -959,6 +959,7 @@ struct BwdSizes {
   int64_t G, ntile;
   BwdPlan plan;
   size_t ck, bc, rec, dA, s, d, total;
+  size_t planes;  // bytes
 };
 
 BwdSizes bwd_sizes(int64_t B, int64_t D, int64_t N, int64_t L, bool ckpt, bool gated, bool pre) {
@@ -970,8 +971,16 @@ BwdSizes bwd_sizes(int64_t B, int64_t D, int64_t N, int64_t L, bool ckpt, bool g
   const int64_t rows = z.plan.rows16 ? 16 : BW_ROWS;
   z.G = (D + rows - 1) / rows;
   const size_t R = (size_t)(B * D), nseg = (size_t)z.plan.nseg;
-  // without the forward's checkpoints the call rebuilds them in the workspace
+  // without the forward's checkpoints the call rebuilds them in the workspace,
+  // where before that the ungated forward keeps its planes of y (N > 16)
   z.ck = ckpt ? 0 : R * (size_t)z.ntile * BW_N;
+  z.planes = 0;
+  for (const bool bf16 : {false, true}) {
+    const size_t p = pre ? (size_t)selective_fwd_workspace(B, D, N, L, bf16, false, false) : 0;
+    if (z.planes < p) z.planes = p;
+  }
+  const size_t pw = (z.planes / sizeof(float) + 3) / 4 * 4;
+  if (z.ck < pw) z.ck = pw;
   z.bc = (size_t)(B * z.G) * (size_t)L * BW_N;
   z.rec = 2 * R * BW_N * (nseg - 1);
   z.dA = R * BW_N * nseg;
@@ -1059,6 +1068,10 @@ int selective_bwd(const BwdArgs& a) {
     fa.bf16_in = a.bf16_in;
     fa.softplus = a.softplus;
     fa.vec = a.vec;
+    if (z.planes > 0) {
+      fa.ws = w.ck;
+      fa.ws_bytes = z.planes;
+    }
     if (!a.ckpt && a.N <= BW_N) {
       fa.ckpt = w.ck;
       ab.ckpt = w.ck;

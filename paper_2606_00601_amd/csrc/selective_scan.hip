@@ -683,9 +683,9 @@ bool row16_whole_vectors(const SelArgs& a) {
   return row16_path<IN>(a) && a.vec && a.L % (16 / (int64_t)sizeof(IN)) == 0;
 }
 
-// The planes of a call stay in the stream-ordered pool after it, so they are
-// bounded: calls that need more than 1 GiB (over 4e9 states
-// times steps at N = 64) keep the 8-lane kernel, which needs none.
+// The planes of a call are bounded, as the pool keeps those it gave: calls that
+// need more than 1 GiB (over 4e9 states times steps at N = 64) keep the 8-lane
+// kernel, which needs none.
 constexpr int64_t GROUPS_MAX_BYTES = (int64_t)1 << 30;
 
 // Whether a call that lanes16_path admits takes the 16-lane kernels rather
@@ -785,6 +785,23 @@ SelPlan selective_plan(const SelArgs& a, int cus) {
   q.nseg = 1;
   q.lseg = a.L;
   return q;
+}
+
+int64_t selective_fwd_workspace(int64_t B, int64_t D, int64_t N, int64_t L, bool bf16_in, bool z,
+                                bool aligned) {
+  if (N <= 16 || B * D <= 0 || L <= 0) return 0;
+  SelArgs a{};
+  a.B = B;
+  a.D = D;
+  a.N = N;
+  a.L = L;
+  a.bf16_in = bf16_in;
+  a.vec = aligned && L % 4 == 0;  // (other rows only raise the 8-lane kernel's price)
+  a.z = z ? &a : nullptr;  // (only tested)
+  if (step_path(a)) return 0;
+  const bool groups = bf16_in ? lanes16_path<uint16_t>(a) && groups_pay<uint16_t>(a)
+                              : lanes16_path<float>(a) && groups_pay<float>(a);
+  return groups ? (N + 15) / 16 * B * D * L * (int64_t)sizeof(float) : 0;
 }
 
 int selective_states_fwd(const SelArgs& a, int grp, bool* taken) {

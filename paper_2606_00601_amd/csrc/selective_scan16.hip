@@ -1135,7 +1135,8 @@ double row16_groups_us(const SelArgs& a, int cus) {
 }
 
 // N other than 16 (row16_fits): one group of up to 16 states writes y itself;
-// several write planes of a per-call workspace that a last kernel adds up.
+// several write planes of a workspace (the caller's, or one taken for the call)
+// that a last kernel adds up.
 // At B=2, D=1024, N=64, L=1024 (fp32) the 8-lane kernel, with 256 wavefronts
 // for the GPU's 1024 SIMDs, took 125 us.
 template <typename IN>
@@ -1151,8 +1152,11 @@ int launch_row16_groups(const SelArgs& a, hipStream_t s) {
   if (st != SW_OK) return st;
   SelArgs g = a;
   if (ngrp > 1) {
-    st = workspace_alloc(&g.y, (size_t)ngrp * (size_t)R * (size_t)a.L * sizeof(float), s);
-    if (st != SW_OK) return st;
+    const size_t need = (size_t)ngrp * (size_t)R * (size_t)a.L * sizeof(float);
+    if (a.ws && a.ws_bytes < need)
+      return fail(SW_ERR_INVALID_ARG, "workspace of %zu bytes, %zu needed", a.ws_bytes, need);
+    g.y = a.ws;
+    if (!a.ws && (st = workspace_alloc(&g.y, need, s)) != SW_OK) return st;
     g.Dskip = nullptr;
     g.z = nullptr;
     g.s_out = nullptr;
@@ -1170,7 +1174,7 @@ int launch_row16_groups(const SelArgs& a, hipStream_t s) {
                          static_cast<const IN*>(a.z), a.Dskip, a.y, a.s_out, R, a.D, a.L, nch, a.y_bf16);
       st = check_launch("row16_groups_kernel");
     }
-    workspace_free(g.y, s);
+    if (!a.ws) workspace_free(g.y, s);
   }
   return st;
 }

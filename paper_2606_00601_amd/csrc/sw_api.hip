@@ -233,17 +233,19 @@ int selective_common(SelArgs a) {
   if ((st = check_ptr(a.h_last, 4, "h_last", false, dev)) != SW_OK) return st;
   if ((st = check_ptr(a.ckpt, 4, "ckpt", false, dev)) != SW_OK) return st;
   if ((st = check_ptr(a.s_out, 4, "s_pre", false, dev)) != SW_OK) return st;
+  if ((st = check_ptr(a.ws, 16, "workspace", false, dev)) != SW_OK) return st;
   if (a.ckpt && N > 16)
     return fail(SW_ERR_UNSUPPORTED, "checkpoints need N <= 16 (got %lld)", (long long)N);
   const size_t nck = (size_t)R * (size_t)((L + 7) / 8) * 16;
   Span outs[] = {{a.y, (size_t)nx * ys, "y"}, {a.h_last, (size_t)nh * 4, "h_last"},
-                 {a.ckpt, nck * 4, "ckpt"}, {a.s_out, (size_t)nx * 4, "s_pre"}};
+                 {a.ckpt, nck * 4, "ckpt"}, {a.s_out, (size_t)nx * 4, "s_pre"},
+                 {a.ws, a.ws_bytes, "workspace"}};
   Span ins[] = {{a.x, (size_t)nx * es, "x"},          {a.delta, (size_t)nx * es, "delta"},
                 {a.A, (size_t)(D * N) * 4, "A"},      {a.Bm, (size_t)nbc * es, "Bm"},
                 {a.Cm, (size_t)nbc * es, "Cm"},       {a.Dskip, (size_t)D * 4, "Dskip"},
                 {a.z, (size_t)nx * es, "z"},          {a.delta_bias, (size_t)D * 4, "delta_bias"},
                 {a.h0, (size_t)nh * 4, "h0"}};
-  if ((st = check_spans(outs, 4, ins, 9)) != SW_OK) return st;
+  if ((st = check_spans(outs, 5, ins, 9)) != SW_OK) return st;
   a.vec = L % 4 == 0 && all_aligned16({a.x, a.delta, a.y, a.z, a.s_out});
   return a.blelloch ? selective_blelloch_fwd(a) : selective_fwd(a);
 }
@@ -695,11 +697,13 @@ SW_API int sw_selective_scan_fwd_bf16(const uint16_t* x, const uint16_t* delta, 
       sw::sel_args(x, delta, A, Bm, Cm, Dskip, y, h_last, B, D, N, L, true));
 }
 
-SW_API int sw_selective_scan_fwd_ex(const void* x, const void* delta, const float* A,
+SW_API int sw_selective_scan_fwd_ws(const void* x, const void* delta, const float* A,
                                     const void* Bm, const void* Cm, const float* Dskip,
                                     const void* z, const float* delta_bias, const float* h0,
                                     void* y, float* h_last, int64_t B, int64_t D, int64_t N,
-                                    int64_t L, int in_dtype, int out_dtype, int flags) {
+                                    int64_t L, int in_dtype, int out_dtype, int flags,
+                                    void* workspace, int64_t workspace_bytes) {
+  if (workspace_bytes < 0) return sw::fail(SW_ERR_INVALID_ARG, "negative workspace size");
   if ((in_dtype != SW_DTYPE_F32 && in_dtype != SW_DTYPE_BF16) ||
       (out_dtype != SW_DTYPE_F32 && out_dtype != SW_DTYPE_BF16))
     return sw::fail(SW_ERR_INVALID_ARG, "unknown dtype (in=%d out=%d)", in_dtype, out_dtype);
@@ -712,7 +716,27 @@ SW_API int sw_selective_scan_fwd_ex(const void* x, const void* delta, const floa
   a.h0 = h0;
   a.y_bf16 = out_dtype == SW_DTYPE_BF16;
   a.softplus = (flags & SW_DELTA_SOFTPLUS) != 0;
+  a.ws = workspace;
+  a.ws_bytes = workspace ? (size_t)workspace_bytes : 0;
   return sw::selective_common(a);
+}
+
+SW_API int64_t sw_selective_scan_fwd_workspace(int64_t B, int64_t D, int64_t N, int64_t L,
+                                               int in_dtype, int z, int aligned) {
+  int64_t n;
+  if (B <= 0 || D <= 0 || N < 1 || N > 64 || L <= 0 || !sw::mul_ok(B, D, &n) || !sw::mul_ok(n, L, &n) ||
+      !sw::mul_ok(n, 64, &n))
+    return 0;
+  return sw::selective_fwd_workspace(B, D, N, L, in_dtype == SW_DTYPE_BF16, z != 0, aligned != 0);
+}
+
+SW_API int sw_selective_scan_fwd_ex(const void* x, const void* delta, const float* A,
+                                    const void* Bm, const void* Cm, const float* Dskip,
+                                    const void* z, const float* delta_bias, const float* h0,
+                                    void* y, float* h_last, int64_t B, int64_t D, int64_t N,
+                                    int64_t L, int in_dtype, int out_dtype, int flags) {
+  return sw_selective_scan_fwd_ws(x, delta, A, Bm, Cm, Dskip, z, delta_bias, h0, y, h_last, B, D, N,
+                                  L, in_dtype, out_dtype, flags, nullptr, 0);
 }
 
 SW_API int sw_selective_scan_plan(int64_t B, int64_t D, int64_t N, int64_t L, int in_dtype,

@@ -87,8 +87,16 @@ struct SelArgs {
   float* ckpt = nullptr;  // (B*D, ceil(L/8), 16): states at 8-step boundaries (N <= 16)
   bool ckpt_seg = false;  // a call with checkpoints may cut its rows into segments (N = 16)
   float* s_out = nullptr;  // (B, D, L) fp32: y before the output gate (with the options)
+  // memory for the planes of the state groups (selective_fwd_workspace bytes);
+  // NULL: taken from the stream-ordered pool for the call
+  void* ws = nullptr;
+  size_t ws_bytes = 0;
 };
 int selective_fwd(const SelArgs& a);
+// Bytes of planes a forward of these sizes needs (N > 16; 0: none) if its arrays
+// are 16-byte aligned, or else may need.
+int64_t selective_fwd_workspace(int64_t B, int64_t D, int64_t N, int64_t L, bool bf16_in, bool z,
+                                bool aligned);
 int selective_blelloch_fwd(const SelArgs& a);
 // The kernels a forward call takes: layout 16 (one lane per state), 4 (four
 // lanes per row, four states each) or 8 (the 8-lane kernel of any N, which

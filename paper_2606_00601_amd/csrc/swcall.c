@@ -105,6 +105,10 @@ SW_CALL(sw_selective_scan_fwd_schedule, "PPPPPPPPLLLLII", 14,
 SW_CALL(sw_selective_scan_fwd_ex, "PPPPPPPPPPPLLLLIII", 18,
         sw_selective_scan_fwd_ex(AP(0), AP(1), AP(2), AP(3), AP(4), AP(5), AP(6), AP(7), AP(8), AP(9),
                                  AP(10), AL(11), AL(12), AL(13), AL(14), AI(15), AI(16), AI(17)))
+SW_CALL(sw_selective_scan_fwd_ws, "PPPPPPPPPPPLLLLIIIPL", 20,
+        sw_selective_scan_fwd_ws(AP(0), AP(1), AP(2), AP(3), AP(4), AP(5), AP(6), AP(7), AP(8), AP(9),
+                                 AP(10), AL(11), AL(12), AL(13), AL(14), AI(15), AI(16), AI(17), AP(18),
+                                 AL(19)))
 SW_CALL(sw_selective_scan_fwd_train, "PPPPPPPPPPPPPLLLLIII", 20,
         sw_selective_scan_fwd_train(AP(0), AP(1), AP(2), AP(3), AP(4), AP(5), AP(6), AP(7), AP(8), AP(9),
                                     AP(10), AP(11), AP(12), AL(13), AL(14), AL(15), AL(16), AI(17),
@@ -126,6 +130,15 @@ SW_CALL(sw_selective_scan_bwd_ex, "PPPPPPPPPPPPPPPPPPPPPPLLLLIIIIPL", 32,
                               AP(11), AP(12), AP(13), AP(14), AP(15), AP(16), AP(17), AP(18), AP(19),
                               AP(20), AP(21), AL(22), AL(23), AL(24), AL(25), AI(26), AI(27), AI(28),
                                  AI(29), AP(30), AL(31)))
+
+static PyObject* py_sw_selective_scan_fwd_workspace(PyObject* self, PyObject* const* args,
+                                                    Py_ssize_t nargs) {
+  (void)self;
+  Arg v[7];
+  if (!parse(args, nargs, "LLLLIII", v, "sw_selective_scan_fwd_workspace")) return NULL;
+  return PyLong_FromLongLong(
+      sw_selective_scan_fwd_workspace(AL(0), AL(1), AL(2), AL(3), AI(4), AI(5), AI(6)));
+}
 
 static PyObject* py_sw_selective_scan_bwd_workspace(PyObject* self, PyObject* const* args,
                                                     Py_ssize_t nargs) {
@@ -200,6 +213,8 @@ static PyMethodDef methods[] = {
     FAST(sw_selective_scan_fwd_train),
     FAST(sw_selective_scan_fwd_train_seg),
     FAST(sw_selective_scan_bwd),
+    FAST(sw_selective_scan_fwd_ws),
+    FAST(sw_selective_scan_fwd_workspace),
     FAST(sw_selective_scan_bwd_ex),
     FAST(sw_selective_scan_bwd_workspace),
     FAST(sw_selective_scan_plan),

@@ -3,6 +3,8 @@ one group (N = 10, 14; N = 4, 8 on long
 calls of few rows) writing y itself and several adding up planes of y (the
 last group full or not), whole rows and segments of either form, at aligned
 and ragged lengths, against the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -54,3 +56,63 @@ def test_group_checkpoints(sw):  # noqa: F811
     g0 = sw.selective_scan_bwd(*args, dy, h0=dev(ex["h0"]))
     for k in g0:
         assert torch.equal(g0[k], g1[k]), k
+
+
+def _pool_high(dev, reset):
+    """The most bytes in use of the device's default stream-ordered pool since
+    the last reset (hipMemPoolAttrUsedMemHigh)."""
+    path = next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64.so" in ln)
+    hip, pool, v = ctypes.CDLL(path), ctypes.c_void_p(), ctypes.c_uint64(0)
+    assert hip.hipDeviceGetDefaultMemPool(ctypes.byref(pool), dev) == 0
+    if reset:
+        assert hip.hipMemPoolSetAttribute(pool, 8, ctypes.byref(v)) == 0
+    assert hip.hipMemPoolGetAttribute(pool, 8, ctypes.byref(v)) == 0
+    return v.value
+
+
+@pytest.mark.parametrize("N", [24, 64])
+@pytest.mark.parametrize("train", [False, True])
+def test_planes_come_from_the_callers_allocator(sw, N, train):  # noqa: F811
+    """A forward of several state groups, and the gated backward that runs one
+    without the gate, leave no planes in the library's own pool, which never
+    gives memory back."""
+    B, D, L = 2, 200, 1500
+    planes = (N + 15) // 16 * B * D * L * 4
+    x, z = (torch.randn((B, D, L), device="cuda") for _ in range(2))
+    Bm = torch.randn((B, L, N), device="cuda")
+    A = -torch.rand((D, N), device="cuda")
+    assert sw.lib().sw_selective_scan_fwd_workspace(B, D, N, L, 0, 1, 1) == planes
+    torch.cuda.synchronize()
+    before = _pool_high(0, True)
+    if train:
+        sw.selective_scan_bwd(x, x.abs() * 0.01, A, Bm, Bm, None, x, z=z)
+    else:
+        sw.selective_scan_fwd(x, x.abs() * 0.01, A, Bm, Bm, z=z)
+        assert sw.last_launch().startswith("selective_row16_kernel"), sw.last_launch()
+    torch.cuda.synchronize()
+    assert _pool_high(0, False) - before < planes
+
+
+def test_workspace_of_the_forward(sw):  # noqa: F811
+    """Planes in the caller's workspace give the bits of planes from the pool;
+    one that is too small is refused before anything is enqueued."""
+    B, D, N, L = 1, 37, 40, 900
+    x = torch.randn((B, D, L), device="cuda")
+    dl, Bm = x.abs() * 0.01, torch.randn((B, L, N), device="cuda")
+    A = -torch.rand((D, N), device="cuda")
+    y = [torch.full_like(x, float("nan")) for _ in range(3)]
+    n = sw.lib().sw_selective_scan_fwd_workspace(B, D, N, L, 0, 0, 1)
+    ws = torch.empty((n + 64,), dtype=torch.uint8, device="cuda")
+
+    def call(out, wsp, nbytes):
+        ptrs = [t.data_ptr() for t in (x, dl, A, Bm, Bm)] + [None] * 4 + [out.data_ptr(), None]
+        with sw._on(x.device):
+            return sw.lib().sw_selective_scan_fwd_ws(*ptrs, B, D, N, L, 0, 0, 0, wsp, nbytes)
+
+    assert n == 3 * B * D * L * 4
+    assert call(y[0], ws.data_ptr(), n) == 0 and call(y[1], None, 0) == 0
+    assert torch.equal(y[0], y[1]) and bool(torch.isfinite(y[0]).all())
+    assert call(y[2], ws.data_ptr(), n - 16) == 1  # SW_ERR_INVALID_ARG
+    assert call(y[2], ws.data_ptr() + 4, n) == 1  # not 16-byte aligned
+    assert call(y[2], y[2].data_ptr(), n) == 1  # overlaps y
+    assert bool(torch.isnan(y[2]).all())
