@@ -171,10 +171,11 @@ __global__ __launch_bounds__(BL_THREADS) void affine_blelloch_kernel(
 }
 
 template <typename T>
-int launch_blelloch(const T* a, const T* bx, const T* h0, T* h, int64_t R, int64_t L, bool vec) {
+int launch_blelloch(const T* a, const T* bx, const T* h0, T* h, int64_t R, int64_t L) {
   hipStream_t s = current_stream();
   const int64_t grid = R < ((int64_t)1 << 30) ? R : ((int64_t)1 << 30);
-  if (vec)
+  // 16-byte accesses: rows of whole vectors, arrays on the 16-byte grid
+  if (L % 4 == 0 && (((uintptr_t)a | (uintptr_t)bx | (uintptr_t)h) & 15) == 0)
     hipLaunchKernelGGL((affine_blelloch_kernel<T, true>), dim3((unsigned)grid), dim3(BL_THREADS),
                        0, s, a, bx, h0, h, R, L);
   else
@@ -186,13 +187,13 @@ int launch_blelloch(const T* a, const T* bx, const T* h0, T* h, int64_t R, int64
 }  // namespace
 
 int affine_blelloch_f32(const float* a, const float* bx, const float* h0, float* h, int64_t R,
-                        int64_t L, bool vec) {
-  return launch_blelloch<float>(a, bx, h0, h, R, L, vec);
+                        int64_t L) {
+  return launch_blelloch<float>(a, bx, h0, h, R, L);
 }
 
 int affine_blelloch_u32(const uint32_t* a, const uint32_t* bx, const uint32_t* h0, uint32_t* h,
-                        int64_t R, int64_t L, bool vec) {
-  return launch_blelloch<uint32_t>(a, bx, h0, h, R, L, vec);
+                        int64_t R, int64_t L) {
+  return launch_blelloch<uint32_t>(a, bx, h0, h, R, L);
 }
 
 }  // namespace sw

@@ -480,29 +480,28 @@ int launch_affine(const AffIO<T>& io, int64_t R, int64_t L, bool fixed = false) 
 }  // namespace
 
 int affine_scan_f32(const float* a, const float* bx, const float* h0, float* h, int64_t R,
-                    int64_t L, bool /*vec*/) {
+                    int64_t L) {
   return launch_affine<float, false>(AffIO<float>{a, bx, nullptr, nullptr, h0, h, nullptr}, R, L);
 }
 
 int affine_scan_f32_noalloc(const float* a, const float* bx, const float* h0, float* h,
-                            int64_t R, int64_t L, bool /*vec*/) {
+                            int64_t R, int64_t L) {
   return launch_affine<float, false>(AffIO<float>{a, bx, nullptr, nullptr, h0, h, nullptr}, R, L, true);
 }
 
 int affine_scan_u32(const uint32_t* a, const uint32_t* bx, const uint32_t* h0, uint32_t* h,
-                    int64_t R, int64_t L, bool /*vec*/) {
+                    int64_t R, int64_t L) {
   return launch_affine<uint32_t, false>(
       AffIO<uint32_t>{a, bx, nullptr, nullptr, h0, h, nullptr}, R, L);
 }
 
 int affine_scan_io_f32(const float* a, const float* b, const float* x, const float* c,
-                       const float* h0, float* y, float* h_last, int64_t R, int64_t L, bool /*vec*/) {
+                       const float* h0, float* y, float* h_last, int64_t R, int64_t L) {
   return launch_affine<float, true>(AffIO<float>{a, b, x, c, h0, y, h_last}, R, L);
 }
 
 int affine_scan_io_u32(const uint32_t* a, const uint32_t* b, const uint32_t* x, const uint32_t* c,
-                       const uint32_t* h0, uint32_t* y, uint32_t* h_last, int64_t R, int64_t L,
-                       bool /*vec*/) {
+                       const uint32_t* h0, uint32_t* y, uint32_t* h_last, int64_t R, int64_t L) {
   return launch_affine<uint32_t, true>(AffIO<uint32_t>{a, b, x, c, h0, y, h_last}, R, L);
 }
 

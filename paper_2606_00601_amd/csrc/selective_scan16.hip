@@ -823,13 +823,13 @@ __global__ __launch_bounds__(256) void row16_groups_kernel(
 
 }  // namespace
 
-// The fold of the correction form, shared with the quad layout
-// (selective_scan_quad.hip), which keeps its records in the same places.
+// The fold of the correction form over ngrp planes of R rows, shared with the
+// quad layout (selective_scan_quad.hip), which keeps its records in the same places.
 void launch_fold_corr(float* y, float* h_last, int64_t R, int64_t L, int64_t nseg, int64_t Lseg,
-                      hipStream_t s) {
-  const int64_t lanes = R * R16_N;
+                      int N, int ngrp, hipStream_t s) {
+  const int64_t lanes = R * ngrp * R16_N;
   hipLaunchKernelGGL(row16_fold_corr_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0,
-                     s, y, h_last, R, L, nseg, Lseg, R16_N, R);
+                     s, y, h_last, R * ngrp, L, nseg, Lseg, N, R);
 }
 
 template <typename IN>
@@ -1065,9 +1065,7 @@ void launch_row16_corr(const SelArgs& a, int64_t ndb, uint32_t flags, int64_t ns
                      static_cast<const IN*>(a.Bm), static_cast<const IN*>(a.Cm), a.Dskip,
                      static_cast<const IN*>(a.z), a.delta_bias, a.h0, a.y, a.h_last, a.D, a.L,
                      ndb, flags, nullptr, (int64_t)0, a.s_out, nseg, Lseg, (int)a.N, ngrp, R * a.L);
-  const int64_t lanes = R * ngrp * R16_N;
-  hipLaunchKernelGGL(row16_fold_corr_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0,
-                     s, static_cast<float*>(a.y), a.h_last, R * ngrp, a.L, nseg, Lseg, (int)a.N, R);
+  launch_fold_corr(static_cast<float*>(a.y), a.h_last, R, a.L, nseg, Lseg, (int)a.N, ngrp, s);
   hipLaunchKernelGGL((selective_row16_kernel<IN, OPT, false, R16_SEG_CORR, KIND>),
                      dim3((unsigned)(rblocks * (nseg - 1))), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,

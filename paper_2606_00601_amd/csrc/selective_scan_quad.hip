@@ -39,7 +39,7 @@ namespace sw {
 
 // The fold of the correction form (selective_scan16.hip).
 void launch_fold_corr(float* y, float* h_last, int64_t R, int64_t L, int64_t nseg, int64_t Lseg,
-                      hipStream_t s);
+                      int N, int ngrp, hipStream_t s);
 
 namespace {
 
@@ -420,7 +420,7 @@ void launch_quad_t(const SelArgs& a, uint32_t flags, int64_t nseg, int64_t Lseg,
                      a.delta_bias, a.h0, static_cast<float*>(a.y), a.h_last, (int)a.D, (int)a.L,
                      (int)nblk, flags, a.s_out, (int)nseg, (int)Lseg);
   if (nseg < 2) return;
-  launch_fold_corr(static_cast<float*>(a.y), a.h_last, a.B * a.D, a.L, nseg, Lseg, s);
+  launch_fold_corr(static_cast<float*>(a.y), a.h_last, a.B * a.D, a.L, nseg, Lseg, Q_N, 1, s);
   hipLaunchKernelGGL((selective_quad_kernel<IN, OPT, Q_CORR>),
                      dim3((unsigned)(blocks * (nseg - 1))), dim3(256), 0, s,
                      static_cast<const IN*>(a.x), static_cast<const IN*>(a.delta), a.A,

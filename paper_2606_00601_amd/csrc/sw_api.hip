@@ -15,20 +15,19 @@
 namespace sw {
 
 int affine_scan_f32(const float* a, const float* bx, const float* h0, float* h, int64_t R,
-                    int64_t L, bool vec);
+                    int64_t L);
 int affine_scan_u32(const uint32_t* a, const uint32_t* bx, const uint32_t* h0, uint32_t* h,
-                    int64_t R, int64_t L, bool vec);
+                    int64_t R, int64_t L);
 int affine_scan_f32_noalloc(const float* a, const float* bx, const float* h0, float* h,
-                            int64_t R, int64_t L, bool vec);
+                            int64_t R, int64_t L);
 int affine_blelloch_f32(const float* a, const float* bx, const float* h0, float* h, int64_t R,
-                        int64_t L, bool vec);
+                        int64_t L);
 int affine_blelloch_u32(const uint32_t* a, const uint32_t* bx, const uint32_t* h0, uint32_t* h,
-                        int64_t R, int64_t L, bool vec);
+                        int64_t R, int64_t L);
 int affine_scan_io_f32(const float* a, const float* b, const float* x, const float* c,
-                       const float* h0, float* y, float* h_last, int64_t R, int64_t L, bool vec);
+                       const float* h0, float* y, float* h_last, int64_t R, int64_t L);
 int affine_scan_io_u32(const uint32_t* a, const uint32_t* b, const uint32_t* x, const uint32_t* c,
-                       const uint32_t* h0, uint32_t* y, uint32_t* h_last, int64_t R, int64_t L,
-                       bool vec);
+                       const uint32_t* h0, uint32_t* y, uint32_t* h_last, int64_t R, int64_t L);
 
 namespace {
 thread_local hipStream_t tls_stream = nullptr;
@@ -122,7 +121,7 @@ bool all_aligned16(std::initializer_list<const void*> ps) {
 
 template <typename T>
 int affine_common(const T* a, const T* bx, const T* h0, T* h_out, int64_t B, int64_t D,
-                  int64_t L, int (*run)(const T*, const T*, const T*, T*, int64_t, int64_t, bool)) {
+                  int64_t L, int (*run)(const T*, const T*, const T*, T*, int64_t, int64_t)) {
   if (B < 0 || D < 0 || L < 0)
     return fail(SW_ERR_INVALID_ARG, "negative size (B=%lld D=%lld L=%lld)", (long long)B,
                 (long long)D, (long long)L);
@@ -140,8 +139,7 @@ int affine_common(const T* a, const T* bx, const T* h0, T* h_out, int64_t B, int
   Span outs[] = {{h_out, big, "h_out"}};
   Span ins[] = {{a, big, "a"}, {bx, big, "bx"}, {h0, small, "h0"}};
   if ((st = check_spans(outs, 1, ins, 3)) != SW_OK) return st;
-  const bool vec = L % 4 == 0 && all_aligned16({a, bx, h_out});
-  return run(a, bx, h0, h_out, R, L, vec);
+  return run(a, bx, h0, h_out, R, L);
 }
 
 // Validation of the output-projection form (Eq. (3)-(4)); see include/scanweaver.h.
@@ -149,7 +147,7 @@ template <typename T>
 int affine_proj_common(const T* a, const T* b, const T* x, const T* c, const T* h0, T* y,
                        T* h_last, int64_t B, int64_t D, int64_t L,
                        int (*run)(const T*, const T*, const T*, const T*, const T*, T*, T*,
-                                  int64_t, int64_t, bool)) {
+                                  int64_t, int64_t)) {
   if (B < 0 || D < 0 || L < 0)
     return fail(SW_ERR_INVALID_ARG, "negative size (B=%lld D=%lld L=%lld)", (long long)B,
                 (long long)D, (long long)L);
@@ -181,8 +179,7 @@ int affine_proj_common(const T* a, const T* b, const T* x, const T* c, const T* 
   Span outs[] = {{y, big, "y"}, {h_last, small, "h_last"}};
   Span ins[] = {{a, big, "a"}, {b, big, "b"}, {x, big, "x"}, {c, big, "c"}, {h0, small, "h0"}};
   if ((st = check_spans(outs, 2, ins, 5)) != SW_OK) return st;
-  const bool vec = L % 4 == 0 && all_aligned16({a, b, x, c, y});
-  return run(a, b, x, c, h0, y, h_last, R, L, vec);
+  return run(a, b, x, c, h0, y, h_last, R, L);
 }
 
 // Validation shared by the fused entry points; see include/scanweaver.h.
