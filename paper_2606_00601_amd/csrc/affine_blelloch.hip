@@ -173,7 +173,7 @@ __global__ __launch_bounds__(BL_THREADS) void affine_blelloch_kernel(
 template <typename T>
 int launch_blelloch(const T* a, const T* bx, const T* h0, T* h, int64_t R, int64_t L) {
   hipStream_t s = current_stream();
-  const int64_t grid = R < ((int64_t)1 << 30) ? R : ((int64_t)1 << 30);
+  const int64_t grid = R < SW_MAX_WGS ? R : SW_MAX_WGS;  // (the workgroups stride over the rows)
   // 16-byte accesses: rows of whole vectors, arrays on the 16-byte grid
   if (L % 4 == 0 && (((uintptr_t)a | (uintptr_t)bx | (uintptr_t)h) & 15) == 0)
     hipLaunchKernelGGL((affine_blelloch_kernel<T, true>), dim3((unsigned)grid), dim3(BL_THREADS),

@@ -148,7 +148,7 @@ int selective_blelloch_fwd(const SelArgs& a) {
   if (a.N > SB_MAXN) return fail(SW_ERR_UNSUPPORTED, "N=%lld above %d", (long long)a.N, SB_MAXN);
   if (a.z || a.delta_bias || a.h0 || a.softplus || a.y_bf16)
     return fail(SW_ERR_UNSUPPORTED, "the Blelloch schedule runs the plain form only");
-  const int64_t grid = R < ((int64_t)1 << 30) ? R : ((int64_t)1 << 30);
+  const int64_t grid = R < SW_MAX_WGS ? R : SW_MAX_WGS;  // (the workgroups stride over the rows)
   if (a.bf16_in)
     hipLaunchKernelGGL((selective_blelloch_kernel<uint16_t>), dim3((unsigned)grid),
                        dim3(SB_THREADS), 0, s, static_cast<const uint16_t*>(a.x),

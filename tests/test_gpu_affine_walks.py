@@ -75,3 +75,16 @@ def test_more_rows_than_a_grid_holds(sw):  # noqa: F811
     h0 = bx.view(1, R)
     y, hl = sw.affine_scan_proj_i32(a, bx, None, a, h0)
     assert torch.equal(hl, 4 * h0) and torch.equal(y, 12 * bx)
+
+
+def test_more_rows_than_a_grid_holds_blelloch(sw):  # noqa: F811
+    """The paper's schedule, a workgroup per row, on more than 2^24 rows."""
+    R = 2 ** 24 + 5
+    bx = torch.arange(R, dtype=torch.int32, device="cuda").view(1, R, 1)
+    h = sw.affine_scan_schedule_i32(torch.full_like(bx, 3), bx, bx.view(1, R), schedule="blelloch")
+    assert torch.equal(h, 4 * bx)
+    x = bx.float()
+    one = torch.ones((1, 1, 1), device="cuda")
+    y, hl = sw.selective_scan_fwd_schedule(x, torch.ones_like(x), -torch.ones((R, 1), device="cuda"),
+                                           one, one, schedule="blelloch")
+    assert torch.equal(y, x) and torch.equal(hl, x)
