@@ -338,10 +338,11 @@ int sw_selective_scan_fwd_train(const void* x, const void* delta, const float* A
 
 /*
  * sw_selective_scan_fwd_train that may cut each row into segments where its
- * rows leave the GPU idle (N = 16; the records form of sw_selective_scan_fwd,
- * whose last launch walks every segment from its composed state and writes
- * its checkpoints): y, s_pre, h_last and ckpt agree with those of
- * sw_selective_scan_fwd_train within fp32 rounding, not bit for bit.
+ * rows leave the GPU idle (N = 16 and the even N below 16 that take the
+ * 16-lane kernels; the records form of sw_selective_scan_fwd, whose last launch
+ * walks every segment from its composed state and writes its checkpoints): y,
+ * s_pre, h_last and ckpt agree with those of sw_selective_scan_fwd_train within
+ * fp32 rounding, not bit for bit.
  */
 int sw_selective_scan_fwd_train_seg(const void* x, const void* delta, const float* A,
                                     const void* Bm, const void* Cm, const float* Dskip,

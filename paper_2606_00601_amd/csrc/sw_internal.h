@@ -43,12 +43,11 @@ int zero_words(uint32_t* p, size_t words, hipStream_t s);
 // workgroups and a ticket counter.  It is zeroed once when (re)allocated and
 // never again: each launch tags the carry words it writes with a fresh
 // epoch, so words left by earlier launches never match, and the ticket
-// counter only grows (a launch knows the value it starts from).  The session
-// holds a lock from reserve() until it is destroyed, so the order in which
-// launches are enqueued on the stream is the order in which epochs and ticket
-// ranges were handed out.
-// Counters of the launches that hand out the segments of each row by a ticket
-// of its own: each leaves the counters it used at zero.
+// counter only grows (a launch knows the value it starts from).  Launches that
+// hand out each row's segments by a ticket of its own have a counter per row
+// beside it, and leave those they used at zero.  The session holds a lock from
+// reserve() until it is destroyed, so the order in which launches are enqueued
+// on the stream is the order in which epochs and ticket ranges were handed out.
 constexpr int SW_ROW_TICKETS = 512, SW_TICKET_STRIDE = 16;  // 64 bytes apart
 struct ScratchSession {
   ScratchSession();
@@ -85,7 +84,7 @@ struct SelArgs {
   bool bf16_in, y_bf16, softplus, vec;
   bool blelloch = false;  // the paper's schedule (plain form only)
   float* ckpt = nullptr;  // (B*D, ceil(L/8), 16): states at 8-step boundaries (N <= 16)
-  bool ckpt_seg = false;  // a call with checkpoints may cut its rows into segments (N = 16)
+  bool ckpt_seg = false;  // a call with checkpoints may cut its rows into segments (16-lane kernels)
   float* s_out = nullptr;  // (B, D, L) fp32: y before the output gate (with the options)
   // memory for the planes of the state groups (selective_fwd_workspace bytes);
   // NULL: taken from the stream-ordered pool for the call
@@ -99,8 +98,9 @@ int64_t selective_fwd_workspace(int64_t B, int64_t D, int64_t N, int64_t L, bool
                                 bool aligned);
 int selective_blelloch_fwd(const SelArgs& a);
 // The kernels a forward call takes: layout 16 (one lane per state), 4 (four
-// lanes per row, four states each) or 8 (the 8-lane kernel of any N, which
-// chains its own sequence chunks); nseg segments of lseg steps (the last
+// lanes per row, four states each) or 8 (the kernels of any N: the 8-lane one,
+// the one for at most 16 steps, the 16-lane ones on groups of states, whose
+// segments are not planned here); nseg segments of lseg steps (the last
 // the rest; 1 and L for whole rows); form 0 whole rows, 1 records, 2
 // correction.  Layout 0, nseg 0: nothing to launch (B*D or L zero).
 struct SelPlan {
