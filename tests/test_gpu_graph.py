@@ -4,12 +4,11 @@ replays, gives the eager result bit for bit.
 
 The N = 16 forward takes no scratch memory and allocates nothing, so it can be
 captured; the calls that use the per-stream scratch (the bare scan's
-look-back, the persistent kernel of N != 16) or allocate (the backward) are
+segments, the persistent kernel of N != 16) or allocate (the backward) are
 not graph-replay safe, and the library refuses them while the stream is
 capturing (checked here).  The bare scan's entry point that allocates
-nothing keeps its look-back words in a static array that every call clears
-with a fill kernel and starts from the same epoch and ticket, so its
-look-back path can be captured too (checked here).
+nothing keeps its tickets and records in a static array that every call clears
+with a fill kernel, so its segments can be captured too (checked here).
 """
 import sys
 
@@ -87,7 +86,7 @@ def test_forward_graph_replays_match_eager(sw, options):
 
 def test_capture_refuses_calls_that_need_scratch_or_workspace(sw):
     """While the stream is capturing, the calls that use the per-stream scratch
-    (the bare scan's look-back over chunks of a few long rows, the persistent
+    (the bare scan's segments of a few long rows, the persistent
     kernel of N != 16) or allocate a workspace (the backward) raise instead of
     recording a graph whose replay would write nothing; a legal call captured
     beside them replays correctly, and the refused calls still work eagerly."""
@@ -95,10 +94,10 @@ def test_capture_refuses_calls_that_need_scratch_or_workspace(sw):
     rng = np.random.Generator(np.random.PCG64(779))
     dev = "cuda"
     # bare scan (int32 ring: exact, so any carry order gives the same bits),
-    # 4 rows of 8192 steps: 4 chunks per row, chained by look-back
-    ai = torch.from_numpy(rng.integers(-2**31, 2**31, (1, 4, 8192), dtype=np.int64)
+    # 4 rows of 16384 steps: 8 chunks per row, a segment each
+    ai = torch.from_numpy(rng.integers(-2**31, 2**31, (1, 4, 16384), dtype=np.int64)
                           .astype(np.int32)).to(dev)
-    bi = torch.from_numpy(rng.integers(-2**31, 2**31, (1, 4, 8192), dtype=np.int64)
+    bi = torch.from_numpy(rng.integers(-2**31, 2**31, (1, 4, 16384), dtype=np.int64)
                           .astype(np.int32)).to(dev)
     # fused forward with N = 8 (persistent kernel with a ticket counter)
     B, D, L = 1, 16, 64
@@ -112,7 +111,7 @@ def test_capture_refuses_calls_that_need_scratch_or_workspace(sw):
     B16, C16, Dk, dy = f32(B, L, 16), f32(B, L, 16), f32(D), f32(B, D, L)
 
     refused = {
-        "bare scan with look-back": lambda: sw.affine_scan_i32(ai, bi),
+        "bare scan in segments": lambda: sw.affine_scan_i32(ai, bi),
         "forward N=8": lambda: sw.selective_scan_fwd(x, dl, A8, B8, C8, Dk),
         "backward": lambda: sw.selective_scan_bwd(x, dl, A16, B16, C16, Dk, dy),
     }
@@ -157,13 +156,13 @@ def test_capture_refuses_calls_that_need_scratch_or_workspace(sw):
 
 def test_noalloc_scan_graph_replays_match_eager(sw):
     """The bare scan through the entry point that allocates nothing, on its
-    look-back path (three rows of 40 chunks: carries and tickets in the
+    segments (three rows of 40 chunks: records and tickets in the
     library's static array, cleared by a fill kernel at every call), captured
     into a HIP graph: every replay, with eager calls of both bare-scan entry
     points between the replays, gives the eager result bit for bit.  The
     inputs keep every partial composition an integer below 2^24 (a in {0, 1},
     small integer bx), exact in fp32 in any association order, so the
-    look-back's order cannot change a bit."""
+    cuts cannot change a bit."""
     B, D, L = 1, 3, 40 * 2048 - 5
     _say("case graph replay noalloc", B, D, L)
     g_ = np.random.default_rng(780)

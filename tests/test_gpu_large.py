@@ -33,8 +33,8 @@ def sw():
 
 def test_affine_i32_single_row_past_2_31_steps(sw):
     """One row of 2^31 + 37 steps with a = 1, bx = 1 and h0 = 5: the states
-    are h_t = t + 6 modulo 2^32, whatever the schedule (every chunk carry
-    crosses workgroups by look-back; t passes 2^31)."""
+    are h_t = t + 6 modulo 2^32, whatever the schedule (the segments' totals
+    cross workgroups; t passes 2^31)."""
     L = (1 << 31) + 37
     _say("case affine i32 L =", L)
     a = torch.ones((1, 1, L), dtype=torch.int32, device="cuda")

@@ -81,8 +81,8 @@ def test_affine_i32_ragged_and_multichunk_bitexact(sw, L):
 
 
 def test_affine_i32_long_single_row_repeatable(sw):
-    """One long row: every chunk carry crosses workgroups by look-back.  The
-    ring is exact, so any lost or misordered carry shows as a bit difference;
+    """One long row in segments, whose totals cross workgroups.  The
+    ring is exact, so any lost or misordered total shows as a bit difference;
     20 repeats must agree bit for bit."""
     _say("case affine i32 long row repeat")
     inp = wl.affine_inputs_i32(1, 1, 1 << 21, 77, "odd")
@@ -103,9 +103,8 @@ def test_affine_f32_ragged(sw, B, D, L):
     assert_gate(st, f"affine f32 {B}x{D}x{L}")
 
 
-# Shapes with at least 2048 rows and rows longer than one 2048-step chunk run
-# the row-per-workgroup kernel (carry kept on chip); fewer rows run the
-# chunk-parallel look-back kernel.  L % 4 == 0 takes the 16-byte path.
+# At least 2048 rows, longer than one 2048-step chunk: a workgroup walks whole
+# rows (carry kept on chip), where few long rows are cut into segments.
 @pytest.mark.parametrize("L", [2 * 2048 + 4, 2 * 2048 + 37, 3 * 2048])
 def test_affine_i32_many_rows_bitexact(sw, L):
     _say("case affine i32 many rows L", L)
@@ -248,8 +247,10 @@ def test_selective_chained_chunks_bitexact(sw, monkeypatch, dtype):
     must be bit-identical, and within the oracle gate."""
     _say("case selective chained chunks", dtype)
     inp = wl.selective_inputs(2, 21, 16, 3001, 6060, dtype)
+    monkeypatch.setenv("SW_SS_LAYOUT", "8")
     monkeypatch.setenv("SW_SS_TASKS_PER_WAVE", "1")
     y1, h1 = _run_selective(sw, inp, dtype)
+    assert "selective_fwd_kernel" in sw.last_launch(), sw.last_launch()
     monkeypatch.setenv("SW_SS_TASKS_PER_WAVE", "16")  # 16 chunks of 192 steps per row
     y2, h2 = _run_selective(sw, inp, dtype)
     assert torch.equal(y1, y2) and torch.equal(h1, h2)
@@ -378,7 +379,8 @@ def _y_gate(yt, o, y_bf16, what, rows=None):
         assert_gate(fp_gate(yg, o["y"], o["y_mag"], o["y_sens"]), what)
 
 
-# (B, D, N, L): N = 16 with L % 8 == 0 takes the 16-lane kernel; the others the 8-lane one
+# (B, D, N, L): N = 16 takes the 16-lane kernel, on whole vectors and on ragged rows; N = 5
+# the 8-lane one
 _EX_SHAPES = [(2, 37, 16, 520), (1, 20, 16, 133), (2, 9, 5, 96)]
 _EX_OPTS = [("h0",), ("bias", "softplus"), ("softplus",), ("z",), ("ybf16",),
             ("h0", "bias", "softplus", "z", "ybf16")]
@@ -398,6 +400,25 @@ def test_selective_mamba_options(sw, shape, dtype, opts):
     _y_gate(y, o, y_bf16, f"y {dtype} {shape} {opts}")
     assert_gate(fp_gate(hl.cpu().numpy(), o["h_last"], o["h_mag"], o["h_sens"]),
                 f"h_last {dtype} {shape} {opts}")
+
+
+@pytest.mark.parametrize("shape", _EX_SHAPES + [(1, 33, 3, 37), (1, 40, 12, 64), (1, 40, 17, 33),
+                                               (2, 9, 32, 129), (3, 31, 64, 100), (1, 6, 40, 128)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("opts", [(), _EX_OPTS[-1]])
+def test_selective_8_lane_kernel(sw, monkeypatch, shape, dtype, opts):
+    """The kernel of any N with each count of states per lane, also on calls that
+    the 16-lane kernels take."""
+    monkeypatch.setenv("SW_SS_LAYOUT", "8")
+    B, D, N, L = shape
+    _say("case selective 8 lanes", dtype, shape, opts)
+    inp, ex = _ex_inputs(B, D, N, L, 7100 + B + D + N + L, dtype, opts)
+    y, hl = _run_ex(sw, inp, ex, dtype, "softplus" in opts, "ybf16" in opts)
+    assert "selective_fwd_kernel" in sw.last_launch(), sw.last_launch()
+    o = _ex_oracle(inp, ex, "softplus" in opts)
+    _y_gate(y, o, "ybf16" in opts, f"8 lanes y {dtype} {shape} {opts}")
+    assert_gate(fp_gate(hl.cpu().numpy(), o["h_last"], o["h_mag"], o["h_sens"]),
+                f"8 lanes h_last {dtype} {shape} {opts}")
 
 
 @pytest.mark.parametrize("shape", _EX_SHAPES)
@@ -747,8 +768,8 @@ def _proj_inputs(B, D, L, seed, dtype="f32"):
     return a, b, x, c, h0
 
 
-# (B, D, L): element path (ragged L), one chunk, look-back chunks, and >= 2048
-# rows longer than a chunk (the row-per-workgroup kernel), vector and ragged
+# (B, D, L): a wavefront per row (ragged L), one chunk, whole rows of three chunks,
+# segments, and >= 2048 rows longer than a chunk, vector and ragged
 _PROJ_SHAPES = [(2, 5, 37), (3, 7, 1024), (1, 3, 5003), (1, 2, 20480), (2, 1100, 4100),
                 (1, 2100, 2049)]
 _PROJ_OPTS = [("x", "c", "h0"), ("c",), ("x",), ()]

@@ -1,8 +1,8 @@
-"""Concurrency: the look-back scratch (ticket counter and carry words) is kept
+"""Concurrency: the scratch (tickets, records and carry words) is kept
 per (device, stream), and the stream setting is per host thread.  Calls on two
 streams, interleaved without synchronisation, and calls from two host threads
 each on its own stream, must give the oracle's results bit for bit (int32
-ring, multi-chunk rows whose carries cross workgroups by look-back; fused scan
+ring, rows cut into segments whose totals cross workgroups; fused scan
 with its sequence chunks chained through carry words)."""
 import sys
 import threading

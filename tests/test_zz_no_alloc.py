@@ -1,12 +1,12 @@
 """The entry point that allocates nothing, sw_affine_scan_noalloc, against the
 bare scan it varies, sw_affine_scan, through the C ABI.
 
-Both run the same look-back schedule; the only difference is where the
-tickets and chunk carries live (a static array cleared by the call, against
+Both run the same schedule; the only difference is where the
+tickets and the segments' records live (a static array cleared by the call, against
 the per-stream scratch).  Two calls in a row, the second smaller, must match
 sw_affine_scan to the fp32 gate (and the fp64 oracle); on inputs whose every
 composition is exact in fp32 (a in {0, 1}, small integer bx) the two must
-agree bit for bit, which shows every carry crossed the static scratch
+agree bit for bit, which shows every record crossed the static scratch
 intact.  The largest call the array admits runs; one chunk more is refused
 before anything is enqueued.
 """
@@ -22,7 +22,7 @@ from gate import assert_gate, fp_gate
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-CH = 2048          # steps per look-back chunk
+CH = 2048          # steps per chunk
 MAX_CHUNKS = 65536  # SW_NOALLOC_MAX_CHUNKS
 
 
@@ -71,7 +71,7 @@ def _exact_inputs(B, D, L, seed, bmax):
 
 
 def test_two_calls_second_smaller_against_sw_affine_scan(sw):
-    # 2 x 3 rows of 147 chunks, then 1 x 2 rows of 49: both take the look-back kernel
+    # 2 x 3 rows of 147 chunks, then 1 x 2 rows of 49: both are cut into segments
     for (B, D, L) in [(2, 3, 300_007), (1, 2, 100_001)]:
         _say("case noalloc fp32", B, D, L)
         inp = wl.affine_inputs(B, D, L, 7000 + L, with_h0=True)
@@ -98,7 +98,7 @@ def test_two_calls_second_smaller_bit_exact(sw):
 
 @pytest.mark.parametrize("B,D,L", [(1, 5, 2048), (1, 1, 1), (2, 1100, 4100)])
 def test_calls_without_scratch(sw, B, D, L):
-    # one chunk per row, and enough rows for one workgroup each: no look-back
+    # one chunk per row, and enough rows for one workgroup each: no segments
     _say("case noalloc no scratch", B, D, L)
     inp = wl.affine_inputs(B, D, L, 9000 + L, with_h0=False)
     got, ref = _both(sw, torch.from_numpy(inp["a"]).cuda(), torch.from_numpy(inp["bx"]).cuda())
