@@ -642,6 +642,7 @@ template <typename IN>
 int launch_row16_groups(const SelArgs& a, hipStream_t s);
 template <typename IN>
 double row16_groups_us(const SelArgs& a, int cus);
+double row16_rows_us(int64_t wgs, int64_t L, int cus);
 template <typename IN>
 int launch_row16_states(const SelArgs& a, int grp, hipStream_t s);
 template <typename IN>
@@ -690,19 +691,28 @@ constexpr int64_t GROUPS_MAX_BYTES = (int64_t)1 << 30;
 
 // Whether a call that lanes16_path admits takes the 16-lane kernels rather
 // than the 8-lane one.  Up to 16 states always: us per call, 8-lane / 16-lane,
-// B=1 D=1000 N=12 L=1000 57 / 23, B=8 D=1536 N=12 L=2048 184 / 124 (fp32).
-// Above, both are priced.  The groups: their walk on whole rows (the per-step
-// times of the 16-lane plan), the traffic of the planes at the rate of a copy,
-// and at least 35 us, the host's time for the planes' workspace and the
-// launches.  The 8-lane kernel: its measured time per step with w wavefronts
-// on a compute unit, 6 (N <= 32) or 3 (by LDS) of them at a time, 1.15 times
-// that where N is padded.  Measured: B=2 D=1024 N=64 L=1024 128 / 70, B=16
-// D=2560 N=48 L=200 373 / 219, B=1 D=768 N=24 L=500 48 / 43, but B=2 D=512 N=48
-// L=100 29 / 35, B=1 D=256 N=32 L=64 14 / 35, B=8 D=2048 N=32 L=1024 180 / 224.
+// B=1 D=1000 N=12 L=1000 58 / 22, B=8 D=1536 N=12 L=2048 179 / 118 (fp32).
+// Above, both are priced, on whole tiles of 32 steps.  The groups: their walk on
+// whole rows (where rows are few enough for segments the groups win by far
+// without them), in bf16 a tile more to fill and drain the wider super-tile, the
+// traffic of the planes near the rate of a copy, and at least 14 us, the host's
+// time for the launches, or 35 where the planes' memory has to come from the
+// pool.  The 8-lane kernel: three quarters of a tile to start, and its measured
+// time per step with w wavefronts on a compute unit, 6 (N <= 32) or 3 (by LDS)
+// of them at a time, 1.2 times that where N is padded.  bf16 rows of less than
+// a tile leave a super-tile nearly empty (B=16 D=5120 N=64 L=26 182 / 250) and
+// stay with the 8-lane kernel.  The constants are fits to 298 timed calls (B = 1
+// to 16, D = 200 to 5120, N = 18 to 64, L = 20 to 16384): over 250 others the
+// choice is 6% from the faster kernel on average (27% without a start term and
+// with the pool's 35 us for every call), always on the 8-lane side.  Measured:
+// B=2 D=1024 N=64 L=1024 125 / 58, B=16 D=2560 N=48 L=200 364 / 191, B=1 D=768
+// N=24 L=250 26 / 14, B=2 D=512 N=48 L=100 28 / 14, B=4 D=1536 N=32 L=1024
+// 84 / 77, but B=1 D=256 N=32 L=64 9.5 / 13.8, N=64 11.4 / 13.3, B=8 D=2048 N=32
+// L=1024 166 / 185, B=8 D=5120 N=32 L=160 94 / 105.
 // Up to 8 states the 8-lane kernel has one per lane and half the lanes of a
 // group idle: the groups take long calls on few rows, where their segments
-// win: B=1 D=768 N=4 L=3000 116 / 40, B=1 D=256 N=4 L=16000 584 / 72, but B=2
-// D=1536 N=8 L=2000 71 / 69.
+// win: B=1 D=768 N=4 L=3000 114 / 36, B=1 D=256 N=4 L=16000 585 / 68, but B=2
+// D=1536 N=8 L=2000 69 / 66.
 template <typename IN>
 bool groups_pay(const SelArgs& a) {
   int cus = 0;
@@ -715,20 +725,21 @@ bool groups_pay(const SelArgs& a) {
   if (a.N <= 16) return true;
   const int64_t R = a.B * a.D, ngrp = (a.N + 15) / 16;
   if (R > GROUPS_MAX_BYTES / 4 / ngrp / a.L) return false;
-  const int64_t per = (a.B * ((a.D + 15) / 16) * ngrp + cus - 1) / cus;
-  const double rest[3] = {0.0, 28.8, 42.3};
-  const double walk = (double)a.L * ((double)(per / 3) * 57.1 + rest[per % 3]) * 1e-3;
+  if (a.bf16_in && a.L < 32) return false;
+  const int64_t T = (a.L + 31) / 32 * 32;
+  const double walk = row16_rows_us(a.B * ((a.D + 15) / 16) * ngrp, T + (a.bf16_in ? 32 : 0), cus);
   const int passes = (int)(2 * ngrp + 1) + (a.z ? 2 : 0);
-  const double planes = (double)R * (double)a.L * 4.0 * passes / 5.0e6;
+  const double planes = (double)R * (double)a.L * 4.0 * passes / 4.5e6;
   double groups = walk + planes + 5.0;
-  if (groups < 35.0) groups = 35.0;
+  const double least = a.ws ? 14.0 : 35.0;
+  if (groups < least) groups = least;
   const double w = (double)R / (8.0 * cus);
   const double wc = w < 1.0 ? 1.0 : w;
   double step = a.N > 32 ? (w <= 1.0 ? 0.125 : 0.15 * (wc > 3.0 ? wc / 3.0 : 1.0))
                          : 0.09 + 0.012 * ((wc < 6.0 ? wc : 6.0) - 1.0);
   if (a.N <= 32 && wc > 6.0) step *= wc / 6.0;
-  if ((a.N != 32 && a.N != 64) || !vector_path<IN>(a)) step *= 1.15;
-  return groups < step * (double)a.L;
+  if ((a.N != 32 && a.N != 64) || !vector_path<IN>(a)) step *= 1.2;
+  return groups < 1.0 + step * (double)(T + 24);
 }
 
 // Calls of at most 16 steps take the kernel of selective_step.hip, which moves
@@ -797,7 +808,8 @@ int64_t selective_fwd_workspace(int64_t B, int64_t D, int64_t N, int64_t L, bool
   a.L = L;
   a.bf16_in = bf16_in;
   a.vec = aligned && L % 4 == 0;  // (other rows only raise the 8-lane kernel's price)
-  a.z = z ? &a : nullptr;  // (only tested)
+  a.z = z ? &a : nullptr;  // (this and ws are only tested)
+  a.ws = &a;
   if (step_path(a)) return 0;
   const bool groups = bf16_in ? lanes16_path<uint16_t>(a) && groups_pay<uint16_t>(a)
                               : lanes16_path<float>(a) && groups_pay<float>(a);
