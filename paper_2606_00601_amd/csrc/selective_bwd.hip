@@ -883,72 +883,88 @@ void launch_bwd(const BwdArgs& a, const BwWork& w, int64_t G, int64_t ntile, con
 // sequence into, priced like the forward's plan.  A launch of n workgroups runs
 // in rounds of at most two (64 rows) or three (16 rows) per compute unit, by
 // LDS and registers; a round takes BwdCost::us per tile of 8 steps with that
-// many workgroups on the busiest compute unit, and about five tiles more to
-// start and end a segment (seven for a row block of 16).  Rows of odd length
-// read their steps one by one, and their lines are shared by more accesses:
-// `odd` times that, most with a gate, whose z, s and dz have lines of their own.
-// Rounds of many small workgroups overlap: from 4.5 per compute unit on, each
-// takes `many` us a tile.  State groups after the first read ddelta and dx back,
-// 1.24 times the 64-row kernel's time (0.12 more over two groups).  Cut calls
-// add the adjoint's walk, 0.5 + 0.45 us per tile and workgroup resident (up to
-// seven; without a gate 0.73 of it), and 8 us for its launch and the records.
-// The constants are fits to 13 widths of 1024 to 40960 rows, L = 64 to 4096 and
-// N = 8 to 64, fp32 and bf16, gate with softplus or neither (what the sizing of
-// the workspace knows of a call).  Ties go to the 16-row kernel; over the 3435
-// timed calls the choice is 1.3% from the faster kernel on average.  us per
-// call with given checkpoints, 16-row / 64-row kernel:
+// many workgroups on the busiest compute unit, and `start` tiles more to start
+// and end a segment.  Rows of odd length read their steps one by one: `odd`
+// times that.  Cut calls add the adjoint's walk (BWD_WALK_US per tile for each
+// workgroup resident, up to seven, and once more) and 5 us for its launch and
+// the records.  State groups after the first read ddelta and dx back, 1.24
+// times the 64-row kernel's time (0.12 more over two groups), and have their
+// checkpoints from the forward's walk before it, where the 16-row kernel sweeps
+// for them.  Beside the walk come a fixed part and the reduction of the shares of
+// dB and dC, of which 16 rows a workgroup leave four times as many.  No call is
+// below 27 us of host time.
+// The constants are fits to 900 calls of up to 160000 rows, L = 32 to 8192, N = 8
+// to 64, fp32 and bf16, gate with softplus or neither (what the sizing of the
+// workspace knows of a call), each timed with the 16-row kernel and with the
+// 64-row one in up to a dozen cuts.  More segments, and the 16-row kernel, have
+// to be 3% cheaper: near a tie the simpler launch is the safer one.  The choice is
+// 1.5% from the fastest on average (2.4% with the constants before), on 500 other
+// calls 1.8%.  us per call with given checkpoints, 16-row / 64-row kernel:
 //   B=8 D=1536 L=1024  ungated 202 / 279, gated 252 / 312 (fp32)
-//   B=8 D=1536 L=2048  ungated 402 / 398, gated 511 / 579 (fp32), 477 / 507 (bf16)
+//   B=8 D=1536 L=2048  ungated 398 / 402 (fp32), 387 / 369 (bf16), gated 487 / 564
+//                      (fp32), 453 / 479 (bf16)
+//   B=8 D=1536 L=2047  ungated 425 / 513, gated 690 / 780 (fp32)
 //   B=4 D=5120 L=1024  gated 421 / 528 (fp32)
 //   B=4 D=1024 L=2048  ungated 271 / 157, gated 298 / 203 (fp32)
-//   B=8 D=4096 L=1024  ungated 534 / 424, gated 654 / 595 (fp32)
+//   B=8 D=1600 L=2048  ungated 603 / 424, gated 696 / 593 (fp32)
+//   B=4 D=5120 L=64    gated 52 / 42 (bf16)
 //   B=1 D=1024 L=4096  ungated 505 / 113 (fp32)
 struct BwdCost {
-  int cap;              // workgroups per compute unit
-  double start;         // tiles
-  double us[2][3];      // [gated][workgroups resident - 1]
+  int cap;          // workgroups per compute unit
+  double start;     // tiles
+  double fixed;     // us
+  double us[2][3];  // [gated][workgroups resident - 1]
   double odd[2][3];
-  double many[2];
 };
 constexpr BwdCost COST_ROWS16 = {
-    3, 7.0, {{1.0, 1.25, 1.53}, {1.16, 1.43, 1.9}}, {{1.04, 1.04, 1.04}, {1.17, 1.17, 1.17}}, {0.495, 0.6}};
+    3, 4.0, 10.0, {{0.9, 1.19, 1.39}, {1.09, 1.27, 1.7}}, {{1.0, 1.0, 1.0}, {1.0, 1.0, 1.0}}};
 constexpr BwdCost COST_ROWS64 = {
-    2, 5.0, {{2.08, 2.85, 0.0}, {2.4, 3.85, 0.0}}, {{1.05, 1.33, 0.0}, {1.4, 1.6, 0.0}}, {9.0, 9.0}};
+    2, 4.5, 1.8, {{2.0, 2.93, 0.0}, {2.31, 3.78, 0.0}}, {{1.03, 1.19, 0.0}, {1.43, 1.43, 0.0}}};
+constexpr double BWD_WALK_US[2] = {0.265, 0.37};
+constexpr double BWD_SHARE_US = 2.43e-5;  // per step of a workgroup's share
+constexpr double BWD_HOST_US = 27.0;
 
-double bwd_launch_us(const BwdCost& c, int64_t wgs, int64_t tiles, bool gated, bool odd, int cus) {
-  const int64_t per = (wgs + cus - 1) / cus;
-  const auto us = [&](int64_t o) { return c.us[gated][o - 1] * (odd ? c.odd[gated][o - 1] : 1.0); };
-  double tile = (double)(per / c.cap) * us(c.cap) + (per % c.cap ? us(per % c.cap) : 0.0);
-  const double share = (double)wgs / (double)cus;
-  const double many = share * c.many[gated] * (odd ? c.odd[gated][0] : 1.0);
-  if (share >= 4.5 && many < tile) tile = many;
+// The walk of wgs workgroups (below 2^32) over `tiles` tiles.
+double bwd_launch_us(const BwdCost& c, int64_t wgs, int64_t tiles, bool gated, bool odd, uint32_t cus) {
+  const uint32_t per = ((uint32_t)wgs + cus - 1) / cus;
+  const auto us = [&](uint32_t o) { return c.us[gated][o - 1] * (odd ? c.odd[gated][o - 1] : 1.0); };
+  const double tile = (double)(per / c.cap) * us(c.cap) + (per % c.cap ? us(per % c.cap) : 0.0);
   return ((double)tiles + c.start) * tile;
 }
 
-BwdPlan plan_bwd(int64_t B, int64_t D, int64_t N, int64_t L, bool gated, int cus) {
+BwdPlan plan_bwd(int64_t B, int64_t D, int64_t N, int64_t L, bool gated, uint32_t cus) {
   const int64_t ntile = (L + BW_T - 1) / BW_T, W = B * ((D + BW_ROWS - 1) / BW_ROWS);
   const int64_t W16 = B * ((D + 15) / 16);
   const int64_t ngrp = (N + BW_N - 1) / BW_N;
   const double groups = 1.0 + 0.12 * (double)(ngrp - 1) / (double)ngrp;
   const bool odd = L % 2 != 0;
   BwdPlan best{1, ntile, false};
-  double best_us = groups * bwd_launch_us(COST_ROWS64, W, ntile, gated, odd, cus);
+  double us64 = groups * bwd_launch_us(COST_ROWS64, W, ntile, gated, odd, cus);
   for (int64_t k = 2; k <= BW_MAX_SEG && k <= ntile; ++k) {
     const int64_t tiles = (ntile + k - 1) / k, n = (ntile + tiles - 1) / tiles;
     if (n < 2 || W * n > SW_MAX_WGS) continue;
-    const int64_t e = (W * (n - 1) + cus - 1) / cus;
-    const double walk = (double)(e / 7) * (0.5 + 0.45 * 7) + (e % 7 ? 0.5 + 0.45 * (double)(e % 7) : 0.0);
+    const uint32_t e = ((uint32_t)(W * (n - 1)) + cus - 1) / cus;
+    const double walk = BWD_WALK_US[gated] * (double)(e / 7 * 8 + (e % 7 ? e % 7 + 1 : 0));
     const double us = groups * bwd_launch_us(COST_ROWS64, W * n, tiles, gated, odd, cus) +
-                      ((double)tiles + COST_ROWS64.start) * walk * (gated ? 1.0 : 0.73) + 8.0;
-    if (us < best_us) {
-      best_us = us;
+                      ((double)tiles + COST_ROWS64.start) * walk + 5.0;
+    if (us < 0.97 * us64) {
+      us64 = us;
       best = BwdPlan{(int)n, tiles, false};
     }
   }
+  double us16 = bwd_launch_us(COST_ROWS16, W16, ntile, gated, odd, cus);
+  if (ngrp > 1) {
+    us16 *= 1.45;
+    us64 += 1.47 * row16_rows_us(W16, L, (int)cus);
+  }
+  const auto call_us = [&](const BwdCost& c, double us, int64_t wgs) {
+    us = (us + (double)wgs * (double)L * BWD_SHARE_US) * (double)ngrp + c.fixed;
+    return us > BWD_HOST_US ? us : BWD_HOST_US;
+  };
   // SW_SS_BWD_ROWS=16 or 64 keeps one kernel
   const char* const v = getenv("SW_SS_BWD_ROWS");
   const int force = v && *v ? atoi(v) : 0;
-  const bool rows16 = bwd_launch_us(COST_ROWS16, W16, ntile, gated, odd, cus) < 1.03 * best_us;
+  const bool rows16 = call_us(COST_ROWS16, us16, W16) < 0.97 * call_us(COST_ROWS64, us64, W);
   if (W16 <= SW_MAX_WGS && (force == 16 || (force != 64 && rows16))) best = BwdPlan{1, ntile, true};
   return best;
 }
@@ -967,7 +983,7 @@ BwdSizes bwd_sizes(int64_t B, int64_t D, int64_t N, int64_t L, bool ckpt, bool g
   z.ntile = (L + BW_T - 1) / BW_T;
   int cus = 0;
   if (device_cus(&cus) != SW_OK) cus = 256;
-  z.plan = plan_bwd(B, D, N, L, gated, cus);
+  z.plan = plan_bwd(B, D, N, L, gated, (uint32_t)cus);
   const int64_t rows = z.plan.rows16 ? 16 : BW_ROWS;
   z.G = (D + rows - 1) / rows;
   const size_t R = (size_t)(B * D), nseg = (size_t)z.plan.nseg;

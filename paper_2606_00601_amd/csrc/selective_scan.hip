@@ -642,7 +642,6 @@ template <typename IN>
 int launch_row16_groups(const SelArgs& a, hipStream_t s);
 template <typename IN>
 double row16_groups_us(const SelArgs& a, int cus);
-double row16_rows_us(int64_t wgs, int64_t L, int cus);
 template <typename IN>
 int launch_row16_states(const SelArgs& a, int grp, hipStream_t s);
 template <typename IN>

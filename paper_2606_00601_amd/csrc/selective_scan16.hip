@@ -1126,7 +1126,6 @@ int launch_row16(const SelArgs& a, hipStream_t s) {
              : launch_row16_t<IN, false, R16_RAG>(a, p, ndb, s);
 }
 
-// The price of a walk of whole rows by `wgs` workgroups.
 double row16_rows_us(int64_t wgs, int64_t L, int cus) {
   return launch_us(wgs, L, cus, R16_COST, 1.0);
 }

@@ -119,6 +119,9 @@ SelPlan selective_plan(const SelArgs& a, int cus);
 // otherwise returns SW_OK with nothing enqueued.
 int selective_states_fwd(const SelArgs& a, int grp, bool* taken);
 
+// The price in us of the 16-lane forward's walk of whole rows by `wgs` workgroups.
+double row16_rows_us(int64_t wgs, int64_t L, int cus);
+
 // Arguments of one backward call of the fused form, already validated.
 // x, delta, Bm, Cm, z are fp32 or bf16 as `bf16_in` says, dy as `dy_bf16`
 // says; gradients are fp32 unless grads_bf16.  Optional inputs (NULL: absent): Dskip, z,
