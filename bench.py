@@ -61,9 +61,10 @@ def algorithmic_bytes(w) -> int:
 
 # the sources each path's kernels are built from (traffic records are keyed to them)
 FWD_SOURCES = ("selective_common.h", "selective_scan.hip", "selective_scan16.hip",
-               "selective_scan_quad.hip", "sw_internal.h")
+               "selective_scan_quad.hip", "selective_step.hip", "sw_internal.h")
 AFFINE_SOURCES = ("affine_scan.hip", "sw_internal.h")
-BWD_SOURCES = ("selective_bwd.hip", "selective_common.h", "sw_internal.h")
+BWD_SOURCES = ("bwd_common.h", "selective_bwd.hip", "selective_bwd16.hip", "selective_common.h",
+               "sw_internal.h")
 
 # workload -> committed HBM traffic record (rocprofv3 FETCH_SIZE / WRITE_SIZE)
 TRAFFIC_RECORDS = {
@@ -72,7 +73,7 @@ TRAFFIC_RECORDS = {
         "selective_row16_f32_b4_d2048_n16_l8192_stress_traffic.txt",
     "selective_bf16_b8_d1536_n16_l2048": "selective_row16_bf16_b8_d1536_n16_l2048_traffic.txt",
     "affine_f32_b1_d5120_l65536": "affine_rows_f32_b1_d5120_l65536_traffic.txt",
-    "affine_f32_b8_d1536_l2048": "affine_scan_f32_b8_d1536_l2048_traffic.txt",
+    "affine_f32_b8_d1536_l2048": "affine_rows_f32_b8_d1536_l2048_traffic.txt",
 }
 # the backward given the forward's checkpoints (no Mamba-block options)
 BWD_TRAFFIC_RECORDS = {

@@ -22,8 +22,7 @@
 // workgroups, three to a compute unit, so that calls of two or three of them
 // per compute unit need no segments and no second walk.  The rule between the
 // two, with both sides measured, is plan_bwd (selective_bwd.hip).  Bound by
-// instruction issue and LDS at 149 VGPRs and 48 KB (three wavefronts a SIMD): B=8
-// D=1536 L=2048 in fp32, gate and softplus, 486 us beside 42 for the reduction.
+// instruction issue and LDS at 149 VGPRs and 48 KB (three wavefronts a SIMD).
 #include "bwd_common.h"
 
 namespace sw {
