@@ -386,8 +386,9 @@ int sw_selective_scan_fwd_train_seg(const void* x, const void* delta, const floa
  * Results are deterministic: cross-row sums are added in a fixed order.
  * N in [1, 64] (states above 16 run as further passes over the sequence,
  * 16 states each); with ckpt, N <= 16.  A workspace of about
- * (B*D*L*8 without ckpt + B*ceil(D/16)*L*128 + B*D*L*4 if z) bytes is taken from the
- * device's stream-ordered pool for the call.  Other conventions (and
+ * (B*D*L*8 without ckpt + B*ceil(D/16)*L*128 + B*D*L*4 if z without s_pre) bytes,
+ * where N > 32 with z at most ceil(N/16)*B*D*L*4 in place of the first term, is
+ * taken from the device's stream-ordered pool for the call.  Other conventions (and
  * errors) as for sw_selective_scan_fwd_ex.
  */
 int sw_selective_scan_bwd(const void* x, const void* delta, const float* A, const void* Bm,
