@@ -302,7 +302,7 @@ def _fwd(x, delta, A, Bm, Cm, Dskip, y, h_last, want_h_last, z, delta_bias, h0, 
                 _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(z),
                 _ptr(delta_bias), _ptr(h0), _ptr(y), _ptr(h_last), _ptr(ckpt), _ptr(s_pre),
                 B, D, N, L, in_dt, out_dt, flags), "sw_selective_scan_fwd_train")
-        elif (ws := _fwd_workspace(x, delta, Bm, Cm, z, y, N, in_dt)) is not None:
+        elif N > 16 and (ws := _fwd_workspace(x, delta, Bm, Cm, z, y, N, in_dt)) is not None:
             check(fast().sw_selective_scan_fwd_ws(
                 _ptr(x), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dskip), _ptr(z),
                 _ptr(delta_bias), _ptr(h0), _ptr(y), _ptr(h_last), B, D, N, L, in_dt, out_dt,
@@ -328,8 +328,6 @@ def _fwd_workspace(x, delta, Bm, Cm, z, y, N, in_dt):
     takes them back after the call (None: none needed, or no memory for them;
     the library then asks its own pool and, failing that, takes the kernel that
     needs none)."""
-    if N <= 16:
-        return None
     B, D, L = x.shape
     at = x.data_ptr() | delta.data_ptr() | Bm.data_ptr() | Cm.data_ptr() | y.data_ptr()
     if z is not None:
